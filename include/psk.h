@@ -426,7 +426,7 @@ typedef struct psk_slab {
  * 0 when the sizes are outside the limits above. */
 size_t psk_slab_mem_bytes(int64_t rows, int64_t cols, int64_t nnz);
 size_t psk_slab_mem_bytes_f64(int64_t rows, int64_t cols, int64_t nnz);
-/* Bytes of scratch memory psk_slab_build_csr needs (about 16 bytes per entry); free to reuse afterwards. */
+/* Bytes of scratch memory psk_slab_build_csr needs (about 5 bytes per entry; 16 for more than 256 slabs); free to reuse afterwards. */
 size_t psk_slab_build_workspace_bytes(int64_t rows, int64_t cols, int64_t nnz);
 size_t psk_slab_build_workspace_bytes_f64(int64_t rows, int64_t cols, int64_t nnz);
 /* Bytes of workspace a product over S needs (the pair sums and the carry records); 0 if S is NULL. */
@@ -434,8 +434,8 @@ size_t psk_slab_spmv_workspace_bytes(const psk_slab *S);
 
 /*
  * The analysis step: builds the structure from a CSR matrix, entirely on the device (a histogram of the
- * slabs per block of 2048 positions, prefix sums, a stable scatter, the pairs of every chunk and their prefix sums, the
- * row lists and their position cut).  `mem` (psk_slab_mem_bytes, 256-byte aligned) receives the arrays and
+ * slabs per block of 2048 positions, prefix sums, a stable scatter that finds the pairs on its way, the numbers of the
+ * pairs, the row lists and their position cut).  `mem` (psk_slab_mem_bytes, 256-byte aligned) receives the arrays and
  * must stay allocated while *out is used; `workspace` (psk_slab_build_workspace_bytes, 256-byte aligned) is
  * scratch.  *out (HOST pointer) receives the sizes and the device pointers.  pos, crd, vals: as for
  * psk_spmv_csr (same unchecked preconditions).  This call SYNCHRONISES `stream` (it reads three counts

@@ -105,10 +105,12 @@ int build_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, const
     }
     if (vbytes == 8)
         e = launch_slab_build_f64((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, static_cast<const double *>(vals), w,
-                                  static_cast<double *>(m.svals), m.scol, m.chunk_pair, m.slab_chunk, m.qpos, m.qidx, s);
+                                  static_cast<double *>(m.svals), m.scol, m.chunk_pair, m.slab_chunk, m.qpos, m.qidx, slab_tile(vbytes),
+                                  m.qtile_row, s);
     else
         e = launch_slab_build((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, static_cast<const float *>(vals), w,
-                              static_cast<float *>(m.svals), m.scol, m.chunk_pair, m.slab_chunk, m.qpos, m.qidx, s);
+                              static_cast<float *>(m.svals), m.scol, m.chunk_pair, m.slab_chunk, m.qpos, m.qidx, slab_tile(vbytes),
+                                  m.qtile_row, s);
     if (e != hipSuccess) return PSK_ERR_HIP;
     int32_t meta[3] = {0, 0, 0};
     if (hipMemcpyAsync(meta, w.meta, sizeof(meta), hipMemcpyDeviceToHost, s) != hipSuccess) return PSK_ERR_HIP;
@@ -118,8 +120,10 @@ int build_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, const
     d.npairs = meta[1];
     d.nq = meta[2];
     // the position cut of the row lists, kept with the structure (it depends only on A)
-    e = launch_partition(rows, d.nq, m.qpos, slab_tile(vbytes), 0, m.qtile_row, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (S > kStageSlabs) {
+        e = launch_partition(rows, d.nq, m.qpos, slab_tile(vbytes), 0, m.qtile_row, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
     *out = d;
     return hip_status(e);
 }

@@ -163,18 +163,25 @@ inline int64_t slab_max_slots(int64_t cols, int64_t nnz, int32_t W)
     const int64_t padded = nnz + S * (kSlabChunk - 1);
     return (padded + kSlabChunk - 1) / kSlabChunk * kSlabChunk;
 }
+constexpr int32_t kStageSlabs = 256;        // up to this many slabs the analysis works block by block (k_block_place)
 struct SlabBuildSpace {
-    int32_t *meta, *tile_row, *H, *srow, *src, *F, *mark, *pair_at, *scan_tmp;
+    int32_t *meta, *tile_row, *H, *src;
+    int32_t *srow, *F, *mark, *pair_at, *scan_tmp;                      // more than kStageSlabs slabs
+    int32_t *total, *part;                                              // at most kStageSlabs slabs
+    uint16_t *H16, *N16, *pbits_pre;
+    unsigned long long *pbits, *chunk_at;
     size_t bytes;
 };
 size_t scan_tmp_ints(int64_t n);
 SlabBuildSpace carve_slab_build(void *base, int64_t rows, int64_t cols, int64_t nnz, int32_t W);
 hipError_t launch_slab_build(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                              const float *vals, const SlabBuildSpace &w, float *svals, uint16_t *scol,
-                             int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx, hipStream_t s);
+                             int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx, int32_t qtile,
+                             int32_t *qtile_row, hipStream_t s);
 hipError_t launch_slab_build_f64(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                  const double *vals, const SlabBuildSpace &w, double *svals, uint16_t *scol,
-                                 int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx, hipStream_t s);
+                                 int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx, int32_t qtile,
+                             int32_t *qtile_row, hipStream_t s);
 hipError_t launch_slab_pairs_f64(const double *svals, const uint16_t *scol, const int32_t *chunk_pair,
                                  const int32_t *slab_chunk, const double *x, double *P, int32_t cols, int32_t nslabs,
                                  int32_t nchunks, int32_t nwg, int32_t *gap, hipStream_t s);

@@ -72,6 +72,11 @@ __device__ __forceinline__ int wave_scan_add(int v)
     v += dpp_i<0x143, 0xC>(v);
     return v;
 }
+// bits of `mask` that belong to lanes below this one
+__device__ __forceinline__ int lanes_below(unsigned long long mask)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
 // Inclusive segmented sum: a lane with f != 0 starts afresh (takes nothing from the lanes below it).
 template <typename T>
 __device__ __forceinline__ T wave_segscan(T v, int f)
@@ -494,135 +499,489 @@ __global__ __launch_bounds__(64) void k_slab_scatter(int rows, int nnz, const in
     }
 }
 
-// The same bucketing for matrices of at most STAGE_SLABS slabs, with coalesced stores: a workgroup of four waves takes
-// the block, wave w its w-th quarter (8 steps of 64 positions).  The waves first count their positions per slab; from
-// the counts every (wave, slab) gets its place in a staging area in LDS that holds the block's entries ordered by slab
-// (and inside a slab by CSR position: wave after wave, step after step, lane after lane -- the same stable order).  The
-// entries are then ranked as above, staged, and written out in staging order, so that a slab's entries of this block
-// (33 on average for 62 slabs) leave as one run of consecutive slots instead of 64 scattered stores per step.
-constexpr int STAGE_SLABS = 256;
+// ---- matrices of at most kStageSlabs slabs (8.4 M columns; 4.2 M with fp64 values)
+//
+// The structure follows from counts per (block of BUILD_BT positions, slab): how many entries, whether one of them belongs to
+// the row that enters the block from before (head) and whether one belongs to the row that leaves it (tail).  With these a
+// block knows by itself for every entry whether its predecessor and its successor in the slab belong to the same row, i.e.
+// where pairs start and end, so every entry is read once, written once and never looked at again.  What is left are
+// numbers per start of a pair, not per entry.
+// A version that left a row and a source position with every slot (14 bytes written per entry instead of 6), found the
+// pairs from them and formed the row lists through two arrays over all entries moved 3.7 GB in 1.28 ms for the power-law matrix
+// of 2 M rows and 56.5 M entries; this one moves 1.1 GB.
+//
+//   k_block_hist   H[b][s] = count | head << 12 | tail << 13
+//   k_col_*        E[b][s] = entries of slab s in the blocks before b; totals -> slab_chunk (k_block_bases)
+//   k_block_place  values and columns with their end bits to the slots; per start of a pair its slab and rank, in CSR order;
+//                  N[b][s] = starts of block b in slab s, N[b][nslabs] = all starts of block b
+//   k_col_*        F = the same scan of N; totals -> first pair of every slab (k_block_bases2)
+//   k_block_pairs  qidx: pair number = first pair of the slab + F[b][s] + rank
+//   k_block_rows   qpos, the position cut of the row lists, chunk_pair, pad slots
+constexpr int H_HEAD = 1 << 12, H_TAIL = 1 << 13, H_COUNT = (1 << 12) - 1;
+constexpr int BITS_W = BUILD_BT / 64;                 // 64-bit words of a bitmap over a block's positions
+static_assert(BUILD_BT <= H_COUNT, "a block's count fits its field");
+
+// Rows that cross the borders of block b: positions below `head` belong to the row that began before the block, positions
+// from `tail` on to the row that goes on behind it (tile_row = position cut of pos with tiles of BUILD_BT).
+__device__ __forceinline__ void block_borders(const int *__restrict__ pos, const int *__restrict__ tile_row, int b, int nblk,
+                                              long long p0, int nvalid, int &head, int &tail)
+{
+    const int r_lo = tile_row[b], r_hi = tile_row[b + 1];
+    head = 0;
+    tail = nvalid;
+    if (pos[r_lo] < p0) head = (int)min((long long)nvalid, (long long)pos[r_lo + 1] - p0);
+    if (b + 1 < nblk && pos[r_hi] < p0 + BUILD_BT) tail = (int)max(0ll, (long long)pos[r_hi] - p0);
+}
+
+// A thread takes 8 consecutive positions and adds runs of one slab at once: in the sorted columns of a long row all 64 lanes
+// of an instruction that took neighbouring positions would add to one LDS word.
+template <int W>
+__global__ __launch_bounds__(256) void k_block_hist(int nnz, const int *__restrict__ pos, const int *__restrict__ crd,
+                                                    const int *__restrict__ tile_row, int nslabs, int nblk, int vec_ok,
+                                                    unsigned short *__restrict__ H)
+{
+    constexpr int EPT = BUILD_BT / 256;
+    static_assert(EPT == 8, "two 16-byte loads per thread");
+    __shared__ int hist[kStageSlabs];
+    __shared__ unsigned char hflag[kStageSlabs], tflag[kStageSlabs];
+    const int b = xcd_tile(blockIdx.x, nblk), tid = threadIdx.x;
+    if (b < 0) return;
+    hist[tid] = 0;
+    hflag[tid] = 0;
+    tflag[tid] = 0;
+    const long long p0 = (long long)b * BUILD_BT;
+    const int nvalid = (int)min((long long)BUILD_BT, (long long)nnz - p0), i0 = tid * EPT;
+    int c[EPT];
+    if (vec_ok && i0 + EPT <= nvalid) {
+#pragma unroll
+        for (int g = 0; g < EPT / 4; ++g) {
+            const v4i t = ld_stream(reinterpret_cast<const v4i *>(crd + p0 + i0 + 4 * g));
+            c[4 * g] = t.x; c[4 * g + 1] = t.y; c[4 * g + 2] = t.z; c[4 * g + 3] = t.w;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) c[j] = i0 + j < nvalid ? crd[p0 + i0 + j] : 0;
+    }
+    int head, tail;
+    block_borders(pos, tile_row, b, nblk, p0, nvalid, head, tail);
+    __syncthreads();
+    int cur = -1, n = 0;
+#pragma unroll
+    for (int j = 0; j < EPT; ++j) {
+        const int i = i0 + j;
+        if (i < nvalid) {
+            const int sl = (int)((unsigned)c[j] / W);
+            if (i < head) hflag[sl] = 1;
+            if (i >= tail) tflag[sl] = 1;
+            if (sl != cur) {
+                if (n) atomicAdd(&hist[cur], n);
+                cur = sl;
+                n = 0;
+            }
+            ++n;
+        }
+    }
+    if (n) atomicAdd(&hist[cur], n);
+    __syncthreads();
+    if (tid < nslabs)
+        H[(long long)b * nslabs + tid] = (unsigned short)(hist[tid] | (hflag[tid] ? H_HEAD : 0) | (tflag[tid] ? H_TAIL : 0));
+}
+
+// ---- exclusive scans down the columns of a matrix M[nblk][S] (the low 12 bits of every entry): sums over chunks of COL_CH
+// rows, a scan of every column's chunk sums by one workgroup, then every chunk again on top of its sum.  A thread owns a
+// column and every RG-th part of the chunk's rows, so that all accesses run along the rows of M.
+constexpr int COL_CH = 64;
+__device__ __forceinline__ int col_width(int S) { return S <= 64 ? 64 : (S <= 128 ? 128 : 256); }
+
+template <bool APPLY>
+__global__ __launch_bounds__(256) void k_col_chunks(const unsigned short *__restrict__ M, int nblk, int S,
+                                                    int *__restrict__ part, int *__restrict__ out)
+{
+    __shared__ int red[256];
+    const int P = col_width(S), RG = 256 / P, rows = COL_CH / RG;
+    const int rg = threadIdx.x / P;
+    const int b0 = blockIdx.x * COL_CH + rg * rows, b1 = min(min(b0 + rows, (int)(blockIdx.x + 1) * COL_CH), nblk);
+    for (int c0 = 0; c0 < S; c0 += P) {                    // more than one round only when S = 257
+        const int col = c0 + threadIdx.x % P;
+        int sum = 0;
+        if (col < S) {
+#pragma unroll 8
+            for (int b = b0; b < b1; ++b) sum += M[(long long)b * S + col] & H_COUNT;
+        }
+        __syncthreads();
+        red[threadIdx.x] = sum;
+        __syncthreads();
+        if (!APPLY) {
+            if (rg == 0 && col < S) {
+                for (int g = 1; g < RG; ++g) sum += red[threadIdx.x + g * P];
+                part[(long long)blockIdx.x * S + col] = sum;
+            }
+        } else if (col < S) {
+            int run = part[(long long)blockIdx.x * S + col];
+            for (int g = 0; g < rg; ++g) run += red[threadIdx.x % P + g * P];
+#pragma unroll 8
+            for (int b = b0; b < b1; ++b) {
+                out[(long long)b * S + col] = run;
+                run += M[(long long)b * S + col] & H_COUNT;
+            }
+        }
+    }
+}
+
+// one workgroup per column: exclusive scan of its chunk sums in place, total[col] = their sum
+__global__ __launch_bounds__(256) void k_col_scan(int *__restrict__ part, int nparts, int S, int *__restrict__ total)
+{
+    __shared__ int s_w[4];
+    int carry = 0;
+    for (int b0 = 0; b0 < nparts; b0 += 256) {
+        const int i = b0 + threadIdx.x;
+        const int v = i < nparts ? part[(long long)i * S + blockIdx.x] : 0;
+        int sum;
+        const int inc = block_scan_256(v, s_w, &sum);
+        if (i < nparts) part[(long long)i * S + blockIdx.x] = carry + inc - v;
+        carry += sum;
+    }
+    if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+
+// slab_chunk = exclusive scan of the slabs' sizes in chunks; meta[0] = number of slots
+__global__ __launch_bounds__(256) void k_block_bases(const int *__restrict__ total, int nslabs, int *__restrict__ slab_chunk,
+                                                     int *__restrict__ meta)
+{
+    __shared__ int s_w[4];
+    const int tid = threadIdx.x;
+    const int chunks = tid < nslabs ? (total[tid] + SLAB_CH - 1) / SLAB_CH : 0;
+    int sum;
+    const int inc = block_scan_256(chunks, s_w, &sum);
+    if (tid < nslabs) slab_chunk[tid] = inc - chunks;
+    if (tid == 0) {
+        slab_chunk[nslabs] = sum;
+        meta[0] = sum * SLAB_CH;
+    }
+}
+
+// slab_pair[s] = first pair of slab s: its starts, and one more pair for its pad slots if it has any (fewer than a chunk, all
+// behind the slab's last entry).  meta[1] = pairs, meta[2] = listed pairs.
+__global__ __launch_bounds__(256) void k_block_bases2(const int *__restrict__ total, const int *__restrict__ starts, int nslabs,
+                                                      const int *__restrict__ slab_chunk, int *__restrict__ slab_pair,
+                                                      int *__restrict__ chunk_pair, int *__restrict__ meta)
+{
+    __shared__ int s_w[4];
+    const int tid = threadIdx.x;
+    const int pairs = tid < nslabs ? starts[tid] + (total[tid] % SLAB_CH != 0 ? 1 : 0) : 0;
+    int sum;
+    const int inc = block_scan_256(pairs, s_w, &sum);
+    if (tid < nslabs) slab_pair[tid] = inc - pairs;
+    if (tid == 0) {
+        chunk_pair[slab_chunk[nslabs]] = sum;
+        meta[1] = sum;
+        meta[2] = starts[nslabs];
+    }
+}
+
+// A workgroup of four waves per block; wave w takes the w-th quarter, 64 positions per step.  The lanes of a step that share a
+// slab are ranked by lane (one ballot per bit of the slab number), a counter per (wave, slab) carries the rank from step to
+// step; from the counters every entry gets its place in a staging area in LDS ordered by slab and, inside a slab, by CSR
+// position.  Neighbours in the staging area are neighbours in the slab, so starts and ends of pairs are a comparison of row
+// ordinals (the number of row starts up to a position: a bitmap and its prefix counts, no search) -- and for the first and
+// last entry of a slab's run the question whether the row has entries of this slab in other blocks, answered from H and E.
+// The entries leave as runs of consecutive slots; blocks are dealt to the dies in contiguous ranges, so that the runs of
+// neighbouring blocks meet in one L2 and reach memory as whole lines.
 template <typename T>
-__global__ __launch_bounds__(256) void k_slab_scatter_staged(int rows, int nnz, const int *__restrict__ pos,
-                                                            const int *__restrict__ crd, const T *__restrict__ vals,
-                                                            const int *__restrict__ tile_row,
-                                                            const int *__restrict__ E,
-                                                            const int *__restrict__ slab_chunk, int nslabs, int nblk,
-                                                            int nbits, T *__restrict__ svals,
-                                                            unsigned short *__restrict__ scol,
-                                                            int *__restrict__ srow, int *__restrict__ src)
+__global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restrict__ pos, const int *__restrict__ crd,
+                                                     const T *__restrict__ vals, const int *__restrict__ tile_row,
+                                                     const unsigned short *__restrict__ H, const int *__restrict__ E,
+                                                     const int *__restrict__ slab_chunk, int nslabs, int nblk, int nbits,
+                                                     T *__restrict__ svals, unsigned short *__restrict__ scol,
+                                                     unsigned short *__restrict__ N, int *__restrict__ starts,
+                                                     unsigned long long *__restrict__ pbits,
+                                                     unsigned short *__restrict__ pbits_pre,
+                                                     unsigned long long *__restrict__ chunk_at)
 {
     constexpr int W = SlabOf<T>::W, NW = 4, QUART = BUILD_BT / NW, STEPS = QUART / WAVE;
-    __shared__ int woff[NW][STAGE_SLABS];        // entries of (wave, slab); later: where that wave's next entry of the slab goes
-    __shared__ int lbase[STAGE_SLABS + 1];       // first staging index of each slab
-    __shared__ int gbase[STAGE_SLABS];           // first slot (global) of this block's entries of each slab
-    __shared__ int spos[SCATTER_ROWS];
+    constexpr int ROWS_WALK = 8 * BUILD_BT;
+    __shared__ unsigned short woff[NW][kStageSlabs];   // entries of (wave, slab) so far; later the place of the wave's first one
+    __shared__ int lbase[kStageSlabs + 1];             // first staging place of each slab
+    __shared__ int2 gbase[kStageSlabs];                // x: slot of a staged entry = x + its place; y: bit 0 = the slab's run
+                                                       // continues a pair of an earlier block, bit 1 = it is continued
+    __shared__ int sbase[kStageSlabs];                 // starts before the slab's first staging place
     __shared__ T s_val[BUILD_BT];
-    __shared__ int s_row[BUILD_BT];
-    __shared__ unsigned short s_col[BUILD_BT], s_idx[BUILD_BT], s_slab[BUILD_BT];
+    __shared__ unsigned s_all[BUILD_BT + 2];           // one entry of no slab on either side
+    unsigned *const s_meta = s_all + 1;                // row ordinal (12 bits) | position << 12 (11 bits) | slab << 23
+    __shared__ unsigned short s_col[BUILD_BT];
+    __shared__ unsigned rowbits[2 * BITS_W], posbits[2 * BITS_W];
+    __shared__ unsigned long long startbits[BITS_W];
+    __shared__ int row_pre[BITS_W], pos_pre[BITS_W + 1], start_pre[BITS_W + 1];
     __shared__ int s_w[4];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int b = xcd_tile(blockIdx.x, nblk);
+    if (b < 0) return;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const long long p0 = (long long)b * BUILD_BT;
     const int nvalid = (int)min((long long)BUILD_BT, (long long)nnz - p0);
-    const int r_lo = tile_row[b], r_hi = tile_row[b + 1];
-    const bool local = r_hi - r_lo < SCATTER_ROWS;
-    for (int i = tid; i < NW * STAGE_SLABS; i += 256) (&woff[0][0])[i] = 0;
-    if (local)
-        for (int i = tid; i <= r_hi - r_lo; i += 256) spos[i] = pos[r_lo + i];
-    for (int sl = tid; sl < nslabs; sl += 256)
-        gbase[sl] = slab_chunk[sl] * SLAB_CH + (E[(long long)sl * nblk + b] - E[(long long)sl * nblk]);
-    __syncthreads();
-    // this lane's positions: wave * QUART + st * 64 + lane
-    int c[STEPS], r[STEPS];
+
+    unsigned c[STEPS];
     T v[STEPS];
 #pragma unroll
     for (int st = 0; st < STEPS; ++st) {
         const int i = wave * QUART + st * WAVE + lane;
-        c[st] = 0; v[st] = T(0);
-        if (i < nvalid) { c[st] = crd[p0 + i]; v[st] = vals[p0 + i]; }
+        c[st] = 0;
+        v[st] = T(0);
+        if (i < nvalid) { c[st] = (unsigned)ld_stream(crd + p0 + i); v[st] = ld_stream(vals + p0 + i); }
     }
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        const int i = wave * QUART + st * WAVE + lane;
-        r[st] = 0;
-        if (i < nvalid) {
+    const int r_lo = tile_row[b], r_hi = tile_row[b + 1];
+    for (int i = tid; i < NW * kStageSlabs; i += 256) (&woff[0][0])[i] = 0;
+    if (tid < 2 * BITS_W) { rowbits[tid] = 0; posbits[tid] = 0; }
+    if (tid == 0) { s_all[0] = ~0u; s_meta[nvalid] = ~0u; }
+    if (tid < nslabs) {
+        const int h = H[(long long)b * nslabs + tid], e = E[(long long)b * nslabs + tid];
+        int x = 0;
+        if (h & H_HEAD) {           // the slab's first entry belongs to row r_lo, which began in block bp
+            const long long bp = pos[r_lo] / BUILD_BT;
+            if ((H[bp * nslabs + tid] & H_TAIL) || e - E[(bp + 1) * nslabs + tid] > 0) x |= 1;
+        }
+        if (h & H_TAIL) {           // the slab's last entry belongs to row r_hi, which ends in block be
+            const long long be = (pos[r_hi + 1] - 1) / BUILD_BT;
+            if ((H[be * nslabs + tid] & H_HEAD) || E[be * nslabs + tid] - e - (h & H_COUNT) > 0) x |= 2;
+        }
+        gbase[tid] = make_int2(slab_chunk[tid] * SLAB_CH + e, x);
+    }
+    __syncthreads();
+    // row starts inside the block; rows that start at its first position need no bit (nothing precedes them here)
+    if (r_hi - r_lo <= ROWS_WALK) {
+        for (int r = r_lo + 1 + tid; r <= r_hi; r += 256) {
+            const long long i = (long long)pos[r] - p0;
+            if (i < nvalid) atomicOr(&rowbits[i >> 5], 1u << (i & 31));
+        }
+    } else {                        // a long run of empty rows: ask for every position instead
+        for (int i = tid; i < nvalid; i += 256) {
             const int p = (int)(p0 + i);
-            atomicAdd(&woff[wave][c[st] / W], 1);
             int lo = r_lo, hi = r_hi;
-            if (local) {
-                while (lo < hi) {
-                    const int mid = lo + ((hi - lo + 1) >> 1);
-                    if (spos[mid - r_lo] <= p) lo = mid; else hi = mid - 1;
-                }
-            } else {
-                while (lo < hi) {
-                    const int mid = lo + ((hi - lo + 1) >> 1);
-                    if (pos[mid] <= p) lo = mid; else hi = mid - 1;
-                }
+            while (lo < hi) {
+                const int mid = lo + ((hi - lo + 1) >> 1);
+                if (pos[mid] <= p) lo = mid; else hi = mid - 1;
             }
-            r[st] = lo;
+            if (i > 0 && pos[lo] == p) atomicOr(&rowbits[i >> 5], 1u << (i & 31));
         }
     }
-    __syncthreads();
-    // staging index of each slab = exclusive scan of the block's count per slab (two slabs per thread), then the
-    // waves' places inside each slab
-    {
-        const int s0 = 2 * tid, s1 = 2 * tid + 1;
-        int n0 = 0, n1 = 0;
-        if (s0 < nslabs) n0 = woff[0][s0] + woff[1][s0] + woff[2][s0] + woff[3][s0];
-        if (s1 < nslabs) n1 = woff[0][s1] + woff[1][s1] + woff[2][s1] + woff[3][s1];
-        int total;
-        const int inc = block_scan_256(n0 + n1, s_w, &total);
-        const int b0 = inc - n0 - n1;
-        if (s0 < nslabs) {
-            lbase[s0] = b0;
-            int o = b0;
-            for (int w = 0; w < NW; ++w) { const int t = woff[w][s0]; woff[w][s0] = o; o += t; }
-        }
-        if (s1 < nslabs) {
-            lbase[s1] = b0 + n0;
-            int o = b0 + n0;
-            for (int w = 0; w < NW; ++w) { const int t = woff[w][s1]; woff[w][s1] = o; o += t; }
-        }
-    }
-    __syncthreads();
-    // rank and stage (a wave touches only its own row of woff; its LDS operations execute in program order)
-    const unsigned long long below = (1ull << lane) - 1ull;
+    // rank of every entry among the wave's entries of its slab (a wave touches only its own row of woff; its LDS operations
+    // execute in program order)
+    int rank[STEPS];
 #pragma unroll
     for (int st = 0; st < STEPS; ++st) {
-        const int i = wave * QUART + st * WAVE + lane;
-        const bool valid = i < nvalid;
-        const int sl = valid ? c[st] / W : 0;
-        unsigned long long peers = __ballot(valid);
-        for (int k = 0; k < nbits; ++k) {
-            const bool one = (sl >> k) & 1;
-            const unsigned long long m = __ballot(valid && one);
-            peers &= one ? m : ~m;
+        const bool valid = wave * QUART + st * WAVE + lane < nvalid;
+        const unsigned sl = c[st] / W;
+        c[st] = (c[st] - sl * W) | (sl << 16);              // column in the slab (15 bits), slab
+        const unsigned long long all = __ballot(valid);
+        unsigned plo = (unsigned)all, phi = (unsigned)(all >> 32);     // peers: the valid lanes with this lane's slab
+        if (__ballot(valid && sl != (unsigned)__builtin_amdgcn_readfirstlane((int)sl)) != 0) {   // sorted columns of a long row: one slab
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (k >= nbits) break;
+                const int one = __builtin_amdgcn_sbfe((int)sl, k, 1);          // bit k, spread over the word
+                const unsigned long long m = __ballot(one != 0);
+                plo = __builtin_amdgcn_bitop3_b32(plo, (unsigned)m, (unsigned)one, 0x90);              // a & ~(b ^ c)
+                phi = __builtin_amdgcn_bitop3_b32(phi, (unsigned)(m >> 32), (unsigned)one, 0x90);
+            }
         }
-        int li = 0;
-        if (valid) li = woff[wave][sl] + __popcll(peers & below);
+        const int before = woff[wave][sl];
+        const int mine = (int)__builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
+        rank[st] = before + mine;
         __builtin_amdgcn_wave_barrier();
-        if (valid && (peers & below) == 0) woff[wave][sl] += __popcll(peers);
+        if (valid && mine == 0) woff[wave][sl] = (unsigned short)(before + __popc(plo) + __popc(phi));
         __builtin_amdgcn_wave_barrier();
-        if (valid) {
-            s_val[li] = v[st];
-            s_col[li] = (unsigned short)(c[st] - sl * W);
-            s_row[li] = r[st];
-            s_idx[li] = (unsigned short)i;
-            s_slab[li] = (unsigned short)sl;
+    }
+    __syncthreads();
+    {
+        int n[NW], sum = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            n[w] = tid < nslabs ? woff[w][tid] : 0;
+            sum += n[w];
+        }
+        int total;
+        int o = block_scan_256(sum, s_w, &total) - sum;
+        if (tid < nslabs) {
+            lbase[tid] = o;
+            gbase[tid].x -= o;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) { woff[w][tid] = (unsigned short)o; o += n[w]; }
+        }
+        if (tid == 0) lbase[nslabs] = total;
+        if (wave == 0) {            // row starts before each word of the bitmap
+            const int k = lane < BITS_W ? __popc(rowbits[2 * lane]) + __popc(rowbits[2 * lane + 1]) : 0;
+            const int inc = wave_scan_add(k);
+            if (lane < BITS_W) row_pre[lane] = inc - k;
         }
     }
     __syncthreads();
-    for (int i = tid; i < nvalid; i += 256) {
-        const int sl = s_slab[i];
-        const int dst = gbase[sl] + (i - lbase[sl]);
-        svals[slab_value_index<SlabOf<T>::G>(dst)] = s_val[i];
-        scol[dst] = s_col[i];
-        srow[dst] = s_row[i];
-        src[dst] = (int)(p0 + s_idx[i]);
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const int w = wave * STEPS + st, i = w * WAVE + lane;
+        const unsigned lo = (unsigned)rl((int)rowbits[2 * w], 0), hi = (unsigned)rl((int)rowbits[2 * w + 1], 0);
+        const unsigned long long word = ((unsigned long long)hi << 32) | lo;
+        const int ord = rl(row_pre[w], 0) + (int)(word & 1) + lanes_below(word >> 1);      // row starts up to position i
+        if (i < nvalid) {
+            const unsigned sl = c[st] >> 16;
+            const int li = woff[wave][sl] + rank[st];
+            s_val[li] = v[st];
+            s_col[li] = (unsigned short)c[st];
+            s_meta[li] = (unsigned)ord | ((unsigned)i << 12) | (sl << 23);
+        }
+    }
+    __syncthreads();
+    constexpr unsigned ORD = 0xfffu, SLAB = 0xff800000u;
+    unsigned mine = 0;                                 // bit k: this thread's k-th entry starts a pair
+#pragma unroll
+    for (int k = 0; k < BUILD_BT / 256; ++k) {
+        const int li = tid + 256 * k;
+        bool start = false;
+        if (li < nvalid) {
+            const unsigned m = s_meta[li], dp = m ^ s_meta[li - 1], dn = m ^ s_meta[li + 1];
+            const int2 g = gbase[m >> 23];
+            const int dst = g.x + li;
+            const bool p_same = ((dp & SLAB) == 0 & (dp & ORD) == 0) | ((dp & SLAB) != 0 & (g.y & 1) != 0);
+            const bool n_same = ((dn & SLAB) == 0 & (dn & ORD) == 0) | ((dn & SLAB) != 0 & (g.y & 2) != 0);
+            start = ((dst & (SLAB_CH - 1)) == 0) | !p_same;
+            const bool end = ((dst & (SLAB_CH - 1)) == SLAB_CH - 1) | !n_same;
+            svals[slab_value_index<SlabOf<T>::G>(dst)] = s_val[li];
+            scol[dst] = (unsigned short)(s_col[li] | (end ? 0x8000u : 0u));
+            const unsigned i = (m >> 12) & (BUILD_BT - 1);
+            if (start) atomicOr(&posbits[i >> 5], 1u << (i & 31));
+        }
+        const unsigned long long w = __ballot(start);
+        if (lane == 0) startbits[4 * k + wave] = w;
+        mine |= start ? 1u << k : 0u;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const int k = lane < BITS_W ? __popcll(startbits[lane]) : 0;
+        const int inc = wave_scan_add(k);
+        if (lane <= BITS_W) start_pre[lane] = inc - k;
+    } else if (wave == 1) {
+        const unsigned lo = lane < BITS_W ? posbits[2 * lane] : 0, hi = lane < BITS_W ? posbits[2 * lane + 1] : 0;
+        const int k = __popc(lo) + __popc(hi);
+        const int inc = wave_scan_add(k);
+        if (lane < BITS_W) {
+            pos_pre[lane] = inc - k;
+            pbits[(long long)b * BITS_W + lane] = ((unsigned long long)hi << 32) | lo;
+            pbits_pre[(long long)b * BITS_W + lane] = (unsigned short)(inc - k);
+        }
+    }
+    __syncthreads();
+    auto starts_before = [&](int li) {                 // starts at staging places below li
+        const int w = li >> 6;
+        return li >= BUILD_BT ? start_pre[BITS_W] : start_pre[w] + __popcll(startbits[w] & ((1ull << (li & 63)) - 1ull));
+    };
+    if (tid < nslabs) {
+        const int n0 = starts_before(lbase[tid]), n1 = starts_before(lbase[tid + 1]);
+        sbase[tid] = n0;
+        N[(long long)b * (nslabs + 1) + tid] = (unsigned short)(n1 - n0);
+    }
+    if (tid == 0) N[(long long)b * (nslabs + 1) + nslabs] = (unsigned short)start_pre[BITS_W];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < BUILD_BT / 256; ++k) {
+        const int w = 4 * k + wave;
+        if (__ballot((mine >> k) & 1u) == 0) continue;
+        const int nth_start = start_pre[w] + lanes_below(startbits[w]);
+        if ((mine >> k) & 1u) {
+            const int li = tid + 256 * k;
+            const unsigned m = s_meta[li], sl = m >> 23;
+            const int dst = gbase[sl].x + li;
+            const unsigned e = (sl << 16) | (unsigned)(nth_start - sbase[sl]);
+            const unsigned i = (m >> 12) & (BUILD_BT - 1), iw = i >> 6;
+            const unsigned long long word = ((unsigned long long)posbits[2 * iw + 1] << 32) | posbits[2 * iw];
+            starts[p0 + pos_pre[iw] + __popcll(word & ((1ull << (i & 63)) - 1ull))] = (int)e;
+            if ((dst & (SLAB_CH - 1)) == 0) chunk_at[dst / SLAB_CH] = ((unsigned long long)b << 32) | e;
+        }
     }
 }
 
+// qidx: a wave per block writes the pair numbers of the block's starts, in CSR order
+__global__ __launch_bounds__(256) void k_block_pairs(const unsigned short *__restrict__ N, const int *__restrict__ F,
+                                                     const int *__restrict__ slab_pair, const int *__restrict__ starts, int nslabs,
+                                                     int nblk, int *__restrict__ qidx)
+{
+    const int g = xcd_tile(blockIdx.x, (nblk + 3) / 4), lane = threadIdx.x & (WAVE - 1);
+    const int b = g * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    if (g < 0 || b >= nblk) return;
+    const long long row = (long long)b * (nslabs + 1);
+    const int n = N[row + nslabs], q0 = F[row + nslabs];
+    for (int k0 = lane; k0 < n; k0 += 8 * WAVE) {          // 337 starts per block on average: one round, all loads in flight
+        int e[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) e[u] = k0 + u * WAVE < n ? ld_stream(starts + (long long)b * BUILD_BT + k0 + u * WAVE) : 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) e[u] = slab_pair[e[u] >> 16] + F[row + (e[u] >> 16)] + (e[u] & 0xffff);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (k0 + u * WAVE < n) qidx[q0 + k0 + u * WAVE] = e[u];
+    }
+}
+
+// Thread g: row g's first listed pair (the starts before pos[g]: the block's count plus the bits below it) and the table
+// entries of the row-list tiles that begin in the row; chunk g's first pair; pad slot g % 512 of slab g / 512.
+template <typename T>
+__global__ __launch_bounds__(256) void k_block_rows(int rows, int nnz, const int *__restrict__ pos, const int *__restrict__ F,
+                                                    const unsigned long long *__restrict__ pbits,
+                                                    const unsigned short *__restrict__ pbits_pre,
+                                                    const unsigned long long *__restrict__ chunk_at,
+                                                    const int *__restrict__ total, const int *__restrict__ slab_pair,
+                                                    const int *__restrict__ slab_chunk, int nslabs, int tile,
+                                                    const int *__restrict__ meta, T *__restrict__ svals,
+                                                    unsigned short *__restrict__ scol, int *__restrict__ chunk_pair,
+                                                    int *__restrict__ qpos, int *__restrict__ qtile_row)
+{
+    const long long g = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int nq = meta[2], S1 = nslabs + 1;
+    auto listed = [&](int p) -> int {                  // starts at CSR positions below p
+        if (p >= nnz) return nq;
+        const long long b = p / BUILD_BT;
+        const int i = p % BUILD_BT;
+        const long long w = b * BITS_W + (i >> 6);
+        return F[b * S1 + nslabs] + pbits_pre[w] + __popcll(pbits[w] & ((1ull << (i & 63)) - 1ull));
+    };
+    int t_lo = 0, t_hi = -1;
+    if (g <= rows) {
+        const int q = listed(pos[g]);
+        qpos[g] = q;
+        if (g < rows) {
+            const int q1 = listed(pos[g + 1]);
+            if (q1 > q) {
+                t_lo = (int)(((long long)q + tile - 1) / tile);
+                t_hi = (q1 - 1) / tile;
+            }
+        } else qtile_row[((long long)nq + tile - 1) / tile] = rows;
+    }
+    const int n = t_hi - t_lo + 1;
+    if (n > 0 && n <= 16)
+        for (int t = t_lo; t <= t_hi; ++t) qtile_row[t] = (int)g;
+    unsigned long long big = __ballot(n > 16);
+    while (big) {
+        const int src = __ffsll((long long)big) - 1;
+        big &= big - 1;
+        const int lo = __shfl(t_lo, src, WAVE), hi = __shfl(t_hi, src, WAVE), row = __shfl((int)g, src, WAVE);
+        for (int t = lo + lane; t <= hi; t += WAVE) qtile_row[t] = row;
+    }
+    if (g < meta[0] / SLAB_CH) {
+        const unsigned long long a = chunk_at[g];
+        const int sl = (int)((a >> 16) & 0xffff);
+        chunk_pair[g] = slab_pair[sl] + F[(long long)(a >> 32) * S1 + sl] + (int)(a & 0xffff);
+    }
+    if (g < (long long)nslabs * SLAB_CH) {
+        const int sl = (int)(g / SLAB_CH);
+        const long long hi = (long long)slab_chunk[sl + 1] * SLAB_CH;
+        const long long j = (long long)slab_chunk[sl] * SLAB_CH + total[sl] + g % SLAB_CH;
+        if (j < hi) {               // value 0, column 0; the last one ends the pads' pair
+            svals[slab_value_index<SlabOf<T>::G>((int)j)] = T(0);
+            scol[j] = j + 1 == hi ? 0x8000u : 0u;
+        }
+    }
+}
+
+// ---- more slabs: a row and a source position per slot, pairs found from them
 // Pairs.  One wave per chunk; slot j = chunk * CH + it * 64 + lane (it = 0 .. 7), so that the rows of the slots are read
 // with full-width loads.  A slot starts a pair when it is the chunk's first or its row differs from the row of the slot
 // before it (the lane below, or lane 63 of the round before); m[it] = the ballot of the starts of round it.
@@ -740,8 +1099,23 @@ SlabBuildSpace carve_slab_build(void *base, int64_t rows, int64_t cols, int64_t 
     char *p = static_cast<char *>(base);
     size_t o = 0;
     auto take = [&](size_t bytes) { char *q = p + o; o += align256(bytes); return q; };
+    w = SlabBuildSpace{};
     w.meta = reinterpret_cast<int32_t *>(take(256));
     w.tile_row = reinterpret_cast<int32_t *>(take((size_t)(nblk + 1) * 4));
+    if (S <= kStageSlabs) {
+        const size_t S1 = (size_t)S + 1;
+        w.total = reinterpret_cast<int32_t *>(take(3 * S1 * 4));
+        w.part = reinterpret_cast<int32_t *>(take((size_t)((nblk + COL_CH - 1) / COL_CH) * S1 * 4));
+        w.H16 = reinterpret_cast<uint16_t *>(take((size_t)nblk * (size_t)S * 2));
+        w.N16 = reinterpret_cast<uint16_t *>(take((size_t)nblk * S1 * 2));
+        w.H = reinterpret_cast<int32_t *>(take((size_t)nblk * S1 * 4));
+        w.src = reinterpret_cast<int32_t *>(take((size_t)(nnz + 1) * 4));                 // starts of pairs, per block
+        w.pbits = reinterpret_cast<unsigned long long *>(take((size_t)nblk * BITS_W * 8));
+        w.pbits_pre = reinterpret_cast<uint16_t *>(take((size_t)nblk * BITS_W * 2));
+        w.chunk_at = reinterpret_cast<unsigned long long *>(take((size_t)(nmax / SLAB_CH + 1) * 8));
+        w.bytes = o;
+        return w;
+    }
     w.H = reinterpret_cast<int32_t *>(take((size_t)(S * nblk + 1) * 4));
     w.srow = reinterpret_cast<int32_t *>(take((size_t)(nmax + 1) * 4));
     w.src = reinterpret_cast<int32_t *>(take((size_t)(nmax + 1) * 4));
@@ -755,12 +1129,13 @@ SlabBuildSpace carve_slab_build(void *base, int64_t rows, int64_t cols, int64_t 
     return w;
 }
 
-// Enqueues the whole analysis on `s`.  When it has run, meta[0..2] = {slots, pairs, listed pairs}.
+// Enqueues the whole analysis on `s`.  When it has run, meta[0..2] = {slots, pairs, listed pairs}.  qtile_row (the position
+// cut of the row lists) is written for at most kStageSlabs slabs; with more the caller makes it once it knows their number.
 template <typename T>
 static hipError_t launch_slab_build_t(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                       const T *vals, const SlabBuildSpace &w, T *svals, uint16_t *scol,
                                       int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx,
-                                      hipStream_t s)
+                                      int32_t qtile, int32_t *qtile_row, hipStream_t s)
 {
     constexpr int W = SlabOf<T>::W;
     const int S = (int)(((int64_t)cols + W - 1) / W);
@@ -769,20 +1144,39 @@ static hipError_t launch_slab_build_t(int32_t rows, int32_t cols, int32_t nnz, c
     unsigned short *scol_d = reinterpret_cast<unsigned short *>(scol);
     hipError_t e = launch_partition(rows, nnz, pos, BUILD_BT, 0, w.tile_row, s);
     if (e != hipSuccess) return e;
-    const size_t lds = (size_t)S * 4;
     int nbits = 0;                                  // bits of a slab number
     while ((1 << nbits) < S) ++nbits;
+    if (S <= kStageSlabs) {
+        const int S1 = S + 1, nparts = (nblk + COL_CH - 1) / COL_CH, grid = xcd_grid(nblk);
+        int32_t *total = w.total, *starts_total = w.total + S1, *slab_pair = w.total + 2 * S1, *E = w.H, *F = w.H;
+        const int vec_ok = (reinterpret_cast<uintptr_t>(crd) & 15) == 0;
+        PSK_LAUNCH(k_block_hist<W>, dim3(grid), dim3(256), 0, s, nnz, pos, crd, w.tile_row, S, nblk, vec_ok, w.H16);
+        PSK_LAUNCH(k_col_chunks<false>, dim3(nparts), dim3(256), 0, s, w.H16, nblk, S, w.part, E);
+        PSK_LAUNCH(k_col_scan, dim3(S), dim3(256), 0, s, w.part, nparts, S, total);
+        PSK_LAUNCH(k_col_chunks<true>, dim3(nparts), dim3(256), 0, s, w.H16, nblk, S, w.part, E);
+        PSK_LAUNCH(k_block_bases, dim3(1), dim3(256), 0, s, total, S, slab_chunk, w.meta);
+        PSK_LAUNCH(k_block_place<T>, dim3(grid), dim3(256), 0, s, nnz, pos, crd, vals, w.tile_row, w.H16, E, slab_chunk, S, nblk,
+                   nbits, svals, scol_d, w.N16, w.src, w.pbits, w.pbits_pre, w.chunk_at);
+        PSK_LAUNCH(k_col_chunks<false>, dim3(nparts), dim3(256), 0, s, w.N16, nblk, S1, w.part, F);
+        PSK_LAUNCH(k_col_scan, dim3(S1), dim3(256), 0, s, w.part, nparts, S1, starts_total);
+        PSK_LAUNCH(k_col_chunks<true>, dim3(nparts), dim3(256), 0, s, w.N16, nblk, S1, w.part, F);
+        PSK_LAUNCH(k_block_bases2, dim3(1), dim3(256), 0, s, total, starts_total, S, slab_chunk, slab_pair, chunk_pair, w.meta);
+        PSK_LAUNCH(k_block_pairs, dim3(xcd_grid((nblk + 3) / 4)), dim3(256), 0, s, w.N16, F, slab_pair, w.src, S, nblk, qidx);
+        int64_t span = (int64_t)rows + 1;
+        if (nmax / SLAB_CH > span) span = nmax / SLAB_CH;
+        if ((int64_t)S * SLAB_CH > span) span = (int64_t)S * SLAB_CH;
+        PSK_LAUNCH(k_block_rows<T>, dim3((unsigned)((span + 255) / 256)), dim3(256), 0, s, rows, nnz, pos, F, w.pbits, w.pbits_pre,
+                   w.chunk_at, total, slab_pair, slab_chunk, S, qtile, w.meta, svals, scol_d, chunk_pair, qpos, qtile_row);
+        return take_launch_status();
+    }
+    const size_t lds = (size_t)S * 4;
     PSK_LAUNCH(k_slab_hist, dim3(nblk), dim3(256), (unsigned)lds, s, nnz, crd, W, S, nblk, w.H);
     PSK_LAUNCH(k_fill_int, dim3(1), dim3(64), 0, s, w.H + (long long)S * nblk, 1ll, 0);      // the scan's total slot
     launch_scan(w.H, w.H, (int64_t)S * nblk + 1, w.scan_tmp, false, s);
     PSK_LAUNCH(k_slab_bases, dim3(1), dim3(256), 0, s, w.H, S, nblk, slab_chunk, w.meta);
     PSK_LAUNCH(k_slab_pads<T>, dim3(S), dim3(64), 0, s, w.H, nblk, slab_chunk, svals, scol_d, w.srow, w.src);
-    if (S <= STAGE_SLABS)
-        PSK_LAUNCH(k_slab_scatter_staged<T>, dim3(nblk), dim3(256), 0, s, rows, nnz, pos, crd, vals, w.tile_row, w.H,
-                   slab_chunk, S, nblk, nbits, svals, scol_d, w.srow, w.src);
-    else
-        PSK_LAUNCH(k_slab_scatter<T>, dim3(nblk), dim3(64), (unsigned)(lds + SCATTER_ROWS * 4), s, rows, nnz, pos, crd, vals,
-                   w.tile_row, w.H, slab_chunk, S, nblk, nbits, svals, scol_d, w.srow, w.src);
+    PSK_LAUNCH(k_slab_scatter<T>, dim3(nblk), dim3(64), (unsigned)(lds + SCATTER_ROWS * 4), s, rows, nnz, pos, crd, vals,
+               w.tile_row, w.H, slab_chunk, S, nblk, nbits, svals, scol_d, w.srow, w.src);
     const int nmaxchunks = (int)(nmax / SLAB_CH);
     PSK_LAUNCH(k_slab_count, dim3((unsigned)(nmaxchunks / 4 + 1)), dim3(256), 0, s, w.meta, w.srow, nmaxchunks, w.F);
     launch_scan(w.F, chunk_pair, (int64_t)nmaxchunks + 1, w.scan_tmp, false, s);
@@ -802,16 +1196,18 @@ static hipError_t launch_slab_build_t(int32_t rows, int32_t cols, int32_t nnz, c
 
 hipError_t launch_slab_build(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                              const float *vals, const SlabBuildSpace &w, float *svals, uint16_t *scol,
-                             int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx, hipStream_t s)
+                             int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx, int32_t qtile,
+                             int32_t *qtile_row, hipStream_t s)
 {
-    return launch_slab_build_t<float>(rows, cols, nnz, pos, crd, vals, w, svals, scol, chunk_pair, slab_chunk, qpos, qidx, s);
+    return launch_slab_build_t<float>(rows, cols, nnz, pos, crd, vals, w, svals, scol, chunk_pair, slab_chunk, qpos, qidx, qtile, qtile_row, s);
 }
 
 hipError_t launch_slab_build_f64(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                  const double *vals, const SlabBuildSpace &w, double *svals, uint16_t *scol,
-                                 int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx, hipStream_t s)
+                                 int32_t *chunk_pair, int32_t *slab_chunk, int32_t *qpos, int32_t *qidx, int32_t qtile,
+                             int32_t *qtile_row, hipStream_t s)
 {
-    return launch_slab_build_t<double>(rows, cols, nnz, pos, crd, vals, w, svals, scol, chunk_pair, slab_chunk, qpos, qidx, s);
+    return launch_slab_build_t<double>(rows, cols, nnz, pos, crd, vals, w, svals, scol, chunk_pair, slab_chunk, qpos, qidx, qtile, qtile_row, s);
 }
 
 #ifdef PSK_CU_TRACE
