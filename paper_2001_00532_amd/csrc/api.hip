@@ -454,10 +454,11 @@ int psk_spmm_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, co
         if (ntiles == 0) {
             e = launch_fill_zero_2d(C, rows, k, ldc, s);
         } else {
-            e = launch_spmm_csr_main((int32_t)rows, (int32_t)nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s);
+            e = launch_spmm_csr_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s);
         }
     }
-    if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess) e = launch_carry_fixup(ntiles, 1, k, ldc, tile, pos, ws, C, s);
+    if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
+        e = launch_carry_fixup(ntiles, 1, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, false, spmm_overhang(tile));
     return hip_status(e);
 }
 
@@ -511,7 +512,8 @@ int psk_spmm_bcsr(int64_t brows, int64_t bcols, int64_t nblocks, int32_t bs, con
             e = launch_spmm_bcsr_main(bs, (int32_t)brows, (int32_t)nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s);
         }
     }
-    if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess) e = launch_carry_fixup(ntiles, bs, k, ldc, tile, pos, ws, C, s);
+    if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
+        e = launch_carry_fixup(ntiles, bs, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, false, spmm_overhang(tile));
     return hip_status(e);
 }
 

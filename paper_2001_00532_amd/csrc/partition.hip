@@ -232,11 +232,11 @@ hipError_t launch_fill_zero_2d(float *p, int64_t rows, int32_t width, int64_t ld
 // in the walk depends on another.  The run is added in tile order, in fp64, to the owner's partial
 // result.  out element (r, e) lives at out[(r*nsub + e / k) * ld + e % k].
 __device__ __forceinline__ int run_length(const int *__restrict__ pos, const int *__restrict__ pos2, int r, int t,
-                                          int tile, int shift, int ntiles)
+                                          int tile, int shift, int ntiles, int over)
 {
     const int last = (pos2 ? pos2[pos[r + 1]] : pos[r + 1]) - 1;
     int e = shift >= 0 ? last >> shift : last / tile;
-    int len = e - t + 1;
+    int len = e - t + (last - e * tile < over ? 0 : 1);     // a short tail has no record of its own
     len = len < 1 ? 1 : len;
     return len > ntiles - t ? ntiles - t : len;
 }
@@ -252,7 +252,8 @@ __global__ __launch_bounds__(256) void k_carry_fixup1(int ntiles, long long ld, 
                                                       const int *__restrict__ pos,
                                                       const int *__restrict__ carry_row,
                                                       const V *__restrict__ carry_val,
-                                                      V *__restrict__ out, int carry_groups, int *__restrict__ gap)
+                                                      V *__restrict__ out, int carry_groups, int *__restrict__ gap,
+                                                      const int *__restrict__ rowmap)
 {
     if ((int)blockIdx.x >= carry_groups) {
         const int fillers = (int)gridDim.x - carry_groups, me = (int)blockIdx.x - carry_groups;
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(256) void k_carry_fixup1(int ntiles, long long ld, 
     if (t < ntiles) {
         r = carry_row[t];
         const int prev = t > 0 ? carry_row[t - 1] : -1;
-        if (r >= 0 && prev != r) len = run_length(pos, nullptr, r, t, tile, shift, ntiles);
+        if (r >= 0 && prev != r) len = run_length(pos, nullptr, r, t, tile, shift, ntiles, 0);
     }
     if (len > 0 && len <= 8) {
         V v[8];
@@ -286,7 +287,8 @@ __global__ __launch_bounds__(256) void k_carry_fixup1(int ntiles, long long ld, 
         double sum = 0.0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) sum += (double)v[i];
-        out[r * ld] = (V)((double)out[r * ld] + sum);
+        V *dst = out + (rowmap ? rowmap[r] : r) * ld;
+        *dst = (V)((double)*dst + sum);
     }
     unsigned long long big = __ballot(len > 8);
     while (big) {
@@ -297,67 +299,84 @@ __global__ __launch_bounds__(256) void k_carry_fixup1(int ntiles, long long ld, 
         for (int u = lane; u < n; u += WAVE) acc += (double)carry_val[t0 + u];
 #pragma unroll
         for (int m = 1; m < WAVE; m <<= 1) acc += __shfl_xor(acc, m, WAVE);
-        if (lane == src) out[row * ld] = (V)((double)out[row * ld] + acc);
+        if (lane == src) {
+            V *dst = out + (rowmap ? rowmap[row] : row) * ld;
+            *dst = (V)((double)*dst + acc);
+        }
     }
 }
 
-// any width: a lane per (tile, element); the run is walked eight records at a time.
-__global__ __launch_bounds__(256) void k_carry_fixup(int ntiles, int width, int nsub, int k, long long ld, int tile,
-                                                     int shift, const int *__restrict__ pos,
+// any width: a wave looks at up to 64 tiles at once, one per lane, and adds the runs that begin among them, one run per group
+// of 2^eshift lanes (the elements of a record); a run is walked eight records at a time.
+__global__ __launch_bounds__(256) void k_carry_fixup(int ntiles, int per_wave, int eshift, int width, int nsub, int k,
+                                                     long long ld, int tile, int shift, int over,
+                                                     const int *__restrict__ pos,
                                                      const int *__restrict__ pos2,
                                                      const int *__restrict__ rowmap,
                                                      const int *__restrict__ carry_row,
                                                      const float *__restrict__ carry_val,
                                                      float *__restrict__ out)
 {
-    const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long total = (long long)ntiles * width;
-    if (g >= total) return;
-    int t, e;
-    if (total <= 0xffffffffll) {          // the usual case: a 32-bit division is several times cheaper
-        const unsigned gg = (unsigned)g;
-        t = (int)(gg / (unsigned)width);
-        e = (int)(gg - (unsigned)t * (unsigned)width);
-    } else {
-        t = (int)(g / width);
-        e = (int)(g % width);
+    const int lane = threadIdx.x & (WAVE - 1);
+    const long long first = ((long long)blockIdx.x * (256 / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE)) * per_wave;
+    int t_l = 0, row_l = 0, len_l = 0;
+    if (lane < per_wave && first + lane < ntiles) {
+        t_l = (int)first + lane;
+        const int r = carry_row[t_l], prev = t_l > 0 ? carry_row[t_l - 1] : -1;
+        if (r >= 0 && prev != r) {
+            len_l = run_length(pos, pos2, r, t_l, tile, shift, ntiles, over);
+            row_l = rowmap ? rowmap[r] : r;
+        }
     }
-    const int r = carry_row[t];
-    if (r < 0) return;
-    if (t > 0 && carry_row[t - 1] == r) return;
-    const int len = run_length(pos, pos2, r, t, tile, shift, ntiles);
-    double sum = 0.0;
-    for (int u = 0; u < len; u += 8) {
-        float v[8];
+    const unsigned long long heads = __ballot(len_l > 0);
+    const int at_once = WAVE >> eshift;                       // runs per round
+    const unsigned long long mask = ~0ull >> (WAVE - at_once);
+    for (int h = 0; h < per_wave; h += at_once) {
+        if (((heads >> h) & mask) == 0) continue;
+        const int src = h + (lane >> eshift);
+        const int t = __shfl(t_l, src, WAVE), len = __shfl(len_l, src, WAVE);
+        const long long row = __shfl(row_l, src, WAVE);
+        if (len == 0) continue;
+        for (int e = lane & ((1 << eshift) - 1); e < width; e += 1 << eshift) {
+            float *dst = out + (row * nsub + (nsub == 1 ? 0 : e / k)) * ld + (nsub == 1 ? e : e % k);
+            const double had = (double)*dst;
+            double sum = 0.0;
+            for (int u = 0; u < len; u += 8) {
+                float v[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = u + i < len ? carry_val[(long long)(t + u + i) * width + e] : 0.0f;
+                for (int i = 0; i < 8; ++i) v[i] = u + i < len ? carry_val[(long long)(t + u + i) * width + e] : 0.0f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) sum += (double)v[i];
+                for (int i = 0; i < 8; ++i) sum += (double)v[i];
+            }
+            *dst = (float)(had + sum);
+        }
     }
-    const long long row = rowmap ? rowmap[r] : r;
-    float *dst = out + (row * nsub + e / k) * ld + e % k;
-    *dst = (float)((double)*dst + sum);
 }
 
 hipError_t launch_carry_fixup(int32_t ntiles, int32_t nsub, int32_t k, int64_t ld, int32_t tile, const int32_t *pos,
                               const Workspace &w, float *out, hipStream_t s, const int32_t *pos2,
-                              const int32_t *rowmap, bool gaps)
+                              const int32_t *rowmap, bool gaps, int32_t over)
 {
     const int width = nsub * k;
     gaps = gaps && width == 1 && !pos2 && !rowmap && ntiles >= 1;
     if (ntiles <= 1 && !gaps) return hipSuccess;   // tile 0 never has a carry
     int shift = -1;
     if ((tile & (tile - 1)) == 0) { shift = 0; while ((1 << shift) < tile) ++shift; }
-    if (width == 1 && !pos2 && !rowmap) {
+    if (width == 1 && !pos2 && over == 0) {
         const int carry_groups = ntiles <= 1 ? 0 : (ntiles + 255) / 256;
         int *gap = gaps ? w.gap : nullptr;
         PSK_LAUNCH(k_carry_fixup1<float>, dim3((unsigned)(carry_groups + (gaps ? kGapFillGroups : 0))), dim3(256), 0, s,
-                   ntiles, (long long)ld, tile, shift, pos, w.carry_row, w.carry_val, out, carry_groups, gap);
+                   ntiles, (long long)ld, tile, shift, pos, w.carry_row, w.carry_val, out, carry_groups, gap, rowmap);
         return take_launch_status();
     }
-    const int64_t n = (int64_t)ntiles * width;
-    PSK_LAUNCH(k_carry_fixup, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ntiles, width, nsub, k,
-                       (long long)ld, tile, shift, pos, pos2, rowmap, w.carry_row, w.carry_val, out);
+    int eshift = 0;
+    while ((1 << eshift) < width && eshift < 6) ++eshift;
+    // tiles per wave: a full round of runs at least, more only when the waves would be more than the chip holds at once
+    int per_wave = WAVE >> eshift;
+    while (per_wave < WAVE && (int64_t)per_wave * 8192 < ntiles) per_wave *= 2;
+    const int64_t waves = ((int64_t)ntiles + per_wave - 1) / per_wave;
+    PSK_LAUNCH(k_carry_fixup, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, ntiles, per_wave, eshift, width, nsub, k,
+                       (long long)ld, tile, shift, over, pos, pos2, rowmap, w.carry_row, w.carry_val, out);
     return take_launch_status();
 }
 
@@ -371,7 +390,8 @@ hipError_t launch_carry_fixup_f64(int32_t ntiles, int32_t tile, const int32_t *p
     const int carry_groups = ntiles <= 1 ? 0 : (ntiles + 255) / 256;
     int *gap = gaps ? w.gap : nullptr;
     PSK_LAUNCH(k_carry_fixup1<double>, dim3((unsigned)(carry_groups + (gaps ? kGapFillGroups : 0))), dim3(256), 0, s, ntiles,
-               1ll, tile, shift, pos, w.carry_row, reinterpret_cast<const double *>(w.carry_val), out, carry_groups, gap);
+               1ll, tile, shift, pos, w.carry_row, reinterpret_cast<const double *>(w.carry_val), out, carry_groups, gap,
+               static_cast<const int *>(nullptr));
     return take_launch_status();
 }
 

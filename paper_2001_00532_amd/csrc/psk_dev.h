@@ -86,6 +86,53 @@ __device__ __forceinline__ void st_vec(float *p, const float (&s)[VEC])
     __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
 }
 
+// the same with the alignment of a float only
+typedef float v2f_u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));
+template <int VEC> struct VecU;
+template <> struct VecU<1> { typedef float type; };
+template <> struct VecU<2> { typedef v2f_u type; };
+template <> struct VecU<4> { typedef v4f_u type; };
+template <int VEC>
+__device__ __forceinline__ float vec_at(const typename VecU<VEC>::type &v, int i)
+{
+    if constexpr (VEC == 1) return v;
+    else return v[i];
+}
+
+// Positions and rows of tile t where a row that reaches at most `over` positions past the end of a tile is finished by that
+// tile (SpMM kernels: a carry record is k floats written, read and added again, a few more positions cost nothing).  A row
+// that reaches further ends at the border as the cut says and its part in the next tile becomes that tile's carry.  Both
+// tiles at a border decide from pos alone and decide alike; over <= T, so a tile holds at most T + over positions.
+struct TileSpan {
+    int t0, cnt;           // first position, number of positions (0 when the previous tile took them all)
+    int r0, r1;            // table entries
+    int rbeg, rend;        // rows written here (rbeg is carried when has_carry)
+    bool has_carry;        // row r0 began in an earlier tile
+    bool straddle;         // row r1 goes on in the next tile
+};
+__device__ __forceinline__ TileSpan tile_span(const int *__restrict__ tile_row, const int *__restrict__ pos, int t, int T, int nnz,
+                                              int ntiles, int over)
+{
+    TileSpan s;
+    const int c0 = t * T, c1 = nnz - c0 < T ? nnz : c0 + T;
+    s.r0 = tile_row[t];
+    s.r1 = tile_row[t + 1];
+    const bool last = t + 1 == ntiles;                    // r1 = rows: no row goes on
+    const int b0 = pos[s.r0], e0 = pos[s.r0 + 1], b1 = pos[s.r1], e1 = last ? nnz : pos[s.r1 + 1];
+    const bool inside = t > 0 && b0 < c0;                 // the tile begins inside row r0
+    const bool taken = inside && e0 - c0 <= over;         // ... whose rest the previous tile took
+    s.has_carry = inside && !taken;
+    s.rbeg = t == 0 ? 0 : (taken ? s.r0 + 1 : s.r0);
+    s.t0 = taken ? e0 : c0;
+    const bool open = !last && b1 < c1;                   // row r1 goes on behind the border
+    const bool take = open && e1 - c1 <= over;
+    s.straddle = open && !take;
+    s.rend = open ? s.r1 + 1 : s.r1;
+    s.cnt = (take ? e1 : c1) - s.t0;
+    return s;
+}
+
 // ---- per-workgroup trace (only in the instrumented build, -DPSK_CU_TRACE): every workgroup of a traced kernel
 // records its start and end on the 100 MHz wall clock and the compute unit it ran on (HW_ID: cu, sh, se;
 // XCC_ID: die) into a caller-supplied buffer of 3 x 64 bits per workgroup, from which the host forms each
@@ -131,7 +178,6 @@ inline hipError_t cu_trace_set_here(void *buf, unsigned records)
 // positions two wide loads replace four narrow ones.  The choice is made per wave (one ballot) so that
 // both variants stay straight-line code with every load issued before the first use; unstructured
 // matrices never take the wide path and keep their 4-byte gathers.
-typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));
 struct RunPlan { int lenA; int colB; bool ok; };
 __device__ __forceinline__ RunPlan run_plan(v4i c, int cols)
 {

@@ -84,10 +84,11 @@ hipError_t launch_probe_locality(int32_t nnz, const int32_t *crd, int32_t *resul
 // out[(row*nsub + e / k) * ld + e % k].
 // `pos2` (optional): two-level hierarchy, a row's last position is pos2[pos[r+1]] - 1.  `rowmap` (optional):
 // row r of the hierarchy is stored at output row rowmap[r].
+// over: the tiles take up to that many positions of a row past their end, such a tail has no record (SpMM)
 // gaps = true (CSR SpMV only): extra workgroups clear the long runs of empty rows that the tile kernel listed in w.gap
 hipError_t launch_carry_fixup(int32_t ntiles, int32_t nsub, int32_t k, int64_t ld, int32_t tile, const int32_t *pos,
                               const Workspace &w, float *out, hipStream_t s, const int32_t *pos2 = nullptr,
-                              const int32_t *rowmap = nullptr, bool gaps = false);
+                              const int32_t *rowmap = nullptr, bool gaps = false, int32_t over = 0);
 // A tile whose rows span more than this many rows does not walk them: it finds the rows of its positions by search
 // and leaves the run of empty rows to the fix-up step (which clears it with many workgroups).
 constexpr int32_t kGapRows = 32768;
@@ -123,12 +124,15 @@ hipError_t launch_carry_fixup_f64(int32_t ntiles, int32_t tile, const int32_t *p
                                   hipStream_t s, bool gaps = false);
 
 // CSR SpMM
+// a row that reaches at most this far past the end of a tile is finished by that tile (tile_span in psk_dev.h)
+inline int32_t spmm_overhang(int32_t tile) { return tile / 2; }
 bool spmm_csr_tile_ok(int32_t tile);
-hipError_t launch_spmm_csr_main(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd,
+hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
                                 int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s);
-// k <= 32: the wave is split into groups that take consecutive positions
-hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd,
+// k <= kGroupColumns: the wave is split into groups that take consecutive positions
+constexpr int32_t kGroupColumns = 128;
+hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
                                   int32_t tile, const Workspace &w, hipStream_t s);
 hipError_t launch_spmm_rowsplit(int32_t rows, const int32_t *pos, const int32_t *crd, const float *vals,

@@ -31,11 +31,11 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
                                                   float *__restrict__ C, long long ldc,
                                                   const int *__restrict__ tile_row,
                                                   int *__restrict__ carry_row,
-                                                  float *__restrict__ carry_val, int ntiles, int T)
+                                                  float *__restrict__ carry_val, int ntiles, int T, int over)
 {
     constexpr int THREADS = 256, NW = THREADS / WAVE, KW = WAVE * VEC;
     constexpr int U = BS == 1 ? 8 : (BS == 2 ? 4 : (BS == 4 ? 2 : 1));   // positions whose B rows are in flight together
-    extern __shared__ int sflag[];                // T ints
+    extern __shared__ int sflag[];                // T + over ints
     __shared__ float srec[2 * NW][BS][KW];
     __shared__ int srec_row[2 * NW];              // -2 unused, -1 open segment, >= 0 row that ended
 
@@ -45,21 +45,15 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
     // BS == 1: tell the compiler that the wave index is uniform (scalar loop control).  With blocks the
     // generated code measured 3 % slower that way, so there it stays a per-lane value.
     const int wave = BS == 1 ? __builtin_amdgcn_readfirstlane(tid / WAVE) : tid / WAVE;
-    const int t0 = t * T;
-    const int cnt = (nnz - t0 < T) ? nnz - t0 : T;
-    const int t1 = t0 + cnt;
+    const TileSpan span = tile_span(tile_row, pos, t, T, nnz, ntiles, over);
+    const int t0 = span.t0, cnt = span.cnt, r0 = span.r0, r1 = span.r1, rbeg = span.rbeg, rend = span.rend;
+    const bool has_carry = span.has_carry, straddle = span.straddle;
     const int col = blockIdx.y * KW + lane * VEC;
     const bool active = col < k;
     const int lcol = active ? col : 0;            // lanes past the last column load column 0 and store nothing
 
-    for (int i = tid; i < T; i += THREADS) sflag[i] = -1;
+    for (int i = tid; i < cnt; i += THREADS) sflag[i] = -1;
     if (tid < 2 * NW) srec_row[tid] = -2;
-
-    const int r0 = tile_row[t], r1 = tile_row[t + 1];
-    const bool has_carry = (t > 0) && (pos[r0] < t0);
-    const int rbeg = (t == 0) ? 0 : r0;
-    const bool straddle = pos[r1] != t1;          // row r1 continues into the next tile
-    const int rend = straddle ? r1 + 1 : r1;
     if (tid == 0 && blockIdx.y == 0 && !has_carry) carry_row[t] = -1;
     __syncthreads();
 
@@ -86,7 +80,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
     __syncthreads();
 
     // ---- the wave's positions
-    const int CH = T / NW;
+    const int CH = (cnt + NW - 1) / NW;
     const int wbeg = wave * CH < cnt ? wave * CH : cnt;
     const int wend = wbeg + CH < cnt ? wbeg + CH : cnt;
     float acc[BS][VEC] = {};
@@ -242,10 +236,11 @@ static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos,
     if (BS == 8 && vec == 4) vec = 2;             // 8 x 8 blocks: the LDS records of four columns per lane do not fit
     const int kw = WAVE * vec;
     const dim3 grid(xcd_grid(ntiles), (k + kw - 1) / kw);
-    const size_t lds = (size_t)tile * sizeof(int);
+    const int32_t over = spmm_overhang(tile);
+    const size_t lds = (size_t)(tile + over) * sizeof(int);
 #define PSK_GO(V)                                                                                              \
     PSK_LAUNCH((k_spmm_pos<BS, V>), grid, dim3(256), lds, s, rows, nnz, pos, crd, vals, B, k,          \
-                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile)
+                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over)
     if (vec == 4) {
         if constexpr (BS < 8) PSK_GO(4);
     } else if (vec == 2) PSK_GO(2);
@@ -254,11 +249,19 @@ static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos,
     return take_launch_status();
 }
 
-hipError_t launch_spmm_csr_main(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd,
+hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
                                 int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s)
 {
-    if (k <= 32) return launch_spmm_csr_narrow(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s);
+    // Groups of lanes or the wide kernel (us, 10^6 rows unless stated):
+    //   k <= 32: groups; mean row of 1 / 7 / 16 / 300 entries, k = 16: 43 / 94 / 303 against 54 / 99 / 300 for groups of one column
+    //     per lane, which they replace; 10^5 rows of 1000 entries, k = 32: 1252 against 1784
+    //   k <= 64: groups when the mean row has 8 entries or more (300: k = 40 356 against 423; 4: 189 against 181)
+    //   k <= 128: groups where a lane of the wide kernel could not own two columns and would walk A twice (16: k = 99 1223
+    //     against 1776; where it can the wide kernel is 1-3 % faster, k = 128 1190 against 1223)
+    const bool groups = k <= 32 || (k <= 64 && nnz >= 8ll * rows) ||
+                        (k > 64 && k <= kGroupColumns && pick_vec(B, k, ldb, C, ldc) == 1);
+    if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s);
     return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s);
 }
 

@@ -1,0 +1,57 @@
+"""SpMM where its kernels change over and where tiles hand rows to each other: numbers of columns around the group widths,
+rows that reach a little (finished by the tile they begin in) or far (carried) past a tile's end, rows of one and two entries
+(several ends in one step), operands whose rows are not aligned.  Oracle and bar as for the other SpMM tests:
+|got - ref| <= 1e-5 * sum |a b| + 1e-30 per element."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2001_00532_amd as psk  # noqa: E402
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def check(lengths, k, tile, bs=1, pad=1):
+    cols = 900
+    A = wl.csr_from_lengths(np.asarray(lengths), cols, seed=k + 1, bs=bs)
+    Bh = wl.dense_uniform(cols * bs * (k + pad), 3, wl.S_B).reshape(cols * bs, k + pad)
+    Bd = dev(Bh)[:, :k]
+    C = torch.full((A.rows * bs, k + pad), float("nan"), device="cuda")
+    if bs == 1:
+        psk.psk_spmm_csr(A.rows, cols, A.nnz, dev(A.pos), dev(A.crd), dev(A.vals), Bd, C[:, :k], tile=tile)
+        ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh[:, :k])
+    else:
+        psk.psk_spmm_bcsr(A.rows, cols, A.nnz, bs, dev(A.pos), dev(A.crd), dev(A.vals), Bd, C[:, :k], tile=tile)
+        ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, np.ascontiguousarray(Bh[:, :k]), bs)
+    torch.cuda.synchronize()
+    got = C.cpu().numpy()
+    assert np.isnan(got[:, k:]).all(), "columns past k were written"
+    ok, worst = oracle.within_tolerance(got[:, :k], ref, mag)
+    assert ok, "k %d tile %d bs %d: %.3g of the bar" % (k, tile, bs, worst)
+
+
+def borders(T):
+    """Rows that end 1 before, at, and 1 behind a tile's end, at the last position still taken over, one behind it, two tiles on."""
+    h = T // 2
+    return [T - 1, 2, T - 1 + h, 0, 0, T - h, h + 1 + T, 1, 1, T - 3 - h, 3 * T + h, 2 * T - 1, 5, 0, T]
+
+
+@pytest.mark.parametrize("k", [1, 3, 4, 5, 8, 15, 16, 17, 31, 32, 33, 63, 64, 65, 67, 99, 127, 128, 129])
+def test_group_widths_and_tile_borders(k):
+    check(borders(256), k, 256)
+    rng = np.random.default_rng(k)
+    check(rng.choice([0, 1, 2, 3, 9], size=1500), k, 0, pad=0)           # several row ends in one step
+    check(np.full(300, 40), k, 512, pad=4)
+
+
+@pytest.mark.parametrize("bs,k", [(2, 33), (4, 64), (4, 130), (8, 20)])
+def test_block_rows_at_tile_borders(bs, k):
+    check(borders(64), k, 64, bs=bs)
+    check(np.full(200, 8), k, 0, bs=bs, pad=0)
