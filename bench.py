@@ -743,10 +743,10 @@ def main():
         },
     }
 
-    if kind == "csr_spmv" and not f64 and path == "csr" and not tile_given and col_passes <= 1 and 0 < A.nnz <= 16384:
-        # a problem of one tile: the library takes it as one launch of one workgroup; what counts is time per call
+    if kind == "csr_spmv" and not f64 and path == "csr" and not tile_given and col_passes <= 1 and 0 < A.nnz <= 49152 and A.rows <= 65536:
+        # a small problem: the library takes it as one launch; what counts is time per call
         rec["roofline"]["launches_per_step"] = 1
-        rec["roofline"]["kernel"] = "k_spmv_pos<1024,16,*,7> (the whole matrix as one tile)"
+        rec["roofline"]["kernel"] = "k_spmv_row_blocks<float> (blocks of whole rows)"
         iso = time_phase(psk.PSK_PHASE_ALL, reps=32, warm=8, inner=1)     # one call between two events, stream idle before
         # the same product with the arguments marshalled once (the Python side of a call costs more than the kernel)
         calls = [psk.psk_spmv_csr_prepared(A.rows, A.cols, A.nnz, s_["pos"], s_["crd"], s_["vals"], s_["dense"], s_["out"],

@@ -140,8 +140,8 @@ int psk_partition_csr(int64_t rows, int64_t nnz, const int32_t *pos, int32_t til
  * the tile, one carry record per tile for a row that began in an earlier tile
  * (instead of the schedule's atomics), carries added by a second small kernel.
  * x has cols entries, y rows entries.  tile in {0, 256, 512, 1024, 2048, 4096}; 0 means 2048, or
- * 1024 when col_passes > 1 (psk_workspace_bytes with tile = 0 covers both).  With tile = 0, col_passes <= 1
- * and nnz <= 16384 the whole matrix is taken as one tile by one workgroup: one launch (in PSK_PHASE_MAIN),
+ * 1024 when col_passes > 1 (psk_workspace_bytes with tile = 0 covers both).  With tile = 0, col_passes <= 1,
+ * nnz <= 49152 and rows <= 65536 the rows are summed in blocks of whole rows: one launch (in PSK_PHASE_MAIN),
  * no table, no carries; such problems are bound by launch latency.
  *
  * col_passes (0 or 1 = off, at most PSK_MAX_COL_PASSES): the main step is run that many times, pass q
@@ -161,10 +161,10 @@ int psk_spmv_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, co
  * psk_spmv_csr for callers that cannot allocate device memory and have no workspace to pass: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same product (all three phases), same
  * kernels and bit-identical results as psk_spmv_csr with the same tile and col_passes; the table, the carry
- * records, the column ranges and the run list live in a built-in device array of PSK_STATIC_SCRATCH_BYTES (4 MiB per GPU,
+ * records and the column ranges live in a built-in device array of PSK_STATIC_SCRATCH_BYTES (4 MiB per GPU,
  * held until the process ends) instead of a caller's workspace.  The call allocates nothing.
  *  - Limit: psk_workspace_bytes(PSK_OP_SPMV_CSR, rows, nnz, 1, 1, tile) must not exceed
- *    psk_static_scratch_bytes(), i.e. about 74 000 tiles (153 M nonzeros at tile 2048, 76 M at 1024);
+ *    psk_static_scratch_bytes(), i.e. about 87 000 tiles (178 M nonzeros at tile 2048, 89 M at 1024);
  *    beyond that PSK_ERR_WORKSPACE and nothing is enqueued.
  *  - tile in {0, 256, 512, 1024, 2048, 4096}; 0 means 2048, or 1024 when col_passes > 1.
  *  - All calls on one GPU share that GPU's array: calls that may overlap in time on one GPU (different
@@ -296,7 +296,8 @@ int psk_spmv_csr_rowsplit(int64_t rows, int64_t cols, int64_t nnz, const int32_t
  * carry records (doubles) and fix-up as psk_spmv_csr, column passes included (col_passes as there; x is
  * twice as large per column, so slices of the same byte size hold half the columns); products and sums in fp64.
  * vals [nnz], x [cols], y [rows] doubles, 8-byte aligned (PSK_ERR_ALIGNMENT otherwise); crd and vals
- * 16-byte aligned selects the 16-byte load path.  tile in {0, 256, 512, 1024, 2048}, 0 = 1024.
+ * 16-byte aligned selects the 16-byte load path.  tile in {0, 256, 512, 1024, 2048}, 0 = 1024 (blocks of whole
+ * rows as in psk_spmv_csr for nnz <= 24576).
  * Workspace from psk_workspace_bytes(PSK_OP_SPMV_CSR_F64, rows, nnz, 1, 1, tile).
  * Deterministic; |y - exact| <= 1e-14 * sum_j |a_ij x_j| per row.
  */

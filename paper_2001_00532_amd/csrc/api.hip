@@ -101,6 +101,13 @@ int check_common(int op, int64_t rows, int64_t cols, int64_t nnz, const void *po
     return PSK_OK;
 }
 
+// Whether the tile kernel finds its rows itself instead of reading the table of a partition step: both steps are wanted and
+// the tiles are few (kSearchTiles).
+inline int searches(int phases, int32_t ntiles)
+{
+    return (phases & PSK_PHASE_PARTITION) && (phases & PSK_PHASE_MAIN) && ntiles > 0 && ntiles <= kSearchTiles;
+}
+
 inline int hip_status(hipError_t e) { return e == hipSuccess ? PSK_OK : PSK_ERR_HIP; }
 
 }  // namespace
@@ -228,9 +235,8 @@ int psk_spmv_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, co
                  void *workspace, size_t workspace_bytes, void *stream)
 {
     if (col_passes < 0 || col_passes > PSK_MAX_COL_PASSES) return PSK_ERR_SIZE;
-    // a matrix of a few thousand entries is bound by launch latency: with the default tile it is taken as ONE tile
-    // by one workgroup -- no table, no carries, one launch instead of three
-    const bool single = tile == 0 && col_passes <= 1 && nnz > 0 && nnz <= kSingleTile && rows <= 4 * kSingleTile;
+    // a small matrix is bound by launch latency: with the default tile its rows are summed in blocks by one launch
+    const bool single = tile == 0 && col_passes <= 1 && spmv_small(rows, nnz, 4);
     if (tile == 0 && col_passes > 1) tile = 1024;   // gather-bound passes prefer the smaller tile (measured)
     Workspace ws;
     int st = check_common(PSK_OP_SPMV_CSR, rows, cols, nnz, pos, crd, vals, 1, 1, &tile, phases, workspace,
@@ -240,19 +246,20 @@ int psk_spmv_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, co
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (single) {
         if (!(phases & PSK_PHASE_MAIN)) return PSK_OK;
-        return hip_status(launch_spmv_csr_single((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, y, s));
+        return hip_status(launch_spmv_csr_small((int32_t)rows, (int32_t)nnz, pos, crd, vals, x, y, s));
     }
     const int32_t ntiles = (int32_t)psk_num_tiles(nnz, tile);
     hipError_t e = hipSuccess;
-    // long runs of empty rows: the tile that spans one lists it (ws.gap) and the fix-up step clears it at full width
-    if ((phases & PSK_PHASE_PARTITION) && e == hipSuccess) e = launch_partition(rows, nnz, pos, tile, 0, ws.tile_row, s, ws.gap);
+    const int search = searches(phases, ntiles);
+    if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(rows, nnz, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         if (ntiles == 0) e = launch_fill_zero(y, rows, s);
         else e = launch_spmv_csr_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, y, tile, col_passes, ws, s,
-                                      nullptr, true);
+                                      search, nullptr, true);
     }
+    // (long runs of empty rows are left to the fix-up step, which clears them with many workgroups)
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
-        e = launch_carry_fixup(ntiles, 1, 1, 1, tile, pos, ws, y, s, nullptr, nullptr, true);
+        e = launch_carry_fixup(ntiles, 1, 1, 1, tile, pos, ws, y, s, nullptr, nullptr, (int32_t)rows);
     return hip_status(e);
 }
 
@@ -281,6 +288,7 @@ int psk_spmv_csr_static(int64_t rows, int64_t cols, int64_t nnz, const int32_t *
                         const float *vals, const float *x, float *y, int32_t tile, int32_t col_passes, void *stream)
 {
     if (col_passes < 0 || col_passes > PSK_MAX_COL_PASSES) return PSK_ERR_SIZE;
+    const int32_t asked = tile;
     if (tile == 0) tile = col_passes > 1 ? 1024 : default_tile(PSK_OP_SPMV_CSR);
     if (!tile_ok(PSK_OP_SPMV_CSR, tile)) return PSK_ERR_TILE;
     if (nnz >= 0 && nnz <= kMaxI32 &&
@@ -297,7 +305,7 @@ int psk_spmv_csr_static(int64_t rows, int64_t cols, int64_t nnz, const int32_t *
     if (!base) return PSK_ERR_HIP;
     // every part of the scratch memory that a product reads is written earlier in the same product (table by
     // the partition, carry records and column ranges by the tile kernel), so nothing needs clearing
-    return psk_spmv_csr(rows, cols, nnz, pos, crd, vals, x, y, tile, col_passes, PSK_PHASE_ALL, base,
+    return psk_spmv_csr(rows, cols, nnz, pos, crd, vals, x, y, asked, col_passes, PSK_PHASE_ALL, base,
                         PSK_STATIC_SCRATCH_BYTES, stream);
 }
 
@@ -306,6 +314,7 @@ int psk_spmv_csr_f64(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos
                      void *workspace, size_t workspace_bytes, void *stream)
 {
     if (col_passes < 0 || col_passes > PSK_MAX_COL_PASSES) return PSK_ERR_SIZE;
+    const bool single = tile == 0 && col_passes <= 1 && spmv_small(rows, nnz, 8);      // as in psk_spmv_csr
     Workspace ws;
     int st = check_common(PSK_OP_SPMV_CSR_F64, rows, cols, nnz, pos, crd, vals, 1, 1, &tile, phases, workspace,
                           workspace_bytes, &ws);
@@ -314,15 +323,20 @@ int psk_spmv_csr_f64(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos
     if ((reinterpret_cast<uintptr_t>(vals) | reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 7)
         return PSK_ERR_ALIGNMENT;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (single) {
+        if (!(phases & PSK_PHASE_MAIN)) return PSK_OK;
+        return hip_status(launch_spmv_csr_small((int32_t)rows, (int32_t)nnz, pos, crd, vals, x, y, s));
+    }
     const int32_t ntiles = (int32_t)psk_num_tiles(nnz, tile);
     hipError_t e = hipSuccess;
-    if ((phases & PSK_PHASE_PARTITION) && e == hipSuccess) e = launch_partition(rows, nnz, pos, tile, 0, ws.tile_row, s, ws.gap);
+    const int search = searches(phases, ntiles);
+    if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(rows, nnz, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         if (ntiles == 0) e = launch_fill_zero(reinterpret_cast<float *>(y), 2 * rows, s);
         else e = launch_spmv_csr_f64_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, y, tile, col_passes,
-                                          ws, s, true);
+                                          ws, s, search);
     }
-    if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess) e = launch_carry_fixup_f64(ntiles, tile, pos, ws, y, s, true);
+    if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess) e = launch_carry_fixup_f64(ntiles, tile, pos, ws, y, s, (int32_t)rows);
     return hip_status(e);
 }
 
@@ -353,12 +367,13 @@ int psk_spmv_dcsr(int64_t rows, int64_t cols, int64_t nstored, int64_t nnz, cons
         }
         return hip_status(e);
     }
-    if ((phases & PSK_PHASE_PARTITION) && e == hipSuccess) e = launch_partition(nstored, nnz, pos, tile, 0, ws.tile_row, s);
+    const int search = searches(phases, ntiles);
+    if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(nstored, nnz, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         e = launch_fill_zero(y, rows, s);
         if (ntiles > 0 && e == hipSuccess)
             e = launch_spmv_csr_main((int32_t)nstored, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, y, tile,
-                                     col_passes, ws, s, crd_i);
+                                     col_passes, ws, s, search, crd_i);
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess && ntiles > 0)
         e = launch_carry_fixup(ntiles, 1, 1, 1, tile, pos, ws, y, s, nullptr, crd_i);
@@ -409,7 +424,7 @@ int psk_spmv_csr_atomics(int64_t rows, int64_t cols, int64_t nnz, const int32_t 
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         e = launch_fill_zero(y, rows, s);
         if (ntiles > 0 && e == hipSuccess)
-            e = launch_spmv_csr_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, y, tile, -1, ws, s);
+            e = launch_spmv_csr_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, y, tile, -1, ws, s, 0);
     }
     return hip_status(e);
 }
@@ -429,7 +444,7 @@ int psk_spmv_csr_notemp(int64_t rows, int64_t cols, int64_t nnz, const int32_t *
     if ((phases & PSK_PHASE_PARTITION) && e == hipSuccess) e = launch_partition(rows, nnz, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         if (ntiles == 0) e = launch_fill_zero(y, rows, s);
-        else e = launch_spmv_csr_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, y, tile, -2, ws, s);
+        else e = launch_spmv_csr_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, y, tile, -2, ws, s, 0);
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess && ntiles > 0)
         e = launch_carry_fixup(ntiles, 1, 1, 1, tile, pos, ws, y, s);
@@ -449,16 +464,17 @@ int psk_spmm_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, co
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int32_t ntiles = (int32_t)psk_num_tiles(nnz, tile);
     hipError_t e = hipSuccess;
-    if ((phases & PSK_PHASE_PARTITION) && e == hipSuccess) e = launch_partition(rows, nnz, pos, tile, 0, ws.tile_row, s);
+    const int search = searches(phases, ntiles);
+    if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(rows, nnz, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         if (ntiles == 0) {
             e = launch_fill_zero_2d(C, rows, k, ldc, s);
         } else {
-            e = launch_spmm_csr_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s);
+            e = launch_spmm_csr_main((int32_t)rows, (int32_t)cols, (int32_t)nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s, search);
         }
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
-        e = launch_carry_fixup(ntiles, 1, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, false, spmm_overhang(tile));
+        e = launch_carry_fixup(ntiles, 1, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, 0, spmm_overhang(tile));
     return hip_status(e);
 }
 
@@ -478,11 +494,12 @@ int psk_spmv_bcsr(int64_t brows, int64_t bcols, int64_t nblocks, int32_t bs, con
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int32_t ntiles = (int32_t)psk_num_tiles(nblocks, tile);
     hipError_t e = hipSuccess;
-    if ((phases & PSK_PHASE_PARTITION) && e == hipSuccess) e = launch_partition(brows, nblocks, pos, tile, 0, ws.tile_row, s);
+    const int search = searches(phases, ntiles);
+    if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(brows, nblocks, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         if (ntiles == 0) e = launch_fill_zero(y, brows * bs, s);
-        else if (bs == 4) e = launch_spmv_bcsr4_main((int32_t)brows, (int32_t)nblocks, pos, crd, vals, x, y, tile, ws, s);
-        else e = launch_spmv_bcsr_g_main(bs, (int32_t)brows, (int32_t)nblocks, pos, crd, vals, x, y, tile, ws, s);
+        else if (bs == 4) e = launch_spmv_bcsr4_main((int32_t)brows, (int32_t)nblocks, pos, crd, vals, x, y, tile, ws, s, search);
+        else e = launch_spmv_bcsr_g_main(bs, (int32_t)brows, (int32_t)nblocks, pos, crd, vals, x, y, tile, ws, s, search);
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess) e = launch_carry_fixup(ntiles, 1, bs, bs, tile, pos, ws, y, s);
     return hip_status(e);
@@ -504,16 +521,17 @@ int psk_spmm_bcsr(int64_t brows, int64_t bcols, int64_t nblocks, int32_t bs, con
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int32_t ntiles = (int32_t)psk_num_tiles(nblocks, tile);
     hipError_t e = hipSuccess;
-    if ((phases & PSK_PHASE_PARTITION) && e == hipSuccess) e = launch_partition(brows, nblocks, pos, tile, 0, ws.tile_row, s);
+    const int search = searches(phases, ntiles);
+    if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(brows, nblocks, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         if (ntiles == 0) {
             e = launch_fill_zero_2d(C, brows * bs, k, ldc, s);
         } else {
-            e = launch_spmm_bcsr_main(bs, (int32_t)brows, (int32_t)nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s);
+            e = launch_spmm_bcsr_main(bs, (int32_t)brows, (int32_t)nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s, search);
         }
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
-        e = launch_carry_fixup(ntiles, bs, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, false, spmm_overhang(tile));
+        e = launch_carry_fixup(ntiles, bs, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, 0, spmm_overhang(tile));
     return hip_status(e);
 }
 

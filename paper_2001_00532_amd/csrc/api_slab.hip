@@ -171,13 +171,13 @@ int spmv_slab(const psk_slab *S, const void *x, void *y, int vbytes, int phases,
         if (phases & PSK_PHASE_MAIN) {
             e = launch_slab_pairs_f64(static_cast<const double *>(S->svals), S->scol, S->chunk_pair, S->slab_chunk,
                                       static_cast<const double *>(x), P, (int32_t)S->cols, (int32_t)S->nslabs,
-                                      (int32_t)S->nchunks, cus, ws.gap, s);
+                                      (int32_t)S->nchunks, cus, s);
             if (e == hipSuccess) {
                 if (ntiles == 0) e = launch_fill_zero(static_cast<float *>(y), zero_words, s);
                 else e = launch_spmv_csr_f64_ones((int32_t)S->rows, (int32_t)S->nq, S->qpos, S->qidx, P, yd, tile, ws, s);
             }
         }
-        if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess) e = launch_carry_fixup_f64(ntiles, tile, S->qpos, ws, yd, s, true);
+        if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess) e = launch_carry_fixup_f64(ntiles, tile, S->qpos, ws, yd, s, (int32_t)S->rows);
         return hip_status(e);
     }
     float *P = static_cast<float *>(workspace);
@@ -185,7 +185,7 @@ int spmv_slab(const psk_slab *S, const void *x, void *y, int vbytes, int phases,
     if (phases & PSK_PHASE_MAIN) {
         e = launch_slab_pairs(static_cast<const float *>(S->svals), S->scol, S->chunk_pair, S->slab_chunk,
                               static_cast<const float *>(x), P, (int32_t)S->cols, (int32_t)S->nslabs,
-                              (int32_t)S->nchunks, cus, ws.gap, s);
+                              (int32_t)S->nchunks, cus, s);
         // step 2: rows add up their pairs (position cut of the row lists, carries)
         if (e == hipSuccess) {
             if (ntiles == 0) e = launch_fill_zero(yf, S->rows, s);
@@ -193,7 +193,7 @@ int spmv_slab(const psk_slab *S, const void *x, void *y, int vbytes, int phases,
         }
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
-        e = launch_carry_fixup(ntiles, 1, 1, 1, tile, S->qpos, ws, yf, s, nullptr, nullptr, true);
+        e = launch_carry_fixup(ntiles, 1, 1, 1, tile, S->qpos, ws, yf, s, nullptr, nullptr, (int32_t)S->rows);
     return hip_status(e);
 }
 

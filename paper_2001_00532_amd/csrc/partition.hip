@@ -8,11 +8,9 @@ namespace psk {
 // coordinate of a tile of the position space is recovered by a binary search over pos).
 // One lane per table entry; pos[0] = 0 makes i = 0 always admissible.
 __global__ __launch_bounds__(256) void k_partition(int rows, int nnz, const int *__restrict__ pos,
-                                                   int tile, int ntiles, int *__restrict__ tile_row,
-                                                   int *__restrict__ gap)
+                                                   int tile, int ntiles, int *__restrict__ tile_row)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t == 0 && gap) { gap[0] = 0; gap[1] = 0; }
     if (t > ntiles) return;
     const long long first = (long long)t * tile;
     const int target = first < nnz ? (int)first : nnz;
@@ -33,16 +31,13 @@ __global__ __launch_bounds__(256) void k_partition(int rows, int nnz, const int 
 // written by their whole wave.
 __global__ __launch_bounds__(256) void k_partition_scan(int rows, int nnz, const int *__restrict__ pos, int tile,
                                                         int shift, int ntiles, int *__restrict__ tile_row,
-                                                        int vec_ok, int *__restrict__ gap)
+                                                        int vec_ok)
 {
     constexpr int RPT = 4;                                   // rows per thread
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & (WAVE - 1);
     const int rbase = g * RPT;
-    if (g == 0) {
-        tile_row[ntiles] = rows;
-        if (gap) { gap[0] = 0; gap[1] = 0; }
-    }
+    if (g == 0) tile_row[ntiles] = rows;
     int p[RPT + 1];
     if (vec_ok && rbase + RPT <= rows) {
         const v4i v = *reinterpret_cast<const v4i *>(pos + rbase);
@@ -80,7 +75,7 @@ __global__ __launch_bounds__(256) void k_partition_scan(int rows, int nnz, const
 
 // method: 0 = choose, 1 = binary search per tile, 2 = one scan over the rows
 hipError_t launch_partition(int64_t rows, int64_t nnz, const int32_t *pos, int32_t tile, int method,
-                            int32_t *tile_row, hipStream_t s, int32_t *gap)
+                            int32_t *tile_row, hipStream_t s)
 {
     const int64_t ntiles = nnz <= 0 ? 0 : (nnz + tile - 1) / tile;
     if (method == 0) method = (ntiles > 0 && rows <= (int64_t(1) << 23)) ? 2 : 1;
@@ -90,12 +85,12 @@ hipError_t launch_partition(int64_t rows, int64_t nnz, const int32_t *pos, int32
         const int vec_ok = (reinterpret_cast<uintptr_t>(pos) & 15) == 0;
         const int64_t threads = (rows + 3) / 4;
         PSK_LAUNCH(k_partition_scan, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, (int)rows,
-                           (int)nnz, pos, tile, shift, (int)ntiles, tile_row, vec_ok, gap);
+                           (int)nnz, pos, tile, shift, (int)ntiles, tile_row, vec_ok);
         return take_launch_status();
     }
     const int64_t n = ntiles + 1;
     PSK_LAUNCH(k_partition, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (int)rows, (int)nnz, pos,
-                       tile, (int)ntiles, tile_row, gap);
+                       tile, (int)ntiles, tile_row);
     return take_launch_status();
 }
 
@@ -243,33 +238,28 @@ __device__ __forceinline__ int run_length(const int *__restrict__ pos, const int
 
 // width = 1 (SpMV): a lane per tile; runs of more than 8 records are summed by the whole wave.
 // V = float: fp32 records and output, summed in fp64.  V = double: all fp64.
-// Workgroups from `carry_groups` on (launched only for the CSR SpMV) clear the runs of empty rows that tiles listed in
-// `gap` instead of walking them (gap[0] = number of runs, then first and end row of each): every row r of a run with
-// pos[r] = pos[r+1] becomes 0; rows with entries were written by their tiles.  The last of these workgroups to finish
-// resets the two counters, so that a product which reuses the table (no partition step) starts from an empty list.
+// Workgroups from `carry_groups` on (launched only for the CSR SpMV with more than kGapRows rows) clear the empty rows of tiles
+// that span more than kGapRows rows: workgroup q looks up the tile that owns row q * kGapStep (tile t owns the rows from its
+// table entry, tile 0 from row 0, to the next entry) and, if it is such a tile, clears the rows from there to the next
+// workgroup's row -- from the tile's first row on if no earlier workgroup's row lies in the tile.  Only rows r with pos[r] =
+// pos[r+1] are touched; rows with entries were written by their tiles.
 template <typename V>
 __global__ __launch_bounds__(256) void k_carry_fixup1(int ntiles, long long ld, int tile, int shift,
                                                       const int *__restrict__ pos,
                                                       const int *__restrict__ carry_row,
                                                       const V *__restrict__ carry_val,
-                                                      V *__restrict__ out, int carry_groups, int *__restrict__ gap,
-                                                      const int *__restrict__ rowmap)
+                                                      V *__restrict__ out, int carry_groups,
+                                                      const int *__restrict__ tile_row, const int *__restrict__ rowmap)
 {
     if ((int)blockIdx.x >= carry_groups) {
-        const int fillers = (int)gridDim.x - carry_groups, me = (int)blockIdx.x - carry_groups;
-        int n = gap[0];
-        if (n == 0) return;                      // the usual case: no run was listed, nothing to clear or to reset
-        n = n < ntiles ? n : ntiles;
-        for (int e = 0; e < n; ++e) {
-            const long long lo = gap[2 + 2 * e], hi = gap[3 + 2 * e];
-            for (long long r = lo + (long long)me * 256 + threadIdx.x; r < hi; r += (long long)fillers * 256)
-                if (pos[r] == pos[r + 1]) out[r * ld] = V(0);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            __threadfence();
-            if (atomicAdd(&gap[1], 1) == fillers - 1) { gap[0] = 0; gap[1] = 0; }
-        }
+        const int q = ((int)blockIdx.x - carry_groups) * kGapStep;
+        const int last = pos[q + 1] - 1;          // position before the end of row q: the last tile that owns row q holds it
+        const int t = last < 0 ? 0 : (shift >= 0 ? last >> shift : last / tile);
+        const int lo = t == 0 ? 0 : tile_row[t], hi = tile_row[t + 1];
+        if (hi - lo <= kGapRows) return;
+        const int beg = q - kGapStep < lo ? lo : q, end = hi - q < kGapStep ? hi : q + kGapStep;
+        for (long long r = (long long)beg + threadIdx.x; r < end; r += 256)
+            if (pos[r] == pos[r + 1]) out[r * ld] = V(0);
         return;
     }
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -355,18 +345,17 @@ __global__ __launch_bounds__(256) void k_carry_fixup(int ntiles, int per_wave, i
 
 hipError_t launch_carry_fixup(int32_t ntiles, int32_t nsub, int32_t k, int64_t ld, int32_t tile, const int32_t *pos,
                               const Workspace &w, float *out, hipStream_t s, const int32_t *pos2,
-                              const int32_t *rowmap, bool gaps, int32_t over)
+                              const int32_t *rowmap, int32_t gap_rows, int32_t over)
 {
     const int width = nsub * k;
-    gaps = gaps && width == 1 && !pos2 && !rowmap && ntiles >= 1;
-    if (ntiles <= 1 && !gaps) return hipSuccess;   // tile 0 never has a carry
+    const int fillers = gap_rows > kGapRows && ntiles >= 1 ? (gap_rows - 1) / kGapStep + 1 : 0;
+    if (ntiles <= 1 && !fillers) return hipSuccess;   // tile 0 never has a carry
     int shift = -1;
     if ((tile & (tile - 1)) == 0) { shift = 0; while ((1 << shift) < tile) ++shift; }
     if (width == 1 && !pos2 && over == 0) {
         const int carry_groups = ntiles <= 1 ? 0 : (ntiles + 255) / 256;
-        int *gap = gaps ? w.gap : nullptr;
-        PSK_LAUNCH(k_carry_fixup1<float>, dim3((unsigned)(carry_groups + (gaps ? kGapFillGroups : 0))), dim3(256), 0, s,
-                   ntiles, (long long)ld, tile, shift, pos, w.carry_row, w.carry_val, out, carry_groups, gap, rowmap);
+        PSK_LAUNCH(k_carry_fixup1<float>, dim3((unsigned)(carry_groups + fillers)), dim3(256), 0, s,
+                   ntiles, (long long)ld, tile, shift, pos, w.carry_row, w.carry_val, out, carry_groups, w.tile_row, rowmap);
         return take_launch_status();
     }
     int eshift = 0;
@@ -381,17 +370,16 @@ hipError_t launch_carry_fixup(int32_t ntiles, int32_t nsub, int32_t k, int64_t l
 }
 
 hipError_t launch_carry_fixup_f64(int32_t ntiles, int32_t tile, const int32_t *pos, const Workspace &w, double *out,
-                                  hipStream_t s, bool gaps)
+                                  hipStream_t s, int32_t gap_rows)
 {
-    gaps = gaps && ntiles >= 1;
-    if (ntiles <= 1 && !gaps) return hipSuccess;
+    const int fillers = gap_rows > kGapRows && ntiles >= 1 ? (gap_rows - 1) / kGapStep + 1 : 0;
+    if (ntiles <= 1 && !fillers) return hipSuccess;
     int shift = -1;
     if ((tile & (tile - 1)) == 0) { shift = 0; while ((1 << shift) < tile) ++shift; }
     const int carry_groups = ntiles <= 1 ? 0 : (ntiles + 255) / 256;
-    int *gap = gaps ? w.gap : nullptr;
-    PSK_LAUNCH(k_carry_fixup1<double>, dim3((unsigned)(carry_groups + (gaps ? kGapFillGroups : 0))), dim3(256), 0, s, ntiles,
-               1ll, tile, shift, pos, w.carry_row, reinterpret_cast<const double *>(w.carry_val), out, carry_groups, gap,
-               static_cast<const int *>(nullptr));
+    PSK_LAUNCH(k_carry_fixup1<double>, dim3((unsigned)(carry_groups + fillers)), dim3(256), 0, s, ntiles,
+               1ll, tile, shift, pos, w.carry_row, reinterpret_cast<const double *>(w.carry_val), out, carry_groups,
+               w.tile_row, static_cast<const int *>(nullptr));
     return take_launch_status();
 }
 

@@ -100,6 +100,45 @@ __device__ __forceinline__ float vec_at(const typename VecU<VEC>::type &v, int i
     else return v[i];
 }
 
+// Largest i in [0, n] with a[i] <= target (a non-decreasing, a[0] <= target taken for granted), for two targets at once, by a
+// whole wave: every round probes 64 places at equal steps, log64(n) dependent loads instead of log2(n).
+__device__ __forceinline__ void wave_search2(const int *__restrict__ a, int n, int target0, int target1, int &r0, int &r1)
+{
+    const unsigned lane = threadIdx.x & (WAVE - 1);
+    unsigned lo0 = 0, hi0 = (unsigned)n, lo1 = 0, hi1 = (unsigned)n;
+    while (lo0 < hi0 || lo1 < hi1) {
+        const unsigned s0 = (hi0 - lo0 + WAVE - 1) / WAVE, s1 = (hi1 - lo1 + WAVE - 1) / WAVE;
+        const unsigned i0 = lo0 + (lane + 1) * s0, i1 = lo1 + (lane + 1) * s1;
+        const int v0 = s0 && i0 <= hi0 ? a[i0] : 0x7fffffff, v1 = s1 && i1 <= hi1 ? a[i1] : 0x7fffffff;
+        const unsigned c0 = (unsigned)__popcll(__ballot(s0 && i0 <= hi0 && v0 <= target0));
+        const unsigned c1 = (unsigned)__popcll(__ballot(s1 && i1 <= hi1 && v1 <= target1));
+        lo0 += c0 * s0;
+        lo1 += c1 * s1;
+        if (s0) hi0 = min(hi0, lo0 + s0 - 1);
+        if (s1) hi1 = min(hi1, lo1 + s1 - 1);
+    }
+    r0 = (int)lo0;
+    r1 = (int)lo1;
+}
+
+// First row of tile t and of the next one: from the table, or by the kernel's own search, which leaves the table entry for
+// the steps that read the table.  (With few tiles the search costs less than the launch of the partition kernel.)
+__device__ __forceinline__ void tile_rows(const int *__restrict__ pos, int rows, int nnz, int T, int t, int ntiles, int *tile_row,
+                                          int search, int &r0, int &r1)
+{
+    if (!search) {
+        r0 = tile_row[t];
+        r1 = tile_row[t + 1];
+        return;
+    }
+    const int c0 = t * T;
+    wave_search2(pos, rows, c0, nnz - c0 < T ? nnz : c0 + T, r0, r1);
+    if (threadIdx.x == 0 && blockIdx.y == 0) {
+        tile_row[t] = r0;
+        if (t + 1 == ntiles) tile_row[ntiles] = rows;
+    }
+}
+
 // Positions and rows of tile t where a row that reaches at most `over` positions past the end of a tile is finished by that
 // tile (SpMM kernels: a carry record is k floats written, read and added again, a few more positions cost nothing).  A row
 // that reaches further ends at the border as the cut says and its part in the next tile becomes that tile's carry.  Both
@@ -111,13 +150,12 @@ struct TileSpan {
     bool has_carry;        // row r0 began in an earlier tile
     bool straddle;         // row r1 goes on in the next tile
 };
-__device__ __forceinline__ TileSpan tile_span(const int *__restrict__ tile_row, const int *__restrict__ pos, int t, int T, int nnz,
-                                              int ntiles, int over)
+__device__ __forceinline__ TileSpan tile_span(int rows, const int *__restrict__ pos, int t, int T, int nnz, int ntiles, int over,
+                                              int *tile_row, int search)
 {
     TileSpan s;
     const int c0 = t * T, c1 = nnz - c0 < T ? nnz : c0 + T;
-    s.r0 = tile_row[t];
-    s.r1 = tile_row[t + 1];
+    tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, search, s.r0, s.r1);
     const bool last = t + 1 == ntiles;                    // r1 = rows: no row goes on
     const int b0 = pos[s.r0], e0 = pos[s.r0 + 1], b1 = pos[s.r1], e1 = last ? nnz : pos[s.r1 + 1];
     const bool inside = t > 0 && b0 < c0;                 // the tile begins inside row r0

@@ -39,15 +39,13 @@ inline void launch_kernel(void (*kern)(KA...), dim3 grid, dim3 block, unsigned s
 
 // Workspace carving: [tile_row: ntiles+1 int32][carry_row: ntiles int32][carry_val: ntiles*width float]
 // [tile_aux: ntiles+1 int32 (second table of a two-level cut)][tile_cols: ntiles*8 int32 (column range of each
-// tile, one min/max pair per wave, written by the first column pass)][gap: 2+2*ntiles int32 (the long runs of
-// empty rows that the fix-up step clears with many workgroups)], each part starting on a 256-byte boundary.
+// tile, one min/max pair per wave, written by the first column pass)], each part starting on a 256-byte boundary.
 struct Workspace {
     int32_t *tile_row;
     int32_t *carry_row;
     float   *carry_val;
     int32_t *tile_aux;
     int32_t *tile_cols;
-    int32_t *gap;        // [2 + 2*ntiles]: count, arrivals, then (first row, end row) of every long run of rows a tile spans
     size_t   bytes;
 };
 inline size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
@@ -63,17 +61,14 @@ inline Workspace carve(void *base, int64_t ntiles, int64_t width)
     const size_t d = align256(size_t(ntiles) * 32 + 4);
     w.tile_aux = reinterpret_cast<int32_t *>(p + a + b + c);
     w.tile_cols = reinterpret_cast<int32_t *>(p + a + b + c + a);
-    const size_t g = align256(size_t(ntiles) * 8 + 8);
-    w.gap = reinterpret_cast<int32_t *>(p + a + b + c + a + d);
-    w.bytes = a + b + c + a + d + g;
+    w.bytes = a + b + c + a + d;
     return w;
 }
 
 // Every launcher enqueues on `s` and returns the status of its own launches (take_launch_status()).
 
-// gap (optional): the run list of the workspace; its two counters are cleared here
 hipError_t launch_partition(int64_t rows, int64_t nnz, const int32_t *pos, int32_t tile, int method,
-                            int32_t *tile_row, hipStream_t s, int32_t *gap = nullptr);
+                            int32_t *tile_row, hipStream_t s);
 hipError_t launch_fill_zero(float *p, int64_t n, hipStream_t s);
 hipError_t launch_fill_zero_2d(float *p, int64_t rows, int32_t width, int64_t ld, hipStream_t s);
 hipError_t launch_validate_csr(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
@@ -85,24 +80,37 @@ hipError_t launch_probe_locality(int32_t nnz, const int32_t *crd, int32_t *resul
 // `pos2` (optional): two-level hierarchy, a row's last position is pos2[pos[r+1]] - 1.  `rowmap` (optional):
 // row r of the hierarchy is stored at output row rowmap[r].
 // over: the tiles take up to that many positions of a row past their end, such a tail has no record (SpMM)
-// gaps = true (CSR SpMV only): extra workgroups clear the long runs of empty rows that the tile kernel listed in w.gap
+// gap_rows = rows (CSR SpMV only): extra workgroups clear the long runs of empty rows that the tile kernels leave out
 hipError_t launch_carry_fixup(int32_t ntiles, int32_t nsub, int32_t k, int64_t ld, int32_t tile, const int32_t *pos,
                               const Workspace &w, float *out, hipStream_t s, const int32_t *pos2 = nullptr,
-                              const int32_t *rowmap = nullptr, bool gaps = false, int32_t over = 0);
-// A tile whose rows span more than this many rows does not walk them: it finds the rows of its positions by search
-// and leaves the run of empty rows to the fix-up step (which clears it with many workgroups).
+                              const int32_t *rowmap = nullptr, int32_t gap_rows = 0, int32_t over = 0);
+// A tile whose rows span more than this many rows (by the table) does not walk them: it finds the rows of its positions by
+// search and leaves the empty rows to the fix-up step.  A workgroup of that step stands for kGapStep rows, looks up the tile
+// that owns the first of them and clears its share of the span if the tile is such a one.
 constexpr int32_t kGapRows = 32768;
-constexpr int32_t kGapFillGroups = 512;
+constexpr int32_t kGapStep = 8192;
+// Up to this many tiles the tile kernel searches its rows itself and the partition kernel is not launched: 196 tiles 17.4
+// -> 14.4 us per product, 1953 tiles 33.4 against 33.2, 3907 tiles (4x4 blocks) 43 -> 48: from a few tiles per CU on the
+// searches of the workgroups queue behind each other.
+constexpr int32_t kSearchTiles = 1024;
 
 // CSR SpMV
 bool spmv_csr_tile_ok(int32_t tile);
 hipError_t launch_spmv_csr_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *x, float *y, int32_t tile, int32_t col_passes,
-                                const Workspace &w, hipStream_t s, const int32_t *rowmap = nullptr, bool gaps = false);
-// the whole matrix as one tile of one workgroup (nnz <= kSingleTile): no table, no carries
-constexpr int32_t kSingleTile = 16384;
-hipError_t launch_spmv_csr_single(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
-                                  const float *vals, const float *x, float *y, hipStream_t s);
+                                const Workspace &w, hipStream_t s, int search, const int32_t *rowmap = nullptr,
+                                bool gaps = false);
+// Small matrices: blocks of whole rows, one launch, no table, no carries.  The limits are set by the worst case, all entries
+// in one row, i.e. in one workgroup: 2.4 us per 8192 entries (fp64 4.6), against about 16 us for three launches.
+constexpr int32_t kSmallNnz = 49152, kSmallNnzF64 = 24576, kSmallRows = 65536;
+inline bool spmv_small(int64_t rows, int64_t nnz, int vbytes)
+{
+    return nnz > 0 && nnz <= (vbytes == 8 ? kSmallNnzF64 : kSmallNnz) && rows <= kSmallRows;
+}
+hipError_t launch_spmv_csr_small(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const float *vals,
+                                 const float *x, float *y, hipStream_t s);
+hipError_t launch_spmv_csr_small(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const double *vals,
+                                 const double *x, double *y, hipStream_t s);
 // rowmap (optional, both launchers): row r of the hierarchy is row rowmap[r] of y (DCSR)
 hipError_t launch_spmv_rowsplit(int32_t rows, const int32_t *pos, const int32_t *crd, const float *vals,
                                 const float *x, float *y, int variant, hipStream_t s,
@@ -119,9 +127,9 @@ hipError_t launch_spmv_csr_divide(int32_t rows, int32_t cols, int32_t nnz, const
 bool spmv_csr_f64_tile_ok(int32_t tile);
 hipError_t launch_spmv_csr_f64_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                     const double *vals, const double *x, double *y, int32_t tile, int32_t col_passes,
-                                    const Workspace &w, hipStream_t s, bool gaps = false);
+                                    const Workspace &w, hipStream_t s, int search);
 hipError_t launch_carry_fixup_f64(int32_t ntiles, int32_t tile, const int32_t *pos, const Workspace &w, double *out,
-                                  hipStream_t s, bool gaps = false);
+                                  hipStream_t s, int32_t gap_rows);
 
 // CSR SpMM
 // a row that reaches at most this far past the end of a tile is finished by that tile (tile_span in psk_dev.h)
@@ -129,12 +137,12 @@ inline int32_t spmm_overhang(int32_t tile) { return tile / 2; }
 bool spmm_csr_tile_ok(int32_t tile);
 hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
-                                int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s);
+                                int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search);
 // k <= kGroupColumns: the wave is split into groups that take consecutive positions
 constexpr int32_t kGroupColumns = 128;
 hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
-                                  int32_t tile, const Workspace &w, hipStream_t s);
+                                  int32_t tile, const Workspace &w, hipStream_t s, int search);
 hipError_t launch_spmm_rowsplit(int32_t rows, const int32_t *pos, const int32_t *crd, const float *vals,
                                 const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
                                 hipStream_t s);
@@ -144,13 +152,13 @@ bool bcsr_tile_ok(int32_t tile);
 bool bcsr_g_tile_ok(int32_t bs, int32_t tile);
 hipError_t launch_spmv_bcsr_g_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                    const float *vals, const float *x, float *y, int32_t tile, const Workspace &w,
-                                   hipStream_t s);
+                                   hipStream_t s, int search);
 hipError_t launch_spmv_bcsr4_main(int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *x, float *y, int32_t tile,
-                                  const Workspace &w, hipStream_t s);
+                                  const Workspace &w, hipStream_t s, int search);
 hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
-                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s);
+                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search);
 
 // Column-slab hierarchy of a CSR matrix (slab.hip)
 constexpr int32_t kSlabCols = 32736;        // columns per slab: 32 * 1023 floats = 127.9 KB of x in LDS (15-bit in-slab column)
@@ -188,10 +196,10 @@ hipError_t launch_slab_build_f64(int32_t rows, int32_t cols, int32_t nnz, const 
                              int32_t *qtile_row, hipStream_t s);
 hipError_t launch_slab_pairs_f64(const double *svals, const uint16_t *scol, const int32_t *chunk_pair,
                                  const int32_t *slab_chunk, const double *x, double *P, int32_t cols, int32_t nslabs,
-                                 int32_t nchunks, int32_t nwg, int32_t *gap, hipStream_t s);
+                                 int32_t nchunks, int32_t nwg, hipStream_t s);
 hipError_t launch_slab_pairs(const float *svals, const uint16_t *scol, const int32_t *chunk_pair,
                              const int32_t *slab_chunk, const float *x, float *P, int32_t cols, int32_t nslabs,
-                             int32_t nchunks, int32_t nwg, int32_t *gap, hipStream_t s);
+                             int32_t nchunks, int32_t nwg, hipStream_t s);
 hipError_t launch_fill_int(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 // y = Q * P with unit values: the tile kernel of the CSR SpMV without the load of vals (tile 2048)
 hipError_t launch_spmv_csr_ones(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,

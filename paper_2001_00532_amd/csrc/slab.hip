@@ -113,13 +113,11 @@ __global__ __launch_bounds__(SlabOf<T>::WAVES * WAVE) void k_slab_pairs(const T 
                                                      const int *__restrict__ chunk_pair,
                                                      const int *__restrict__ slab_chunk,
                                                      const T *__restrict__ x, T *__restrict__ P, int cols,
-                                                     int nslabs, int nchunks, int cpw, int *__restrict__ gap)
+                                                     int nslabs, int nchunks, int cpw)
 {
     constexpr int WAVES = SlabOf<T>::WAVES;
     constexpr int W = SlabOf<T>::W, G = SlabOf<T>::G, NV = 8 / G;      // NV 16-byte loads of values per lane
     typedef typename SlabOf<T>::V V;
-    // the run list of the second step starts empty (that step's tiles append to it, the fix-up consumes it)
-    if (blockIdx.x == 0 && threadIdx.x == 0 && gap) { gap[0] = 0; gap[1] = 0; }
     __shared__ T xs[W];
     __shared__ T stage[WAVES * SLAB_CH + 32];         // + one dummy word per LDS bank
     static_assert(sizeof(T) * (W + WAVES * SLAB_CH + 32) <= 163840, "the window and the staging area fill the CU's LDS");
@@ -220,29 +218,29 @@ __global__ __launch_bounds__(SlabOf<T>::WAVES * WAVE) void k_slab_pairs(const T 
 template <typename T>
 static hipError_t launch_slab_pairs_t(const T *svals, const uint16_t *scol, const int32_t *chunk_pair,
                                       const int32_t *slab_chunk, const T *x, T *P, int32_t cols, int32_t nslabs,
-                                      int32_t nchunks, int32_t nwg, int32_t *gap, hipStream_t s)
+                                      int32_t nchunks, int32_t nwg, hipStream_t s)
 {
     if (nchunks <= 0) return hipSuccess;
     if (nwg < 1) nwg = 1;
     const int cpw = (nchunks + nwg - 1) / nwg;
     const int grid = xcd_grid((nchunks + cpw - 1) / cpw);
     PSK_LAUNCH(k_slab_pairs<T>, dim3(grid), dim3(SlabOf<T>::WAVES * WAVE), 0, s, svals, scol, chunk_pair, slab_chunk, x, P, cols, nslabs,
-               nchunks, cpw, gap);
+               nchunks, cpw);
     return take_launch_status();
 }
 
 hipError_t launch_slab_pairs(const float *svals, const uint16_t *scol, const int32_t *chunk_pair,
                              const int32_t *slab_chunk, const float *x, float *P, int32_t cols, int32_t nslabs,
-                             int32_t nchunks, int32_t nwg, int32_t *gap, hipStream_t s)
+                             int32_t nchunks, int32_t nwg, hipStream_t s)
 {
-    return launch_slab_pairs_t<float>(svals, scol, chunk_pair, slab_chunk, x, P, cols, nslabs, nchunks, nwg, gap, s);
+    return launch_slab_pairs_t<float>(svals, scol, chunk_pair, slab_chunk, x, P, cols, nslabs, nchunks, nwg, s);
 }
 
 hipError_t launch_slab_pairs_f64(const double *svals, const uint16_t *scol, const int32_t *chunk_pair,
                                  const int32_t *slab_chunk, const double *x, double *P, int32_t cols, int32_t nslabs,
-                                 int32_t nchunks, int32_t nwg, int32_t *gap, hipStream_t s)
+                                 int32_t nchunks, int32_t nwg, hipStream_t s)
 {
-    return launch_slab_pairs_t<double>(svals, scol, chunk_pair, slab_chunk, x, P, cols, nslabs, nchunks, nwg, gap, s);
+    return launch_slab_pairs_t<double>(svals, scol, chunk_pair, slab_chunk, x, P, cols, nslabs, nchunks, nwg, s);
 }
 
 // ------------------------------------------------------------------ prefix sums over int32 arrays

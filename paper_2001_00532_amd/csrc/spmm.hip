@@ -29,9 +29,10 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
                                                   const float *__restrict__ vals,
                                                   const float *__restrict__ B, int k, long long ldb,
                                                   float *__restrict__ C, long long ldc,
-                                                  const int *__restrict__ tile_row,
+                                                  int *tile_row,
                                                   int *__restrict__ carry_row,
-                                                  float *__restrict__ carry_val, int ntiles, int T, int over)
+                                                  float *__restrict__ carry_val, int ntiles, int T, int over,
+                                                  int search)
 {
     constexpr int THREADS = 256, NW = THREADS / WAVE, KW = WAVE * VEC;
     constexpr int U = BS == 1 ? 8 : (BS == 2 ? 4 : (BS == 4 ? 2 : 1));   // positions whose B rows are in flight together
@@ -45,7 +46,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
     // BS == 1: tell the compiler that the wave index is uniform (scalar loop control).  With blocks the
     // generated code measured 3 % slower that way, so there it stays a per-lane value.
     const int wave = BS == 1 ? __builtin_amdgcn_readfirstlane(tid / WAVE) : tid / WAVE;
-    const TileSpan span = tile_span(tile_row, pos, t, T, nnz, ntiles, over);
+    const TileSpan span = tile_span(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
     const int t0 = span.t0, cnt = span.cnt, r0 = span.r0, r1 = span.r1, rbeg = span.rbeg, rend = span.rend;
     const bool has_carry = span.has_carry, straddle = span.straddle;
     const int col = blockIdx.y * KW + lane * VEC;
@@ -228,7 +229,7 @@ static int pick_vec(const float *B, int32_t k, int64_t ldb, const float *C, int6
 template <int BS>
 static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
-                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s)
+                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     if (ntiles == 0) return hipSuccess;
@@ -240,7 +241,7 @@ static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos,
     const size_t lds = (size_t)(tile + over) * sizeof(int);
 #define PSK_GO(V)                                                                                              \
     PSK_LAUNCH((k_spmm_pos<BS, V>), grid, dim3(256), lds, s, rows, nnz, pos, crd, vals, B, k,          \
-                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over)
+                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, search)
     if (vec == 4) {
         if constexpr (BS < 8) PSK_GO(4);
     } else if (vec == 2) PSK_GO(2);
@@ -251,7 +252,7 @@ static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos,
 
 hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
-                                int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s)
+                                int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search)
 {
     // Groups of lanes or the wide kernel (us, 10^6 rows unless stated):
     //   k <= 32: groups; mean row of 1 / 7 / 16 / 300 entries, k = 16: 43 / 94 / 303 against 54 / 99 / 300 for groups of one column
@@ -261,17 +262,17 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     //     against 1776; where it can the wide kernel is 1-3 % faster, k = 128 1190 against 1223)
     const bool groups = k <= 32 || (k <= 64 && nnz >= 8ll * rows) ||
                         (k > 64 && k <= kGroupColumns && pick_vec(B, k, ldb, C, ldc) == 1);
-    if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s);
-    return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s);
+    if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
+    return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
 }
 
 hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                  const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
-                                 int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s)
+                                 int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search)
 {
-    if (bs == 2) return launch_spmm_pos<2>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s);
-    if (bs == 4) return launch_spmm_pos<4>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s);
-    if (bs == 8) return launch_spmm_pos<8>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s);
+    if (bs == 2) return launch_spmm_pos<2>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
+    if (bs == 4) return launch_spmm_pos<4>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
+    if (bs == 8) return launch_spmm_pos<8>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
     return hipErrorInvalidValue;
 }
 

@@ -25,9 +25,9 @@ __global__ __launch_bounds__(256) void k_spmv_bcsr4(int brows, int nblocks, cons
                                                     const int *__restrict__ crd,
                                                     const float *__restrict__ vals,
                                                     const float *__restrict__ x, float *__restrict__ y,
-                                                    const int *__restrict__ tile_row,
+                                                    int *tile_row,
                                                     int *__restrict__ carry_row,
-                                                    float *__restrict__ carry_val, int ntiles)
+                                                    float *__restrict__ carry_val, int ntiles, int search)
 {
     constexpr int THREADS = 256, NW = THREADS / WAVE, NPASS = TB / 64;
     constexpr int LONG = 16;                 // blocks of one block row inside the tile handled by a whole wave
@@ -47,7 +47,8 @@ __global__ __launch_bounds__(256) void k_spmv_bcsr4(int brows, int nblocks, cons
     const int t1 = t0 + cnt;
 
     // the dependent chain tile_row -> pos is started first and runs underneath the streaming loads
-    const int r0 = tile_row[t], r1 = tile_row[t + 1];
+    int r0 = 0, r1 = 0;
+    if (!search) { r0 = tile_row[t]; r1 = tile_row[t + 1]; }
 
     v4f a[NPASS];
     int jb[NPASS];
@@ -63,6 +64,7 @@ __global__ __launch_bounds__(256) void k_spmv_bcsr4(int brows, int nblocks, cons
         }
     }
 
+    if (search) tile_rows(pos, brows, nblocks, TB, t, ntiles, tile_row, 1, r0, r1);
     const int p_r0 = pos[r0], p_r1 = pos[r1];
     const int rbeg = (t == 0) ? 0 : r0;
     int my_lo = 0, my_hi = 0;                     // pos pair of the first block row this lane looks at
@@ -141,14 +143,14 @@ __global__ __launch_bounds__(256) void k_spmv_bcsr4(int brows, int nblocks, cons
 
 hipError_t launch_spmv_bcsr4_main(int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *x, float *y, int32_t tile,
-                                  const Workspace &w, hipStream_t s)
+                                  const Workspace &w, hipStream_t s, int search)
 {
     const int ntiles = (int)(((int64_t)nblocks + tile - 1) / tile);
     if (ntiles == 0) return hipSuccess;
     const int grid = xcd_grid(ntiles);
 #define PSK_GO(TB)                                                                                           \
     PSK_LAUNCH((k_spmv_bcsr4<TB>), dim3(grid), dim3(256), 0, s, brows, nblocks, pos, crd, vals, x, y, \
-                       w.tile_row, w.carry_row, w.carry_val, ntiles)
+                       w.tile_row, w.carry_row, w.carry_val, ntiles, search)
     switch (tile) {
         case 64: PSK_GO(64); break;
         case 128: PSK_GO(128); break;

@@ -15,9 +15,9 @@ __global__ __launch_bounds__(256) void k_spmv_bcsr_g(int brows, int nblocks, con
                                                      const int *__restrict__ crd,
                                                      const float *__restrict__ vals,
                                                      const float *__restrict__ x, float *__restrict__ y,
-                                                     const int *__restrict__ tile_row,
+                                                     int *tile_row,
                                                      int *__restrict__ carry_row,
-                                                     float *__restrict__ carry_val, int ntiles)
+                                                     float *__restrict__ carry_val, int ntiles, int search)
 {
     static_assert(BS == 2 || BS == 8, "block edge");
     constexpr int THREADS = 256, NW = THREADS / WAVE;
@@ -41,7 +41,8 @@ __global__ __launch_bounds__(256) void k_spmv_bcsr_g(int brows, int nblocks, con
     const int cnt = (nblocks - t0 < TB) ? nblocks - t0 : TB;
     const int t1 = t0 + cnt;
 
-    const int r0 = tile_row[t], r1 = tile_row[t + 1];
+    int r0 = 0, r1 = 0;
+    if (!search) { r0 = tile_row[t]; r1 = tile_row[t + 1]; }
 
     v4f a[NPASS];
     int jb[NPASS];
@@ -56,6 +57,7 @@ __global__ __launch_bounds__(256) void k_spmv_bcsr_g(int brows, int nblocks, con
             jb[g] = ld_stream(crd + p);
         }
     }
+    if (search) tile_rows(pos, brows, nblocks, TB, t, ntiles, tile_row, 1, r0, r1);
     const int p_r0 = pos[r0], p_r1 = pos[r1];
 
     if (tid == 0) nlong = 0;
@@ -130,14 +132,14 @@ bool bcsr_g_tile_ok(int32_t bs, int32_t tile)
 
 hipError_t launch_spmv_bcsr_g_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                    const float *vals, const float *x, float *y, int32_t tile, const Workspace &w,
-                                   hipStream_t s)
+                                   hipStream_t s, int search)
 {
     const int ntiles = (int)(((int64_t)nblocks + tile - 1) / tile);
     if (ntiles == 0) return hipSuccess;
     const int grid = xcd_grid(ntiles);
 #define PSK_GO(B, TB)                                                                                              \
     PSK_LAUNCH((k_spmv_bcsr_g<B, TB>), dim3(grid), dim3(256), 0, s, brows, nblocks, pos, crd, vals, x, y, \
-                       w.tile_row, w.carry_row, w.carry_val, ntiles)
+                       w.tile_row, w.carry_row, w.carry_val, ntiles, search)
     if (bs == 2) {
         switch (tile) {
             case 512: PSK_GO(2, 512); break;

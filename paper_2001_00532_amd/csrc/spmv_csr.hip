@@ -37,8 +37,6 @@ __device__ __forceinline__ int tile_index(int g, int tid)
 // 3: one pass without the per-thread temporary and without the unrolled load loop (the ablation of
 //    Section 8.3): each thread walks its positions in a rolled loop, one load -> gather -> multiply -> LDS
 //    store after the other.
-// 7: the whole matrix is one tile (nnz <= T): no table, no carries, no fix-up -- one launch per product for
-//    problems of a few thousand entries, which are bound by launch latency.
 // 6: one pass with unit values: vals is not read (the second step of the product over the column-slab
 //    hierarchy, where the "matrix" only lists which partial sums belong to a row).
 template <int THREADS, int NPT, int MODE, int VARIANT>
@@ -46,11 +44,11 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
                                                       const int *__restrict__ crd,
                                                       const float *__restrict__ vals,
                                                       const float *__restrict__ x, float *__restrict__ y,
-                                                      const int *__restrict__ tile_row,
+                                                      int *tile_row,
                                                       int *__restrict__ carry_row,
                                                       float *__restrict__ carry_val, int ntiles, int clo,
                                                       int chi, int accum, const int *__restrict__ rowmap,
-                                                      int *__restrict__ tile_cols, int *__restrict__ gap)
+                                                      int *__restrict__ tile_cols, int gaps, int search)
 {
     constexpr int T = THREADS * NPT;
     constexpr int NW = THREADS / WAVE;
@@ -60,7 +58,6 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
     constexpr bool WIN = VARIANT == 1 || VARIANT == 5, ATOM = VARIANT == 2, NOTEMP = VARIANT == 3;
     constexpr bool ROWMAP = VARIANT == 4 || VARIANT == 5;
     constexpr bool ONES = VARIANT == 6;
-    constexpr bool SINGLE = VARIANT == 7;
     constexpr bool GAPS = VARIANT == 0 || VARIANT == 1 || VARIANT == 6;   // may leave long runs of empty rows to the fix-up
     static_assert(NPT % 4 == 0, "NPT must be a multiple of 4");
     __shared__ float sprod[skewed_size<1>(T)];
@@ -69,7 +66,7 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
     __shared__ float swave[NW];
     __shared__ int srowid[GAPS ? T : 1];
 
-    const int t = SINGLE ? (blockIdx.x == 0 ? 0 : -1) : xcd_tile(blockIdx.x, ntiles);
+    const int t = xcd_tile(blockIdx.x, ntiles);
     if (t < 0) return;
     PSK_TRACE_WORKGROUP();
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
@@ -92,8 +89,11 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
 
     // Issue order matters more than anything else here: the tile's row bounds hang off a chain of
     // dependent loads (tile_row -> pos), so that chain is started first and runs underneath the
-    // streaming loads and the gather instead of after them.
-    const int r0 = SINGLE ? 0 : tile_row[t], r1 = SINGLE ? rows : tile_row[t + 1];
+    // streaming loads and the gather instead of after them.  (A search, which is several rounds of loads, is started
+    // behind the streaming loads: they do not depend on it.)
+    if (VARIANT == 6) search = 0;      // the table is part of the structure
+    int r0 = 0, r1 = 0;
+    if (!search) { r0 = tile_row[t]; r1 = tile_row[t + 1]; }
 
     // ---- 1. stream + gather + multiply
     float prod[NPT];
@@ -121,6 +121,7 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
     }
 
     // ---- 2. rows of this tile (loads issued before the gather)
+    if (search) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
     const int p_r0 = pos[r0], p_r1 = pos[r1];
     const int rbeg = (t == 0) ? 0 : r0;
     int my_lo = 0, my_hi = 0;                       // pos pair of the first row this thread will look at
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
 
     const bool has_carry = (t > 0) && (p_r0 < t0);
     const int rend = (p_r1 == t1) ? r1 : r1 + 1;   // last tile: r1 = rows and pos[rows] = nnz = t1
-    if (tid == 0 && !has_carry && !ATOM && !SINGLE) carry_row[t] = -1;
+    if (tid == 0 && !has_carry && !ATOM) carry_row[t] = -1;
     // a later column pass adds to what the first one stored (same lane, same order: deterministic)
     auto emit = [&](int r, float v) {
         if (ATOM) {
@@ -278,12 +279,12 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
         for (int g = 0; g < NPT; ++g) sprod[skew<1>(tile_index<MODE, THREADS>(g, tid))] = prod[g];
     }
     __syncthreads();
-    if (GAPS && gap && rend - rbeg > kGapRows) {
+    if (GAPS && gaps && r1 - rbeg > kGapRows) {
         // The tile's rows span a long run of empty rows (Section 6.2 walks past empty rows one by one; here that walk
         // would be done by this one workgroup).  Instead the row of every position is found by search -- a thread takes
         // NPT consecutive positions, searches once for the first and again whenever a row ends --, the row segments
-        // are summed by the thread that holds their first position, and the run of rows is handed to the fix-up step,
-        // whose extra workgroups clear its empty rows at full width.
+        // are summed by the thread that holds their first position, and the empty rows are left to the fix-up step,
+        // whose extra workgroups clear them at full width.
         const int i0 = tid * NPT;
         if (i0 < cnt) {
             int lo = r0, hi = r1;                       // max { r in [r0, r1] : pos[r] <= t0 + i0 }
@@ -317,10 +318,6 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
             float sum = 0.0f;
             for (int j = i; j < cnt && srowid[j] == r; ++j) sum += sprod[skew<1>(j)];
             emit(r, sum);
-        }
-        if (tid == 0 && !(WIN && accum)) {
-            const int e = atomicAdd(&gap[0], 1);
-            if (e < ntiles) { gap[2 + 2 * e] = rbeg; gap[3 + 2 * e] = rend; }
         }
         return;
     }
@@ -365,12 +362,12 @@ bool spmv_csr_tile_ok(int32_t tile)
 template <int THREADS, int NPT>
 static void launch_pos(int mode, int grid, hipStream_t s, int rows, int cols, int nnz, const int *pos, const int *crd,
                        const float *vals, const float *x, float *y, const Workspace &w, int ntiles, int clo, int chi,
-                       int accum, const int *rowmap, int *gap)
+                       int accum, const int *rowmap, int gaps, int search)
 {
 #define PSK_GO(M, W)                                                                                             \
     PSK_LAUNCH((k_spmv_pos<THREADS, NPT, M, W>), dim3(grid), dim3(THREADS), 0, s, rows, cols, nnz, pos,  \
                        crd, vals, x, y, w.tile_row, w.carry_row, w.carry_val, ntiles, clo, chi, accum, rowmap,    \
-                       w.tile_cols, gap)
+                       w.tile_cols, gaps, search)
     const bool window = clo > 0 || chi < cols;
     const int variant = rowmap ? (window ? 5 : 4) : (accum >= 2 ? accum : (window ? 1 : 0));
     if (variant == 3) PSK_GO(0, 3);
@@ -381,22 +378,123 @@ static void launch_pos(int mode, int grid, hipStream_t s, int rows, int cols, in
 #undef PSK_GO
 }
 
-// nnz <= kSingleTile: the whole product in one launch of one workgroup
-hipError_t launch_spmv_csr_single(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
-                                  const float *vals, const float *x, float *y, hipStream_t s)
+// Small matrices: they are bound by launch latency, so one launch, and by the chain of dependent loads, so no search.  A
+// workgroup takes a block of whole rows (their positions are pos[first] .. pos[last + 1]: one load), walks them in chunks of
+// CH positions, the next chunk's loads in flight, and keeps its row sums in LDS.  In a chunk a row segment shorter than LONG
+// is summed by one thread, a longer one by a wave, one of VLONG or more by all waves.  Blocks are unequal in positions when
+// rows are; the size limit bounds what one workgroup can get.
+// 1024 rows of 10 entries: 4.0 us (as one tile of one workgroup 7.9); 2000 rows of 20: 4.0 (tiles and fix-up 10.0 in 3 launches).
+template <typename T>
+__global__ __launch_bounds__(1024) void k_spmv_row_blocks(int rows, const int *__restrict__ pos, const int *__restrict__ crd,
+                                                          const T *__restrict__ vals, const T *__restrict__ x,
+                                                          T *__restrict__ y, int block_rows)
 {
-    if (nnz <= 0 || nnz > kSingleTile) return hipErrorInvalidValue;
-    const int *notable = nullptr;
-    int *nocarry = nullptr;
-    float *nocarryval = nullptr;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(crd) | reinterpret_cast<uintptr_t>(vals)) & 15) == 0;
-    if (aligned)
-        PSK_LAUNCH((k_spmv_pos<1024, 16, 1, 7>), dim3(1), dim3(1024), 0, s, rows, cols, nnz, pos, crd, vals, x, y, notable,
-                   nocarry, nocarryval, 1, 0, cols, 0, notable, nocarry, nocarry);
-    else
-        PSK_LAUNCH((k_spmv_pos<1024, 16, 0, 7>), dim3(1), dim3(1024), 0, s, rows, cols, nnz, pos, crd, vals, x, y, notable,
-                   nocarry, nocarryval, 1, 0, cols, 0, notable, nocarry, nocarry);
+    constexpr int THREADS = 1024, NPT = 8, CH = THREADS * NPT, NW = THREADS / WAVE;
+    constexpr int LONG = 32, MAXLONG = CH / LONG, VLONG = 512, MAXVLONG = CH / VLONG;
+    __shared__ int spos[THREADS + 1];
+    __shared__ T sprod[skewed_size<1>(CH)];
+    __shared__ T ssum[THREADS];
+    __shared__ T swave[MAXVLONG][NW];
+    __shared__ int slong[MAXLONG], svlong[MAXVLONG], nlong, nvlong;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int ra = blockIdx.x * block_rows, n = min(block_rows, rows - ra);          // at most THREADS rows
+    if (tid <= n) spos[tid] = pos[ra + tid];
+    if (tid == 0) { spos[n] = pos[ra + n]; nlong = 0; nvlong = 0; }
+    T sum = 0;
+    ssum[tid] = 0;
+    __syncthreads();
+    const int p1 = spos[n];
+    const int my_lo = tid < n ? spos[tid] : 0, my_hi = tid < n ? spos[tid + 1] : 0;
+    auto wave_total = [&](T s) {
+#pragma unroll
+        for (int m = 1; m < WAVE; m <<= 1) s += __shfl_xor(s, m, WAVE);
+        return s;
+    };
+    int c[NPT];
+    T v[NPT];
+    auto load = [&](int base) {
+#pragma unroll
+        for (int g = 0; g < NPT; ++g) {
+            const int p = base + g * THREADS + tid;
+            c[g] = 0;
+            v[g] = 0;
+            if (base + g * THREADS < p1 && p < p1) { c[g] = crd[p]; v[g] = vals[p]; }
+        }
+    };
+    load(spos[0]);
+    for (int base = spos[0]; base < p1; base += CH) {
+        const int cnt = min(CH, p1 - base);
+#pragma unroll
+        for (int g = 0; g < NPT; ++g) {
+            const int i = g * THREADS + tid;
+            if (i < cnt) sprod[skew<1>(i)] = v[g] * x[c[g]];
+        }
+        if (base + CH < p1) load(base + CH);
+        __syncthreads();
+        const int lo = max(my_lo - base, 0), hi = min(my_hi - base, cnt);
+        if (hi - lo >= VLONG) {
+            svlong[atomicAdd(&nvlong, 1)] = tid;     // the segments are disjoint, so the lists cannot overflow
+        } else if (hi - lo >= LONG) {
+            slong[atomicAdd(&nlong, 1)] = tid;
+        } else {
+            T s = 0;
+            for (int i = lo; i < hi; ++i) s += sprod[skew<1>(i)];
+            sum += s;
+        }
+        __syncthreads();
+        const int nl = nlong, nv = nvlong;
+        for (int e = wave; e < nl; e += NW) {
+            const int r = slong[e], l = max(spos[r] - base, 0), h = min(spos[r + 1] - base, cnt);
+            T s = 0;
+            for (int i = l + lane; i < h; i += WAVE) s += sprod[skew<1>(i)];
+            s = wave_total(s);
+            if (lane == 0) ssum[r] += s;
+        }
+        for (int e = 0; e < nv; ++e) {
+            const int r = svlong[e], l = max(spos[r] - base, 0), h = min(spos[r + 1] - base, cnt);
+            T s = 0;
+            for (int i = l + tid; i < h; i += THREADS) s += sprod[skew<1>(i)];
+            s = wave_total(s);
+            if (lane == 0) swave[e][wave] = s;
+        }
+        __syncthreads();
+        if (tid < nv) {
+            T s = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) s += swave[tid][w];
+            ssum[svlong[tid]] += s;
+        }
+        if (tid == 0) { nlong = 0; nvlong = 0; }
+    }
+    __syncthreads();
+    if (tid < n) y[ra + tid] = sum + ssum[tid];
+}
+
+template <typename T>
+static hipError_t launch_row_blocks(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const T *vals, const T *x,
+                                    T *y, hipStream_t s)
+{
+    if (!spmv_small(rows, nnz, (int)sizeof(T))) return hipErrorInvalidValue;
+    // about 800 positions per workgroup, so that most of them finish with one load per thread
+    int groups = (nnz + 799) / 800;
+    if (groups < (rows + 1023) / 1024) groups = (rows + 1023) / 1024;
+    const int block_rows = (rows + groups - 1) / groups;
+    PSK_LAUNCH(k_spmv_row_blocks<T>, dim3((rows + block_rows - 1) / block_rows), dim3(1024), 0, s, rows, pos, crd, vals, x, y,
+               block_rows);
     return take_launch_status();
+}
+
+hipError_t launch_spmv_csr_small(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const float *vals,
+                                 const float *x, float *y, hipStream_t s)
+{
+    return launch_row_blocks<float>(rows, nnz, pos, crd, vals, x, y, s);
+}
+
+hipError_t launch_spmv_csr_small(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const double *vals,
+                                 const double *x, double *y, hipStream_t s)
+{
+    return launch_row_blocks<double>(rows, nnz, pos, crd, vals, x, y, s);
 }
 
 hipError_t launch_spmv_csr_ones(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
@@ -409,21 +507,21 @@ hipError_t launch_spmv_csr_ones(int32_t rows, int32_t cols, int32_t nnz, const i
     const int *nomap = nullptr;
     if ((reinterpret_cast<uintptr_t>(crd) & 15) == 0)
         PSK_LAUNCH((k_spmv_pos<256, 8, 1, 6>), dim3(grid), dim3(256), 0, s, rows, cols, nnz, pos, crd, none, x, y,
-                   w.tile_row, w.carry_row, w.carry_val, ntiles, 0, cols, 0, nomap, w.tile_cols, w.gap);
+                   w.tile_row, w.carry_row, w.carry_val, ntiles, 0, cols, 0, nomap, w.tile_cols, 1, 0);
     else
         PSK_LAUNCH((k_spmv_pos<256, 8, 0, 6>), dim3(grid), dim3(256), 0, s, rows, cols, nnz, pos, crd, none, x, y,
-                   w.tile_row, w.carry_row, w.carry_val, ntiles, 0, cols, 0, nomap, w.tile_cols, w.gap);
+                   w.tile_row, w.carry_row, w.carry_val, ntiles, 0, cols, 0, nomap, w.tile_cols, 1, 0);
     return take_launch_status();
 }
 
 hipError_t launch_spmv_csr_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *x, float *y, int32_t tile, int32_t col_passes,
-                                const Workspace &w, hipStream_t s, const int32_t *rowmap, bool gaps)
+                                const Workspace &w, hipStream_t s, int search, const int32_t *rowmap, bool gaps)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     if (ntiles == 0) return hipSuccess;
     const int grid = xcd_grid(ntiles);
-    int *gap = gaps ? w.gap : nullptr;
+    const int gap = gaps ? 1 : 0;
     // baselines: -1 = one pass with atomic adds for rows that span tiles, -2 = one pass without the
     // register temporary and the unrolled load loop
     const int baseline = col_passes == -1 ? 2 : (col_passes == -2 ? 3 : 0);
@@ -434,11 +532,11 @@ hipError_t launch_spmv_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     const bool aligned = ((reinterpret_cast<uintptr_t>(crd) | reinterpret_cast<uintptr_t>(vals)) & 15) == 0;
     const int vec = aligned ? 1 : 0;
     switch (tile) {
-        case 256:  launch_pos<64, 4>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap); break;
-        case 512:  launch_pos<128, 4>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap); break;
-        case 1024: launch_pos<256, 4>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap); break;
-        case 2048: launch_pos<256, 8>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap); break;
-        case 4096: launch_pos<256, 16>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap); break;
+        case 256:  launch_pos<64, 4>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap, p == 0 ? search : 0); break;
+        case 512:  launch_pos<128, 4>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap, p == 0 ? search : 0); break;
+        case 1024: launch_pos<256, 4>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap, p == 0 ? search : 0); break;
+        case 2048: launch_pos<256, 8>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap, p == 0 ? search : 0); break;
+        case 4096: launch_pos<256, 16>(vec, grid, s, rows, cols, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, rowmap, gap, p == 0 ? search : 0); break;
         default: return hipErrorInvalidValue;
     }
     }

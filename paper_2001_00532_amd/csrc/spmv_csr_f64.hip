@@ -28,11 +28,10 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
                                                           const int *__restrict__ crd,
                                                           const double *__restrict__ vals,
                                                           const double *__restrict__ x, double *__restrict__ y,
-                                                          const int *__restrict__ tile_row,
+                                                          int *tile_row,
                                                           int *__restrict__ carry_row,
                                                           double *__restrict__ carry_val, int ntiles, int clo,
-                                                          int chi, int accum, int *__restrict__ tile_cols,
-                                                          int *__restrict__ gap)
+                                                          int chi, int accum, int *__restrict__ tile_cols, int search)
 {
     constexpr int T = THREADS * NPT;
     constexpr int NW = THREADS / WAVE;
@@ -64,7 +63,9 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
     }
 
     // the dependent chain tile_row -> pos is started first and runs underneath the streams
-    const int r0 = tile_row[t], r1 = tile_row[t + 1];
+    if (ONES) search = 0;              // the table is part of the structure
+    int r0 = 0, r1 = 0;
+    if (!search) { r0 = tile_row[t]; r1 = tile_row[t + 1]; }
 
     double prod[NPT];
     int cmin = 0x7fffffff, cmax = -1;             // column range of the tile (first column pass)
@@ -92,6 +93,7 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
                 v[g] = ONES ? 1.0 : ld_stream(vals + t0 + g * THREADS + tid);
             }
         }
+        if (search) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
         double xg[NPT];
 #pragma unroll
         for (int g = 0; g < NPT; ++g) xg[g] = (!WIN || (c[g] >= clo && c[g] < chi)) ? x[c[g]] : 0.0;
@@ -103,6 +105,7 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
         }
     }
 
+    if (search && !full) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
     const int p_r0 = pos[r0], p_r1 = pos[r1];
     const int rbeg = (t == 0) ? 0 : r0;
     int my_lo = 0, my_hi = 0;
@@ -170,11 +173,11 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
 #pragma unroll
     for (int g = 0; g < NPT; ++g) sprod[skew<1>(index(g))] = prod[g];
     __syncthreads();
-    if (gap && rend - rbeg > kGapRows) {
+    if (r1 - rbeg > kGapRows) {
         // The tile's rows span a long run of empty rows (Section 6.2 walks past empty rows one by one; here that walk
         // would be done by this one workgroup).  As in the fp32 kernel: the row of every position is found by search (a
         // thread takes NPT consecutive positions), the row segments are summed by the thread that holds their first
-        // position, and the run of rows is handed to the fix-up step, whose extra workgroups clear its empty rows.
+        // position, and the empty rows are left to the fix-up step, whose extra workgroups clear them.
         const int i0 = tid * NPT;
         if (i0 < cnt) {
             int lo = r0, hi = r1;                       // max { r in [r0, r1] : pos[r] <= t0 + i0 }
@@ -208,10 +211,6 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
             double sum = 0.0;
             for (int j = i; j < cnt && srowid[j] == r; ++j) sum += sprod[skew<1>(j)];
             emit(r, sum);
-        }
-        if (tid == 0 && !(WIN && accum)) {
-            const int e = atomicAdd(&gap[0], 1);
-            if (e < ntiles) { gap[2 + 2 * e] = rbeg; gap[3 + 2 * e] = rend; }
         }
         return;
     }
@@ -251,12 +250,12 @@ bool spmv_csr_f64_tile_ok(int32_t tile) { return tile == 256 || tile == 512 || t
 template <int THREADS, int NPT>
 static void go(bool vec, bool win, int grid, hipStream_t s, int rows, int nnz, const int *pos, const int *crd,
                const double *vals, const double *x, double *y, const Workspace &w, int ntiles, int clo, int chi, int accum,
-               int *gap)
+               int search)
 {
     double *cv = reinterpret_cast<double *>(w.carry_val);
 #define PSK_GO(V, W)                                                                                                  \
     PSK_LAUNCH((k_spmv_pos_f64<THREADS, NPT, V, W>), dim3(grid), dim3(THREADS), 0, s, rows, nnz, pos, crd, vals, \
-                       x, y, w.tile_row, w.carry_row, cv, ntiles, clo, chi, accum, w.tile_cols, gap)
+                       x, y, w.tile_row, w.carry_row, cv, ntiles, clo, chi, accum, w.tile_cols, search)
     if (vec) { if (win) PSK_GO(true, true); else PSK_GO(true, false); }
     else { if (win) PSK_GO(false, true); else PSK_GO(false, false); }
 #undef PSK_GO
@@ -264,9 +263,8 @@ static void go(bool vec, bool win, int grid, hipStream_t s, int rows, int nnz, c
 
 hipError_t launch_spmv_csr_f64_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                     const double *vals, const double *x, double *y, int32_t tile, int32_t col_passes,
-                                    const Workspace &w, hipStream_t s, bool gaps)
+                                    const Workspace &w, hipStream_t s, int search)
 {
-    int *gap = gaps ? w.gap : nullptr;
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     if (ntiles == 0) return hipSuccess;
     const int grid = xcd_grid(ntiles);
@@ -277,10 +275,10 @@ hipError_t launch_spmv_csr_f64_main(int32_t rows, int32_t cols, int32_t nnz, con
         const bool win = col_passes > 1;
         const int accum = p > 0;
         switch (tile) {
-            case 256:  go<64, 4>(vec, win, grid, s, rows, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, gap); break;
-            case 512:  go<128, 4>(vec, win, grid, s, rows, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, gap); break;
-            case 1024: go<256, 4>(vec, win, grid, s, rows, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, gap); break;
-            case 2048: go<256, 8>(vec, win, grid, s, rows, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, gap); break;
+            case 256:  go<64, 4>(vec, win, grid, s, rows, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, p == 0 ? search : 0); break;
+            case 512:  go<128, 4>(vec, win, grid, s, rows, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, p == 0 ? search : 0); break;
+            case 1024: go<256, 4>(vec, win, grid, s, rows, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, p == 0 ? search : 0); break;
+            case 2048: go<256, 8>(vec, win, grid, s, rows, nnz, pos, crd, vals, x, y, w, ntiles, clo, chi, accum, p == 0 ? search : 0); break;
             default: return hipErrorInvalidValue;
         }
     }
@@ -300,7 +298,7 @@ hipError_t launch_spmv_csr_f64_ones(int32_t rows, int32_t nnz, const int32_t *po
     const bool vec = (reinterpret_cast<uintptr_t>(crd) & 15) == 0;
 #define PSK_GO(NPT, V)                                                                                                   \
     PSK_LAUNCH((k_spmv_pos_f64<256, NPT, V, false, true>), dim3(grid), dim3(256), 0, s, rows, nnz, pos, crd, none, x, y, \
-               w.tile_row, w.carry_row, cv, ntiles, 0, 0x7fffffff, 0, w.tile_cols, w.gap)
+               w.tile_row, w.carry_row, cv, ntiles, 0, 0x7fffffff, 0, w.tile_cols, 0)
     if (tile == 2048) { if (vec) PSK_GO(8, true); else PSK_GO(8, false); }
     else { if (vec) PSK_GO(4, true); else PSK_GO(4, false); }
 #undef PSK_GO

@@ -1,0 +1,75 @@
+"""Small products: blocks of whole rows in one launch (around the lengths at which a row is summed by a thread, a wave, a
+workgroup, around chunks, blocks and the size limits), the tile kernels that search their rows themselves (few tiles), and
+the clearing of long runs of empty rows, which the fix-up step finds from the table.  Bars: |got - ref| <= 1e-5 (fp64: 1e-14)
+* sum |a x| + 1e-30 (1e-300) per row; every row of y is preset to NaN."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2001_00532_amd as psk  # noqa: E402
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def check(lengths, f64, tile=0, cols=70_000, phases=(7,), seed=1):
+    A = wl.csr_from_lengths(np.asarray(lengths, dtype=np.int64), cols, seed=seed)
+    pos, crd = dev(A.pos), dev(A.crd)
+    if f64:
+        v, x = wl.dense_uniform_f64(A.nnz, 3, wl.S_VALS), wl.dense_uniform_f64(cols, 3, wl.S_X)
+        ref, mag = oracle.spmv_csr_f64(A.pos, A.crd, v, x)
+        f, op, bar = psk.psk_spmv_csr_f64, psk.PSK_OP_SPMV_CSR_F64, (1e-14, 1e-300)
+    else:
+        v, x = A.vals, wl.dense_uniform(cols, 3, wl.S_X)
+        ref, mag = oracle.spmv_csr(A.pos, A.crd, v, x)
+        f, op, bar = psk.psk_spmv_csr, psk.PSK_OP_SPMV_CSR, (1e-5, 1e-30)
+    y = torch.full((A.rows,), float("nan"), dtype=torch.float64 if f64 else torch.float32, device="cuda")
+    ws = psk.workspace(op, A.rows, A.nnz, tile=tile)
+    ws.fill_(0x7f)
+    for p in phases:
+        f(A.rows, cols, A.nnz, pos, crd, dev(v), dev(x), y, tile=tile, phases=p, ws=ws)
+    torch.cuda.synchronize()
+    ok, worst = oracle.within_tolerance(y.cpu().numpy(), ref, mag, *bar)
+    assert ok, "worst |err|/bar = %.3g" % worst
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("lengths", [
+    [31, 32, 33, 0, 511, 512, 513, 1], [8191], [8192], [8193], [8192 - 600, 600, 600], [0, 0, 24576], [24577], [5] * 1023,
+    [5] * 1024, [5] * 1025, [1] * 4096, [0] * 65535 + [7], [0] * 65536 + [7], [9000, 0, 9000, 3], [512] * 16 + [32] * 256,
+], ids=lambda v: "%dx%d" % (len(v), max(v)))
+def test_row_blocks(lengths, f64):
+    check(lengths, f64)
+
+
+@pytest.mark.parametrize("n", [49151, 49152, 49153])
+def test_size_limit_of_the_one_launch_path(n):
+    check([n], False)
+    check([n // 3, n - n // 3 - 7, 7], False)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("tile", [256, 1024])
+@pytest.mark.parametrize("phases", [(7,), (1, 2, 4), (7, 6)], ids=str)
+def test_tiles_that_search_their_rows(tile, phases, f64):
+    rng = np.random.default_rng(tile)
+    check(rng.choice([0, 1, 3, 20, 700], size=3000, p=[.3, .3, .2, .19, .01]), f64, tile, phases=phases)
+    check([tile] * 5 + [tile // 2] * 3, f64, tile, phases=phases)
+    check([3 * tile + 5, 0, 2], f64, tile, phases=phases)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("rows", [32768, 32769, 40961, 100_000, 8192 * 13, 8192 * 13 + 1])
+def test_long_runs_of_empty_rows_without_a_list(rows, f64):
+    for filled in ([0], [rows - 1], [rows // 2], [0, rows - 1], [8191, 8192, 8193, 40_000 % rows], [5, 33_000 % rows, rows - 2]):
+        L = np.zeros(rows, dtype=np.int64)
+        for i, r in enumerate(filled):
+            L[r] = (3, 700, 256, 1)[i % 4]
+        check(L, f64, 256)
+        check(L, f64, 1024, phases=(1, 2, 4))
