@@ -139,21 +139,24 @@ def lib() -> ctypes.CDLL:
 
 
 def _ptr(t, dtype=None):
-    """Device pointer of a tensor (None -> NULL).  Checks device, dtype and contiguity of the last dim."""
+    """Device address of a tensor (None -> NULL).  Checks device, dtype and contiguity of the last dim.  (An int: ctypes
+    converts it by the declared argument types; making a c_void_p of it first costs as much as the checks.)"""
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("expected a device tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError("expected dtype %s, got %s" % (dtype, t.dtype))
-    if t.numel() and t.stride(-1) != 1:
+    if t.stride(-1) != 1 and t.numel():
         raise ValueError("innermost dimension must be contiguous")
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else ctypes.c_void_p(t.data_ptr() or 0)
+    return t.data_ptr()
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """Address of the stream's hipStream_t.  The current one is asked for without building a Stream object."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _temporary_ws_ok(phases: int, what: str):
