@@ -572,7 +572,7 @@ int psk_mttkrp_csf3(int64_t dim_i, int64_t dim_k, int64_t dim_l, int64_t nslices
         // a compressed first level leaves rows of A without a slice: clear them all first; so does nnz = 0
         if (crd_i || ntiles == 0) e = launch_fill_zero_2d(A, dim_i, j, lda, s);
         if (ntiles > 0 && e == hipSuccess)
-            e = launch_mttkrp_main((int32_t)nslices, (int32_t)nnz, crd_i, pos_k, crd_k, pos_l, crd_l, vals, C, ldc, D,
+            e = launch_mttkrp_main(dim_k, dim_l, (int32_t)nslices, (int32_t)nnz, crd_i, pos_k, crd_k, pos_l, crd_l, vals, C, ldc, D,
                                    ldd, j, A, lda, tile, ws, ws.tile_aux, s);
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)

@@ -6,6 +6,7 @@
 // above the cut the same way it tracks the row of a CSR matrix -- here two levels, fiber and slice.
 #include "psk_dev.h"
 #include "psk_internal.h"
+#include <type_traits>
 
 namespace psk {
 
@@ -46,7 +47,7 @@ hipError_t launch_partition_csf3(int32_t nslices, int32_t nfibers, int32_t nnz, 
     return take_launch_status();
 }
 
-// One workgroup (4 waves) per tile of T leaf positions and per chunk of 64*VEC columns.
+// One workgroup (4 waves) per tile of T leaf positions and per chunk of 64/G columns.
 //
 // Tile metadata in LDS: sflag[i] = s if leaf position i is the last leaf of slice s (slices play the role
 // the rows play in SpMM; a slice's leaves are pos_l[pos_k[s]] .. pos_l[pos_k[s+1]]), and sk[i] = the mode-k
@@ -62,11 +63,11 @@ hipError_t launch_partition_csf3(int32_t nslices, int32_t nfibers, int32_t nnz, 
 // two misses of the D gather costs bandwidth, because the vector memory pipeline returns in order.
 // Segments, records, carries: as in the SpMM kernel (the first and last open segments of each wave are
 // chained by wave 0; a chain whose slice began before the tile becomes the tile's carry record).
-// G > 1 (narrow factor matrices, j <= 64/G, VEC = 1): the wave is split into G groups of 64/G lanes and in one
+// One column per lane.  G > 1 (narrow factor matrices, j <= 64/G): the wave is split into G groups of 64/G lanes and in one
 // step the groups take G consecutive leaves, so that one load instruction fetches G rows of D.  A lane keeps
 // its group's share of the open fiber and of the open slice; a fiber end multiplies every share by the C row
 // (no exchange needed: the product distributes over the shares), a slice end adds the shares across groups.
-template <int VEC, int G>
+template <int G>
 __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const int *__restrict__ crd_i,
                                                     const int *__restrict__ pos_k,
                                                     const int *__restrict__ crd_k,
@@ -81,9 +82,8 @@ __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const 
                                                     int *__restrict__ carry_row,
                                                     float *__restrict__ carry_val, int ntiles, int T)
 {
-    static_assert(G == 1 || VEC == 1, "lane groups only with one column per lane");
-    constexpr int THREADS = 256, NW = THREADS / WAVE, GW = WAVE / G, KW = GW * VEC, LONGF = 32;
-    constexpr int U = G > 1 ? 4 : (VEC == 4 ? 4 : 8);   // steps whose D rows are in flight together
+    constexpr int VEC = 1, THREADS = 256, NW = THREADS / WAVE, GW = WAVE / G, KW = GW * VEC, LONGF = 32;
+    constexpr int U = G > 1 ? 4 : 8;              // steps whose D rows are in flight together
     extern __shared__ int smeta[];                // sflag[T], sk[T], long-fiber queue [3 * T / LONGF]
     int *sflag = smeta, *sk = smeta + T, *slong = smeta + 2 * T;
     __shared__ float srec[2 * NW][KW];
@@ -320,9 +320,238 @@ __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const 
     if (straddle) finalize(r1);
 }
 
+// j > 16: a lane owns four adjacent columns and the 64/G lanes of a group take a chunk of consecutive leaves for themselves.
+// A group walks its leaves one after the other, with its own open fiber and open slice, so nothing is exchanged between
+// groups; in one step the wave's groups fetch G rows of D with one 16-byte load per lane.  The first and the last open
+// segment of every group go to records that wave 0 chains in position order at the end.  blockIdx.y walks chunks of
+// 256/G columns.  (Chunks of 32 columns for j = 64, so that the L2s hold half of D at a time, gained nothing: 1694 us at
+// D = 25.6 MB, the halves of D's rows share the cache sets.)
+// SMALL: byte offsets into C and D fit 32 bits.
+template <bool SMALL> struct OffT;
+template <> struct OffT<true> { typedef unsigned type; };
+template <> struct OffT<false> { typedef unsigned long long type; };
+
+// f(0), f(1), ... f(N - 1) with the index as a constant
+template <int N, typename F, int... I>
+__device__ __forceinline__ void for_each_index_(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void for_each_index(F f) { for_each_index_<N>(f, std::make_integer_sequence<int, N>{}); }
+
+// The value of lane J of every group of GW = 8 or 16 lanes, in all lanes of the group (swizzle of 32 lanes: keep the group's
+// bits, set the others to J).
+template <int GW, int J>
+__device__ __forceinline__ unsigned group_bcast(unsigned v)
+{
+    static_assert(GW == 8 || GW == 16, "group width");
+    return (unsigned)__builtin_amdgcn_ds_swizzle((int)v, (J << 5) | (0x1f & ~(GW - 1)));
+}
+template <int GW, int J>
+__device__ __forceinline__ float group_bcast(float v)
+{
+    return __builtin_bit_cast(float, group_bcast<GW, J>(__builtin_bit_cast(unsigned, v)));
+}
+template <int GW, int J>
+__device__ __forceinline__ unsigned long long group_bcast(unsigned long long v)
+{
+    return ((unsigned long long)group_bcast<GW, J>((unsigned)(v >> 32)) << 32) | group_bcast<GW, J>((unsigned)v);
+}
+
+template <int G, bool SMALL>
+__global__ __launch_bounds__(256) void k_mttkrp_groups(int nslices, int nnz, const int *__restrict__ crd_i,
+                                                       const int *__restrict__ pos_k,
+                                                       const int *__restrict__ crd_k,
+                                                       const int *__restrict__ pos_l,
+                                                       const int *__restrict__ crd_l,
+                                                       const float *__restrict__ vals,
+                                                       const float *__restrict__ C, long long ldc,
+                                                       const float *__restrict__ D, long long ldd, int jdim,
+                                                       float *__restrict__ A, long long lda,
+                                                       const int *__restrict__ tile_slice,
+                                                       const int *__restrict__ tile_fiber,
+                                                       int *__restrict__ carry_row,
+                                                       float *__restrict__ carry_val, int ntiles, int T)
+{
+    constexpr int THREADS = 256, NW = THREADS / WAVE, GW = WAVE / G, NG = NW * G, LONGF = 32, U = 4;
+    extern __shared__ int smeta[];                // sflag[T], sk[T], long-fiber queue [3 * T / LONGF]
+    int *sflag = smeta, *sk = smeta + T, *slong = smeta + 2 * T;
+    __shared__ v4f srec[2 * NG][GW];
+    __shared__ int srec_row[2 * NG];              // -2 unused, -1 open segment, >= 0 slice that ended
+    __shared__ int nlong;
+
+    const int t = xcd_tile(blockIdx.x, ntiles);
+    if (t < 0) return;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int t0 = t * T;
+    const int cnt = (nnz - t0 < T) ? nnz - t0 : T;
+    const int t1 = t0 + cnt;
+    const int g = lane / GW, gl = lane % GW;
+    const int col0 = (blockIdx.y * GW + gl) * 4;
+    const bool active = col0 < jdim;
+    const int col = col0 < jdim - 4 ? col0 : jdim - 4;      // the last lane shares columns with its neighbour, same values
+
+    for (int i = tid; i < T; i += THREADS) { sflag[i] = -1; sk[i] = 0; }
+    if (tid < 2 * NG) srec_row[tid] = -2;
+    if (tid == 0) nlong = 0;
+
+    const int r0 = tile_slice[t], r1 = tile_slice[t + 1];
+    const int q0 = tile_fiber[t], q1 = tile_fiber[t + 1];
+    const int leaf_r0 = pos_l[pos_k[r0]], leaf_r1 = pos_l[pos_k[r1]];   // first leaf of slices r0, r1
+    const bool has_carry = (t > 0) && (leaf_r0 < t0);
+    const int rbeg = (t == 0) ? 0 : r0;
+    const bool straddle = leaf_r1 != t1;          // slice r1 continues into the next tile
+    const int rend = straddle ? r1 + 1 : r1;
+    const int qend = (pos_l[q1] != t1) ? q1 + 1 : q1;   // fibers with leaves in this tile: q0 .. qend-1
+    if (tid == 0 && blockIdx.y == 0 && !has_carry) carry_row[t] = -1;
+    auto store = [&](float *row, v4f v) { __builtin_nontemporal_store((v4f_u)v, reinterpret_cast<v4f_u *>(row + col)); };
+    __syncthreads();
+
+    // ---- slice ends of this tile, zero rows for slices without leaves
+    for (int rb = rbeg + wave * WAVE; rb < rend; rb += THREADS) {
+        const int r = rb + lane;
+        const bool valid = r < rend;
+        const int ps = valid ? pos_l[pos_k[r]] : 0, pe = valid ? pos_l[pos_k[r + 1]] : 1;
+        if (valid && pe > ps) {
+            const int e = pe - 1 - t0;
+            if (e >= 0 && e < cnt) sflag[e] = r;
+        }
+        unsigned long long empty = __ballot(valid && pe == ps);
+        while (empty) {
+            const int j = __ffsll((long long)empty) - 1;
+            empty &= empty - 1;
+            if (active && g == 0) store(A + (long long)(crd_i ? crd_i[rb + j] : rb + j) * lda, v4f{});
+        }
+    }
+    // ---- mode-k coordinate of every leaf of the tile
+    for (int q = q0 + tid; q < qend; q += THREADS) {
+        int lo = pos_l[q] - t0, hi = pos_l[q + 1] - t0;
+        lo = lo < 0 ? 0 : lo;
+        hi = hi > cnt ? cnt : hi;
+        const int kk = crd_k[q];
+        if (hi - lo < LONGF) {
+            for (int i = lo; i < hi; ++i) sk[i] = (i == hi - 1) ? ~kk : kk;
+        } else {
+            const int e = atomicAdd(&nlong, 1);
+            if (e < T / LONGF) { slong[3 * e] = kk; slong[3 * e + 1] = lo; slong[3 * e + 2] = hi; }
+        }
+    }
+    __syncthreads();
+    {
+        const int nl = nlong < T / LONGF ? nlong : T / LONGF;
+        for (int e = wave; e < nl; e += NW) {
+            const int kk = slong[3 * e], lo = slong[3 * e + 1], hi = slong[3 * e + 2];
+            for (int i = lo + lane; i < hi; i += WAVE) sk[i] = (i == hi - 1) ? ~kk : kk;
+        }
+    }
+    __syncthreads();
+
+    // ---- the group's leaves.  A lane holds one leaf of its group's next GW; a step broadcasts the leaf's D offset and value
+    // inside the group.  Which leaves close a fiber is one ballot per GW leaves; the C row is requested where that happens,
+    // together with the D rows.  A group's last leaf closes its part of the open fiber.  FULL: every group has T / NG leaves.
+    const int gi = wave * G + g, per = (cnt + NG - 1) / NG;
+    const int gbeg = gi * per < cnt ? gi * per : cnt;
+    const int gend = gbeg + per < cnt ? gbeg + per : cnt;
+    v4f acc = {}, facc = {};                      // open slice, and sum of b * D(l, :) over the leaves of the open fiber
+    bool seen = false;
+    const char *const Cb = reinterpret_cast<const char *>(C + col), *const Db = reinterpret_cast<const char *>(D + col);
+    typedef typename OffT<SMALL>::type off_t;
+    off_t l_n = 0;
+    float v_n = 0.0f;
+    auto fetch = [&](int b) {                     // the leaves b .. b + GW - 1 of the group, one per lane
+        l_n = 0;
+        v_n = 0.0f;
+        if (b + gl < per && gbeg + b + gl < gend) {
+            l_n = (off_t)ld_stream(crd_l + t0 + gbeg + b + gl) * (off_t)(ldd * 4);
+            v_n = ld_stream(vals + t0 + gbeg + b + gl);
+        }
+    };
+    auto walk = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        fetch(0);
+        for (int b = 0; b < per; b += GW) {
+            const off_t l_l = l_n;
+            const float v_l = v_n;
+            const int mine = gbeg + b + gl;
+            const bool here = FULL || (b + gl < per && mine < gend);
+            const int k_l = here ? sk[mine] : 0;
+            const unsigned long long all = __ballot(here && (k_l < 0 || mine == gend - 1));
+            const unsigned closes = (unsigned)(all >> (g * GW));        // bit j: leaf b + j of the group closes
+            fetch(b + GW);
+            const int n = FULL ? GW : (per - b < GW ? per - b : GW);
+            for_each_index<GW / U>([&](auto part) {
+                constexpr int J0 = decltype(part)::value * U;
+                if (!FULL && J0 >= n) return;
+                v4f_u c[U], d[U];
+                float a[U];
+                int ke[U];
+                for_each_index<U>([&](auto uu) {
+                    constexpr int u = decltype(uu)::value, j = J0 + u;
+                    a[u] = group_bcast<GW, j>(v_l);
+                    d[u] = *reinterpret_cast<const v4f_u *>(Db + group_bcast<GW, j>(l_l));
+                    ke[u] = 0;
+                    if ((closes >> j) & 1u) {
+                        ke[u] = sk[gbeg + b + j];
+                        c[u] = *reinterpret_cast<const v4f_u *>(Cb + (off_t)(ke[u] < 0 ? ~ke[u] : ke[u]) * (off_t)(ldc * 4));
+                    }
+                });
+                for_each_index<U>([&](auto uu) {
+                    constexpr int u = decltype(uu)::value, j = J0 + u;
+                    if (FULL || (j < n && gbeg + b + j < gend)) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) facc[v] = fmaf(a[u], d[u][v], facc[v]);
+                    }
+                    if ((closes >> j) & 1u) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) { acc[v] = fmaf(c[u][v], facc[v], acc[v]); facc[v] = 0.0f; }
+                        const int f = ke[u] < 0 ? sflag[gbeg + b + j] : -1;
+                        if (f >= 0) {             // ... and the slice
+                            if (!seen) {
+                                seen = true;
+                                srec[2 * gi][gl] = acc;
+                                if (gl == 0) srec_row[2 * gi] = f;
+                            } else if (active) {
+                                store(A + (long long)(crd_i ? crd_i[f] : f) * lda, acc);
+                            }
+                            acc = v4f{};
+                        }
+                    }
+                });
+            });
+        }
+    };
+    if (cnt == T && per % GW == 0) walk(std::true_type{});
+    else walk(std::false_type{});
+    if (gbeg < gend) {
+        const int slot = seen ? 2 * gi + 1 : 2 * gi;
+        srec[slot][gl] = acc;
+        if (gl == 0) srec_row[slot] = -1;
+    }
+    __syncthreads();
+
+    // ---- chain the records (wave 0, group 0)
+    if (wave != 0 || g != 0) return;
+    v4f run = {};
+    auto finalize = [&](int r) {
+        if (has_carry && r == r0) {
+            if (active) *reinterpret_cast<v4f_u *>(carry_val + (long long)t * jdim + col) = run;
+            if (lane == 0 && blockIdx.y == 0) carry_row[t] = r;
+        } else if (active) {
+            store(A + (long long)(crd_i ? crd_i[r] : r) * lda, run);
+        }
+        run = v4f{};
+    };
+    for (int rec = 0; rec < 2 * NG; ++rec) {
+        const int code = srec_row[rec];
+        if (code == -2) continue;
+        run += srec[rec][gl];
+        if (code >= 0) finalize(code);
+    }
+    if (straddle) finalize(r1);
+}
+
 bool mttkrp_tile_ok(int32_t tile) { return tile == 256 || tile == 512 || tile == 1024 || tile == 2048; }
 
-hipError_t launch_mttkrp_main(int32_t nslices, int32_t nnz, const int32_t *crd_i, const int32_t *pos_k,
+hipError_t launch_mttkrp_main(int64_t dim_k, int64_t dim_l, int32_t nslices, int32_t nnz, const int32_t *crd_i, const int32_t *pos_k,
                               const int32_t *crd_k, const int32_t *pos_l, const int32_t *crd_l, const float *vals,
                               const float *C, int64_t ldc, const float *D, int64_t ldd, int32_t j, float *A,
                               int64_t lda, int32_t tile, const Workspace &w, const int32_t *tile_fiber,
@@ -330,24 +559,30 @@ hipError_t launch_mttkrp_main(int32_t nslices, int32_t nnz, const int32_t *crd_i
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     if (ntiles == 0) return hipSuccess;
-    const uintptr_t al = reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D) | reinterpret_cast<uintptr_t>(A);
-    int vec = 1;
-    if (j > 64 && j % 2 == 0 && ldc % 2 == 0 && ldd % 2 == 0 && lda % 2 == 0 && (al & 7) == 0) vec = 2;
-    if (j > 128 && j % 4 == 0 && ldc % 4 == 0 && ldd % 4 == 0 && lda % 4 == 0 && (al & 15) == 0) vec = 4;
-    const int groups = j <= 8 ? 8 : (j <= 16 ? 4 : (j <= 32 ? 2 : 1));
-    const int kw = WAVE * vec / groups;
-    const dim3 grid(xcd_grid(ntiles), (j + kw - 1) / kw);
     const size_t lds = ((size_t)2 * tile + 3 * (size_t)(tile / 32)) * sizeof(int);
-#define PSK_GO(V, GG)                                                                                           \
-    PSK_LAUNCH((k_mttkrp_pos<V, GG>), grid, dim3(256), lds, s, nslices, nnz, crd_i, pos_k, crd_k, pos_l,    \
+#define PSK_GO(K, GRID)                                                                                         \
+    PSK_LAUNCH(K, GRID, dim3(256), lds, s, nslices, nnz, crd_i, pos_k, crd_k, pos_l,                            \
                        crd_l, vals, C, (long long)ldc, D, (long long)ldd, j, A, (long long)lda, w.tile_row,         \
                        tile_fiber, w.carry_row, w.carry_val, ntiles, tile)
-    if (groups == 8) PSK_GO(1, 8);
-    else if (groups == 4) PSK_GO(1, 4);
-    else if (groups == 2) PSK_GO(1, 2);
-    else if (vec == 4) PSK_GO(4, 1);
-    else if (vec == 2) PSK_GO(2, 1);
-    else PSK_GO(1, 1);
+    const int nx = xcd_grid(ntiles);
+    const int64_t most = 0xffffffffll / 4;
+    const bool small = ldd <= most / (dim_l > 0 ? dim_l : 1) && ldc <= most / (dim_k > 0 ? dim_k : 1);
+#define PSK_GROUPS(G)                                                                                           \
+    do {                                                                                                         \
+        if (small) PSK_GO((k_mttkrp_groups<G, true>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                  \
+        else PSK_GO((k_mttkrp_groups<G, false>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                       \
+    } while (0)
+    // us at 23 M / 4.6 M leaves, D of 50 000 / 10 000 rows, against one column per lane (two or four above j = 64):
+    //   j = 16: 379 / 114 with four columns per lane against 353 / 114, so not there;  24: 395 / 106 against 503 / 151;
+    //   32: 366 / 97 against 503 / 151;  40: 560 / 116 against 613 / 172;  96: 1094 / 195 against 1124 / 209;  128: 1387 / 207
+    //   against 1538 / 214.  j = 64: 119 against 174 while D (2.6 MB) stays in the L2s; from 12.8 MB on both move D's rows at
+    //   the fabric's rate and one lane per column is 1-2 % ahead (46 M leaves, D 25.6 MB: 1628 against 1595).
+    if (j <= 8) PSK_GO((k_mttkrp_pos<8>), dim3(nx));
+    else if (j <= 16) PSK_GO((k_mttkrp_pos<4>), dim3(nx));
+    else if (j <= 32) PSK_GROUPS(8);
+    else if (j > 48 && j <= 64 && 4 * dim_l * j > (int64_t(8) << 20)) PSK_GO((k_mttkrp_pos<1>), dim3(nx));
+    else PSK_GROUPS(4);
+#undef PSK_GROUPS
 #undef PSK_GO
     return take_launch_status();
 }

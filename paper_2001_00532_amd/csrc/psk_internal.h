@@ -217,7 +217,7 @@ bool mttkrp_tile_ok(int32_t tile);
 hipError_t launch_partition_csf3(int32_t nslices, int32_t nfibers, int32_t nnz, const int32_t *pos_k,
                                  const int32_t *pos_l, int32_t tile, int32_t *tile_slice, int32_t *tile_fiber,
                                  hipStream_t s);
-hipError_t launch_mttkrp_main(int32_t nslices, int32_t nnz, const int32_t *crd_i, const int32_t *pos_k,
+hipError_t launch_mttkrp_main(int64_t dim_k, int64_t dim_l, int32_t nslices, int32_t nnz, const int32_t *crd_i, const int32_t *pos_k,
                               const int32_t *crd_k, const int32_t *pos_l, const int32_t *crd_l, const float *vals,
                               const float *C, int64_t ldc, const float *D, int64_t ldd, int32_t j, float *A,
                               int64_t lda, int32_t tile, const Workspace &w, const int32_t *tile_fiber,

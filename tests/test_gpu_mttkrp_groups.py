@@ -1,0 +1,60 @@
+"""MTTKRP where its kernels change over: numbers of columns around the group widths and chunks, tiles whose leaves divide evenly
+among the groups and tiles that do not (the last one), fibers and slices that end at a group's, a wave's or a tile's border,
+operands whose rows are not aligned, a factor matrix above the size at which 64 columns go to the other kernel.
+Bar: |got - ref| <= 1e-5 * sum |b c d| + 1e-30 per element."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2001_00532_amd as psk  # noqa: E402
+
+
+def dev(a):
+    return None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def check(fibers, leaves, dims, j, tile, pad=1, compressed=False):
+    T = wl.csf3_from_lengths(np.asarray(fibers), np.asarray(leaves), dims, seed=j + 3, compressed_i=compressed)
+    I, K, L = dims
+    C = wl.dense_uniform(K * (j + pad), 7, wl.S_B).reshape(K, j + pad)
+    D = wl.dense_uniform(L * (j + pad), 8, wl.S_B).reshape(L, j + pad)
+    ref, mag = oracle.mttkrp_csf3(T.pos_k, T.crd_k, T.pos_l, T.crd_l, T.vals, C[:, :j], D[:, :j], threads=8)
+    rows = T.crd_i if compressed else np.arange(T.nslices)
+    want, bar = np.zeros((I, j)), np.zeros((I, j))
+    want[rows], bar[rows] = ref, mag
+    A = torch.full((I, j + pad), float("nan"), device="cuda")
+    psk.psk_mttkrp_csf3(dims, dev(T.crd_i), dev(T.pos_k), dev(T.crd_k), dev(T.pos_l), dev(T.crd_l), dev(T.vals),
+                        dev(C)[:, :j], dev(D)[:, :j], A[:, :j], tile=tile)
+    torch.cuda.synchronize()
+    got = A.cpu().numpy()
+    assert np.isnan(got[:, j:]).all(), "columns past j were written"
+    ok, worst = oracle.within_tolerance(got[:, :j], want, bar)
+    assert ok, "j %d tile %d: %.3g of the bar" % (j, tile, worst)
+
+
+@pytest.mark.parametrize("j", [16, 17, 20, 31, 32, 33, 36, 47, 48, 49, 63, 64, 65, 100, 128, 130])
+def test_columns_and_borders(j):
+    rng = np.random.default_rng(j)
+    fps = rng.integers(0, 6, size=400)
+    check(fps, rng.choice([0, 1, 2, 7, 8, 9, 60], size=int(fps.sum())), (400, 300, 500), j, 256)
+    check(fps, rng.choice([1, 8, 16, 64], size=int(fps.sum())), (900, 300, 500), j, 1024, pad=0, compressed=True)
+    check([1, 1, 2, 1], [256, 8, 248, 2048, 5], (4, 30, 3000), j, 256, pad=3)
+
+
+@pytest.mark.parametrize("tile", [0, 256, 512, 1024, 2048])
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 4096 + 31])
+def test_uneven_last_tiles(n, tile):
+    check([1], [n], (1, 5, 5000), 24, tile)
+    check([n // 3, n - 2 * (n // 3)], [1] * (n // 3) + [2] * (n // 3) + [1] * (n - 3 * (n // 3)), (2, 5000, 70), 40, tile)
+
+
+def test_large_factor_matrix():
+    rng = np.random.default_rng(5)
+    for L in (30_000, 40_000):                 # 64 columns: 7.7 MB and 10.2 MB
+        check(np.full(50, 3), rng.integers(1, 40, size=150), (50, 60, L), 64, 0)
+        check(np.full(50, 3), rng.integers(1, 40, size=150), (50, 60, L), 52, 256)
