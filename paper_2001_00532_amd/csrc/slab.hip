@@ -686,7 +686,7 @@ __global__ __launch_bounds__(256) void k_block_bases2(const int *__restrict__ to
 // The entries leave as runs of consecutive slots; blocks are dealt to the dies in contiguous ranges, so that the runs of
 // neighbouring blocks meet in one L2 and reach memory as whole lines.
 template <typename T>
-__global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restrict__ pos, const int *__restrict__ crd,
+__global__ __launch_bounds__(256) void k_block_place(int rows, int nnz, const int *__restrict__ pos, const int *__restrict__ crd,
                                                      const T *__restrict__ vals, const int *__restrict__ tile_row,
                                                      const unsigned short *__restrict__ H, const int *__restrict__ E,
                                                      const int *__restrict__ slab_chunk, int nslabs, int nblk, int nbits,
@@ -700,15 +700,14 @@ __global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restr
     constexpr int ROWS_WALK = 8 * BUILD_BT;
     __shared__ unsigned short woff[NW][kStageSlabs];   // entries of (wave, slab) so far; later the place of the wave's first one
     __shared__ int lbase[kStageSlabs + 1];             // first staging place of each slab
-    __shared__ int2 gbase[kStageSlabs];                // x: slot of a staged entry = x + its place; y: bit 0 = the slab's run
-                                                       // continues a pair of an earlier block, bit 1 = it is continued
-    __shared__ int sbase[kStageSlabs];                 // starts before the slab's first staging place
+    __shared__ int gbase[kStageSlabs];                 // slot of a staged entry = gbase[slab] + its place
+    __shared__ unsigned short sbase[kStageSlabs];      // starts before the slab's first staging place
     __shared__ T s_val[BUILD_BT];
     __shared__ unsigned s_all[BUILD_BT + 2];           // one entry of no slab on either side
     unsigned *const s_meta = s_all + 1;                // row ordinal (12 bits) | position << 12 (11 bits) | slab << 23
     __shared__ unsigned short s_col[BUILD_BT];
     __shared__ unsigned rowbits[2 * BITS_W], posbits[2 * BITS_W];
-    __shared__ unsigned long long startbits[BITS_W];
+    __shared__ unsigned long long startbits[BITS_W], endbits[BITS_W];
     __shared__ int row_pre[BITS_W], pos_pre[BITS_W + 1], start_pre[BITS_W + 1];
     __shared__ int s_w[4];
     const int b = xcd_tile(blockIdx.x, nblk);
@@ -720,37 +719,42 @@ __global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restr
 
     unsigned c[STEPS];
     T v[STEPS];
+    const bool full = nvalid == BUILD_BT;
+    {
+        const int *const cb = crd + p0 + wave * QUART;
+        const T *const vb = vals + p0 + wave * QUART;
+        if (full) {
 #pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        const int i = wave * QUART + st * WAVE + lane;
-        c[st] = 0;
-        v[st] = T(0);
-        if (i < nvalid) { c[st] = (unsigned)ld_stream(crd + p0 + i); v[st] = ld_stream(vals + p0 + i); }
+            for (int st = 0; st < STEPS; ++st) { c[st] = (unsigned)ld_stream(cb + (st * WAVE + lane)); v[st] = ld_stream(vb + (st * WAVE + lane)); }
+        } else {
+#pragma unroll
+            for (int st = 0; st < STEPS; ++st) {
+                const bool valid = wave * QUART + st * WAVE + lane < nvalid;
+                c[st] = valid ? (unsigned)cb[st * WAVE + lane] : 0u;
+                v[st] = valid ? vb[st * WAVE + lane] : T(0);
+            }
+        }
     }
     const int r_lo = tile_row[b], r_hi = tile_row[b + 1];
+    int h = 0, e = 0;
+    if (tid < nslabs) { h = H[(long long)b * nslabs + tid]; e = E[(long long)b * nslabs + tid]; }
+    // row starts: the first 256 rows' positions are requested here, ahead of the barrier
+    const int p_first = r_lo + 1 + tid <= r_hi ? pos[r_lo + 1 + tid] : 0x7fffffff;
+    const int p_lo = pos[r_lo], p_end = r_hi < rows ? pos[r_hi + 1] : nnz;
     for (int i = tid; i < NW * kStageSlabs; i += 256) (&woff[0][0])[i] = 0;
     if (tid < 2 * BITS_W) { rowbits[tid] = 0; posbits[tid] = 0; }
-    if (tid == 0) { s_all[0] = ~0u; s_meta[nvalid] = ~0u; }
-    if (tid < nslabs) {
-        const int h = H[(long long)b * nslabs + tid], e = E[(long long)b * nslabs + tid];
-        int x = 0;
-        if (h & H_HEAD) {           // the slab's first entry belongs to row r_lo, which began in block bp
-            const long long bp = pos[r_lo] / BUILD_BT;
-            if ((H[bp * nslabs + tid] & H_TAIL) || e - E[(bp + 1) * nslabs + tid] > 0) x |= 1;
-        }
-        if (h & H_TAIL) {           // the slab's last entry belongs to row r_hi, which ends in block be
-            const long long be = (pos[r_hi + 1] - 1) / BUILD_BT;
-            if ((H[be * nslabs + tid] & H_HEAD) || E[be * nslabs + tid] - e - (h & H_COUNT) > 0) x |= 2;
-        }
-        gbase[tid] = make_int2(slab_chunk[tid] * SLAB_CH + e, x);
-    }
+    if (tid == 0) s_all[0] = ~0u;
+    for (int i = nvalid + tid; i <= BUILD_BT; i += 256) s_meta[i] = ~0u;
+    if (tid < nslabs) gbase[tid] = slab_chunk[tid] * SLAB_CH + e;
     __syncthreads();
     // row starts inside the block; rows that start at its first position need no bit (nothing precedes them here)
     if (r_hi - r_lo <= ROWS_WALK) {
-        for (int r = r_lo + 1 + tid; r <= r_hi; r += 256) {
-            const long long i = (long long)pos[r] - p0;
+        auto mark = [&](int p) {
+            const long long i = (long long)p - p0;
             if (i < nvalid) atomicOr(&rowbits[i >> 5], 1u << (i & 31));
-        }
+        };
+        mark(p_first);
+        for (int r = r_lo + 257 + tid; r <= r_hi; r += 256) mark(pos[r]);
     } else {                        // a long run of empty rows: ask for every position instead
         for (int i = tid; i < nvalid; i += 256) {
             const int p = (int)(p0 + i);
@@ -762,17 +766,28 @@ __global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restr
             if (i > 0 && pos[lo] == p) atomicOr(&rowbits[i >> 5], 1u << (i & 31));
         }
     }
+    // Whether the slab's entries of this block continue a pair of an earlier block (the first one belongs to row r_lo, which
+    // began in block bp) and whether the last one's row r_hi, which ends in block be, goes on in the slab: requested here,
+    // used when the entries are staged.  (Where the block has no such entry the flags of h are clear and the places asked
+    // for, held inside the arrays, do not matter.)
+    int from = 0, to = 0;
+    if (tid < nslabs) {
+        const long long bp = p_lo / BUILD_BT, b1 = bp < b ? bp + 1 : b;
+        const long long be = max((long long)b, min((long long)nblk - 1, (long long)(p_end > 0 ? p_end - 1 : 0) / BUILD_BT));
+        from = (H[bp * nslabs + tid] & H_TAIL) + (e - E[b1 * nslabs + tid]);
+        to = (H[be * nslabs + tid] & H_HEAD) + (E[be * nslabs + tid] - e - (h & H_COUNT));
+    }
     // rank of every entry among the wave's entries of its slab (a wave touches only its own row of woff; its LDS operations
     // execute in program order)
     int rank[STEPS];
 #pragma unroll
     for (int st = 0; st < STEPS; ++st) {
-        const bool valid = wave * QUART + st * WAVE + lane < nvalid;
+        const int left = nvalid - (wave * QUART + st * WAVE);       // valid lanes of this step (uniform)
+        const unsigned long long all = left >= WAVE ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
         const unsigned sl = c[st] / W;
         c[st] = (c[st] - sl * W) | (sl << 16);              // column in the slab (15 bits), slab
-        const unsigned long long all = __ballot(valid);
         unsigned plo = (unsigned)all, phi = (unsigned)(all >> 32);     // peers: the valid lanes with this lane's slab
-        if (__ballot(valid && sl != (unsigned)__builtin_amdgcn_readfirstlane((int)sl)) != 0) {   // sorted columns of a long row: one slab
+        if ((__ballot(sl != (unsigned)__builtin_amdgcn_readfirstlane((int)sl)) & all) != 0) {   // sorted columns of a long row: one slab
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 if (k >= nbits) break;
@@ -786,7 +801,7 @@ __global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restr
         const int mine = (int)__builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
         rank[st] = before + mine;
         __builtin_amdgcn_wave_barrier();
-        if (valid && mine == 0) woff[wave][sl] = (unsigned short)(before + __popc(plo) + __popc(phi));
+        if (mine == 0 && lane < left) woff[wave][sl] = (unsigned short)(before + __popc(plo) + __popc(phi));
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
@@ -801,7 +816,7 @@ __global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restr
         int o = block_scan_256(sum, s_w, &total) - sum;
         if (tid < nslabs) {
             lbase[tid] = o;
-            gbase[tid].x -= o;
+            gbase[tid] -= o;
 #pragma unroll
             for (int w = 0; w < NW; ++w) { woff[w][tid] = (unsigned short)o; o += n[w]; }
         }
@@ -828,28 +843,44 @@ __global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restr
         }
     }
     __syncthreads();
-    constexpr unsigned ORD = 0xfffu, SLAB = 0xff800000u;
-    unsigned mine = 0;                                 // bit k: this thread's k-th entry starts a pair
+    // starts and ends inside the block, as bitmaps over the staging places: an entry starts a pair where slab or row differ
+    // from the entry before it, and ends one where the next entry starts one (the places behind the last hold no slab)
+    constexpr unsigned KEY = 0xff800fffu;
 #pragma unroll
     for (int k = 0; k < BUILD_BT / 256; ++k) {
-        const int li = tid + 256 * k;
-        bool start = false;
-        if (li < nvalid) {
-            const unsigned m = s_meta[li], dp = m ^ s_meta[li - 1], dn = m ^ s_meta[li + 1];
-            const int2 g = gbase[m >> 23];
-            const int dst = g.x + li;
-            const bool p_same = ((dp & SLAB) == 0 & (dp & ORD) == 0) | ((dp & SLAB) != 0 & (g.y & 1) != 0);
-            const bool n_same = ((dn & SLAB) == 0 & (dn & ORD) == 0) | ((dn & SLAB) != 0 & (g.y & 2) != 0);
-            start = ((dst & (SLAB_CH - 1)) == 0) | !p_same;
-            const bool end = ((dst & (SLAB_CH - 1)) == SLAB_CH - 1) | !n_same;
-            svals[slab_value_index<SlabOf<T>::G>(dst)] = s_val[li];
-            scol[dst] = (unsigned short)(s_col[li] | (end ? 0x8000u : 0u));
-            const unsigned i = (m >> 12) & (BUILD_BT - 1);
-            if (start) atomicOr(&posbits[i >> 5], 1u << (i & 31));
+        const int w = 4 * k + wave, li = w * WAVE + lane;
+        const unsigned m = s_meta[li];
+        const unsigned long long st = __ballot(((m ^ s_meta[li - 1]) & KEY) != 0), en = __ballot(((m ^ s_meta[li + 1]) & KEY) != 0);
+        const int left = nvalid - w * WAVE;                // entries among these places
+        if (lane == 0) { startbits[w] = left >= WAVE ? st : (left > 0 ? st & ((1ull << left) - 1ull) : 0ull); endbits[w] = en; }
+    }
+    __syncthreads();
+    // per slab: no start / end where the row's entries of this slab go on in another block, both at the chunks' borders
+    if (tid < nslabs && lbase[tid] < lbase[tid + 1]) {
+        const int l0 = lbase[tid], l1 = lbase[tid + 1];
+        const int g = gbase[tid];
+        unsigned *const sb = reinterpret_cast<unsigned *>(startbits), *const eb = reinterpret_cast<unsigned *>(endbits);
+        if ((h & H_HEAD) && from > 0) atomicAnd(&sb[l0 >> 5], ~(1u << (l0 & 31)));
+        if ((h & H_TAIL) && to > 0) atomicAnd(&eb[(l1 - 1) >> 5], ~(1u << ((l1 - 1) & 31)));
+        for (int li = l0 + ((SLAB_CH - ((g + l0) & (SLAB_CH - 1))) & (SLAB_CH - 1)); li <= l1; li += SLAB_CH) {   // slots that begin a chunk
+            if (li < l1) atomicOr(&sb[li >> 5], 1u << (li & 31));
+            if (li > l0) atomicOr(&eb[(li - 1) >> 5], 1u << ((li - 1) & 31));
         }
-        const unsigned long long w = __ballot(start);
-        if (lane == 0) startbits[4 * k + wave] = w;
-        mine |= start ? 1u << k : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < BUILD_BT / 256; ++k) {
+        const int w = 4 * k + wave, li = w * WAVE + lane;
+        if (li < nvalid) {
+            const unsigned m = s_meta[li];
+            const int dst = gbase[m >> 23] + li;
+            const unsigned word = lane < 32 ? (unsigned)endbits[w] : (unsigned)(endbits[w] >> 32);
+            svals[slab_value_index<SlabOf<T>::G>(dst)] = s_val[li];
+            scol[dst] = (unsigned short)(s_col[li] | (((word >> (lane & 31)) & 1u) << 15));
+            const unsigned sw = lane < 32 ? (unsigned)startbits[w] : (unsigned)(startbits[w] >> 32);
+            const unsigned i = (m >> 12) & (BUILD_BT - 1);
+            if ((sw >> (lane & 31)) & 1u) atomicOr(&posbits[i >> 5], 1u << (i & 31));
+        }
     }
     __syncthreads();
     if (wave == 0) {
@@ -873,7 +904,7 @@ __global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restr
     };
     if (tid < nslabs) {
         const int n0 = starts_before(lbase[tid]), n1 = starts_before(lbase[tid + 1]);
-        sbase[tid] = n0;
+        sbase[tid] = (unsigned short)n0;
         N[(long long)b * (nslabs + 1) + tid] = (unsigned short)(n1 - n0);
     }
     if (tid == 0) N[(long long)b * (nslabs + 1) + nslabs] = (unsigned short)start_pre[BITS_W];
@@ -881,16 +912,16 @@ __global__ __launch_bounds__(256) void k_block_place(int nnz, const int *__restr
 #pragma unroll
     for (int k = 0; k < BUILD_BT / 256; ++k) {
         const int w = 4 * k + wave;
-        if (__ballot((mine >> k) & 1u) == 0) continue;
-        const int nth_start = start_pre[w] + lanes_below(startbits[w]);
-        if ((mine >> k) & 1u) {
+        const unsigned long long word = startbits[w];
+        const int nth_start = start_pre[w] + lanes_below(word);
+        if ((word >> lane) & 1ull) {
             const int li = tid + 256 * k;
             const unsigned m = s_meta[li], sl = m >> 23;
-            const int dst = gbase[sl].x + li;
+            const int dst = gbase[sl] + li;
             const unsigned e = (sl << 16) | (unsigned)(nth_start - sbase[sl]);
             const unsigned i = (m >> 12) & (BUILD_BT - 1), iw = i >> 6;
-            const unsigned long long word = ((unsigned long long)posbits[2 * iw + 1] << 32) | posbits[2 * iw];
-            starts[p0 + pos_pre[iw] + __popcll(word & ((1ull << (i & 63)) - 1ull))] = (int)e;
+            const unsigned long long pw = ((unsigned long long)posbits[2 * iw + 1] << 32) | posbits[2 * iw];
+            starts[p0 + pos_pre[iw] + __popcll(pw & ((1ull << (i & 63)) - 1ull))] = (int)e;
             if ((dst & (SLAB_CH - 1)) == 0) chunk_at[dst / SLAB_CH] = ((unsigned long long)b << 32) | e;
         }
     }
@@ -1153,7 +1184,7 @@ static hipError_t launch_slab_build_t(int32_t rows, int32_t cols, int32_t nnz, c
         PSK_LAUNCH(k_col_scan, dim3(S), dim3(256), 0, s, w.part, nparts, S, total);
         PSK_LAUNCH(k_col_chunks<true>, dim3(nparts), dim3(256), 0, s, w.H16, nblk, S, w.part, E);
         PSK_LAUNCH(k_block_bases, dim3(1), dim3(256), 0, s, total, S, slab_chunk, w.meta);
-        PSK_LAUNCH(k_block_place<T>, dim3(grid), dim3(256), 0, s, nnz, pos, crd, vals, w.tile_row, w.H16, E, slab_chunk, S, nblk,
+        PSK_LAUNCH(k_block_place<T>, dim3(grid), dim3(256), 0, s, rows, nnz, pos, crd, vals, w.tile_row, w.H16, E, slab_chunk, S, nblk,
                    nbits, svals, scol_d, w.N16, w.src, w.pbits, w.pbits_pre, w.chunk_at);
         PSK_LAUNCH(k_col_chunks<false>, dim3(nparts), dim3(256), 0, s, w.N16, nblk, S1, w.part, F);
         PSK_LAUNCH(k_col_scan, dim3(S1), dim3(256), 0, s, w.part, nparts, S1, starts_total);
