@@ -94,6 +94,74 @@ hipError_t launch_partition(int64_t rows, int64_t nnz, const int32_t *pos, int32
     return take_launch_status();
 }
 
+// Order in which SpMM tiles are worked on when rows are longer than tiles: by the column of a tile's first position, in ORDER_BINS
+// steps.  In CSR order the tiles in flight sit anywhere in their rows and gather from all of B; ordered, they gather from a
+// range of columns about as wide as a tile's.  Only the order changes: tiles, carries and sums stay as they are.  Counting
+// sort over blocks of ORDER_BLOCK tiles, the order inside a step is of no concern.
+constexpr int ORDER_BINS = 64, ORDER_BLOCK = 1024;
+__device__ __forceinline__ int tile_bin(const int *__restrict__ crd, int t, int tile, int cols)
+{
+    return (int)((long long)crd[(long long)t * tile] * ORDER_BINS / cols);
+}
+
+__global__ __launch_bounds__(256) void k_tile_bins(int ntiles, int tile, int cols, const int *__restrict__ crd,
+                                                   int *__restrict__ hist)
+{
+    __shared__ int h[ORDER_BINS];
+    if (threadIdx.x < ORDER_BINS) h[threadIdx.x] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < ORDER_BLOCK; i += 256) {
+        const int t = blockIdx.x * ORDER_BLOCK + i;
+        if (t < ntiles) atomicAdd(&h[tile_bin(crd, t, tile, cols)], 1);
+    }
+    __syncthreads();
+    if (threadIdx.x < ORDER_BINS) hist[blockIdx.x * ORDER_BINS + threadIdx.x] = h[threadIdx.x];
+}
+
+__global__ __launch_bounds__(256) void k_tile_order(int rows, int nnz, int ntiles, int tile, int cols, int over,
+                                                    const int *__restrict__ pos, const int *__restrict__ crd, int *tile_row,
+                                                    const int *__restrict__ hist, int *__restrict__ records)
+{
+    constexpr int PARTS = 256 / ORDER_BINS;
+    __shared__ int sum[PARTS][ORDER_BINS], mine[PARTS][ORDER_BINS], at[ORDER_BINS];
+    const int bin = threadIdx.x % ORDER_BINS, part = threadIdx.x / ORDER_BINS;
+    int all = 0, before = 0;
+    for (int w = part; w < (int)gridDim.x; w += PARTS) {
+        const int v = hist[w * ORDER_BINS + bin];
+        all += v;
+        before += w < (int)blockIdx.x ? v : 0;
+    }
+    sum[part][bin] = all;
+    mine[part][bin] = before;
+    __syncthreads();
+    if (threadIdx.x < ORDER_BINS) {
+        int base = 0;
+        for (int p = 0; p < PARTS; ++p) {
+            base += mine[p][bin];
+            for (int b = 0; b < bin; ++b) base += sum[p][b];
+        }
+        at[bin] = base;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < ORDER_BLOCK; i += 256) {
+        const int t = blockIdx.x * ORDER_BLOCK + i;
+        if (t < ntiles)
+            put_record(records, atomicAdd(&at[tile_bin(crd, t, tile, cols)], 1), t,
+                       tile_span(rows, pos, t, tile, nnz, ntiles, over, tile_row, 0));
+    }
+}
+
+// The records go to the workspace's tile_cols (8 ints per tile), the histograms (64 ints per 1024 tiles) to its tile_aux.
+hipError_t launch_tile_order(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd, int32_t tile,
+                             int32_t over, const Workspace &w, hipStream_t s)
+{
+    const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
+    const dim3 grid((unsigned)((ntiles + ORDER_BLOCK - 1) / ORDER_BLOCK));
+    PSK_LAUNCH(k_tile_bins, grid, dim3(256), 0, s, ntiles, tile, cols, crd, w.tile_aux);
+    PSK_LAUNCH(k_tile_order, grid, dim3(256), 0, s, rows, nnz, ntiles, tile, cols, over, pos, crd, w.tile_row, w.tile_aux, w.tile_cols);
+    return take_launch_status();
+}
+
 // Gather-locality probe: of up to 16384 evenly spaced positions p, how many have their successor's
 // column within the same 128-byte line of x (0 <= crd[p+1] - crd[p] < 32)?  One workgroup; result[0] =
 // hits, result[1] = samples.

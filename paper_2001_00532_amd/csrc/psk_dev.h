@@ -171,6 +171,24 @@ __device__ __forceinline__ TileSpan tile_span(int rows, const int *__restrict__ 
     return s;
 }
 
+// The same as a record of eight ints, so that a tile that is not worked on in CSR order starts with one load instead of the
+// chain order -> table -> row positions (which neighbouring workgroups no longer share).
+__device__ __forceinline__ void put_record(int *records, long long i, int t, const TileSpan &s)
+{
+    v4i *p = reinterpret_cast<v4i *>(records + i * 8);
+    p[0] = v4i{t, s.t0, s.cnt, s.r0};
+    p[1] = v4i{s.r1, s.rbeg, s.rend, (s.has_carry ? 1 : 0) | (s.straddle ? 2 : 0)};
+}
+__device__ __forceinline__ TileSpan get_record(const int *__restrict__ records, long long i, int &t)
+{
+    const v4i *p = reinterpret_cast<const v4i *>(records + i * 8);
+    const v4i a = p[0], b = p[1];
+    TileSpan s;
+    t = a.x; s.t0 = a.y; s.cnt = a.z; s.r0 = a.w;
+    s.r1 = b.x; s.rbeg = b.y; s.rend = b.z; s.has_carry = b.w & 1; s.straddle = b.w & 2;
+    return s;
+}
+
 // ---- per-workgroup trace (only in the instrumented build, -DPSK_CU_TRACE): every workgroup of a traced kernel
 // records its start and end on the 100 MHz wall clock and the compute unit it ran on (HW_ID: cu, sh, se;
 // XCC_ID: die) into a caller-supplied buffer of 3 x 64 bits per workgroup, from which the host forms each

@@ -132,6 +132,9 @@ hipError_t launch_carry_fixup_f64(int32_t ntiles, int32_t tile, const int32_t *p
                                   hipStream_t s, int32_t gap_rows);
 
 // CSR SpMM
+// records of the tiles in w.tile_cols, by the column of their first position (at least 1024 tiles; reads the table)
+hipError_t launch_tile_order(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd, int32_t tile,
+                             int32_t over, const Workspace &w, hipStream_t s);
 // a row that reaches at most this far past the end of a tile is finished by that tile (tile_span in psk_dev.h)
 inline int32_t spmm_overhang(int32_t tile) { return tile / 2; }
 bool spmm_csr_tile_ok(int32_t tile);
@@ -142,7 +145,7 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
 constexpr int32_t kGroupColumns = 128;
 hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
-                                  int32_t tile, const Workspace &w, hipStream_t s, int search);
+                                  int32_t tile, const Workspace &w, hipStream_t s, int search, const int32_t *records);
 hipError_t launch_spmm_rowsplit(int32_t rows, const int32_t *pos, const int32_t *crd, const float *vals,
                                 const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
                                 hipStream_t s);

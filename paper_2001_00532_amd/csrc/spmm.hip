@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
                                                   int *tile_row,
                                                   int *__restrict__ carry_row,
                                                   float *__restrict__ carry_val, int ntiles, int T, int over,
-                                                  int search)
+                                                  int search, const int *__restrict__ records)
 {
     constexpr int THREADS = 256, NW = THREADS / WAVE, KW = WAVE * VEC;
     constexpr int U = BS == 1 ? 8 : (BS == 2 ? 4 : (BS == 4 ? 2 : 1));   // positions whose B rows are in flight together
@@ -40,13 +40,14 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
     __shared__ float srec[2 * NW][BS][KW];
     __shared__ int srec_row[2 * NW];              // -2 unused, -1 open segment, >= 0 row that ended
 
-    const int t = xcd_tile(blockIdx.x, ntiles);
+    int t = xcd_tile(blockIdx.x, ntiles);
     if (t < 0) return;
+    const int slot = t;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     // BS == 1: tell the compiler that the wave index is uniform (scalar loop control).  With blocks the
     // generated code measured 3 % slower that way, so there it stays a per-lane value.
     const int wave = BS == 1 ? __builtin_amdgcn_readfirstlane(tid / WAVE) : tid / WAVE;
-    const TileSpan span = tile_span(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
+    const TileSpan span = records ? get_record(records, slot, t) : tile_span(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
     const int t0 = span.t0, cnt = span.cnt, r0 = span.r0, r1 = span.r1, rbeg = span.rbeg, rend = span.rend;
     const bool has_carry = span.has_carry, straddle = span.straddle;
     const int col = blockIdx.y * KW + lane * VEC;
@@ -229,7 +230,8 @@ static int pick_vec(const float *B, int32_t k, int64_t ldb, const float *C, int6
 template <int BS>
 static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
-                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search)
+                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search,
+                                  const int32_t *records = nullptr)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     if (ntiles == 0) return hipSuccess;
@@ -241,7 +243,7 @@ static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos,
     const size_t lds = (size_t)(tile + over) * sizeof(int);
 #define PSK_GO(V)                                                                                              \
     PSK_LAUNCH((k_spmm_pos<BS, V>), grid, dim3(256), lds, s, rows, nnz, pos, crd, vals, B, k,          \
-                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, search)
+                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, search, records)
     if (vec == 4) {
         if constexpr (BS < 8) PSK_GO(4);
     } else if (vec == 2) PSK_GO(2);
@@ -262,8 +264,21 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     //     against 1776; where it can the wide kernel is 1-3 % faster, k = 128 1190 against 1223)
     const bool groups = k <= 32 || (k <= 64 && nnz >= 8ll * rows) ||
                         (k > 64 && k <= kGroupColumns && pick_vec(B, k, ldb, C, ldc) == 1);
-    if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
-    return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
+    // Tiles in column order (launch_tile_order) when rows are long: then a tile spans the share `span` of the columns, and what
+    // the tiles in flight gather from is about span * B instead of all of B.  It pays when that comes near a die's 4 MB of L2;
+    // otherwise the order only costs (30 us and less locality in A, C and the row tables).  us in CSR order / ordered:
+    //   k = 32, B 12.8 MB: span 0.51 1249 / 1190, 0.26 757 / 572, 0.10 632 / 426, 0.64 511 / 560;  B 6.4 MB: 0.51 451 / 527
+    //   k = 64, B 12.8 MB: 0.51 729 / 667;  B 51 MB: 0.26 1334 / 1160;  k = 128, B 25.6 MB: 0.51 1169 / 1262, B 51 MB: 0.26 2549 / 2160
+    const int32_t *records = nullptr;
+    const int64_t ntiles = ((int64_t)nnz + tile - 1) / tile;
+    const double span = (double)rows * tile / nnz, b_mb = (double)cols * k * 4 / (1 << 20);
+    if (ntiles >= 4096 && b_mb >= 8 && ((span <= 0.55 && span * b_mb <= 8) || (span <= 0.35 && span * b_mb <= 16))) {
+        const hipError_t e = launch_tile_order(rows, cols, nnz, pos, crd, tile, spmm_overhang(tile), w, s);
+        if (e != hipSuccess) return e;
+        records = w.tile_cols;
+    }
+    if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search, records);
+    return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search, records);
 }
 
 hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos_group(int rows, int nnz, const
                                                         int *tile_row,
                                                         int *__restrict__ carry_row,
                                                         float *__restrict__ carry_val, int ntiles, int T, int over,
-                                                  int search)
+                                                  int search, const int *__restrict__ records)
 {
     constexpr int THREADS = 256, NW = THREADS / WAVE, GW = WAVE / G, U = G == 32 ? 2 : 4;
     typedef typename VecU<VEC>::type V;
@@ -63,8 +63,9 @@ __global__ __launch_bounds__(256) void k_spmm_pos_group(int rows, int nnz, const
     __shared__ V srec[2 * NW][GW];
     __shared__ int srec_row[2 * NW];              // -2 unused, -1 open segment, >= 0 row that ended
 
-    const int t = xcd_tile(blockIdx.x, ntiles);
+    int t = xcd_tile(blockIdx.x, ntiles);
     if (t < 0) return;
+    const int slot = t;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int g = lane / GW, gl = lane % GW;
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos_group(int rows, int nnz, const
     const bool writer = active && g == 0;         // group 0 stores on behalf of the wave
     const int col = gl * VEC < k - VEC ? gl * VEC : k - VEC;
 
-    const TileSpan s = tile_span(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
+    const TileSpan s = records ? get_record(records, slot, t) : tile_span(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
     const int t0 = s.t0, cnt = s.cnt;
     for (int i = tid; i < cnt; i += THREADS) {
         const int c = ld_stream(crd + t0 + i);
@@ -229,14 +230,14 @@ __global__ __launch_bounds__(256) void k_spmm_pos_group(int rows, int nnz, const
 template <int G, int VEC>
 static void launch_group(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const float *vals, const float *B,
                          int32_t k, int64_t ldb, float *C, int64_t ldc, int32_t tile, int32_t over, bool small,
-                         const Workspace &w, hipStream_t s, int search)
+                         const Workspace &w, hipStream_t s, int search, const int32_t *records)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     const dim3 grid(xcd_grid(ntiles));
     const unsigned lds = (unsigned)(tile + over) * 12u;
 #define PSK_GO(SM)                                                                                                \
     PSK_LAUNCH((k_spmm_pos_group<G, VEC, SM>), grid, dim3(256), lds, s, rows, nnz, pos, crd, vals, B, k,          \
-                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, search)
+                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, search, records)
     if (small) PSK_GO(true);
     else PSK_GO(false);
 #undef PSK_GO
@@ -245,12 +246,12 @@ static void launch_group(int32_t rows, int32_t nnz, const int32_t *pos, const in
 // cols * ldb decides whether 32-bit byte offsets into B are enough
 hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
-                                  int32_t tile, const Workspace &w, hipStream_t s, int search)
+                                  int32_t tile, const Workspace &w, hipStream_t s, int search, const int32_t *records)
 {
     if (nnz <= 0) return hipSuccess;
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? cols : 1);
     const int32_t over = spmm_overhang(tile);
-#define PSK_GO(GG, VV) launch_group<GG, VV>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, small, w, s, search)
+#define PSK_GO(GG, VV) launch_group<GG, VV>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, small, w, s, search, records)
     if (k < 4) PSK_GO(16, 1);
     else if (k <= 8) PSK_GO(32, 4);
     else if (k <= 16) PSK_GO(16, 4);

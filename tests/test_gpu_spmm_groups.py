@@ -55,3 +55,28 @@ def test_group_widths_and_tile_borders(k):
 def test_block_rows_at_tile_borders(bs, k):
     check(borders(64), k, 64, bs=bs)
     check(np.full(200, 8), k, 0, bs=bs, pad=0)
+
+
+@pytest.mark.parametrize("k,tile,cols,per_row", [(32, 0, 70_000, 2200), (48, 256, 50_000, 1300), (128, 0, 30_000, 2200),
+                                                 (31, 512, 90_000, 4000)])
+def test_tiles_in_column_order(k, tile, cols, per_row):
+    """Long rows and a B of 8 MB and more: the tiles are worked on by the column they begin with.  Sorted and unsorted columns,
+    rows of very different lengths among them, empty rows at both ends."""
+    rows = 4200 * 512 // per_row if tile != 256 else 4200 * 256 // per_row
+    rng = np.random.default_rng(k)
+    L = np.full(rows, per_row)
+    L[rng.integers(0, rows, 20)] = rng.integers(0, 3 * per_row, 20)
+    L[[0, rows - 1]] = 0
+    L[1] += max(0, 4096 * (tile or 512) + 1 - int(L.sum()))
+    assert L.max() <= cols
+    A = wl.csr_from_lengths(L, cols, seed=k)
+    crd = A.crd.copy()
+    half = A.nnz // 2
+    crd[half:] = rng.integers(0, cols, A.nnz - half)                      # the second half: any order, repeated columns
+    Bh = wl.dense_uniform(cols * k, 4, wl.S_B).reshape(cols, k)
+    C = torch.full((rows, k), float("nan"), device="cuda")
+    psk.psk_spmm_csr(rows, cols, A.nnz, dev(A.pos), dev(crd), dev(A.vals), dev(Bh), C, tile=tile)
+    torch.cuda.synchronize()
+    ref, mag = oracle.spmm_csr(A.pos, crd, A.vals, Bh)
+    ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, mag)
+    assert ok, "k %d tile %d: %.3g of the bar" % (k, tile, worst)
