@@ -139,6 +139,10 @@ __device__ __forceinline__ void tile_rows(const int *__restrict__ pos, int rows,
     }
 }
 
+// The table as a tile kernel sees it: read only, or written by its search.
+template <bool SEARCH> struct TablePtr { typedef const int *__restrict__ type; };
+template <> struct TablePtr<true> { typedef int *type; };
+
 // Positions and rows of tile t where a row that reaches at most `over` positions past the end of a tile is finished by that
 // tile (SpMM kernels: a carry record is k floats written, read and added again, a few more positions cost nothing).  A row
 // that reaches further ends at the border as the cut says and its part in the next tile becomes that tile's carry.  Both

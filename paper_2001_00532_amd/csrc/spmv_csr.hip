@@ -39,16 +39,18 @@ __device__ __forceinline__ int tile_index(int g, int tid)
 //    store after the other.
 // 6: one pass with unit values: vals is not read (the second step of the product over the column-slab
 //    hierarchy, where the "matrix" only lists which partial sums belong to a row).
-template <int THREADS, int NPT, int MODE, int VARIANT>
+// SEARCH: the tile searches its rows itself and writes its table entry; otherwise the table is read (with scalar loads: nothing in
+// the kernel writes it).
+template <int THREADS, int NPT, int MODE, int VARIANT, bool SEARCH = false>
 __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nnz, const int *__restrict__ pos,
                                                       const int *__restrict__ crd,
                                                       const float *__restrict__ vals,
                                                       const float *__restrict__ x, float *__restrict__ y,
-                                                      int *tile_row,
+                                                      typename TablePtr<SEARCH>::type tile_row,
                                                       int *__restrict__ carry_row,
                                                       float *__restrict__ carry_val, int ntiles, int clo,
                                                       int chi, int accum, const int *__restrict__ rowmap,
-                                                      int *__restrict__ tile_cols, int gaps, int search)
+                                                      int *__restrict__ tile_cols, int gaps)
 {
     constexpr int T = THREADS * NPT;
     constexpr int NW = THREADS / WAVE;
@@ -91,9 +93,8 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
     // dependent loads (tile_row -> pos), so that chain is started first and runs underneath the
     // streaming loads and the gather instead of after them.  (A search, which is several rounds of loads, is started
     // behind the streaming loads: they do not depend on it.)
-    if (VARIANT == 6) search = 0;      // the table is part of the structure
     int r0 = 0, r1 = 0;
-    if (!search) { r0 = tile_row[t]; r1 = tile_row[t + 1]; }
+    if constexpr (!SEARCH) { r0 = tile_row[t]; r1 = tile_row[t + 1]; }
 
     // ---- 1. stream + gather + multiply
     float prod[NPT];
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
     }
 
     // ---- 2. rows of this tile (loads issued before the gather)
-    if (search) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
+    if constexpr (SEARCH) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
     const int p_r0 = pos[r0], p_r1 = pos[r1];
     const int rbeg = (t == 0) ? 0 : r0;
     int my_lo = 0, my_hi = 0;                       // pos pair of the first row this thread will look at
@@ -364,17 +365,20 @@ static void launch_pos(int mode, int grid, hipStream_t s, int rows, int cols, in
                        const float *vals, const float *x, float *y, const Workspace &w, int ntiles, int clo, int chi,
                        int accum, const int *rowmap, int gaps, int search)
 {
-#define PSK_GO(M, W)                                                                                             \
-    PSK_LAUNCH((k_spmv_pos<THREADS, NPT, M, W>), dim3(grid), dim3(THREADS), 0, s, rows, cols, nnz, pos,  \
+#define PSK_GO_(M, W, S)                                                                                         \
+    PSK_LAUNCH((k_spmv_pos<THREADS, NPT, M, W, S>), dim3(grid), dim3(THREADS), 0, s, rows, cols, nnz, pos,  \
                        crd, vals, x, y, w.tile_row, w.carry_row, w.carry_val, ntiles, clo, chi, accum, rowmap,    \
-                       w.tile_cols, gaps, search)
+                       w.tile_cols, gaps)
+#define PSK_GO(M, W) do { if (search) PSK_GO_(M, W, true); else PSK_GO_(M, W, false); } while (0)
     const bool window = clo > 0 || chi < cols;
     const int variant = rowmap ? (window ? 5 : 4) : (accum >= 2 ? accum : (window ? 1 : 0));
-    if (variant == 3) PSK_GO(0, 3);
+    if (variant == 3) PSK_GO_(0, 3, false);
+    else if (variant == 2) { if (mode == 1) PSK_GO_(1, 2, false); else PSK_GO_(0, 2, false); }
     else if (variant == 4) { if (mode == 1) PSK_GO(1, 4); else PSK_GO(0, 4); }
     else if (variant == 5) { if (mode == 1) PSK_GO(1, 5); else PSK_GO(0, 5); }
-    else if (mode == 1) { if (variant == 2) PSK_GO(1, 2); else if (variant == 1) PSK_GO(1, 1); else PSK_GO(1, 0); }
-    else { if (variant == 2) PSK_GO(0, 2); else if (variant == 1) PSK_GO(0, 1); else PSK_GO(0, 0); }
+    else if (variant == 1) { if (mode == 1) PSK_GO(1, 1); else PSK_GO(0, 1); }
+    else { if (mode == 1) PSK_GO(1, 0); else PSK_GO(0, 0); }
+#undef PSK_GO_
 #undef PSK_GO
 }
 
@@ -507,10 +511,10 @@ hipError_t launch_spmv_csr_ones(int32_t rows, int32_t cols, int32_t nnz, const i
     const int *nomap = nullptr;
     if ((reinterpret_cast<uintptr_t>(crd) & 15) == 0)
         PSK_LAUNCH((k_spmv_pos<256, 8, 1, 6>), dim3(grid), dim3(256), 0, s, rows, cols, nnz, pos, crd, none, x, y,
-                   w.tile_row, w.carry_row, w.carry_val, ntiles, 0, cols, 0, nomap, w.tile_cols, 1, 0);
+                   w.tile_row, w.carry_row, w.carry_val, ntiles, 0, cols, 0, nomap, w.tile_cols, 1);
     else
         PSK_LAUNCH((k_spmv_pos<256, 8, 0, 6>), dim3(grid), dim3(256), 0, s, rows, cols, nnz, pos, crd, none, x, y,
-                   w.tile_row, w.carry_row, w.carry_val, ntiles, 0, cols, 0, nomap, w.tile_cols, 1, 0);
+                   w.tile_row, w.carry_row, w.carry_val, ntiles, 0, cols, 0, nomap, w.tile_cols, 1);
     return take_launch_status();
 }
 
