@@ -320,7 +320,10 @@ int psk_spmv_csr_f64(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos
  *         number of stored rows per tile; no row is divided, so no table, no carries, no fix-up:
  *         only PSK_PHASE_MAIN does anything).  `tile` must still be a valid value (0 is); col_passes is
  *         ignored.
- * The main phase zero-fills y first.
+ * Where the main phase and the fix-up are asked for in one call and the workspace has room for the sums
+ * of the stored rows (psk_workspace_bytes(PSK_OP_SPMV_CSR, nstored, ...) counts 4 B per row for them),
+ * these are formed there and y is written once, zeros included; otherwise the main phase zero-fills y
+ * and each row is stored in place (4 B per stored row less workspace is enough).  Same bits either way.
  */
 enum { PSK_CUT_POSITIONS = 0, PSK_CUT_ROWS = 1 };
 int psk_spmv_dcsr(int64_t rows, int64_t cols, int64_t nstored, int64_t nnz, const int32_t *crd_i,

@@ -70,6 +70,8 @@ inline Workspace carve(void *base, int64_t ntiles, int64_t width)
 hipError_t launch_partition(int64_t rows, int64_t nnz, const int32_t *pos, int32_t tile, int method,
                             int32_t *tile_row, hipStream_t s);
 hipError_t launch_fill_zero(float *p, int64_t n, hipStream_t s);
+// y[crd_i[s]] = sums[s], all other elements 0 (DCSR: row sums in the order of the stored rows)
+hipError_t launch_expand_rows(int64_t rows, int32_t nstored, const int32_t *crd_i, const float *sums, float *y, hipStream_t s);
 hipError_t launch_fill_zero_2d(float *p, int64_t rows, int32_t width, int64_t ld, hipStream_t s);
 hipError_t launch_validate_csr(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                int32_t *result, hipStream_t s);

@@ -1,0 +1,51 @@
+"""DCSR SpMV with the row sums kept in the order of the stored rows and streamed to y in one go: the same bits as the route that
+stores each row where it belongs (a workspace without room for the sums, and phases called one by one), at the edges of the
+pieces in which y is written, for every alignment of y."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2001_00532_amd as psk  # noqa: E402
+
+REL, FLOOR = 1e-5, 1e-30
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+# rows, stored: one piece of 1 024, a piece and a bit, all rows stored (16 loads of entries per piece), 64 and 65 entries, several
+# spans, and enough rows (> 16 384 pieces) that a wave writes more than one piece
+@pytest.mark.parametrize("passes", [1, 3])
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("rows,stored", [(1, 1), (1024, 64), (1025, 65), (4099, 4099), (70_001, 900), (17_000_003, 5000)])
+def test_same_bits_as_storing_rows_in_place(rows, stored, off, passes):
+    rng = np.random.default_rng(rows + stored)
+    L = rng.integers(0, 30, size=stored)
+    L[stored // 2] = 400
+    A = wl.dcsr_from_lengths(rows, L, 2011, seed=7)
+    x = wl.dense_uniform(2011, 9, wl.S_X)
+    args = (A.rows, A.cols, A.nnz, dev(A.crd_i), dev(A.pos), dev(A.crd), dev(A.vals), dev(x))
+    full = psk.workspace(psk.PSK_OP_SPMV_CSR, A.nstored, A.nnz, tile=256)
+    small = full[:full.numel() - (A.nstored * 4 + 255) // 256 * 256].clone()
+
+    def product(ws, phases):
+        y = torch.full((rows + off,), float("nan"), device="cuda")[off:]
+        print("dcsr rows", rows, "stored", stored, "off", off, "passes", passes, "ws", ws.numel(), phases, flush=True)
+        for ph in phases:
+            psk.psk_spmv_dcsr(*args, y, tile=256, col_passes=passes, phases=ph, ws=ws)
+        torch.cuda.synchronize()
+        return y
+
+    y = product(full, [psk.PSK_PHASE_ALL])
+    assert torch.equal(y, product(small, [psk.PSK_PHASE_ALL]))
+    assert torch.equal(y, product(full, [psk.PSK_PHASE_PARTITION, psk.PSK_PHASE_MAIN, psk.PSK_PHASE_FIXUP]))
+    assert torch.equal(y, product(full, [psk.PSK_PHASE_PARTITION, psk.PSK_PHASE_MAIN | psk.PSK_PHASE_FIXUP]))
+    ref, mag = oracle.spmv_dcsr(A.rows, A.crd_i, A.pos, A.crd, A.vals, x)
+    ok, worst = oracle.within_tolerance(y.cpu().numpy(), ref, mag, REL, FLOOR)
+    assert ok, worst
