@@ -123,6 +123,28 @@ inline int searches(int phases, int32_t ntiles)
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? PSK_OK : PSK_ERR_HIP; }
 
+inline hipError_t carry_fixup(int32_t ntiles, int32_t tile, const int32_t *pos, const Workspace &ws, float *y, hipStream_t s, int32_t rows)
+{
+    return launch_carry_fixup(ntiles, 1, 1, 1, tile, pos, ws, y, s, nullptr, nullptr, rows);
+}
+inline hipError_t carry_fixup(int32_t ntiles, int32_t tile, const int32_t *pos, const Workspace &ws, double *y, hipStream_t s, int32_t rows)
+{
+    return launch_carry_fixup_f64(ntiles, tile, pos, ws, y, s, rows);
+}
+// A small product (spmv_small) with tile = 0: row blocks in the main phase.  tables (kNoTableNnz): other calls may read the table or
+// the carry records of this workspace, so each phase leaves what it leaves for a larger matrix.
+template <typename T>
+hipError_t spmv_small_phases(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const T *vals, const T *x, T *y,
+                             int32_t tile, int phases, bool tables, const Workspace &ws, hipStream_t s)
+{
+    if (phases & PSK_PHASE_MAIN) return launch_spmv_csr_small(rows, nnz, pos, crd, vals, x, y, tile, tables ? &ws : nullptr, s);
+    if (!tables) return hipSuccess;
+    hipError_t e = hipSuccess;
+    if (phases & PSK_PHASE_PARTITION) e = launch_partition(rows, nnz, pos, tile, 0, ws.tile_row, s);
+    if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess) e = carry_fixup((nnz + tile - 1) / tile, tile, pos, ws, y, s, rows);
+    return e;
+}
+
 }  // namespace
 
 extern "C" {
@@ -251,10 +273,8 @@ int psk_spmv_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, co
     if (st != PSK_OK) return st;
     if ((rows > 0 && !y) || (nnz > 0 && !x)) return PSK_ERR_NULL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (single) {
-        if (!(phases & PSK_PHASE_MAIN)) return PSK_OK;
-        return hip_status(launch_spmv_csr_small((int32_t)rows, (int32_t)nnz, pos, crd, vals, x, y, s));
-    }
+    if (single)
+        return hip_status(spmv_small_phases((int32_t)rows, (int32_t)nnz, pos, crd, vals, x, y, tile, phases, nnz > kNoTableNnz, ws, s));
     const int32_t ntiles = (int32_t)psk_num_tiles(nnz, tile);
     hipError_t e = hipSuccess;
     const int search = searches(phases, ntiles);
@@ -330,10 +350,8 @@ int psk_spmv_csr_f64(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos
     if ((reinterpret_cast<uintptr_t>(vals) | reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 7)
         return PSK_ERR_ALIGNMENT;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (single) {
-        if (!(phases & PSK_PHASE_MAIN)) return PSK_OK;
-        return hip_status(launch_spmv_csr_small((int32_t)rows, (int32_t)nnz, pos, crd, vals, x, y, s));
-    }
+    if (single)
+        return hip_status(spmv_small_phases((int32_t)rows, (int32_t)nnz, pos, crd, vals, x, y, tile, phases, true, ws, s));
     const int32_t ntiles = (int32_t)psk_num_tiles(nnz, tile);
     hipError_t e = hipSuccess;
     const int search = searches(phases, ntiles);

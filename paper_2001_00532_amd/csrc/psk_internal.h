@@ -109,10 +109,15 @@ inline bool spmv_small(int64_t rows, int64_t nnz, int vbytes)
 {
     return nnz > 0 && nnz <= (vbytes == 8 ? kSmallNnzF64 : kSmallNnz) && rows <= kSmallRows;
 }
+// Up to this many entries (fp32) the workspace is not touched and only the main phase does anything.  Above, a phase may be
+// followed by one of a call that gives the tile's size or of another entry point with the same table, so what those read is
+// there: the partition phase writes the table, the main phase the table and empty carry records (a few dozen words).
+constexpr int32_t kNoTableNnz = 16384;
+// w (optional): also write the table and empty carry records of tiles of `tile` positions there
 hipError_t launch_spmv_csr_small(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const float *vals,
-                                 const float *x, float *y, hipStream_t s);
+                                 const float *x, float *y, int32_t tile, const Workspace *w, hipStream_t s);
 hipError_t launch_spmv_csr_small(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const double *vals,
-                                 const double *x, double *y, hipStream_t s);
+                                 const double *x, double *y, int32_t tile, const Workspace *w, hipStream_t s);
 // rowmap (optional, both launchers): row r of the hierarchy is row rowmap[r] of y (DCSR)
 hipError_t launch_spmv_rowsplit(int32_t rows, const int32_t *pos, const int32_t *crd, const float *vals,
                                 const float *x, float *y, int variant, hipStream_t s,

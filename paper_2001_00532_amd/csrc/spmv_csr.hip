@@ -388,10 +388,13 @@ static void launch_pos(int mode, int grid, hipStream_t s, int rows, int cols, in
 // is summed by one thread, a longer one by a wave, one of VLONG or more by all waves.  Blocks are unequal in positions when
 // rows are; the size limit bounds what one workgroup can get.
 // 1024 rows of 10 entries: 4.0 us (as one tile of one workgroup 7.9); 2000 rows of 20: 4.0 (tiles and fix-up 10.0 in 3 launches).
+// ntiles > 0: the kernel also leaves what the partition and tile kernels of tiles of 2^shift positions would leave for calls that
+// read it, the table (each entry from the row that owns the tile's first position) and, as nothing is carried, empty records.
 template <typename T>
 __global__ __launch_bounds__(1024) void k_spmv_row_blocks(int rows, const int *__restrict__ pos, const int *__restrict__ crd,
                                                           const T *__restrict__ vals, const T *__restrict__ x,
-                                                          T *__restrict__ y, int block_rows)
+                                                          T *__restrict__ y, int block_rows, int shift, int ntiles,
+                                                          int *__restrict__ tile_row, int *__restrict__ carry_row)
 {
     constexpr int THREADS = 1024, NPT = 8, CH = THREADS * NPT, NW = THREADS / WAVE;
     constexpr int LONG = 32, MAXLONG = CH / LONG, VLONG = 512, MAXVLONG = CH / VLONG;
@@ -410,6 +413,13 @@ __global__ __launch_bounds__(1024) void k_spmv_row_blocks(int rows, const int *_
     __syncthreads();
     const int p1 = spos[n];
     const int my_lo = tid < n ? spos[tid] : 0, my_hi = tid < n ? spos[tid + 1] : 0;
+    if (ntiles > 0) {
+        for (int t = (my_lo + (1 << shift) - 1) >> shift; t < ntiles && (t << shift) < my_hi; ++t) {
+            tile_row[t] = ra + tid;
+            carry_row[t] = -1;
+        }
+        if (blockIdx.x == 0 && tid == 0) tile_row[ntiles] = rows;
+    }
     auto wave_total = [&](T s) {
 #pragma unroll
         for (int m = 1; m < WAVE; m <<= 1) s += __shfl_xor(s, m, WAVE);
@@ -477,28 +487,30 @@ __global__ __launch_bounds__(1024) void k_spmv_row_blocks(int rows, const int *_
 
 template <typename T>
 static hipError_t launch_row_blocks(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const T *vals, const T *x,
-                                    T *y, hipStream_t s)
+                                    T *y, int32_t tile, const Workspace *w, hipStream_t s)
 {
     if (!spmv_small(rows, nnz, (int)sizeof(T))) return hipErrorInvalidValue;
     // about 800 positions per workgroup, so that most of them finish with one load per thread
     int groups = (nnz + 799) / 800;
     if (groups < (rows + 1023) / 1024) groups = (rows + 1023) / 1024;
     const int block_rows = (rows + groups - 1) / groups;
+    int shift = 0;
+    while ((1 << shift) < tile) ++shift;                 // (the default tiles are powers of two)
     PSK_LAUNCH(k_spmv_row_blocks<T>, dim3((rows + block_rows - 1) / block_rows), dim3(1024), 0, s, rows, pos, crd, vals, x, y,
-               block_rows);
+               block_rows, shift, w ? (nnz + tile - 1) / tile : 0, w ? w->tile_row : nullptr, w ? w->carry_row : nullptr);
     return take_launch_status();
 }
 
 hipError_t launch_spmv_csr_small(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const float *vals,
-                                 const float *x, float *y, hipStream_t s)
+                                 const float *x, float *y, int32_t tile, const Workspace *w, hipStream_t s)
 {
-    return launch_row_blocks<float>(rows, nnz, pos, crd, vals, x, y, s);
+    return launch_row_blocks<float>(rows, nnz, pos, crd, vals, x, y, tile, w, s);
 }
 
 hipError_t launch_spmv_csr_small(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const double *vals,
-                                 const double *x, double *y, hipStream_t s)
+                                 const double *x, double *y, int32_t tile, const Workspace *w, hipStream_t s)
 {
-    return launch_row_blocks<double>(rows, nnz, pos, crd, vals, x, y, s);
+    return launch_row_blocks<double>(rows, nnz, pos, crd, vals, x, y, tile, w, s);
 }
 
 hipError_t launch_spmv_csr_ones(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,

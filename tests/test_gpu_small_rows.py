@@ -73,3 +73,39 @@ def test_long_runs_of_empty_rows_without_a_list(rows, f64):
             L[r] = (3, 700, 256, 1)[i % 4]
         check(L, f64, 256)
         check(L, f64, 1024, phases=(1, 2, 4))
+
+
+@pytest.mark.parametrize("f64,lengths", [(False, [3] * 7000), (False, [0, 0, 20_000, 5, 0, 9000, 0]), (False, [0] * 40_000 + [300] * 60 + [0]),
+                                         (True, [3] * 800), (True, [0, 5000, 0, 1]), (True, [0] * 40_000 + [300] * 60)],
+                         ids=lambda v: "%dx%d" % (len(v), max(v)) if isinstance(v, list) else "f64" if v else "f32")
+def test_phases_of_a_small_product_with_other_calls(f64, lengths):
+    """The phases of a small product leave what a larger one's do: the table serves calls that give the tile's size (and, in
+    fp32, entry points that share it), and a fix-up with the default tile finishes a main phase with the size given.  The
+    workspace starts out as rows that exist, so that a word that was not written cannot send a kernel out of bounds."""
+    A = wl.csr_from_lengths(np.asarray(lengths, dtype=np.int64), 30_000, seed=2)
+    tile = 1024 if f64 else 2048
+    if f64:
+        v, x = wl.dense_uniform_f64(A.nnz, 3, wl.S_VALS), wl.dense_uniform_f64(30_000, 3, wl.S_X)
+        (ref, mag), f, op, bar = oracle.spmv_csr_f64(A.pos, A.crd, v, x), psk.psk_spmv_csr_f64, psk.PSK_OP_SPMV_CSR_F64, (1e-14, 1e-300)
+    else:
+        v, x = A.vals, wl.dense_uniform(30_000, 3, wl.S_X)
+        (ref, mag), f, op, bar = oracle.spmv_csr(A.pos, A.crd, v, x), psk.psk_spmv_csr, psk.PSK_OP_SPMV_CSR, (1e-5, 1e-30)
+    pos = dev(A.pos)
+    args = (A.rows, 30_000, A.nnz, pos, dev(A.crd), dev(v), dev(x))
+    table = psk.psk_partition_csr(pos, A.nnz, tile)
+    part, main, fix = psk.PSK_PHASE_PARTITION, psk.PSK_PHASE_MAIN, psk.PSK_PHASE_FIXUP
+    orders = [[(f, 0, part), (f, tile, main | fix)], [(f, 0, 7), (f, tile, main), (f, tile, fix)], [(f, 0, main), (f, 0, fix)],
+              [(f, tile, part | main), (f, 0, fix)], [(f, 0, main | fix), (f, 0, fix)], [(f, 0, part), (f, 0, main), (f, 0, fix)]]
+    if not f64:
+        orders += [[(f, 0, part), (g, 0, main | fix)] for g in (psk.psk_spmv_csr_notemp, psk.psk_spmv_csr_atomics)]
+    for calls in orders:
+        ws = psk.workspace(op, A.rows, A.nnz)
+        ws.zero_()
+        y = torch.full((A.rows,), float("nan"), dtype=torch.float64 if f64 else torch.float32, device="cuda")
+        for g, t, phases in calls:
+            print("small phases", g.__name__, "tile", t, "phases", phases, "nnz", A.nnz, flush=True)
+            g(*args, y, tile=t, phases=phases, ws=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(ws[:table.numel() * 4].view(torch.int32), table)
+        ok, worst = oracle.within_tolerance(y.cpu().numpy(), ref, mag, *bar)
+        assert ok, (calls, worst)
