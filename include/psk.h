@@ -317,16 +317,17 @@ int psk_spmv_csr_f64(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos
  *   cut = PSK_CUT_POSITIONS: tiles of `tile` positions of the column level (equal work per tile; a row
  *         may be divided; table, carries and fix-up as in psk_spmv_csr, the table holds stored-row
  *         indices).  tile, col_passes, workspace: as psk_spmv_csr with rows = nstored (psk_analyze_csr
- *         with rows = nstored suggests col_passes).
+ *         with rows = nstored suggests col_passes); a larger workspace makes it faster, see below.
  *   cut = PSK_CUT_ROWS: tiles of four positions of the row level, one wave per stored row (equal
  *         number of stored rows per tile; no row is divided, so no table, no carries, no fix-up:
  *         only PSK_PHASE_MAIN does anything).  `tile` must still be a valid value (0 is); col_passes is
  *         ignored.
  * Where the main phase and the fix-up are asked for in one call and the workspace has room for the sums
- * of the stored rows (psk_workspace_bytes(PSK_OP_SPMV_CSR, nstored, ...) counts 4 B per row for them),
+ * of the stored rows (psk_spmv_dcsr_workspace_bytes: 4 B per stored row more than the CSR product needs),
  * these are formed there and y is written once, zeros included; otherwise the main phase zero-fills y
- * and each row is stored in place (4 B per stored row less workspace is enough).  Same bits either way.
+ * and each row is stored in place.  Same bits either way.
  */
+size_t psk_spmv_dcsr_workspace_bytes(int64_t nstored, int64_t nnz, int32_t tile);
 enum { PSK_CUT_POSITIONS = 0, PSK_CUT_ROWS = 1 };
 int psk_spmv_dcsr(int64_t rows, int64_t cols, int64_t nstored, int64_t nnz, const int32_t *crd_i,
                   const int32_t *pos, const int32_t *crd, const float *vals, const float *x, float *y,

@@ -28,7 +28,7 @@ EXPORTS = [
     "psk_partition_csr", "psk_analyze_csr", "psk_spmv_csr", "psk_spmm_csr", "psk_spmv_bcsr", "psk_spmm_bcsr",
     "psk_spmv_csr_rowsplit", "psk_spmm_csr_rowsplit", "psk_spmv_csr_atomics", "psk_mttkrp_csf3",
     "psk_partition_csf3", "psk_spmv_csr_notemp", "psk_spmv_csr_f64", "psk_spmv_dcsr", "psk_spmv_csr_divide", "psk_suggest_schedule_csr", "psk_default_tile_bcsr", "psk_validate_csr",
-    "psk_spmv_csr_static", "psk_static_scratch_bytes",
+    "psk_spmv_csr_static", "psk_static_scratch_bytes", "psk_spmv_dcsr_workspace_bytes",
     "psk_slab_mem_bytes", "psk_slab_build_workspace_bytes", "psk_slab_spmv_workspace_bytes", "psk_slab_build_csr",
     "psk_spmv_slab", "psk_slab_mem_bytes_f64", "psk_slab_build_workspace_bytes_f64", "psk_slab_build_csr_f64",
     "psk_spmv_slab_f64", "psk_cu_trace_set", "psk_calibrate_stream_read", "psk_calibrate_gather", "psk_calibrate_gather_lds",
@@ -122,6 +122,7 @@ def lib() -> ctypes.CDLL:
         L.psk_spmv_csr_f64.restype = ci
         L.psk_spmv_dcsr.argtypes = [i64, i64, i64, i64, p, p, p, p, p, p, ci, i32, i32, ci, p, sz, p]
         L.psk_spmv_dcsr.restype = ci
+        L.psk_spmv_dcsr_workspace_bytes.argtypes, L.psk_spmv_dcsr_workspace_bytes.restype = [i64, i64, i32], sz
         L.psk_default_tile_bcsr.argtypes = [ci, i32]
         L.psk_default_tile_bcsr.restype = i32
         L.psk_suggest_schedule_csr.argtypes = [i64, i64, p, p, sz, p, p]
@@ -195,13 +196,34 @@ def psk_workspace_bytes(op: int, rows: int, nnz: int, k: int = 1, bs: int = 1, t
     return int(lib().psk_workspace_bytes(int(op), int(rows), int(nnz), int(k), int(bs), int(tile)))
 
 
+def psk_spmv_dcsr_workspace_bytes(nstored: int, nnz: int, tile: int = 0) -> int:
+    return int(lib().psk_spmv_dcsr_workspace_bytes(int(nstored), int(nnz), int(tile)))
+
+
+DCSR_ROOM_ROWS = 1 << 22
+
+
 def workspace(op: int, rows: int, nnz: int, k: int = 1, bs: int = 1, tile: int = 0, device="cuda", stream=None):
-    """A byte tensor of the size the operation needs (torch allocations are 256-byte aligned).
+    """A byte tensor that suits the operation (torch allocations are 256-byte aligned).
+
+    One made for PSK_OP_SPMV_CSR is also what psk_spmv_dcsr takes, so up to DCSR_ROOM_ROWS rows it has the room for row
+    sums that the faster route of that product wants (at most 16 MiB; with more stored rows ask
+    psk_spmv_dcsr_workspace_bytes).
 
     `stream`: the stream the kernels that use it will run on.  The block is allocated under that stream, so
     torch's caching allocator hands it out again only to work that is ordered after those kernels; a
     temporary workspace dropped right after an asynchronous call stays valid until the call has run."""
     n = psk_workspace_bytes(op, rows, nnz, k, bs, tile)
+    if n == 0:
+        raise ValueError("invalid arguments for psk_workspace_bytes")
+    if op == PSK_OP_SPMV_CSR and 0 <= rows <= DCSR_ROOM_ROWS:
+        n = max(n, psk_spmv_dcsr_workspace_bytes(rows, nnz, tile))
+    return _alloc_bytes(n, device, stream)
+
+
+def _csr_ws(rows, nnz, tile, device, stream):
+    """What one CSR product needs, no more (for workspaces that live for one call)."""
+    n = psk_workspace_bytes(PSK_OP_SPMV_CSR, rows, nnz, tile=tile)
     if n == 0:
         raise ValueError("invalid arguments for psk_workspace_bytes")
     return _alloc_bytes(n, device, stream)
@@ -267,7 +289,7 @@ def psk_spmv_csr(rows, cols, nnz, pos, crd, vals, x, y, tile=0, col_passes=1, ph
                  stream=None):
     if ws is None:
         _temporary_ws_ok(phases, "psk_spmv_csr")
-        ws = workspace(PSK_OP_SPMV_CSR, rows, nnz, tile=tile, device=pos.device, stream=stream)
+        ws = _csr_ws(rows, nnz, tile, pos.device, stream)
     st = lib().psk_spmv_csr(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
                             _ptr(vals, torch.float32), _ptr(x, torch.float32), _ptr(y, torch.float32), int(tile),
                             int(col_passes), int(phases), _ptr(ws), ws.numel(), _stream(stream))
@@ -305,7 +327,7 @@ def psk_spmv_csr_prepared(rows, cols, nnz, pos, crd, vals, x, y, tile=0, col_pas
                           stream=None) -> PreparedCall:
     """psk_spmv_csr with the marshalling done once; the returned object repeats the call."""
     if ws is None:
-        ws = workspace(PSK_OP_SPMV_CSR, rows, nnz, tile=tile, device=pos.device, stream=stream)
+        ws = _csr_ws(rows, nnz, tile, pos.device, stream)
     cargs = (int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32), _ptr(vals, torch.float32),
              _ptr(x, torch.float32), _ptr(y, torch.float32), int(tile), int(col_passes), int(phases), _ptr(ws), ws.numel(),
              _stream(stream))
@@ -383,7 +405,7 @@ def psk_mttkrp_csf3(dims, crd_i, pos_k, crd_k, pos_l, crd_l, vals, C, D, A, tile
 def psk_spmv_csr_atomics(rows, cols, nnz, pos, crd, vals, x, y, tile=0, phases=PSK_PHASE_ALL, ws=None, stream=None):
     if ws is None:
         _temporary_ws_ok(phases, "psk_spmv_csr_atomics")
-        ws = workspace(PSK_OP_SPMV_CSR, rows, nnz, tile=tile, device=pos.device, stream=stream)
+        ws = _csr_ws(rows, nnz, tile, pos.device, stream)
     st = lib().psk_spmv_csr_atomics(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
                                     _ptr(vals, torch.float32), _ptr(x, torch.float32), _ptr(y, torch.float32),
                                     int(tile), int(phases), _ptr(ws), ws.numel(), _stream(stream))
@@ -409,7 +431,10 @@ def psk_spmv_dcsr(rows, cols, nnz, crd_i, pos, crd, vals, x, y, cut=PSK_CUT_POSI
     if ws is None and cut == PSK_CUT_POSITIONS:
         _temporary_ws_ok(phases, "psk_spmv_dcsr")
     if ws is None:
-        ws = workspace(PSK_OP_SPMV_CSR, nstored, nnz, tile=tile, device=pos.device, stream=stream)
+        n = psk_spmv_dcsr_workspace_bytes(nstored, nnz, tile)
+        if n == 0:
+            raise ValueError("invalid arguments for psk_spmv_dcsr_workspace_bytes")
+        ws = _alloc_bytes(n, pos.device, stream)
     st = lib().psk_spmv_dcsr(int(rows), int(cols), nstored, int(nnz), _ptr(crd_i, torch.int32), _ptr(pos, torch.int32),
                              _ptr(crd, torch.int32), _ptr(vals, torch.float32), _ptr(x, torch.float32),
                              _ptr(y, torch.float32), int(cut), int(tile), int(col_passes), int(phases), _ptr(ws),
@@ -422,7 +447,7 @@ def psk_spmv_csr_divide(rows, cols, nnz, pos, crd, vals, x, y, parts=0, phases=P
     if ws is None:
         if int(phases) & 6 != 6:      # no table here, but main and fix-up share the carry records
             raise ValueError("psk_spmv_csr_divide: main and fix-up on their own need a workspace that outlives the call")
-        ws = workspace(PSK_OP_SPMV_CSR, rows, nnz, tile=2048, device=pos.device, stream=stream)
+        ws = _csr_ws(rows, nnz, 2048, pos.device, stream)
     st = lib().psk_spmv_csr_divide(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
                                    _ptr(vals, torch.float32), _ptr(x, torch.float32), _ptr(y, torch.float32),
                                    int(parts), int(phases), _ptr(ws), ws.numel(), _stream(stream))
@@ -433,7 +458,7 @@ def psk_spmv_csr_divide(rows, cols, nnz, pos, crd, vals, x, y, parts=0, phases=P
 def psk_spmv_csr_notemp(rows, cols, nnz, pos, crd, vals, x, y, tile=0, phases=PSK_PHASE_ALL, ws=None, stream=None):
     if ws is None:
         _temporary_ws_ok(phases, "psk_spmv_csr_notemp")
-        ws = workspace(PSK_OP_SPMV_CSR, rows, nnz, tile=tile, device=pos.device, stream=stream)
+        ws = _csr_ws(rows, nnz, tile, pos.device, stream)
     st = lib().psk_spmv_csr_notemp(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
                                    _ptr(vals, torch.float32), _ptr(x, torch.float32), _ptr(y, torch.float32),
                                    int(tile), int(phases), _ptr(ws), ws.numel(), _stream(stream))

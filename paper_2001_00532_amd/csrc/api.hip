@@ -81,19 +81,6 @@ int64_t carry_width(int op, int32_t k, int32_t bs)
     }
 }
 
-// Bytes of workspace a call cannot do without.
-size_t needed_bytes(int op, int64_t nnz, int32_t k, int32_t bs, int32_t tile)
-{
-    // CSR SpMV picks 2048, or 1024 with column passes: size for the smaller one, which needs more
-    if (tile == 0) tile = op == PSK_OP_SPMV_CSR ? 1024 : default_tile(op, bs);
-    if (tile <= 0 || nnz < 0 || nnz > kMaxI32) return 0;
-    if ((op == PSK_OP_SPMM_CSR || op == PSK_OP_SPMM_BCSR || op == PSK_OP_MTTKRP_CSF3) && k <= 0) return 0;
-    if ((op == PSK_OP_SPMV_BCSR || op == PSK_OP_SPMM_BCSR) && bs <= 0) return 0;
-    const int64_t width = carry_width(op, k, bs);
-    if (width <= 0) return 0;
-    return carve(nullptr, psk_num_tiles(nnz, tile), width).bytes;
-}
-
 // Common checks of the sparse operand and the execution arguments.  On success *tile holds the
 // effective tile size and *ws the carved workspace.
 int check_common(int op, int64_t rows, int64_t cols, int64_t nnz, const void *pos, const void *crd,
@@ -107,7 +94,7 @@ int check_common(int op, int64_t rows, int64_t cols, int64_t nnz, const void *po
     if (phases <= 0 || (phases & ~PSK_PHASE_ALL)) return PSK_ERR_UNSUPPORTED;
     if (*tile == 0) *tile = default_tile(op, bs);
     if (!tile_ok(op, *tile, bs)) return PSK_ERR_TILE;
-    const size_t need = needed_bytes(op, nnz, k, bs, *tile);
+    const size_t need = psk_workspace_bytes(op, rows, nnz, k, bs, *tile);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) || workspace_bytes < need) return PSK_ERR_WORKSPACE;
     const int64_t ntiles = psk_num_tiles(nnz, *tile);
     *ws = carve(workspace, ntiles, carry_width(op, k, bs));
@@ -182,9 +169,22 @@ int64_t psk_num_tiles(int64_t nnz, int32_t tile)
 
 size_t psk_workspace_bytes(int op, int64_t rows, int64_t nnz, int32_t k, int32_t bs, int32_t tile)
 {
-    const size_t need = needed_bytes(op, nnz, k, bs, tile);
-    if (need == 0 || op != PSK_OP_SPMV_CSR || rows <= 0 || rows > kMaxI32) return need;
-    return need + align256((size_t)rows * 4);       // row sums of a DCSR operand in the order of its stored rows
+    (void)rows;
+    // CSR SpMV picks 2048, or 1024 with column passes: size for the smaller one, which needs more
+    if (tile == 0) tile = op == PSK_OP_SPMV_CSR ? 1024 : default_tile(op, bs);
+    if (tile <= 0 || nnz < 0 || nnz > kMaxI32) return 0;
+    if ((op == PSK_OP_SPMM_CSR || op == PSK_OP_SPMM_BCSR || op == PSK_OP_MTTKRP_CSF3) && k <= 0) return 0;
+    if ((op == PSK_OP_SPMV_BCSR || op == PSK_OP_SPMM_BCSR) && bs <= 0) return 0;
+    const int64_t width = carry_width(op, k, bs);
+    if (width <= 0) return 0;
+    return carve(nullptr, psk_num_tiles(nnz, tile), width).bytes;
+}
+
+size_t psk_spmv_dcsr_workspace_bytes(int64_t nstored, int64_t nnz, int32_t tile)
+{
+    const size_t need = psk_workspace_bytes(PSK_OP_SPMV_CSR, nstored, nnz, 1, 1, tile);
+    if (need == 0 || nstored < 0 || nstored > kMaxI32) return 0;
+    return need + align256((size_t)nstored * 4);
 }
 
 int psk_partition_csr(int64_t rows, int64_t nnz, const int32_t *pos, int32_t tile, int method,
@@ -319,7 +319,7 @@ int psk_spmv_csr_static(int64_t rows, int64_t cols, int64_t nnz, const int32_t *
     if (tile == 0) tile = col_passes > 1 ? 1024 : default_tile(PSK_OP_SPMV_CSR);
     if (!tile_ok(PSK_OP_SPMV_CSR, tile)) return PSK_ERR_TILE;
     if (nnz >= 0 && nnz <= kMaxI32 &&
-        needed_bytes(PSK_OP_SPMV_CSR, nnz, 1, 1, tile) > (size_t)PSK_STATIC_SCRATCH_BYTES)
+        psk_workspace_bytes(PSK_OP_SPMV_CSR, rows, nnz, 1, 1, tile) > (size_t)PSK_STATIC_SCRATCH_BYTES)
         return PSK_ERR_WORKSPACE;               // more tiles than the built-in scratch memory has room for
     // validate before touching the runtime, with a stand-in workspace address that is never dereferenced
     Workspace ws;
@@ -398,7 +398,7 @@ int psk_spmv_dcsr(int64_t rows, int64_t cols, int64_t nstored, int64_t nnz, cons
         workspace_bytes >= ws.bytes + (size_t)nstored * 4) {
         // The product over the stored rows as plain CSR, then one stream over y: 273 -> 220 us at 2^26 rows, 10^6 stored, two
         // column passes; 33 -> 25 at 2 10^7 rows, 20 000 stored; no slower at 2 000 stored rows.  A phase on its own must leave y
-        // as the phases say, and a workspace of the older size has no room for the sums: they store each row in place.
+        // as the phases say, and a workspace of the CSR product's size has no room for the sums: they store each row in place.
         float *sums = reinterpret_cast<float *>(static_cast<char *>(workspace) + ws.bytes);
         if (e == hipSuccess)
             e = launch_spmv_csr_main((int32_t)nstored, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, sums, tile, col_passes, ws,

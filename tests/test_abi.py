@@ -50,6 +50,27 @@ def test_sizes_and_strings():
     assert psk.status_string(99) == "unknown status"
 
 
+@pytest.mark.parametrize("rows", [1, 1 << 20, (1 << 20) + 1, 1 << 26, 2 ** 31 - 2])
+def test_static_scratch_limit_is_the_workspace_size(rows):
+    """psk_spmv_csr_static accepts exactly what psk_workspace_bytes says fits; the rows play no part in it.  (y is NULL, which is
+    found after the limit and before any HIP call.)"""
+    L = psk.lib()
+    one, null = ctypes.c_void_p(256), ctypes.c_void_p(0)
+    for tile in (0, 256, 2048):
+        t = tile or 2048
+        for nnz in (1, 100 * t, 80_000 * t, 87_000 * t, 88_000 * t, 2 ** 31 - 1):
+            if nnz >= 2 ** 31:
+                continue
+            fits = psk.psk_workspace_bytes(psk.PSK_OP_SPMV_CSR, rows, nnz, tile=t) <= psk.psk_static_scratch_bytes()
+            st = L.psk_spmv_csr_static(rows, 4, nnz, one, one, one, one, null, tile, 1, null)
+            assert st == (1 if fits else 4), (rows, tile, nnz)
+            assert fits == (nnz <= 87_000 * t)
+    assert psk.psk_workspace_bytes(psk.PSK_OP_SPMV_CSR, rows, 5000) == psk.psk_workspace_bytes(psk.PSK_OP_SPMV_CSR, 1, 5000)
+    more = psk.psk_spmv_dcsr_workspace_bytes(rows, 5000) - psk.psk_workspace_bytes(psk.PSK_OP_SPMV_CSR, rows, 5000)
+    assert 4 * rows <= more < 4 * rows + 256
+    assert psk.psk_spmv_dcsr_workspace_bytes(-1, 5000) == 0 and psk.psk_spmv_dcsr_workspace_bytes(rows, -1) == 0
+
+
 def test_argument_errors_are_reported_before_any_launch():
     """All of these return on the host-side checks; no HIP call is made."""
     L = psk.lib()
