@@ -280,12 +280,31 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
         for (int g = 0; g < NPT; ++g) sprod[skew<1>(tile_index<MODE, THREADS>(g, tid))] = prod[g];
     }
     __syncthreads();
+    auto take = [&](int r, int lo, int hi) {            // positions lo .. hi - 1 of the tile: the part of row r
+        if (hi - lo < LONG) {
+            // serial, in position order; four reads are issued before their adds so that the LDS
+            // latency is paid once per four elements
+            float s = 0.0f;
+            int i = lo;
+            for (; i + 4 <= hi; i += 4) {
+                const float a = sprod[skew<1>(i)], b = sprod[skew<1>(i + 1)], c = sprod[skew<1>(i + 2)],
+                            d = sprod[skew<1>(i + 3)];
+                s += a; s += b; s += c; s += d;
+            }
+            for (; i < hi; ++i) s += sprod[skew<1>(i)];
+            emit(r, s);
+        } else {
+            const int e = atomicAdd(&nlong, 1);
+            if (e < MAXLONG) { slong[3 * e] = r; slong[3 * e + 1] = lo; slong[3 * e + 2] = hi; }
+        }
+    };
     if (GAPS && gaps && r1 - rbeg > kGapRows) {
         // The tile's rows span a long run of empty rows (Section 6.2 walks past empty rows one by one; here that walk
         // would be done by this one workgroup).  Instead the row of every position is found by search -- a thread takes
         // NPT consecutive positions, searches once for the first and again whenever a row ends --, the row segments
-        // are summed by the thread that holds their first position, and the empty rows are left to the fix-up step,
-        // whose extra workgroups clear them at full width.
+        // are taken up by the thread that holds their first position and summed as below (the same order of additions,
+        // whichever way a segment was found), and the empty rows are left to the fix-up step, whose extra workgroups
+        // clear them at full width.
         const int i0 = tid * NPT;
         if (i0 < cnt) {
             int lo = r0, hi = r1;                       // max { r in [r0, r1] : pos[r] <= t0 + i0 }
@@ -316,32 +335,15 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos(int rows, int cols, int nn
             const int i = i0 + k;
             const int r = srowid[i];
             if (i > 0 && srowid[i - 1] == r) continue;  // not the first position of its row segment
-            float sum = 0.0f;
-            for (int j = i; j < cnt && srowid[j] == r; ++j) sum += sprod[skew<1>(j)];
-            emit(r, sum);
+            take(r, i, min(pos[r + 1] - t0, cnt));
         }
-        return;
-    }
-    for (int r = rbeg + tid; r < rend; r += THREADS) {
-        int lo = my_lo - t0, hi = my_hi - t0;
-        if (r + THREADS < rend) { my_lo = pos[r + THREADS]; my_hi = pos[r + THREADS + 1]; }
-        lo = lo < 0 ? 0 : lo;
-        hi = hi > cnt ? cnt : hi;
-        if (hi - lo < LONG) {
-            // serial, in position order; four reads are issued before their adds so that the LDS
-            // latency is paid once per four elements
-            float s = 0.0f;
-            int i = lo;
-            for (; i + 4 <= hi; i += 4) {
-                const float a = sprod[skew<1>(i)], b = sprod[skew<1>(i + 1)], c = sprod[skew<1>(i + 2)],
-                            d = sprod[skew<1>(i + 3)];
-                s += a; s += b; s += c; s += d;
-            }
-            for (; i < hi; ++i) s += sprod[skew<1>(i)];
-            emit(r, s);
-        } else {
-            const int e = atomicAdd(&nlong, 1);
-            if (e < MAXLONG) { slong[3 * e] = r; slong[3 * e + 1] = lo; slong[3 * e + 2] = hi; }
+    } else {
+        for (int r = rbeg + tid; r < rend; r += THREADS) {
+            int lo = my_lo - t0, hi = my_hi - t0;
+            if (r + THREADS < rend) { my_lo = pos[r + THREADS]; my_hi = pos[r + THREADS + 1]; }
+            lo = lo < 0 ? 0 : lo;
+            hi = hi > cnt ? cnt : hi;
+            take(r, lo, hi);
         }
     }
     __syncthreads();

@@ -49,3 +49,32 @@ def test_same_bits_as_storing_rows_in_place(rows, stored, off, passes):
     ref, mag = oracle.spmv_dcsr(A.rows, A.crd_i, A.pos, A.crd, A.vals, x)
     ok, worst = oracle.within_tolerance(y.cpu().numpy(), ref, mag, REL, FLOOR)
     assert ok, worst
+
+
+@pytest.mark.parametrize("passes", [1, 2])
+@pytest.mark.parametrize("tile", [256, 2048])
+def test_same_bits_around_a_long_run_of_empty_stored_rows(tile, passes):
+    """A tile over more than 32 768 stored rows (empty ones are allowed) finds the rows of its positions by search on the route
+    with the sums kept together and walks them on the other one: rows of less than 32 entries, of 32 and more, and the part of a
+    row that an earlier tile began must be added up in the same order on both."""
+    for lengths in ([100, 0], [1000, 0], [5, 31, 32, 33, 200, 0], [300, 0, 700, 0, 64, 1], [tile + 40, 0, 35]):
+        L = []
+        for n in lengths:
+            L += [n] if n else [0] * 33_500
+        L += [3] * 40 + [0, 0, 90]
+        A = wl.dcsr_from_lengths(len(L) * 5 + 3, np.asarray(L), 4001, seed=len(L))
+        x = wl.dense_uniform(4001, 9, wl.S_X)
+        args = (A.rows, A.cols, A.nnz, dev(A.crd_i), dev(A.pos), dev(A.crd), dev(A.vals), dev(x))
+        small = torch.empty(psk.psk_workspace_bytes(psk.PSK_OP_SPMV_CSR, A.nstored, A.nnz, tile=tile), dtype=torch.uint8, device="cuda")
+        full = torch.empty(psk.psk_spmv_dcsr_workspace_bytes(A.nstored, A.nnz, tile), dtype=torch.uint8, device="cuda")
+        got = []
+        for ws, phases in ((full, [7]), (small, [7]), (full, [1, 2, 4])):
+            y = torch.full((A.rows,), float("nan"), device="cuda")
+            for ph in phases:
+                psk.psk_spmv_dcsr(*args, y, tile=tile, col_passes=passes, phases=ph, ws=ws)
+            torch.cuda.synchronize()
+            got.append(y)
+        assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2]), lengths
+        ref, mag = oracle.spmv_dcsr(A.rows, A.crd_i, A.pos, A.crd, A.vals, x)
+        ok, worst = oracle.within_tolerance(got[0].cpu().numpy(), ref, mag, REL, FLOOR)
+        assert ok, (lengths, worst)
