@@ -388,7 +388,9 @@ static void launch_pos(int mode, int grid, hipStream_t s, int rows, int cols, in
 // workgroup takes a block of whole rows (their positions are pos[first] .. pos[last + 1]: one load), walks them in chunks of
 // CH positions, the next chunk's loads in flight, and keeps its row sums in LDS.  In a chunk a row segment shorter than LONG
 // is summed by one thread, a longer one by a wave, one of VLONG or more by all waves.  Blocks are unequal in positions when
-// rows are; the size limit bounds what one workgroup can get.
+// rows are; the size limit bounds what one workgroup can get.  What the waves and the chunks add to a row is added up in fp64,
+// as the fix-up does with the parts of a row that spans tiles (error of one row of 20 000 positive products 57e-9 -> 29e-9 of
+// its sum, 32e-9 by tiles; rounding the sum to fp32 alone leaves 24e-9).
 // 1024 rows of 10 entries: 4.0 us (as one tile of one workgroup 7.9); 2000 rows of 20: 4.0 (tiles and fix-up 10.0 in 3 launches).
 // ntiles > 0: the kernel also leaves what the partition and tile kernels of tiles of 2^shift positions would leave for calls that
 // read it, the table (each entry from the row that owns the tile's first position) and, as nothing is carried, empty records.
@@ -402,7 +404,7 @@ __global__ __launch_bounds__(1024) void k_spmv_row_blocks(int rows, const int *_
     constexpr int LONG = 32, MAXLONG = CH / LONG, VLONG = 512, MAXVLONG = CH / VLONG;
     __shared__ int spos[THREADS + 1];
     __shared__ T sprod[skewed_size<1>(CH)];
-    __shared__ T ssum[THREADS];
+    __shared__ double ssum[THREADS];
     __shared__ T swave[MAXVLONG][NW];
     __shared__ int slong[MAXLONG], svlong[MAXVLONG], nlong, nvlong;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
@@ -410,7 +412,7 @@ __global__ __launch_bounds__(1024) void k_spmv_row_blocks(int rows, const int *_
     const int ra = blockIdx.x * block_rows, n = min(block_rows, rows - ra);          // at most THREADS rows
     if (tid <= n) spos[tid] = pos[ra + tid];
     if (tid == 0) { spos[n] = pos[ra + n]; nlong = 0; nvlong = 0; }
-    T sum = 0;
+    double sum = 0;
     ssum[tid] = 0;
     __syncthreads();
     const int p1 = spos[n];
@@ -476,15 +478,15 @@ __global__ __launch_bounds__(1024) void k_spmv_row_blocks(int rows, const int *_
         }
         __syncthreads();
         if (tid < nv) {
-            T s = 0;
+            double s = 0;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) s += swave[tid][w];
+            for (int w = 0; w < NW; ++w) s += (double)swave[tid][w];
             ssum[svlong[tid]] += s;
         }
         if (tid == 0) { nlong = 0; nvlong = 0; }
     }
     __syncthreads();
-    if (tid < n) y[ra + tid] = sum + ssum[tid];
+    if (tid < n) y[ra + tid] = (T)(sum + ssum[tid]);
 }
 
 template <typename T>

@@ -109,3 +109,17 @@ def test_phases_of_a_small_product_with_other_calls(f64, lengths):
         assert torch.equal(ws[:table.numel() * 4].view(torch.int32), table)
         ok, worst = oracle.within_tolerance(y.cpu().numpy(), ref, mag, *bar)
         assert ok, (calls, worst)
+
+
+@pytest.mark.parametrize("n", [20_000, 49_152])
+def test_parts_of_a_long_row_are_added_in_fp64(n):
+    """A product 2^24, four products 1 further on, zeros in between: in fp32 every 1 would be lost against 2^24, added up among
+    themselves and in fp64 they count.  (Four 1s: the sum is a float.)"""
+    vals = np.zeros(n, dtype=np.float32)
+    vals[0] = 2.0 ** 24
+    ones = np.arange(2500, n, 4500)[:4]                    # in other tiles of 2048, held by other waves, two in other chunks
+    vals[ones] = 1.0
+    y = torch.empty(1, device="cuda")
+    one = torch.ones(1, device="cuda")
+    psk.psk_spmv_csr(1, 1, n, dev(np.array([0, n], dtype=np.int32)), torch.zeros(n, dtype=torch.int32, device="cuda"), dev(vals), one, y)
+    assert float(y) == 2.0 ** 24 + len(ones)
