@@ -23,6 +23,10 @@ namespace psk {
 //    wave 0 chains the records in position order: consecutive open segments belong to the row of the
 //    next closed one.  A chain whose row began before the tile becomes the tile's carry record; the
 //    open chain at the tile's end is stored by this tile if the row began in it, else carried.
+//  - a row's even and odd positions are summed apart (blocks: the products of a block first), so that a wave's share of up to
+//    3/8 T positions (row tails of other tiles included) makes no larger error than T/4 in one chain: rows of 300 positive
+//    products, k = 128, 127e-9 -> 74e-9 of the sum (93e-9 for shares of T/4); 4 x 4 blocks, 8 per row, 103e-9 -> 69e-9.  The time is
+//    the same but for short rows and k > 128 (20 000 rows of 4, k = 200: 31.5 -> 32.2 us).
 template <int BS, int VEC>
 __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *__restrict__ pos,
                                                   const int *__restrict__ crd,
@@ -85,10 +89,17 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
     const int CH = (cnt + NW - 1) / NW;
     const int wbeg = wave * CH < cnt ? wave * CH : cnt;
     const int wend = wbeg + CH < cnt ? wbeg + CH : cnt;
-    float acc[BS][VEC] = {};
+    float acc[BS][VEC] = {}, odd[BS == 1 ? VEC : 1] = {};      // the open row (BS == 1: its even and its odd positions)
     bool seen = false;
 
+    auto close = [&]() {                          // acc = the whole of the open row
+        if constexpr (BS == 1) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) { acc[0][v] += odd[v]; odd[v] = 0.0f; }
+        }
+    };
     auto flush = [&](int f) {
+        close();
         if (!seen) {
             seen = true;
 #pragma unroll
@@ -156,14 +167,39 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
             for (int u = 0; u < U; ++u) {
                 const int j = j0 + u;
                 if (j < n) {
+                    if constexpr (BS == 1) {
+                        const float a = rl(v_l[0], j);
 #pragma unroll
-                    for (int ii = 0; ii < BS; ++ii)
-#pragma unroll
-                        for (int ji = 0; ji < BS; ++ji) {
-                            const float a = rl(v_l[ii * BS + ji], j);
-#pragma unroll
-                            for (int v = 0; v < VEC; ++v) acc[ii][v] = fmaf(a, b[u][ji][v], acc[ii][v]);
+                        for (int v = 0; v < VEC; ++v) {
+                            if (u & 1) odd[v] = fmaf(a, b[u][0][v], odd[v]);
+                            else acc[0][v] = fmaf(a, b[u][0][v], acc[0][v]);
                         }
+                    } else {
+#pragma unroll
+                        for (int ii = 0; ii < BS; ++ii) {     // the block's share, then one addition to the row
+                            float a[BS], p[VEC];
+                            if constexpr (BS != 4) {          // (all broadcasts first: 8 x 8 blocks 314 -> 296 us, 4 x 4 324 -> 326)
+#pragma unroll
+                                for (int ji = 0; ji < BS; ++ji) a[ji] = rl(v_l[ii * BS + ji], j);
+#pragma unroll
+                                for (int v = 0; v < VEC; ++v) {
+                                    p[v] = a[0] * b[u][0][v];
+#pragma unroll
+                                    for (int ji = 1; ji < BS; ++ji) p[v] = fmaf(a[ji], b[u][ji][v], p[v]);
+                                    acc[ii][v] += p[v];
+                                }
+                            } else {
+#pragma unroll
+                                for (int ji = 0; ji < BS; ++ji) {
+                                    a[ji] = rl(v_l[ii * BS + ji], j);
+#pragma unroll
+                                    for (int v = 0; v < VEC; ++v) p[v] = ji == 0 ? a[0] * b[u][0][v] : fmaf(a[ji], b[u][ji][v], p[v]);
+                                }
+#pragma unroll
+                                for (int v = 0; v < VEC; ++v) acc[ii][v] += p[v];
+                            }
+                        }
+                    }
                     const int f = rl(f_l, j);
                     if (f >= 0) flush(f);
                 }
@@ -171,6 +207,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
         }
     }
     if (wbeg < wend) {
+        close();
         const int slot = seen ? 2 * wave + 1 : 2 * wave;
 #pragma unroll
         for (int ii = 0; ii < BS; ++ii)

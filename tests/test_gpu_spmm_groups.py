@@ -80,3 +80,48 @@ def test_tiles_in_column_order(k, tile, cols, per_row):
     ref, mag = oracle.spmm_csr(A.pos, crd, A.vals, Bh)
     ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, mag)
     assert ok, "k %d tile %d: %.3g of the bar" % (k, tile, worst)
+
+
+def wave_shares(pos, crd, vals, B, share, bs):
+    """Rows summed in fp32, one product after the other (fused multiply-adds) inside shares of `share` positions, and the
+    shares of a row in fp64: a tile of 4 * share positions cut among its four waves."""
+    per = int(pos[1])
+    rows, k = pos.size - 1, B.shape[1]
+    v = vals.reshape(rows, per, bs, bs).astype(np.float64)
+    b = B.reshape(-1, bs, k)[crd].reshape(rows, per, bs, k).astype(np.float64)
+    out = np.zeros((rows, bs, k))
+    acc = np.zeros((rows, bs, k), dtype=np.float32)
+    for i in range(per):
+        new = (pos[:-1] + i) % share == 0
+        out[new] += acc[new]
+        acc[new] = 0
+        for j in range(bs):
+            acc = (acc + v[:, i, :, j, None] * b[:, i, j, None, :]).astype(np.float32)
+    return (out + acc).reshape(rows * bs, k)
+
+
+@pytest.mark.parametrize("rows,per,k,bs", [(4000, 300, 128, 1), (6000, 70, 200, 1), (3000, 640, 128, 1), (20_000, 8, 64, 4), (8000, 20, 130, 2),
+                                           (4000, 6, 64, 8)])
+def test_error_is_not_above_that_of_the_cut(rows, per, k, bs):
+    """The error of the sums (positive operands: rounding is all there is) against that of the cut as it stands, tiles of the
+    default size with a quarter for each wave and fp64 across: a row tail that its tile finishes must not make it larger.
+    (rms over 10^5 elements and more: the two differ by chance by less than 1 %; 5 % is allowed.)"""
+    cols = 3000
+    rng = np.random.default_rng(per)
+    A = wl.csr_from_lengths(np.full(rows, per), cols, seed=per, bs=bs)
+    vals = rng.random(A.vals.size, dtype=np.float32)
+    B = rng.random((cols * bs, k), dtype=np.float32)
+    C = torch.empty((rows * bs, k), device="cuda")
+    if bs == 1:
+        psk.psk_spmm_csr(rows, cols, A.nnz, dev(A.pos), dev(A.crd), dev(vals), dev(B), C)
+    else:
+        psk.psk_spmm_bcsr(rows, cols, A.nnz, bs, dev(A.pos), dev(A.crd), dev(vals), dev(B), C)
+    few = slice(0, 24)                                     # (columns are summed alike)
+    share = psk.psk_default_tile(psk.PSK_OP_SPMM_CSR if bs == 1 else psk.PSK_OP_SPMM_BCSR) // 4
+    v = vals.reshape(rows, per, bs, bs).astype(np.float64)
+    b = B[:, few].reshape(cols, bs, -1).astype(np.float64)[A.crd].reshape(rows, per, bs, -1)
+    exact = np.einsum("rpij,rpjk->rik", v, b).reshape(rows * bs, -1)
+    rms = lambda got: float(np.sqrt(np.mean(((got - exact) / exact) ** 2)))
+    here, cut = rms(C[:, few].cpu().numpy()), rms(wave_shares(A.pos, A.crd, vals, B[:, few], share, bs))
+    print("spmm error", rows, per, k, bs, here, cut, flush=True)
+    assert here <= 1.05 * cut
