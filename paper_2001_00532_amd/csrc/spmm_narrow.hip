@@ -207,21 +207,33 @@ __global__ __launch_bounds__(256) void k_spmm_pos_group(int rows, int nnz, const
     }
     __syncthreads();
 
+    // chain the records (wave 0, group 0), in fp64: a tile holds up to 1.5 T positions of a row, and what it took over from the
+    // next one no longer meets the rest in the fix-up (rows of 1000 positive products, k = 8: error 39.5e-9 -> 34.2e-9 of the
+    // sum, 37.2e-9 without tails; same time)
     if (wave != 0 || g != 0) return;
-    V run{};
+    double run[VEC] = {};
     auto finalize = [&](int r) {
+        V sum;
+        if constexpr (VEC == 1) sum = (float)run[0];
+        else {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) sum[v] = (float)run[v];
+        }
         if (s.has_carry && r == s.r0) {
-            if (active) *reinterpret_cast<V *>(carry_val + (long long)t * k + col) = run;
+            if (active) *reinterpret_cast<V *>(carry_val + (long long)t * k + col) = sum;
             if (lane == 0) carry_row[t] = r;
         } else if (active) {
-            __builtin_nontemporal_store(run, reinterpret_cast<V *>(C + (long long)r * ldc + col));
+            __builtin_nontemporal_store(sum, reinterpret_cast<V *>(C + (long long)r * ldc + col));
         }
-        run = V{};
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) run[v] = 0.0;
     };
     for (int rec = 0; rec < 2 * NW; ++rec) {
         const int code = srec_row[rec];
         if (code == -2) continue;
-        run += srec[rec][gl];
+        const V part = srec[rec][gl];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) run[v] += (double)vec_at<VEC>(part, v);
         if (code >= 0) finalize(code);
     }
     if (s.straddle) finalize(s.r1);

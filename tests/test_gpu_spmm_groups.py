@@ -125,3 +125,15 @@ def test_error_is_not_above_that_of_the_cut(rows, per, k, bs):
     here, cut = rms(C[:, few].cpu().numpy()), rms(wave_shares(A.pos, A.crd, vals, B[:, few], share, bs))
     print("spmm error", rows, per, k, bs, here, cut, flush=True)
     assert here <= 1.05 * cut
+
+
+@pytest.mark.parametrize("k", [1, 3, 4, 8, 16, 32, 64])
+def test_waves_parts_of_a_row_are_added_in_fp64(k):
+    """Group kernels, one row over a tile: 2^24 in the first wave's share, a 1 in each of two others.  Added to 2^24 in fp32 one
+    after the other both would be lost; in fp64 they count (2^24 + 2 is a float)."""
+    vals = np.zeros(512, dtype=np.float32)
+    vals[[0, 200, 400]] = 2.0 ** 24, 1.0, 1.0
+    B, C = torch.ones((1, k), device="cuda"), torch.empty((1, k), device="cuda")
+    psk.psk_spmm_csr(1, 1, 512, dev(np.array([0, 512], dtype=np.int32)), torch.zeros(512, dtype=torch.int32, device="cuda"), dev(vals), B, C,
+                     tile=512)
+    assert bool((C == 2.0 ** 24 + 2).all())
