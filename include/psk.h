@@ -478,8 +478,8 @@ int psk_spmv_slab_f64(const psk_slab *S, const double *x, double *y, int phases,
  * ---- per-CU load balance (instrumented build only) ----
  *
  * The library can be built a second time with -DPSK_CU_TRACE (libpsk_trace.so, python -m paper_2001_00532_amd.build
- * makes both).  In that build every workgroup of the CSR SpMV tile kernel, of the two row-split kernels and of the
- * slab pair kernel writes a record of three 64-bit words: its start and its end on the 100 MHz wall clock, and
+ * makes both).  In that build every workgroup of the CSR SpMV tile kernel, of the row-block kernel that takes its place for
+ * small matrices, of the two row-split kernels and of the slab pair kernel writes a record of three 64-bit words: its start and its end on the 100 MHz wall clock, and
  * (HW_ID & 0xffff) | (XCC_ID << 32), i.e. the compute unit it ran on.  Workgroup b of the slab pair kernel writes
  * record b (b < PSK_CU_TRACE_SLAB_RECORDS), workgroup b of the other kernels record PSK_CU_TRACE_SLAB_RECORDS + b, so
  * that a product over the slab structure, which launches both kinds, can be traced in one go.  The host forms the busy

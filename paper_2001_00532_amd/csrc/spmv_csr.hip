@@ -407,6 +407,7 @@ __global__ __launch_bounds__(1024) void k_spmv_row_blocks(int rows, const int *_
     __shared__ double ssum[THREADS];
     __shared__ T swave[MAXVLONG][NW];
     __shared__ int slong[MAXLONG], svlong[MAXVLONG], nlong, nvlong;
+    PSK_TRACE_WORKGROUP();
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int ra = blockIdx.x * block_rows, n = min(block_rows, rows - ra);          // at most THREADS rows
