@@ -23,15 +23,17 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 // earlier passes stored; the first pass records the tile's column range, later passes skip tiles outside
 // their window.
 // ONES: every stored value is 1 and `vals` is not read (the row sums over the pair array of the slab path).
-template <int THREADS, int NPT, bool VEC, bool WIN, bool ONES = false>
+// SEARCH: the tile searches its rows itself and writes its table entry, as in the fp32 kernel.  (An instance of its own: a run-time
+// switch took the scalar loads of the table away; 10^6 rows of 27 neighbours 75.5 -> 73.9 us, with two column passes 153.5 -> 150.6.)
+template <int THREADS, int NPT, bool VEC, bool WIN, bool ONES = false, bool SEARCH = false>
 __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, const int *__restrict__ pos,
                                                           const int *__restrict__ crd,
                                                           const double *__restrict__ vals,
                                                           const double *__restrict__ x, double *__restrict__ y,
-                                                          int *tile_row,
+                                                          typename TablePtr<SEARCH>::type tile_row,
                                                           int *__restrict__ carry_row,
                                                           double *__restrict__ carry_val, int ntiles, int clo,
-                                                          int chi, int accum, int *__restrict__ tile_cols, int search)
+                                                          int chi, int accum, int *__restrict__ tile_cols)
 {
     constexpr int T = THREADS * NPT;
     constexpr int NW = THREADS / WAVE;
@@ -63,9 +65,8 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
     }
 
     // the dependent chain tile_row -> pos is started first and runs underneath the streams
-    if (ONES) search = 0;              // the table is part of the structure
     int r0 = 0, r1 = 0;
-    if (!search) { r0 = tile_row[t]; r1 = tile_row[t + 1]; }
+    if constexpr (!SEARCH) { r0 = tile_row[t]; r1 = tile_row[t + 1]; }
 
     double prod[NPT];
     int cmin = 0x7fffffff, cmax = -1;             // column range of the tile (first column pass)
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
                 v[g] = ONES ? 1.0 : ld_stream(vals + t0 + g * THREADS + tid);
             }
         }
-        if (search) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
+        if constexpr (SEARCH) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
         double xg[NPT];
 #pragma unroll
         for (int g = 0; g < NPT; ++g) xg[g] = (!WIN || (c[g] >= clo && c[g] < chi)) ? x[c[g]] : 0.0;
@@ -105,7 +106,9 @@ __global__ __launch_bounds__(THREADS) void k_spmv_pos_f64(int rows, int nnz, con
         }
     }
 
-    if (search && !full) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
+    if constexpr (SEARCH) {
+        if (!full) tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, 1, r0, r1);
+    }
     const int p_r0 = pos[r0], p_r1 = pos[r1];
     const int rbeg = (t == 0) ? 0 : r0;
     int my_lo = 0, my_hi = 0;
@@ -253,11 +256,13 @@ static void go(bool vec, bool win, int grid, hipStream_t s, int rows, int nnz, c
                int search)
 {
     double *cv = reinterpret_cast<double *>(w.carry_val);
-#define PSK_GO(V, W)                                                                                                  \
-    PSK_LAUNCH((k_spmv_pos_f64<THREADS, NPT, V, W>), dim3(grid), dim3(THREADS), 0, s, rows, nnz, pos, crd, vals, \
-                       x, y, w.tile_row, w.carry_row, cv, ntiles, clo, chi, accum, w.tile_cols, search)
+#define PSK_GO_(V, W, S)                                                                                              \
+    PSK_LAUNCH((k_spmv_pos_f64<THREADS, NPT, V, W, false, S>), dim3(grid), dim3(THREADS), 0, s, rows, nnz, pos, crd, vals, \
+                       x, y, w.tile_row, w.carry_row, cv, ntiles, clo, chi, accum, w.tile_cols)
+#define PSK_GO(V, W) do { if (search) PSK_GO_(V, W, true); else PSK_GO_(V, W, false); } while (0)
     if (vec) { if (win) PSK_GO(true, true); else PSK_GO(true, false); }
     else { if (win) PSK_GO(false, true); else PSK_GO(false, false); }
+#undef PSK_GO_
 #undef PSK_GO
 }
 
@@ -298,7 +303,7 @@ hipError_t launch_spmv_csr_f64_ones(int32_t rows, int32_t nnz, const int32_t *po
     const bool vec = (reinterpret_cast<uintptr_t>(crd) & 15) == 0;
 #define PSK_GO(NPT, V)                                                                                                   \
     PSK_LAUNCH((k_spmv_pos_f64<256, NPT, V, false, true>), dim3(grid), dim3(256), 0, s, rows, nnz, pos, crd, none, x, y, \
-               w.tile_row, w.carry_row, cv, ntiles, 0, 0x7fffffff, 0, w.tile_cols, 0)
+               w.tile_row, w.carry_row, cv, ntiles, 0, 0x7fffffff, 0, w.tile_cols)
     if (tile == 2048) { if (vec) PSK_GO(8, true); else PSK_GO(8, false); }
     else { if (vec) PSK_GO(4, true); else PSK_GO(4, false); }
 #undef PSK_GO
