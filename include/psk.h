@@ -224,8 +224,9 @@ int psk_suggest_schedule_csr(int64_t rows, int64_t nnz, const int32_t *pos, void
  * split over workgroups and waves, the columns of B over the lanes of a wave, the
  * loop over a wave's positions is innermost.  B is cols x k with row stride ldb
  * (>= k), C is rows x k with row stride ldc (>= k), both in floats.  Any k >= 1
- * (up to 64 columns, at times up to 128, a variant runs in which groups of lanes take consecutive positions).  A row
- * that reaches at most tile / 2 positions past the tile it begins in is finished there and has no carry record.
+ * (up to 64 columns, at times up to 128, a variant runs in which groups of lanes take consecutive positions).  Where the
+ * mean row is shorter than tile / 2, a row that reaches at most tile / 2 positions past the tile it begins in is finished
+ * there and has no carry record.
  * tile in {0, 256, 512, 1024, 2048}.
  */
 int psk_spmm_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, const int32_t *crd,

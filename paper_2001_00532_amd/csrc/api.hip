@@ -513,7 +513,7 @@ int psk_spmm_csr(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos, co
         }
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
-        e = launch_carry_fixup(ntiles, 1, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, 0, spmm_overhang(tile));
+        e = launch_carry_fixup(ntiles, 1, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, 0, spmm_overhang(rows, nnz, tile));
     return hip_status(e);
 }
 
@@ -570,7 +570,7 @@ int psk_spmm_bcsr(int64_t brows, int64_t bcols, int64_t nblocks, int32_t bs, con
         }
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
-        e = launch_carry_fixup(ntiles, bs, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, 0, spmm_overhang(tile));
+        e = launch_carry_fixup(ntiles, bs, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, 0, spmm_overhang_blocks(tile));
     return hip_status(e);
 }
 

@@ -267,7 +267,7 @@ static int pick_vec(const float *B, int32_t k, int64_t ldb, const float *C, int6
 template <int BS>
 static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
-                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search,
+                                  int64_t ldc, int32_t tile, int32_t over, const Workspace &w, hipStream_t s, int search,
                                   const int32_t *records = nullptr)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
@@ -276,7 +276,6 @@ static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos,
     if (BS == 8 && vec == 4) vec = 2;             // 8 x 8 blocks: the LDS records of four columns per lane do not fit
     const int kw = WAVE * vec;
     const dim3 grid(xcd_grid(ntiles), (k + kw - 1) / kw);
-    const int32_t over = spmm_overhang(tile);
     const size_t lds = (size_t)(tile + over) * sizeof(int);
 #define PSK_GO(V)                                                                                              \
     PSK_LAUNCH((k_spmm_pos<BS, V>), grid, dim3(256), lds, s, rows, nnz, pos, crd, vals, B, k,          \
@@ -303,28 +302,33 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
                         (k > 64 && k <= kGroupColumns && pick_vec(B, k, ldb, C, ldc) == 1);
     // Tiles in column order (launch_tile_order) when rows are long: then a tile spans the share `span` of the columns, and what
     // the tiles in flight gather from is about span * B instead of all of B.  It pays when that comes near a die's 4 MB of L2;
-    // otherwise the order only costs (30 us and less locality in A, C and the row tables).  us in CSR order / ordered:
-    //   k = 32, B 12.8 MB: span 0.51 1249 / 1190, 0.26 757 / 572, 0.10 632 / 426, 0.64 511 / 560;  B 6.4 MB: 0.51 451 / 527
-    //   k = 64, B 12.8 MB: 0.51 729 / 667;  B 51 MB: 0.26 1334 / 1160;  k = 128, B 25.6 MB: 0.51 1169 / 1262, B 51 MB: 0.26 2549 / 2160
+    // otherwise the order only costs (30 us and less locality in A, C and the row tables).  us in CSR order / ordered, 40 M entries
+    // in equal rows with sorted columns:
+    //   k = 32, B 12.8 MB: span 0.10 508 / 346, 0.26 512 / 346, 0.51 513 / 377;  B 6.4 MB: 0.51 369 / 357;  k = 64, B 12.8 MB: 0.51 967 /
+    //   624;  B 51 MB: 0.26 1297 / 1011, 0.34 1304 / 1109;  k = 128, B 25.6 MB: 0.26 2254 / 1257, 0.51 2274 / 1902;  B 51 MB: 0.13 2478 /
+    //   1291, 0.26 2501 / 1917;  rows of 200, span 2.6 (not here): k = 64 186 / 229.  10^5 rows of about 1000: log-normal lengths 1264 / 879,
+    //   nine rows in ten of 50 entries 1238 / 825.  Unsorted columns cannot gain; the order costs them 1258 / 1293.
     const int32_t *records = nullptr;
+    const int32_t over = spmm_overhang(rows, nnz, tile);
     const int64_t ntiles = ((int64_t)nnz + tile - 1) / tile;
     const double span = (double)rows * tile / nnz, b_mb = (double)cols * k * 4 / (1 << 20);
     if (ntiles >= 4096 && b_mb >= 8 && ((span <= 0.55 && span * b_mb <= 8) || (span <= 0.35 && span * b_mb <= 16))) {
-        const hipError_t e = launch_tile_order(rows, cols, nnz, pos, crd, tile, spmm_overhang(tile), w, s);
+        const hipError_t e = launch_tile_order(rows, cols, nnz, pos, crd, tile, over, w, s);
         if (e != hipSuccess) return e;
         records = w.tile_cols;
     }
-    if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search, records);
-    return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search, records);
+    if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search, records);
+    return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search, records);
 }
 
 hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                  const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search)
 {
-    if (bs == 2) return launch_spmm_pos<2>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
-    if (bs == 4) return launch_spmm_pos<4>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
-    if (bs == 8) return launch_spmm_pos<8>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, w, s, search);
+    const int32_t over = spmm_overhang_blocks(tile);
+    if (bs == 2) return launch_spmm_pos<2>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
+    if (bs == 4) return launch_spmm_pos<4>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
+    if (bs == 8) return launch_spmm_pos<8>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
     return hipErrorInvalidValue;
 }
 

@@ -258,11 +258,10 @@ static void launch_group(int32_t rows, int32_t nnz, const int32_t *pos, const in
 // cols * ldb decides whether 32-bit byte offsets into B are enough
 hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
-                                  int32_t tile, const Workspace &w, hipStream_t s, int search, const int32_t *records)
+                                  int32_t tile, int32_t over, const Workspace &w, hipStream_t s, int search, const int32_t *records)
 {
     if (nnz <= 0) return hipSuccess;
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? cols : 1);
-    const int32_t over = spmm_overhang(tile);
 #define PSK_GO(GG, VV) launch_group<GG, VV>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, small, w, s, search, records)
     if (k < 4) PSK_GO(16, 1);
     else if (k <= 8) PSK_GO(32, 4);

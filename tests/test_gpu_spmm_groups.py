@@ -38,7 +38,12 @@ def check(lengths, k, tile, bs=1, pad=1):
 
 
 def borders(T):
-    """Rows that end 1 before, at, and 1 behind a tile's end, at the last position still taken over, one behind it, two tiles on."""
+    """Rows that end 1 before, at, and 1 behind a tile's end, at the last position still taken over, one behind it, two tiles on;
+    short rows behind them keep the mean below the length from which nothing is taken over."""
+    return long_borders(T) + [1] * 50
+
+
+def long_borders(T):
     h = T // 2
     return [T - 1, 2, T - 1 + h, 0, 0, T - h, h + 1 + T, 1, 1, T - 3 - h, 3 * T + h, 2 * T - 1, 5, 0, T]
 
@@ -46,6 +51,7 @@ def borders(T):
 @pytest.mark.parametrize("k", [1, 3, 4, 5, 8, 15, 16, 17, 31, 32, 33, 63, 64, 65, 67, 99, 127, 128, 129])
 def test_group_widths_and_tile_borders(k):
     check(borders(256), k, 256)
+    check(long_borders(256), k, 256)
     rng = np.random.default_rng(k)
     check(rng.choice([0, 1, 2, 3, 9], size=1500), k, 0, pad=0)           # several row ends in one step
     check(np.full(300, 40), k, 512, pad=4)
