@@ -63,11 +63,11 @@ hipError_t launch_partition_csf3(int32_t nslices, int32_t nfibers, int32_t nnz, 
 // two misses of the D gather costs bandwidth, because the vector memory pipeline returns in order.
 // Segments, records, carries: as in the SpMM kernel (the first and last open segments of each wave are
 // chained by wave 0; a chain whose slice began before the tile becomes the tile's carry record).
-// One column per lane.  G > 1 (narrow factor matrices, j <= 64/G): the wave is split into G groups of 64/G lanes and in one
+// A lane owns VEC adjacent columns.  G > 1 (VEC = 1, narrow factor matrices, j <= 64/G): the wave is split into G groups of 64/G lanes and in one
 // step the groups take G consecutive leaves, so that one load instruction fetches G rows of D.  A lane keeps
 // its group's share of the open fiber and of the open slice; a fiber end multiplies every share by the C row
 // (no exchange needed: the product distributes over the shares), a slice end adds the shares across groups.
-template <int G>
+template <int VEC, int G>
 __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const int *__restrict__ crd_i,
                                                     const int *__restrict__ pos_k,
                                                     const int *__restrict__ crd_k,
@@ -82,7 +82,8 @@ __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const 
                                                     int *__restrict__ carry_row,
                                                     float *__restrict__ carry_val, int ntiles, int T)
 {
-    constexpr int VEC = 1, THREADS = 256, NW = THREADS / WAVE, GW = WAVE / G, KW = GW * VEC, LONGF = 32;
+    static_assert(VEC == 1 || G == 1, "groups of lanes own single columns");
+    constexpr int THREADS = 256, NW = THREADS / WAVE, GW = WAVE / G, KW = GW * VEC, LONGF = 32;
     constexpr int U = G > 1 ? 4 : 8;              // steps whose D rows are in flight together
     extern __shared__ int smeta[];                // sflag[T], sk[T], long-fiber queue [3 * T / LONGF]
     int *sflag = smeta, *sk = smeta + T, *slong = smeta + 2 * T;
@@ -572,16 +573,36 @@ hipError_t launch_mttkrp_main(int64_t dim_k, int64_t dim_l, int32_t nslices, int
         if (small) PSK_GO((k_mttkrp_groups<G, true>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                  \
         else PSK_GO((k_mttkrp_groups<G, false>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                       \
     } while (0)
-    // us at 23 M / 4.6 M leaves, D of 50 000 / 10 000 rows, against one column per lane (two or four above j = 64):
-    //   j = 16: 379 / 114 with four columns per lane against 353 / 114, so not there;  24: 395 / 106 against 503 / 151;
-    //   32: 366 / 97 against 503 / 151;  40: 560 / 116 against 613 / 172;  96: 1094 / 195 against 1124 / 209;  128: 1387 / 207
-    //   against 1538 / 214.  j = 64: 119 against 174 while D (2.6 MB) stays in the L2s; from 12.8 MB on both move D's rows at
-    //   the fabric's rate and one lane per column is 1-2 % ahead (46 M leaves, D 25.6 MB: 1628 against 1595).
-    if (j <= 8) PSK_GO((k_mttkrp_pos<8>), dim3(nx));
-    else if (j <= 16) PSK_GO((k_mttkrp_pos<4>), dim3(nx));
-    else if (j <= 32) PSK_GROUPS(8);
-    else if (j > 48 && j <= 64 && 4 * dim_l * j > (int64_t(8) << 20)) PSK_GO((k_mttkrp_pos<1>), dim3(nx));
-    else PSK_GROUPS(4);
+    const uintptr_t al = reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D) | reinterpret_cast<uintptr_t>(A);
+    int vec = 1;                                  // adjacent columns that a lane of the wide kernel can load at once
+    if (j > 64 && j % 2 == 0 && ldc % 2 == 0 && ldd % 2 == 0 && lda % 2 == 0 && (al & 7) == 0) vec = 2;
+    if (j > 128 && j % 4 == 0 && ldc % 4 == 0 && ldd % 4 == 0 && lda % 4 == 0 && (al & 15) == 0) vec = 4;
+    const bool lines = ldd % 32 == 0 && (reinterpret_cast<uintptr_t>(D) & 127) == 0;      // rows of D begin 128-byte lines
+    // Groups of four columns per lane or the wide kernel (VEC columns per lane; us groups / wide):
+    //   j <= 16: wide (one column per lane in 8 or 4 groups); 16: 379 / 353 at 23 M leaves
+    //   j <= 64: groups, 1.1 to 1.8 times as fast (0.4 to 9 M leaves: 24 39 / 70, 64 52 / 76;  D 12.8 MB, 9.4 M leaves, 64: 314 / 328) ...
+    //   big: ... but where neither D fits a die's L2 nor the leaves leave room for it in the memory-side cache, both move D's rows
+    //     at the fabric's rate and the wide kernel asks for less at once (46.9 M leaves, 100 000 rows of D: 24 1066 / 994, 28 1288 /
+    //     1148, 44 1666 / 1633, 64 1639 / 1608;  D 8.6 MB: 36 1145 / 1174), rows of up to 32 columns that fill lines excepted (32: 872 / 969)
+    //   j > 64: a group walks A once per 64 columns and neighbouring chunks share a line of every row that does not begin one:
+    //     few workgroups either way (0.9 M leaves: 66 65 / 91, 128 68 / 91;  0.4 M: 200 67 / 90;  1.4 M, 90 000 rows: 96 132 / 108): groups;
+    //     many, rows that begin lines (23 M: 96 1110 / 1135, 128 1407 / 1559, 256 2773 / 3400;  3.2 M: 128 267 / 277;  2.1 M: 128 121 /
+    //     114, 160 161 / 133, 256 210 / 240): groups;
+    //     otherwise wide (23 M: 66 1361 / 1011, 86 1652 / 1371, 112 1619 / 1488, 200 3442 / 2846) where its lanes can own two columns
+    //     (87 1649 / 1872).
+    const bool big = nnz >= (1 << 24) && 4 * dim_l * j > (int64_t(9) << 20);
+    const int64_t groups = (int64_t)ntiles * ((j + 63) / 64);        // workgroups, above 64 columns
+    if (j <= 8) PSK_GO((k_mttkrp_pos<1, 8>), dim3(nx));
+    else if (j <= 16) PSK_GO((k_mttkrp_pos<1, 4>), dim3(nx));
+    else if (j <= 32) {
+        if (big && !lines) PSK_GO((k_mttkrp_pos<1, 2>), dim3(nx));
+        else PSK_GROUPS(8);
+    } else if (j <= 64) {
+        if (big) PSK_GO((k_mttkrp_pos<1, 1>), dim3(nx));
+        else PSK_GROUPS(4);
+    } else if (vec == 1 || groups <= 1100 || (lines && groups >= 3100)) PSK_GROUPS(4);
+    else if (vec == 2) PSK_GO((k_mttkrp_pos<2, 1>), dim3(nx, (j + 127) / 128));
+    else PSK_GO((k_mttkrp_pos<4, 1>), dim3(nx, (j + 255) / 256));
 #undef PSK_GROUPS
 #undef PSK_GO
     return take_launch_status();

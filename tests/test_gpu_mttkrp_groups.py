@@ -1,6 +1,6 @@
 """MTTKRP where its kernels change over: numbers of columns around the group widths and chunks, tiles whose leaves divide evenly
 among the groups and tiles that do not (the last one), fibers and slices that end at a group's, a wave's or a tile's border,
-operands whose rows are not aligned, a factor matrix above the size at which 64 columns go to the other kernel.
+operands whose rows are not aligned, and the sizes from which a product goes to the kernel of one to four columns per lane.
 Bar: |got - ref| <= 1e-5 * sum |b c d| + 1e-30 per element."""
 import numpy as np
 import pytest
@@ -55,6 +55,32 @@ def test_uneven_last_tiles(n, tile):
 
 def test_large_factor_matrix():
     rng = np.random.default_rng(5)
-    for L in (30_000, 40_000):                 # 64 columns: 7.7 MB and 10.2 MB
+    for L in (30_000, 40_000):                 # 64 columns: 7.7 MB and 10.2 MB (few leaves: groups on either side)
         check(np.full(50, 3), rng.integers(1, 40, size=150), (50, 60, L), 64, 0)
         check(np.full(50, 3), rng.integers(1, 40, size=150), (50, 60, L), 52, 256)
+
+
+@pytest.mark.parametrize("j,pad", [(66, 2), (72, 0), (96, 0), (96, 4), (100, 0), (101, 0), (130, 2), (192, 0), (200, 0), (200, 2), (258, 2)])
+def test_many_tiles_above_64_columns(j, pad):
+    """1600 tiles: above 64 columns rows of D that begin 128-byte lines (96 and 192 columns without padding) and odd widths
+    stay with the groups, the others go to two or four columns per lane."""
+    rng = np.random.default_rng(j + pad)
+    fps = rng.integers(0, 9, size=6000)
+    leaves = rng.choice([0, 1, 2, 15, 60], size=int(fps.sum()))
+    leaves[::1000] = 700
+    leaves[-1] += max(0, 1600 * 256 - int(leaves.sum()))
+    check(fps, np.minimum(leaves, 9000), (6000, 300, 9000), j, 256, pad=pad)
+    check(fps, np.minimum(leaves, 9000), (6500, 300, 9000), j, 256, pad=pad, compressed=True)
+
+
+@pytest.mark.parametrize("j,pad", [(24, 0), (32, 0), (44, 1), (64, 0)])
+@pytest.mark.parametrize("n", [(1 << 24) - 1, 1 << 24])
+def test_many_leaves_and_a_large_factor(j, pad, n):
+    """From 2^24 leaves on, with a D of more than 9 MiB, the wide kernel takes 17 to 64 columns (not 32 that fill a line)."""
+    rng = np.random.default_rng(n & 1)
+    leaves = rng.integers(0, 110, size=310_000)
+    leaves[:200] += 5000
+    leaves = np.minimum(leaves, np.maximum(0, n - np.cumsum(leaves) + leaves))
+    leaves[7] += n - int(leaves.sum())
+    assert int(leaves.sum()) == n and leaves.max() <= 100_000
+    check(np.full(31_000, 10), leaves, (31_000, 400, 100_000), j, 0, pad=pad)
