@@ -323,7 +323,7 @@ int psk_spmv_csr_f64(int64_t rows, int64_t cols, int64_t nnz, const int32_t *pos
  *         number of stored rows per tile; no row is divided, so no table, no carries, no fix-up:
  *         only PSK_PHASE_MAIN does anything).  `tile` must still be a valid value (0 is); col_passes is
  *         ignored.
- * Where the main phase and the fix-up are asked for in one call and the workspace has room for the sums
+ * Where few rows are stored, the main phase and the fix-up are asked for in one call and the workspace has room for the sums
  * of the stored rows (psk_spmv_dcsr_workspace_bytes: 4 B per stored row more than the CSR product needs),
  * these are formed there and y is written once, zeros included; otherwise the main phase zero-fills y
  * and each row is stored in place.  Same bits either way.

@@ -394,11 +394,16 @@ int psk_spmv_dcsr(int64_t rows, int64_t cols, int64_t nstored, int64_t nnz, cons
     }
     const int search = searches(phases, ntiles);
     if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(nstored, nnz, pos, tile, 0, ws.tile_row, s);
-    if ((phases & PSK_PHASE_MAIN) && (phases & PSK_PHASE_FIXUP) && ntiles > 0 &&
+    // The product over the stored rows as plain CSR, then one stream over y, where few rows are stored: 273 -> 220 us at 2^26 rows,
+    // 10^6 stored, two column passes; 33 -> 25 at 2 10^7 rows, 20 000 stored.  It moves the sums twice, so not where storing them in
+    // place touches few more lines (us in place | sums, 3 or 10 entries per stored row): 10^7 rows, one in one 180 | 193, in two 107 |
+    // 109, in three 83 | 80, in eight 89 | 83;  10^6 rows, one in three 30.4 | 32.6, in eight 17.3 | 18.1, in sixteen and sparser alike;  2 10^5 rows,
+    // one in one 19.7 | 26.1.  From three column passes on each pass saves its read and write of y: 10^7 rows, all stored 513 | 505.
+    const bool sparse = rows >= nstored * (rows >= (int64_t(1) << 22) ? 3 : 16) || (col_passes >= 3 && rows >= (int64_t(1) << 20));
+    if (sparse && (phases & PSK_PHASE_MAIN) && (phases & PSK_PHASE_FIXUP) && ntiles > 0 &&
         workspace_bytes >= ws.bytes + (size_t)nstored * 4) {
-        // The product over the stored rows as plain CSR, then one stream over y: 273 -> 220 us at 2^26 rows, 10^6 stored, two
-        // column passes; 33 -> 25 at 2 10^7 rows, 20 000 stored; no slower at 2 000 stored rows.  A phase on its own must leave y
-        // as the phases say, and a workspace of the CSR product's size has no room for the sums: they store each row in place.
+        // A phase on its own must leave y as the phases say, and a workspace of the CSR product's size has no room for the sums:
+        // they store each row in place.
         float *sums = reinterpret_cast<float *>(static_cast<char *>(workspace) + ws.bytes);
         if (e == hipSuccess)
             e = launch_spmv_csr_main((int32_t)nstored, (int32_t)cols, (int32_t)nnz, pos, crd, vals, x, sums, tile, col_passes, ws,

@@ -19,11 +19,14 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-# rows, stored: one piece of 1 024, a piece and a bit, all rows stored (16 loads of entries per piece), 64 and 65 entries, several
-# spans, and enough rows (> 16 384 pieces) that a wave writes more than one piece
+# rows, stored: all rows stored (in place on either workspace), one piece of 1 024, a piece and a bit, 64 and 65 entries, one row in
+# sixteen (256 entries per piece) and one more, several spans, enough rows (> 16 384 pieces) that a wave writes more than one piece,
+# one row in three from 2^22 rows on (six loads of entries per piece), all of 2^20 rows (kept together with three passes: 16 loads)
 @pytest.mark.parametrize("passes", [1, 3])
 @pytest.mark.parametrize("off", [0, 1])
-@pytest.mark.parametrize("rows,stored", [(1, 1), (1024, 64), (1025, 65), (4099, 4099), (70_001, 900), (17_000_003, 5000)])
+@pytest.mark.parametrize("rows,stored", [(1, 1), (1024, 64), (1025, 64), (1025, 65), (4099, 4099), (16_000, 1000), (16_000, 1001),
+                                         (70_001, 900), (17_000_003, 5000), (4_194_304, 1_398_101), (4_194_303, 1_398_101),
+                                         (1_048_576, 1_048_576)])
 def test_same_bits_as_storing_rows_in_place(rows, stored, off, passes):
     rng = np.random.default_rng(rows + stored)
     L = rng.integers(0, 30, size=stored)
@@ -62,7 +65,7 @@ def test_same_bits_around_a_long_run_of_empty_stored_rows(tile, passes):
         for n in lengths:
             L += [n] if n else [0] * 33_500
         L += [3] * 40 + [0, 0, 90]
-        A = wl.dcsr_from_lengths(len(L) * 5 + 3, np.asarray(L), 4001, seed=len(L))
+        A = wl.dcsr_from_lengths(len(L) * 16 + 3, np.asarray(L), 4001, seed=len(L))
         x = wl.dense_uniform(4001, 9, wl.S_X)
         args = (A.rows, A.cols, A.nnz, dev(A.crd_i), dev(A.pos), dev(A.crd), dev(A.vals), dev(x))
         small = torch.empty(psk.psk_workspace_bytes(psk.PSK_OP_SPMV_CSR, A.nstored, A.nnz, tile=tile), dtype=torch.uint8, device="cuda")
