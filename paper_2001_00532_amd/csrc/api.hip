@@ -575,7 +575,7 @@ int psk_spmm_bcsr(int64_t brows, int64_t bcols, int64_t nblocks, int32_t bs, con
         }
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)
-        e = launch_carry_fixup(ntiles, bs, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, 0, spmm_overhang_blocks(tile));
+        e = launch_carry_fixup(ntiles, bs, k, ldc, tile, pos, ws, C, s, nullptr, nullptr, 0, spmm_overhang_blocks(brows, nblocks, tile));
     return hip_status(e);
 }
 

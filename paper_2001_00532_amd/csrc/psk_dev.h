@@ -139,9 +139,12 @@ __device__ __forceinline__ void tile_rows(const int *__restrict__ pos, int rows,
     }
 }
 
-// The table as a tile kernel sees it: read only, or written by its search.
+// The table as a tile kernel sees it: read only (then its loads are scalar), or written by a search.
 template <bool SEARCH> struct TablePtr { typedef const int *__restrict__ type; };
 template <> struct TablePtr<true> { typedef int *type; };
+
+// What a kernel instance does for its rows: read the table, search, or either by an argument.
+enum TableUse { TABLE_READ, TABLE_SEARCH, TABLE_EITHER };
 
 // Positions and rows of tile t where a row that reaches at most `over` positions past the end of a tile is finished by that
 // tile (SpMM kernels: a carry record is k floats written, read and added again, a few more positions cost nothing).  A row
@@ -154,12 +157,14 @@ struct TileSpan {
     bool has_carry;        // row r0 began in an earlier tile
     bool straddle;         // row r1 goes on in the next tile
 };
+template <TableUse USE = TABLE_EITHER>
 __device__ __forceinline__ TileSpan tile_span(int rows, const int *__restrict__ pos, int t, int T, int nnz, int ntiles, int over,
-                                              int *tile_row, int search)
+                                              typename TablePtr<USE != TABLE_READ>::type tile_row, int search)
 {
     TileSpan s;
     const int c0 = t * T, c1 = nnz - c0 < T ? nnz : c0 + T;
-    tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, search, s.r0, s.r1);
+    if constexpr (USE == TABLE_READ) { s.r0 = tile_row[t]; s.r1 = tile_row[t + 1]; }
+    else tile_rows(pos, rows, nnz, T, t, ntiles, tile_row, USE == TABLE_SEARCH ? 1 : search, s.r0, s.r1);
     const bool last = t + 1 == ntiles;                    // r1 = rows: no row goes on
     const int b0 = pos[s.r0], e0 = pos[s.r0 + 1], b1 = pos[s.r1], e1 = last ? nnz : pos[s.r1 + 1];
     const bool inside = t > 0 && b0 < c0;                 // the tile begins inside row r0

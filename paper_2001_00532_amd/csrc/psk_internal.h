@@ -145,10 +145,10 @@ hipError_t launch_tile_order(int32_t rows, int32_t cols, int32_t nnz, const int3
 // A row that reaches at most this far past the end of a tile is finished by that tile (tile_span in psk_dev.h).  It saves most of
 // the carries when rows are shorter than tiles; CSR rows of half a tile and more would only make the tiles unequal (0.5 to 1.5 T
 // positions) and leave few carries less: us with tile / 2 | with 0, tile 512: rows of 30, k = 128 41 | 43;  60 404 | 407;  200 457 | 465 (k = 32
-// 87 | 84);  430 162 | 150;  1000 82 | 76, k = 32 in column order 1200 | 875.  4 x 4 blocks (tile 64), k = 128: 8 per row 650 | 650;  40
-// 226 | 252;  200 209 | 208, so always there.
+// 87 | 84);  430 162 | 150;  1000 82 | 76, k = 32 in column order 1200 | 875.  Blocks (tile 64) from two tiles on: 4 x 4, k = 128: 8 per
+// row 650 | 650;  40 226 | 252;  200 209 | 208;  2 x 2, 300 per row: 142 | 140.
 inline int32_t spmm_overhang(int64_t rows, int64_t nnz, int32_t tile) { return 2 * nnz >= rows * tile ? 0 : tile / 2; }
-inline int32_t spmm_overhang_blocks(int32_t tile) { return tile / 2; }
+inline int32_t spmm_overhang_blocks(int64_t brows, int64_t nblocks, int32_t tile) { return nblocks >= 2 * brows * tile ? 0 : tile / 2; }
 bool spmm_csr_tile_ok(int32_t tile);
 hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C,

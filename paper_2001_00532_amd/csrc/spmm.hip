@@ -27,13 +27,13 @@ namespace psk {
 //    3/8 T positions (row tails of other tiles included) makes no larger error than T/4 in one chain: rows of 300 positive
 //    products, k = 128, 127e-9 -> 74e-9 of the sum (93e-9 for shares of T/4); 4 x 4 blocks, 8 per row, 103e-9 -> 69e-9.  The time is
 //    the same but for short rows and k > 128 (20 000 rows of 4, k = 200: 31.5 -> 32.2 us).
-template <int BS, int VEC>
+template <int BS, int VEC, TableUse USE>
 __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *__restrict__ pos,
                                                   const int *__restrict__ crd,
                                                   const float *__restrict__ vals,
                                                   const float *__restrict__ B, int k, long long ldb,
                                                   float *__restrict__ C, long long ldc,
-                                                  int *tile_row,
+                                                  typename TablePtr<USE != TABLE_READ>::type tile_row,
                                                   int *__restrict__ carry_row,
                                                   float *__restrict__ carry_val, int ntiles, int T, int over,
                                                   int search, const int *__restrict__ records)
@@ -51,7 +51,15 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
     // BS == 1: tell the compiler that the wave index is uniform (scalar loop control).  With blocks the
     // generated code measured 3 % slower that way, so there it stays a per-lane value.
     const int wave = BS == 1 ? __builtin_amdgcn_readfirstlane(tid / WAVE) : tid / WAVE;
-    const TileSpan span = records ? get_record(records, slot, t) : tile_span(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
+    TileSpan span = BS == 1 && records ? get_record(records, slot, t) : tile_span<USE>(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
+    if constexpr (BS == 4) {                      // in scalar registers (k = 64: 329.4 -> 327.9 us); the others gain nothing
+        span.t0 = __builtin_amdgcn_readfirstlane(span.t0);
+        span.cnt = __builtin_amdgcn_readfirstlane(span.cnt);
+        span.r0 = __builtin_amdgcn_readfirstlane(span.r0);
+        span.r1 = __builtin_amdgcn_readfirstlane(span.r1);
+        span.rbeg = __builtin_amdgcn_readfirstlane(span.rbeg);
+        span.rend = __builtin_amdgcn_readfirstlane(span.rend);
+    }
     const int t0 = span.t0, cnt = span.cnt, r0 = span.r0, r1 = span.r1, rbeg = span.rbeg, rend = span.rend;
     const bool has_carry = span.has_carry, straddle = span.straddle;
     const int col = blockIdx.y * KW + lane * VEC;
@@ -277,13 +285,23 @@ static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos,
     const int kw = WAVE * vec;
     const dim3 grid(xcd_grid(ntiles), (k + kw - 1) / kw);
     const size_t lds = (size_t)(tile + over) * sizeof(int);
+    // Reading and searching as instances of their own: 2 x 2 blocks, 400 000 rows of 10, k = 16 315 -> 305 us, 8 x 8, 100 000 of 6, k = 64 301
+    // -> 291;  4 x 4, 250 000 of 8, k = 16 276 -> 272 but k = 64 326 -> 332, so not there, and not for single entries (records).
 #define PSK_GO(V)                                                                                              \
-    PSK_LAUNCH((k_spmm_pos<BS, V>), grid, dim3(256), lds, s, rows, nnz, pos, crd, vals, B, k,          \
+    do {                                                                                                       \
+        if constexpr (BS == 2 || BS == 8) {                                                                    \
+            if (search) PSK_GO_(V, TABLE_SEARCH);                                                              \
+            else PSK_GO_(V, TABLE_READ);                                                                       \
+        } else PSK_GO_(V, TABLE_EITHER);                                                                       \
+    } while (0)
+#define PSK_GO_(V, S)                                                                                          \
+    PSK_LAUNCH((k_spmm_pos<BS, V, S>), grid, dim3(256), lds, s, rows, nnz, pos, crd, vals, B, k,          \
                        (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, search, records)
     if (vec == 4) {
         if constexpr (BS < 8) PSK_GO(4);
     } else if (vec == 2) PSK_GO(2);
     else PSK_GO(1);
+#undef PSK_GO_
 #undef PSK_GO
     return take_launch_status();
 }
@@ -325,7 +343,7 @@ hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t nblocks, con
                                  const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search)
 {
-    const int32_t over = spmm_overhang_blocks(tile);
+    const int32_t over = spmm_overhang_blocks(brows, nblocks, tile);
     if (bs == 2) return launch_spmm_pos<2>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
     if (bs == 4) return launch_spmm_pos<4>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
     if (bs == 8) return launch_spmm_pos<8>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);

@@ -60,6 +60,7 @@ def test_group_widths_and_tile_borders(k):
 @pytest.mark.parametrize("bs,k", [(2, 33), (4, 64), (4, 130), (8, 20)])
 def test_block_rows_at_tile_borders(bs, k):
     check(borders(64), k, 64, bs=bs)
+    check([133, 300, 0, 64, 400, 0, 500, 192, 1], k, 64, bs=bs)          # (a mean of two tiles and more: no tails)
     check(np.full(200, 8), k, 0, bs=bs, pad=0)
 
 
