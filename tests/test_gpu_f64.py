@@ -111,8 +111,8 @@ def test_f64_full_size_powerlaw_sampled():
 
 
 def test_f64_long_runs_of_empty_rows():
-    """Ten million empty rows between two groups of stored rows: the tile that spans the run lists it and the fix-up's
-    extra workgroups clear it, as in the fp32 kernel; one and two column passes, a second product on the same table,
+    """Ten million empty rows between two groups of stored rows: the tile that spans the run leaves it to the fix-up's
+    extra workgroups, which find it from the table and clear it, as in the fp32 kernel; one and two column passes, a second product on the same table,
     and the row sums of the fp64 slab path."""
     import time
 

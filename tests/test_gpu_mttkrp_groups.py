@@ -84,3 +84,29 @@ def test_many_leaves_and_a_large_factor(j, pad, n):
     leaves[7] += n - int(leaves.sum())
     assert int(leaves.sum()) == n and leaves.max() <= 100_000
     check(np.full(31_000, 10), leaves, (31_000, 400, 100_000), j, 0, pad=pad)
+
+
+@pytest.mark.parametrize("j", [24, 32, 40, 63])
+def test_offsets_beyond_32_bits(j):
+    """C or D as rows far apart: from 2^30 floats of rows * stride on the byte offsets don't fit 32 bits (another instance of the
+    group kernels, whose offsets are handed on as two words).  One row stride on either side for each of the two."""
+    n = 1100
+    rng = np.random.default_rng(j)
+    fps = np.full(200, 3)
+    T = wl.csf3_from_lengths(fps, rng.integers(1, 60, size=600), (200, n, n), seed=j)
+    assert T.crd_l.max() == n - 1 and T.crd_k.max() >= n - 5
+    Ch, Dh = (wl.dense_uniform(n * j, s, wl.S_B).reshape(n, j) for s in (7, 8))
+    ref, mag = oracle.mttkrp_csf3(T.pos_k, T.crd_k, T.pos_l, T.crd_l, T.vals, Ch, Dh)
+    most = (2 ** 32 - 1) // 4 // n
+    buf = torch.empty(n * (most + 1), device="cuda")
+    for ld in (most, most + 1):
+        far = buf[:n * ld].view(n, ld)[:, ld - j:]
+        for which in ("C", "D"):
+            far.copy_(dev(Ch if which == "C" else Dh))
+            C, D = (far, dev(Dh)) if which == "C" else (dev(Ch), far)
+            A = torch.full((200, j), float("nan"), device="cuda")
+            print("mttkrp offsets j", j, "ld", ld, which, flush=True)
+            psk.psk_mttkrp_csf3((200, n, n), None, dev(T.pos_k), dev(T.crd_k), dev(T.pos_l), dev(T.crd_l), dev(T.vals), C, D, A)
+            torch.cuda.synchronize()
+            ok, worst = oracle.within_tolerance(A.cpu().numpy(), ref, mag)
+            assert ok, "j %d ld %d %s: %.3g of the bar" % (j, ld, which, worst)

@@ -1,7 +1,7 @@
 """GPU parity at the small end and at the shapes of the paper's two synthetic studies.
 
-Small end: with the default tile a matrix of at most 16384 entries is one tile of one workgroup (one launch, no
-table, no carries).  Sweeps: the few-long-rows matrix of Section 8.5 (100 x 100000, 10000 per row) and the
+Small end: with the default tile a matrix of at most 49152 entries (fp64 24576) and 65536 rows is summed in blocks of
+whole rows (one launch, no table read, no carries).  Sweeps: the few-long-rows matrix of Section 8.5 (100 x 100000, 10000 per row) and the
 exponentially skewed rows of Section 8.4 (65536 x 1M, 4M entries, lengths ~ base^rank, shuffled), each through
 the position cut, the divided variant, the row split and the schedule the selector suggests."""
 import sys
@@ -34,25 +34,27 @@ def check(got, ref, mag, what):
 
 
 @pytest.mark.parametrize("kind", ADVERSARIAL_KINDS)
-def test_single_tile_path_structures(kind):
+def test_one_launch_path_structures(kind):
     rng = np.random.default_rng(31)
     for rows, cols in ((3, 2), (7, 5000), (1024, 1024), (5000, 300), (16000, 17)):
         A = wl.csr_from_lengths(adversarial_lengths(rng, rows, cols, kind), cols, seed=rows + cols)
-        if A.nnz > 16384:
+        if A.nnz > 49152:
             continue
         x = wl.dense_uniform(cols, rows, wl.S_X)
         ref, mag = oracle.spmv_csr(A.pos, A.crd, A.vals, x)
-        say("single tile:", kind, rows, "x", cols, "nnz", A.nnz)
+        say("one launch:", kind, rows, "x", cols, "nnz", A.nnz)
         y = torch.full((rows,), float("nan"), device="cuda")
         psk.psk_spmv_csr(rows, cols, A.nnz, dev(A.pos), dev(A.crd), dev(A.vals), dev(x), y)
         torch.cuda.synchronize()
-        check(y.cpu().numpy(), ref, mag, "single tile %s %dx%d" % (kind, rows, cols))
+        check(y.cpu().numpy(), ref, mag, "one launch %s %dx%d" % (kind, rows, cols))
 
 
-@pytest.mark.parametrize("nnz", [1, 2, 63, 64, 65, 4095, 4096, 16383, 16384, 16385, 20000])
-def test_single_tile_boundary_sizes(nnz):
-    """Around the size limit of the one-launch path (16384 entries) and around wave and load granules; rows of
-    mixed lengths, the last row takes what is left.  Unaligned crd/vals take the 4-byte load path."""
+@pytest.mark.parametrize("nnz", [1, 2, 63, 64, 65, 4095, 4096, 8191, 8192, 8193, 16384, 16385, 24575, 24576, 24577, 49151, 49152, 49153,
+                                 60000])
+def test_one_launch_boundary_sizes(nnz):
+    """Around the size limits of the one-launch path (49152 entries, fp64 24576), below which nothing is left in the workspace
+    (16384) and around wave, load and chunk granules; rows of mixed lengths, the last row takes what is left.  Above the
+    limit unaligned crd/vals take the 4-byte load path of the tile kernel."""
     rng = np.random.default_rng(nnz)
     L = []
     left = nnz
@@ -71,10 +73,35 @@ def test_single_tile_boundary_sizes(nnz):
         crd[shift:] = dev(A.crd)
         vals[shift:] = dev(A.vals)
         y = torch.full((A.rows,), float("nan"), device="cuda")
-        say("single tile boundary: nnz", nnz, "rows", A.rows, "shift", shift)
+        say("one launch boundary: nnz", nnz, "rows", A.rows, "shift", shift)
         psk.psk_spmv_csr(A.rows, cols, nnz, dev(A.pos), crd[shift:], vals[shift:], dev(x), y)
         torch.cuda.synchronize()
         check(y.cpu().numpy(), ref, mag, "nnz %d shift %d" % (nnz, shift))
+        v64, x64 = wl.dense_uniform_f64(nnz, nnz, wl.S_VALS), wl.dense_uniform_f64(cols, nnz, wl.S_X)
+        ref64, mag64 = oracle.spmv_csr_f64(A.pos, A.crd, v64, x64)
+        vals64 = torch.zeros(nnz + shift, dtype=torch.float64, device="cuda")
+        vals64[shift:] = dev(v64)
+        y64 = torch.full((A.rows,), float("nan"), dtype=torch.float64, device="cuda")
+        psk.psk_spmv_csr_f64(A.rows, cols, nnz, dev(A.pos), crd[shift:], vals64[shift:], dev(x64), y64)
+        torch.cuda.synchronize()
+        ok, worst = oracle.within_tolerance(y64.cpu().numpy(), ref64, mag64, 1e-14, 1e-300)
+        assert ok, "fp64 nnz %d shift %d: %.3g" % (nnz, shift, worst)
+
+
+@pytest.mark.parametrize("rows", [65535, 65536, 65537])
+def test_one_launch_row_limit(rows):
+    """Few entries in very many rows: up to 65536 rows in one launch, above by tiles."""
+    L = np.zeros(rows, dtype=np.int64)
+    L[::97] = 3
+    L[[0, rows - 1]] = 700, 40
+    A = wl.csr_from_lengths(L, 900, seed=rows)
+    x = wl.dense_uniform(900, rows, wl.S_X)
+    ref, mag = oracle.spmv_csr(A.pos, A.crd, A.vals, x)
+    y = torch.full((rows,), float("nan"), device="cuda")
+    say("one launch row limit", rows, "nnz", A.nnz)
+    psk.psk_spmv_csr(rows, 900, A.nnz, dev(A.pos), dev(A.crd), dev(A.vals), dev(x), y)
+    torch.cuda.synchronize()
+    check(y.cpu().numpy(), ref, mag, "%d rows" % rows)
 
 
 def test_configuration_1_is_one_launch_and_needs_no_table():
@@ -123,7 +150,7 @@ def test_sweep_shapes_every_schedule():
 def test_long_runs_of_empty_rows():
     """Ten million empty rows between two groups of stored rows (and more before the first and after the last): the
     tile that spans the run must not walk it.  Every path that walks rows is exercised: the CSR position cut with one
-    and two column passes and a small tile, a second product on the same table (the run list must start empty again),
+    and two column passes and a small tile, a second product on the same table (nothing of the first one may be left over),
     and the row sums of the slab path."""
     import time
 

@@ -144,3 +144,25 @@ def test_waves_parts_of_a_row_are_added_in_fp64(k):
     psk.psk_spmm_csr(1, 1, 512, dev(np.array([0, 512], dtype=np.int32)), torch.zeros(512, dtype=torch.int32, device="cuda"), dev(vals), B, C,
                      tile=512)
     assert bool((C == 2.0 ** 24 + 2).all())
+
+
+@pytest.mark.parametrize("k", [3, 8, 16, 32, 64, 99])
+def test_offsets_beyond_32_bits(k):
+    """B as rows far apart: from 2^30 floats of cols * ldb on the byte offsets into B don't fit 32 bits (another instance of the
+    group kernels).  One row stride on either side, the last rows of B referred to."""
+    cols, per = 1100, 60
+    A = wl.csr_from_lengths(np.full(300, per), cols, seed=k)
+    assert A.crd.max() == cols - 1
+    Bh = wl.dense_uniform(cols * k, 5, wl.S_B).reshape(cols, k)
+    ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh)
+    most = (2 ** 32 - 1) // 4 // cols
+    buf = torch.empty(cols * (most + 1), device="cuda")
+    for ld in (most, most + 1):
+        B = buf[:cols * ld].view(cols, ld)[:, ld - k:]            # the last columns: offsets up to the end of the buffer
+        B.copy_(dev(Bh))
+        C = torch.full((300, k), float("nan"), device="cuda")
+        print("spmm offsets k", k, "ld", ld, flush=True)
+        psk.psk_spmm_csr(300, cols, A.nnz, dev(A.pos), dev(A.crd), dev(A.vals), B, C)
+        torch.cuda.synchronize()
+        ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, mag)
+        assert ok, "k %d ld %d: %.3g of the bar" % (k, ld, worst)
