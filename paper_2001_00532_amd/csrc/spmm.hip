@@ -9,7 +9,7 @@
 
 namespace psk {
 
-// One workgroup (4 waves) per tile of T positions (T/4 consecutive positions per wave) and per
+// One workgroup (4 waves) per tile of T positions (a quarter of its positions per wave, consecutive ones) and per
 // column chunk.
 //
 //  - row ends: sflag[i] = r when position t0+i is the last stored position of row r, else -1
