@@ -141,8 +141,8 @@ int psk_partition_csr(int64_t rows, int64_t nnz, const int32_t *pos, int32_t til
  * (instead of the schedule's atomics), carries added by a second small kernel.
  * x has cols entries, y rows entries.  tile in {0, 256, 512, 1024, 2048, 4096}; 0 means 2048, or
  * 1024 when col_passes > 1 (psk_workspace_bytes with tile = 0 covers both).  With tile = 0, col_passes <= 1,
- * nnz <= 49152 and rows <= 65536 the rows are summed in blocks of whole rows: one launch (in PSK_PHASE_MAIN),
- * no table is read, nothing is carried; such problems are bound by launch latency.  (Above 16384 entries the table of
+ * nnz <= 49152 (24576 if there is one row only) and rows <= 65536 the rows are summed in blocks of whole rows: one launch (in
+ * PSK_PHASE_MAIN), no table is read, nothing is carried; such problems are bound by launch latency.  (Above 16384 entries the table of
  * tiles of 2048 and empty carry records are left in the workspace all the same, for phases called with tile = 2048 and
  * for entry points that share the table.)
  *
@@ -301,7 +301,7 @@ int psk_spmv_csr_rowsplit(int64_t rows, int64_t cols, int64_t nnz, const int32_t
  * twice as large per column, so slices of the same byte size hold half the columns); products and sums in fp64.
  * vals [nnz], x [cols], y [rows] doubles, 8-byte aligned (PSK_ERR_ALIGNMENT otherwise); crd and vals
  * 16-byte aligned selects the 16-byte load path.  tile in {0, 256, 512, 1024, 2048}, 0 = 1024 (blocks of whole
- * rows as in psk_spmv_csr for nnz <= 24576, with the table of tiles of 1024 left in the workspace).
+ * rows as in psk_spmv_csr for nnz <= 24576 (one row: 12288), with the table of tiles of 1024 left in the workspace).
  * Workspace from psk_workspace_bytes(PSK_OP_SPMV_CSR_F64, rows, nnz, 1, 1, tile).
  * Deterministic; |y - exact| <= 1e-14 * sum_j |a_ij x_j| per row.
  */

@@ -102,12 +102,15 @@ hipError_t launch_spmv_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
                                 const float *vals, const float *x, float *y, int32_t tile, int32_t col_passes,
                                 const Workspace &w, hipStream_t s, int search, const int32_t *rowmap = nullptr,
                                 bool gaps = false);
-// Small matrices: blocks of whole rows, one launch, no table, no carries.  The limits are set by the worst case, all entries
-// in one row, i.e. in one workgroup: 2.4 us per 8192 entries (fp64 4.6), against about 16 us for three launches.
+// Small matrices: blocks of whole rows, one launch, no table, no carries.  What costs is a long row, which one workgroup sums:
+// tiles and fix-up take 10 us whatever the rows are, blocks 7 with 8192 entries in a row, and in one row of scattered columns
+// 14.5 with 24 576, 18.6 with 32 768, 27 with 49 152 (fp64 11 with 12 288, 18.4 with 24 576; two rows of half that each 14.7, 11.1).
+// So a single row goes by tiles above half the limit.  A row with most of the entries among others is not seen from here.
 constexpr int32_t kSmallNnz = 49152, kSmallNnzF64 = 24576, kSmallRows = 65536;
 inline bool spmv_small(int64_t rows, int64_t nnz, int vbytes)
 {
-    return nnz > 0 && nnz <= (vbytes == 8 ? kSmallNnzF64 : kSmallNnz) && rows <= kSmallRows;
+    const int32_t most = vbytes == 8 ? kSmallNnzF64 : kSmallNnz;
+    return nnz > 0 && nnz <= (rows == 1 ? most / 2 : most) && rows <= kSmallRows;
 }
 // Up to this many entries (fp32) the workspace is not touched and only the main phase does anything.  Above, a phase may be
 // followed by one of a call that gives the tile's size or of another entry point with the same table, so what those read is

@@ -54,6 +54,25 @@ def test_size_limit_of_the_one_launch_path(n):
     check([n // 3, n - n // 3 - 7, 7], False)
 
 
+@pytest.mark.parametrize("f64,n,tiles", [(False, 24576, False), (False, 24577, True), (False, 49152, True),
+                                         (True, 12288, False), (True, 12289, True), (True, 24576, True)])
+def test_one_long_row_goes_by_tiles(f64, n, tiles):
+    """A row is one workgroup's in the row blocks; by tiles its later parts wait for the fix-up step.  (All terms are 1.)"""
+    dt, tile = (torch.float64, 1024) if f64 else (torch.float32, 2048)
+    f, op = (psk.psk_spmv_csr_f64, psk.PSK_OP_SPMV_CSR_F64) if f64 else (psk.psk_spmv_csr, psk.PSK_OP_SPMV_CSR)
+    check([n], f64)
+    check([n], f64, phases=(1, 2, 4))
+    pos = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    crd = torch.arange(n, dtype=torch.int32, device="cuda") % 3000
+    ws = psk.workspace(op, 1, n)
+    y = torch.full((1,), float("nan"), dtype=dt, device="cuda")
+    args = (1, 3000, n, pos, crd, torch.ones(n, dtype=dt, device="cuda"), torch.ones(3000, dtype=dt, device="cuda"), y)
+    f(*args, phases=psk.PSK_PHASE_PARTITION | psk.PSK_PHASE_MAIN, ws=ws)
+    assert y.item() == (tile if tiles else n)
+    f(*args, phases=psk.PSK_PHASE_FIXUP, ws=ws)
+    assert y.item() == n
+
+
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("tile", [256, 1024])
 @pytest.mark.parametrize("phases", [(7,), (1, 2, 4), (7, 6)], ids=str)
