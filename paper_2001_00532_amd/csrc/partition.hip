@@ -94,71 +94,61 @@ hipError_t launch_partition(int64_t rows, int64_t nnz, const int32_t *pos, int32
     return take_launch_status();
 }
 
-// Order in which SpMM tiles are worked on when rows are longer than tiles: by the column of a tile's first position, in ORDER_BINS
-// steps.  In CSR order the tiles in flight sit anywhere in their rows and gather from all of B; ordered, they gather from a
-// range of columns about as wide as a tile's.  Only the order changes: tiles, carries and sums stay as they are.  Counting
-// sort over blocks of ORDER_BLOCK tiles, the order inside a step is of no concern.
-constexpr int ORDER_BINS = 64, ORDER_BLOCK = 1024;
-__device__ __forceinline__ int tile_bin(const int *__restrict__ crd, int t, int tile, int cols)
+// Order in which SpMM tiles are worked on when rows are longer than tiles.  In CSR order the tiles in flight sit anywhere in their
+// rows and gather from all of B.  A tile sweeps over `span` of the columns while it is worked on; here the tiles of a run (a
+// workgroup, `len` neighbouring tiles) are ordered by the column they begin with, and len is such that the next tile to start
+// begins about where the tiles in flight have got to: they move over the columns together, and a die's L2 holds the rows of B
+// around that place.  Only the order changes: tiles, carries and sums stay as they are.
+// All tiles in one order by column (what this replaces) leaves the tiles in flight anywhere in their sweeps, so B * span had to
+// fit the L2; and it took two kernels of 6 + 24 us for 195 000 tiles, this one 13.  10^5 rows of 1000, k = 32 (B 12.8 MB, same tile
+// kernel) 864 -> 790 us for the product;  40 000 of 1000, k = 100 (38 MB) 2500 -> 1560.
+// Counting sort by 1024 steps of columns; the order inside a step is of no concern.
+constexpr int SWEEP_BINS = 1024;
+__global__ __launch_bounds__(1024) void k_tile_sweeps(int rows, int nnz, int ntiles, int tile, int cols, int over, int len,
+                                                      const int *__restrict__ pos, const int *__restrict__ crd,
+                                                      const int *__restrict__ tile_row, int *__restrict__ records)
 {
-    return (int)((long long)crd[(long long)t * tile] * ORDER_BINS / cols);
+    __shared__ int at[SWEEP_BINS], swave[1024 / WAVE];
+    static_assert(SWEEP_BINS == 1024, "one step per thread");
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    const int b0 = blockIdx.x * len, n = min(len, ntiles - b0);
+    auto bin_of = [&](int t) {
+        return (int)((unsigned long long)(unsigned)crd[(long long)t * tile] * SWEEP_BINS / (unsigned)cols) & (SWEEP_BINS - 1);
+    };
+    at[tid] = 0;
+    __syncthreads();
+    for (int i = tid; i < n; i += 1024) atomicAdd(&at[bin_of(b0 + i)], 1);
+    __syncthreads();
+    const int mine = at[tid];
+    int inc = mine;
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        const int p = __shfl_up(inc, d, WAVE);
+        inc += lane >= d ? p : 0;
+    }
+    if (lane == WAVE - 1) swave[wave] = inc;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) inc += swave[w];
+    at[tid] = inc - mine;
+    __syncthreads();
+    for (int i = tid; i < n; i += 1024)
+        put_record(records, b0 + atomicAdd(&at[bin_of(b0 + i)], 1), b0 + i,
+                   tile_span<TABLE_READ>(rows, pos, b0 + i, tile, nnz, ntiles, over, tile_row, 0));
 }
 
-__global__ __launch_bounds__(256) void k_tile_bins(int ntiles, int tile, int cols, const int *__restrict__ crd,
-                                                   int *__restrict__ hist)
-{
-    __shared__ int h[ORDER_BINS];
-    if (threadIdx.x < ORDER_BINS) h[threadIdx.x] = 0;
-    __syncthreads();
-    for (int i = threadIdx.x; i < ORDER_BLOCK; i += 256) {
-        const int t = blockIdx.x * ORDER_BLOCK + i;
-        if (t < ntiles) atomicAdd(&h[tile_bin(crd, t, tile, cols)], 1);
-    }
-    __syncthreads();
-    if (threadIdx.x < ORDER_BINS) hist[blockIdx.x * ORDER_BINS + threadIdx.x] = h[threadIdx.x];
-}
-
-__global__ __launch_bounds__(256) void k_tile_order(int rows, int nnz, int ntiles, int tile, int cols, int over,
-                                                    const int *__restrict__ pos, const int *__restrict__ crd, int *tile_row,
-                                                    const int *__restrict__ hist, int *__restrict__ records)
-{
-    constexpr int PARTS = 256 / ORDER_BINS;
-    __shared__ int sum[PARTS][ORDER_BINS], mine[PARTS][ORDER_BINS], at[ORDER_BINS];
-    const int bin = threadIdx.x % ORDER_BINS, part = threadIdx.x / ORDER_BINS;
-    int all = 0, before = 0;
-    for (int w = part; w < (int)gridDim.x; w += PARTS) {
-        const int v = hist[w * ORDER_BINS + bin];
-        all += v;
-        before += w < (int)blockIdx.x ? v : 0;
-    }
-    sum[part][bin] = all;
-    mine[part][bin] = before;
-    __syncthreads();
-    if (threadIdx.x < ORDER_BINS) {
-        int base = 0;
-        for (int p = 0; p < PARTS; ++p) {
-            base += mine[p][bin];
-            for (int b = 0; b < bin; ++b) base += sum[p][b];
-        }
-        at[bin] = base;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < ORDER_BLOCK; i += 256) {
-        const int t = blockIdx.x * ORDER_BLOCK + i;
-        if (t < ntiles)
-            put_record(records, atomicAdd(&at[tile_bin(crd, t, tile, cols)], 1), t,
-                       tile_span(rows, pos, t, tile, nnz, ntiles, over, tile_row, 0));
-    }
-}
-
-// The records go to the workspace's tile_cols (8 ints per tile), the histograms (64 ints per 1024 tiles) to its tile_aux.
-hipError_t launch_tile_order(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd, int32_t tile,
-                             int32_t over, const Workspace &w, hipStream_t s)
+// The records go to the workspace's tile_cols (8 ints per tile).
+hipError_t launch_tile_sweeps(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd, int32_t tile,
+                              int32_t over, const Workspace &w, hipStream_t s)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
-    const dim3 grid((unsigned)((ntiles + ORDER_BLOCK - 1) / ORDER_BLOCK));
-    PSK_LAUNCH(k_tile_bins, grid, dim3(256), 0, s, ntiles, tile, cols, crd, w.tile_aux);
-    PSK_LAUNCH(k_tile_order, grid, dim3(256), 0, s, rows, nnz, ntiles, tile, cols, over, pos, crd, w.tile_row, w.tile_aux, w.tile_cols);
+    // A die holds about 768 tiles (waves); 768 / span of them cover the columns once.  Runs of 700 / 1000 / 1400 over span, us: 4000 per
+    // row, k = 128 815 / 819 / 813;  1000, k = 64 888 / 834 / 778;  1000, k = 100 1554 / 1564 / 1730;  k = 32 818 / 790 / 814.  Runs of more than
+    // 4096 tiles keep too few workgroups busy here: 20 000 per row, 40 M entries, k = 32 (limit 1024 / 4096 / none) 291 / 278 / 436;
+    // 10 000, k = 64 764 / 489 / 522.
+    const double len = 1000.0 * nnz / ((double)rows * tile);
+    const int run = len < 256 ? 256 : (len > 4096 ? 4096 : (int)len);
+    PSK_LAUNCH(k_tile_sweeps, dim3((unsigned)((ntiles + run - 1) / run)), dim3(1024), 0, s, rows, nnz, ntiles, tile, cols, over, run,
+               pos, crd, w.tile_row, w.tile_cols);
     return take_launch_status();
 }
 

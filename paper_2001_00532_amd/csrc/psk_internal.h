@@ -142,9 +142,9 @@ hipError_t launch_carry_fixup_f64(int32_t ntiles, int32_t tile, const int32_t *p
                                   hipStream_t s, int32_t gap_rows);
 
 // CSR SpMM
-// records of the tiles in w.tile_cols, by the column of their first position (at least 1024 tiles; reads the table)
-hipError_t launch_tile_order(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd, int32_t tile,
-                             int32_t over, const Workspace &w, hipStream_t s);
+// records of the tiles in w.tile_cols, in the order in which they sweep over the columns (reads the table)
+hipError_t launch_tile_sweeps(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd, int32_t tile,
+                              int32_t over, const Workspace &w, hipStream_t s);
 // A row that reaches at most this far past the end of a tile is finished by that tile (tile_span in psk_dev.h).  It saves most of
 // the carries when rows are shorter than tiles; CSR rows of half a tile and more would only make the tiles unequal (0.5 to 1.5 T
 // positions) and leave few carries less: us with tile / 2 | with 0, tile 512: rows of 30, k = 128 41 | 43;  60 404 | 407;  200 457 | 465 (k = 32
@@ -161,6 +161,10 @@ constexpr int32_t kGroupColumns = 128;
 hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
                                   int32_t tile, int32_t over, const Workspace &w, hipStream_t s, int search, const int32_t *records);
+// k >= 4, many tiles: a wave per tile (reads the table)
+hipError_t launch_spmm_csr_wave(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
+                                const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
+                                int32_t tile, int32_t over, const Workspace &w, hipStream_t s, const int32_t *records);
 hipError_t launch_spmm_rowsplit(int32_t rows, const int32_t *pos, const int32_t *crd, const float *vals,
                                 const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
                                 hipStream_t s);

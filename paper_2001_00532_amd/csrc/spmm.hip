@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
                                                   typename TablePtr<USE != TABLE_READ>::type tile_row,
                                                   int *__restrict__ carry_row,
                                                   float *__restrict__ carry_val, int ntiles, int T, int over,
-                                                  int search, const int *__restrict__ records)
+                                                  int search)
 {
     constexpr int THREADS = 256, NW = THREADS / WAVE, KW = WAVE * VEC;
     constexpr int U = BS == 1 ? 8 : (BS == 2 ? 4 : (BS == 4 ? 2 : 1));   // positions whose B rows are in flight together
@@ -44,14 +44,13 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
     __shared__ float srec[2 * NW][BS][KW];
     __shared__ int srec_row[2 * NW];              // -2 unused, -1 open segment, >= 0 row that ended
 
-    int t = xcd_tile(blockIdx.x, ntiles);
+    const int t = xcd_tile(blockIdx.x, ntiles);
     if (t < 0) return;
-    const int slot = t;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     // BS == 1: tell the compiler that the wave index is uniform (scalar loop control).  With blocks the
     // generated code measured 3 % slower that way, so there it stays a per-lane value.
     const int wave = BS == 1 ? __builtin_amdgcn_readfirstlane(tid / WAVE) : tid / WAVE;
-    TileSpan span = BS == 1 && records ? get_record(records, slot, t) : tile_span<USE>(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
+    TileSpan span = tile_span<USE>(rows, pos, t, T, nnz, ntiles, over, tile_row, search);
     if constexpr (BS == 4) {                      // in scalar registers (k = 64: 329.4 -> 327.9 us); the others gain nothing
         span.t0 = __builtin_amdgcn_readfirstlane(span.t0);
         span.cnt = __builtin_amdgcn_readfirstlane(span.cnt);
@@ -275,8 +274,7 @@ static int pick_vec(const float *B, int32_t k, int64_t ldb, const float *C, int6
 template <int BS>
 static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
-                                  int64_t ldc, int32_t tile, int32_t over, const Workspace &w, hipStream_t s, int search,
-                                  const int32_t *records = nullptr)
+                                  int64_t ldc, int32_t tile, int32_t over, const Workspace &w, hipStream_t s, int search)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     if (ntiles == 0) return hipSuccess;
@@ -296,7 +294,7 @@ static hipError_t launch_spmm_pos(int32_t rows, int32_t nnz, const int32_t *pos,
     } while (0)
 #define PSK_GO_(V, S)                                                                                          \
     PSK_LAUNCH((k_spmm_pos<BS, V, S>), grid, dim3(256), lds, s, rows, nnz, pos, crd, vals, B, k,          \
-                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, search, records)
+                       (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, search)
     if (vec == 4) {
         if constexpr (BS < 8) PSK_GO(4);
     } else if (vec == 2) PSK_GO(2);
@@ -318,25 +316,39 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     //     against 1776; where it can the wide kernel is 1-3 % faster, k = 128 1190 against 1223)
     const bool groups = k <= 32 || (k <= 64 && nnz >= 8ll * rows) ||
                         (k > 64 && k <= kGroupColumns && pick_vec(B, k, ldb, C, ldc) == 1);
-    // Tiles in column order (launch_tile_order) when rows are long: then a tile spans the share `span` of the columns, and what
-    // the tiles in flight gather from is about span * B instead of all of B.  It pays when that comes near a die's 4 MB of L2;
-    // otherwise the order only costs (30 us and less locality in A, C and the row tables).  us in CSR order / ordered, 40 M entries
-    // in equal rows with sorted columns:
-    //   k = 32, B 12.8 MB: span 0.10 508 / 346, 0.26 512 / 346, 0.51 513 / 377;  B 6.4 MB: 0.51 369 / 357;  k = 64, B 12.8 MB: 0.51 967 /
-    //   624;  B 51 MB: 0.26 1297 / 1011, 0.34 1304 / 1109;  k = 128, B 25.6 MB: 0.26 2254 / 1257, 0.51 2274 / 1902;  B 51 MB: 0.13 2478 /
-    //   1291, 0.26 2501 / 1917;  rows of 200, span 2.6 (not here): k = 64 186 / 229.  10^5 rows of about 1000: log-normal lengths 1264 / 879,
-    //   nine rows in ten of 50 entries 1238 / 825.  Unsorted columns cannot gain; the order costs them 1258 / 1293.
+    // Tiles in the order of their sweeps over the columns (launch_tile_sweeps) when rows are long.  It pays where B (MB: b_mb) is larger
+    // than the L2 and its rows are used by several of the 768 tiles that a die works on at once: the sweeps of a die read B
+    // rows / 768 times, so 2 * cols < 768 * mean row.  us before / ordered, columns sorted in the rows:
+    //   1000 per row, k = 32, B 12.8 MB 873 / 790 (10^5 rows);  k = 64, 12.8 MB 794 / 642;  k = 64, 24 MB 1236 / 834;  k = 100, 38 MB 2495 / 1564;
+    //   k = 128, 14.6 MB 1086 / 667, 49 MB (4000 per row) 1340 / 819;  k = 256, 16 MB 414 / 178 (4000 rows), 64 MB 536 / 403;  700 per row (span 0.73),
+    //   k = 256, 59 MB 3783 / 3297.  On the other side: span 0.93 413 / 420, B of 6 MB 1000 per row k = 16 41 / 47, k = 32 45 / 49.
+    // Columns that are not sorted inside the rows gain nothing from the order; it costs the kernel that makes it (13 us of 870).
     const int32_t *records = nullptr;
     const int32_t over = spmm_overhang(rows, nnz, tile);
     const int64_t ntiles = ((int64_t)nnz + tile - 1) / tile;
     const double span = (double)rows * tile / nnz, b_mb = (double)cols * k * 4 / (1 << 20);
-    if (ntiles >= 4096 && b_mb >= 8 && ((span <= 0.55 && span * b_mb <= 8) || (span <= 0.35 && span * b_mb <= 16))) {
-        const hipError_t e = launch_tile_order(rows, cols, nnz, pos, crd, tile, over, w, s);
+    if (ntiles >= 4096 && b_mb >= 8 && span <= 0.8 && 2.0 * cols * rows <= 768.0 * nnz) {
+        const hipError_t e = launch_tile_sweeps(rows, cols, nnz, pos, crd, tile, over, w, s);
         if (e != hipSuccess) return e;
         records = w.tile_cols;
     }
+    // A wave per tile (k_spmm_wave) or a workgroup.  The first is limited by the L2, so it gains where B fits it; rows of B from
+    // memory come at the fabric's rate in all kernels, and the workgroups' are a little better at that.  us, 4 M entries unless
+    // stated, workgroup / wave:
+    //   tiles: 1016, B 2 MB 26 / 32 (4 per row, k = 64), 12.5 / 13.8 (100, k = 32);  1953: 40 / 34, 17.4 / 17.3, k = 128 44 / 30;  3906: 70 / 45, 27.2 / 23.3, 74 / 50
+    //   B 2 MB: 4 per row k = 32 131 / 56;  16, k = 16 52 / 35;  1000, k = 64 60 / 49;  4, k = 6 61 / 57
+    //   B 6 MB: 4 per row k = 32 128 / 67;  16, k = 24 68 / 61;  100, k = 24 56 / 62;  1000, k = 32 45 / 49;  100, k = 96 137 / 101;  16, k = 200 209 / 212
+    //   B 16 MB and more: 4 per row k = 16 86 / 79, k = 32 131 / 90, 500 MB 145 / 114;  4, k = 64 176 / 184;  100, k = 32 66 / 72;  10^6 rows of 16, 488 MB, k = 128
+    //   1224 / 1250;  more than 256 columns (A is walked again): 4 per row 469 / 484, 16 315 / 289
+    const bool shorts = nnz < 32ll * rows;
+    //   k = 8, 100 per row: 1953 tiles 15.1 / 17.2, 3906 21.8 / 22.2, 7812 34.9 / 33.0
+    const bool wave = k >= 4 && ntiles >= (k <= 8 && !shorts ? 6000 : 1536) &&
+                      (records || b_mb <= 4.5 || (shorts && k <= 64 && b_mb <= 6) || (k > 64 && k <= 128 && b_mb <= 8) ||
+                       (k > 8 && k <= 32 && nnz < 8ll * rows)) &&
+                      (k <= 256 || nnz >= 8ll * rows);
+    if (wave) return launch_spmm_csr_wave(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, records);
     if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search, records);
-    return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search, records);
+    return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
 }
 
 hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,

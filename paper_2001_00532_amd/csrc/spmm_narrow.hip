@@ -39,6 +39,45 @@ __device__ __forceinline__ void group_segscan(float (&v)[VEC], unsigned long lon
     }
 }
 
+// A range of memory for buffer loads: reads behind `bytes` return 0.
+typedef __amdgpu_buffer_rsrc_t buf_t;
+constexpr int BUFFER_NT = 2;                      // non-temporal
+__device__ __forceinline__ buf_t buffer_of(const void *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+
+// Orders a wave's own reads and writes of LDS.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The same sums in fp64, and inside segments: inclusive sums over groups, a lane of `heads` = its group starts a segment.
+template <int GW>
+__device__ __forceinline__ double group_sum(double v)
+{
+#pragma unroll
+    for (int d = GW; d < WAVE; d <<= 1) v += __shfl_xor(v, d, WAVE);
+    return v;
+}
+template <int GW, int D>
+__device__ __forceinline__ void group_segscan(double (&x)[4], unsigned long long heads, int g)
+{
+    if constexpr (D < WAVE) {
+        const bool take = g >= D / GW && ((heads >> (threadIdx.x & (WAVE - 1))) & 1) == 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double p = __shfl_up(x[q], D, WAVE);
+            x[q] += take ? p : 0.0;
+        }
+        group_segscan<GW, 2 * D>(x, heads | (heads << D), g);
+    }
+}
+
+constexpr int kWaveBlock = 576;                   // positions of a tile that a wave stages at a time
+
 // The last lane of a group whose columns would pass the end of the row takes the last VEC columns instead: it computes and
 // stores some of its neighbour's values a second time, bit by bit the same.  So any k >= VEC works, and rows need no
 // alignment beyond that of a float.
@@ -239,6 +278,242 @@ __global__ __launch_bounds__(256) void k_spmm_pos_group(int rows, int nnz, const
     if (s.straddle) finalize(s.r1);
 }
 
+// Many tiles: a wave takes a whole tile, alone, so that no wave waits for another and the chain of dependent loads at a tile's
+// start (table, row positions, entries) is paid by a wave among many instead of by a workgroup four times as often.  The tile's
+// entries are staged in LDS, up to kWaveBlock at a time, the end of a row marked in the entry itself.
+//   no row ends in the tile: the groups take neighbouring positions, every lane adds to its group's share of the open row;
+//   else every group walks a run of positions of its own: rows that end inside the run are stored by the group (no sums across
+//   lanes), and one segmented sum per block hands each group what the groups before it leave of its first row.
+// Bound by the requests to the L2: a row of B in the L2 costs 4.0 ps per 128 bytes on the whole chip however it is asked for, and
+// the stream of entries, 8 bytes each from memory, adds 0.8 to 1.7; measured 6.4 ps at k = 32.  Before, us (k_spmm_pos_group / k_spmm_pos, whose
+// workgroups wait on barriers) and now: 40 000 rows of 1000 x 25 000, k = 32 360 -> 252;  6000 columns, k = 128 1130 -> 690;  10^6 rows of 16,
+// 25 000 columns, k = 16 186 -> 111, k = 32 228 -> 128;  of 5, k = 32 141 -> 75.  Eight steps of loads in flight against four: k = 8 231 -> 205, k = 128
+// 705 -> 660; more waves per CU (fewer registers) gain nothing.
+template <int G, bool SMALL>
+__global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int *__restrict__ pos, const int *__restrict__ crd,
+                                                   const float *__restrict__ vals, const float *__restrict__ B, int k,
+                                                   long long ldb, float *__restrict__ C, long long ldc,
+                                                   const int *__restrict__ tile_row, int *__restrict__ carry_row,
+                                                   float *__restrict__ carry_val, int ntiles, int T, int over,
+                                                   const int *__restrict__ records)
+{
+    constexpr int GW = WAVE / G, U = 8, LD = kWaveBlock / WAVE;
+    constexpr int PLACES = kWaveBlock + G;        // (runs an odd number of places apart)
+    typedef v4f_u V;
+    extern __shared__ int smem[];
+    const int lane = threadIdx.x & (WAVE - 1), g = lane / GW, gl = lane % GW;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    int2 *const ent = reinterpret_cast<int2 *>(smem) + wave * PLACES;       // {offset or column | row end, value}
+    unsigned short *const srow = reinterpret_cast<unsigned short *>(smem + 4 * 2 * PLACES) + wave * kWaveBlock;   // row that ends
+    const int quad = xcd_tile(blockIdx.x, (ntiles + 3) / 4), slot = quad * 4 + wave;
+    if (quad < 0 || slot >= ntiles) return;                                     // (no barriers: waves don't wait for each other)
+    const int col0 = blockIdx.y * (GW * 4) + gl * 4;
+    const bool active = col0 < k;
+    const int col = col0 < k - 4 ? col0 : k - 4;
+
+    int t = slot;
+    TileSpan s = records ? get_record(records, slot, t) : tile_span<TABLE_READ>(rows, pos, t, T, nnz, ntiles, over, tile_row, 0);
+    t = __builtin_amdgcn_readfirstlane(t);
+    const int t0 = __builtin_amdgcn_readfirstlane(s.t0), cnt = __builtin_amdgcn_readfirstlane(s.cnt);
+    const int r0 = __builtin_amdgcn_readfirstlane(s.r0), r1 = __builtin_amdgcn_readfirstlane(s.r1);
+    const int rbeg = __builtin_amdgcn_readfirstlane(s.rbeg), rend = __builtin_amdgcn_readfirstlane(s.rend);
+    const bool first_y = blockIdx.y == 0;
+
+    if (lane == 0 && first_y && !s.has_carry) carry_row[t] = -1;
+    const bool solid = s.straddle && rbeg == r1;  // no row ends in this tile
+    const bool near = rend - rbeg < 0xffff;       // the rows' numbers fit 16 bits
+
+    const char *const Bb = reinterpret_cast<const char *>(B);
+    const unsigned col4 = (unsigned)col * 4u;
+    auto row_of_B = [&](int x) -> V {
+        if constexpr (SMALL) return *reinterpret_cast<const V *>(Bb + (((unsigned)x & ~1u) + col4));
+        else return *reinterpret_cast<const V *>(B + (long long)(x & 0x7fffffff) * ldb + col);
+    };
+    auto ends_row = [&](int x) -> bool { return SMALL ? (x & 1) != 0 : x < 0; };
+    auto row_at = [&](int b0, int i) -> int {     // the row that ends at place i of the block
+        if (near) return rbeg + srow[i];
+        int lo = r0, hi = r1;                     // a long run of empty rows: max { r : pos[r] <= t0 + b0 + i }
+        while (lo < hi) {
+            const int mid = lo + ((hi - lo + 1) >> 1);
+            if (pos[mid] <= t0 + b0 + i) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    auto store = [&](int r, const auto (&o)[4]) {
+        __builtin_nontemporal_store(V{(float)o[0], (float)o[1], (float)o[2], (float)o[3]}, reinterpret_cast<V *>(C + (long long)r * ldc + col));
+    };
+    auto emit = [&](int r, const double (&o)[4]) {                  // a row that may have begun in an earlier tile
+        if (s.has_carry && r == r0) {
+            *reinterpret_cast<V *>(carry_val + (long long)t * k + col) = V{(float)o[0], (float)o[1], (float)o[2], (float)o[3]};
+            if (gl == 0 && first_y) carry_row[t] = r;
+        } else store(r, o);
+    };
+    auto total = [&](const double (&x)[4], double (&o)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = group_sum<GW>(x[q]);
+    };
+
+    double open[4] = {};                          // this group's share of the row that is open
+    const int nb = (cnt + kWaveBlock - 1) / kWaveBlock, bn = nb ? (cnt + nb - 1) / nb : 0;
+    for (int b0 = 0; b0 < cnt || b0 == 0; b0 += bn) {
+        const int n = cnt - b0 < bn ? cnt - b0 : bn;
+        // a run of positions for each group, an odd number of places apart (the groups' reads hit different banks)
+        const int run = (n + G - 1) / G, step = solid ? run : run | 1;
+        const unsigned inv = run > 0 ? 0xffffffffu / (unsigned)run + 1 : 0;               // i / run = i * inv / 2^32 for i < kWaveBlock
+        auto place = [&](int i) { return step == run ? i : i + (int)__umulhi((unsigned)i, inv); };
+        {
+            // (places behind the block's end read as 0: the range check of the buffer loads)
+            const buf_t cb = buffer_of(crd + t0 + b0, n > 0 ? n * 4 : 0), vb = buffer_of(vals + t0 + b0, n > 0 ? n * 4 : 0);
+            int c[LD], r = rbeg + lane;
+            float v[LD];
+#pragma unroll
+            for (int u = 0; u < LD; ++u) {
+                c[u] = __builtin_amdgcn_raw_buffer_load_b32(cb, lane * 4 + u * WAVE * 4, 0, BUFFER_NT);
+                v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vb, lane * 4 + u * WAVE * 4, 0, BUFFER_NT));
+            }
+            int ps = r < rend ? pos[r] : 0, pe = r < rend ? pos[r + 1] : 1;
+#pragma unroll
+            for (int u = 0; u < LD; ++u) {
+                const int i = u * WAVE + lane;
+                if (i < n) ent[place(i)] = make_int2(SMALL ? (int)((unsigned)c[u] * (unsigned)ldb * 4u) : c[u], __builtin_bit_cast(int, v[u]));
+            }
+            wave_fence();
+            for (int rb = rbeg; rb < rend; rb += WAVE) {
+                const int e = pe - 1 - t0 - b0;
+                const bool here = r < rend && pe > ps && e >= 0 && e < n;
+                if (here) {
+                    ent[place(e)].x |= SMALL ? 1 : (int)0x80000000u;
+                    srow[e] = (unsigned short)(near ? r - rbeg : 0);
+                }
+                unsigned long long empty = b0 == 0 ? __ballot(r < rend && pe == ps) : 0;
+                r += WAVE;
+                if (rb + WAVE < rend) { ps = r < rend ? pos[r] : 0; pe = r < rend ? pos[r + 1] : 1; }
+                while (empty) {
+                    const int j = __ffsll((long long)empty) - 1;
+                    empty &= empty - 1;
+                    if (active && g == 0) __builtin_nontemporal_store(V{}, reinterpret_cast<V *>(C + (long long)(rb + j) * ldc + col));
+                }
+            }
+            wave_fence();
+        }
+        if (n <= 0) break;
+        if (solid) {
+            // no row ends here: the groups take neighbouring positions
+            for (int i = 0; i < n; i += U * G) {
+                V b[U];
+                float a[U], even[4] = {}, odd[4] = {};
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int j = i + u * G + g;
+                    const int2 e = ent[j < n ? j : n - 1];
+                    a[u] = __builtin_bit_cast(float, e.y);
+                    b[u] = row_of_B(e.x);
+                }
+                if (i + U * G <= n) {
+#pragma unroll
+                    for (int u = 0; u < U; u += 2)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            even[q] = fmaf(a[u], b[u][q], even[q]);
+                            odd[q] = fmaf(a[u + 1], b[u + 1][q], odd[q]);
+                        }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (i + u * G + g < n) {
+                            float(&to)[4] = u & 1 ? odd : even;
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) to[q] = fmaf(a[u], b[u][q], to[q]);
+                        }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) open[q] += (double)(even[q] + odd[q]);
+            }
+        } else {
+            const int j0 = g * run, len = n - j0 < run ? n - j0 : run;
+            const int first = g * step;           // place of the run (lanes without a position read the block's first entry)
+            // sums of the open row: the last positions, even and odd ones, and what they were added up to before, as the
+            // sum of two floats (a step of Knuth's exact addition: at a row's end cheaper than fp64, 5 per row, k = 32 82 -> 75 us)
+            float even[4] = {}, odd[4] = {}, hi[4] = {}, lo[4] = {}, head[4] = {};
+            int hrow = -1;                        // row of the first end in this group's run; its sum, without what lies before, in head
+            auto fold = [&]() {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float x = even[q] + odd[q], t = hi[q] + x, z = t - hi[q];
+                    lo[q] += (hi[q] - (t - z)) + (x - z);
+                    hi[q] = t;
+                    even[q] = odd[q] = 0.0f;
+                }
+            };
+            auto ended = [&](int i) {             // position i of the run ends a row
+                const int r = row_at(b0, j0 + i);
+                float o[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    o[q] = hi[q] + (lo[q] + (even[q] + odd[q]));
+                    even[q] = odd[q] = hi[q] = lo[q] = 0.0f;
+                }
+                if (hrow < 0) {
+                    hrow = r;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) head[q] = o[q];
+                } else if (active) store(r, o);
+            };
+            auto walk = [&](int i, auto all) {    // U positions; all: every group has them
+                V b[U];
+                int2 e[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    e[u] = ent[all() || i + u < len ? first + i + u : 0];
+                    b[u] = row_of_B(e[u].x);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool have = all() || i + u < len;
+                    float(&to)[4] = u & 1 ? odd : even;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) to[q] = have ? fmaf(__builtin_bit_cast(float, e[u].y), b[u][q], to[q]) : to[q];
+                    if (have && ends_row(e[u].x)) ended(i + u);
+                }
+                fold();
+            };
+            int i = 0;
+            for (; i + U <= n - (G - 1) * run; i += U) walk(i, [] { return true; });      // (the last group has no more than the others)
+            for (; i < run; i += U) walk(i, [] { return false; });
+            double acc[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = (double)hi[q] + (double)lo[q];
+            const unsigned long long has = __ballot(hrow >= 0);
+            if (has == 0) {                       // (a tile of several blocks)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) open[q] += acc[q];
+            } else {
+                // what the groups before this one leave of its first row: sums of the groups' open ends, afresh after each end
+                double before[4], x[4];
+                total(open, before);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[q] = g == 0 && hrow < 0 ? acc[q] + before[q] : acc[q];
+                group_segscan<GW, GW>(x, has, g);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double p = __shfl_up(x[q], GW & (WAVE - 1), WAVE);
+                    x[q] = (double)head[q] + (g == 0 ? before[q] : p);
+                }
+                if (hrow >= 0 && active) emit(hrow, x);
+                const int last = 63 - __clzll((long long)has);     // lanes of the last group with an end, and those behind it
+#pragma unroll
+                for (int q = 0; q < 4; ++q) open[q] = g >= last / GW ? acc[q] : 0.0;
+            }
+        }
+        wave_fence();
+    }
+    if (s.straddle) {                             // the open row goes on in the next tile
+        double o[4];
+        total(open, o);
+        if (active && g == 0) emit(r1, o);
+    }
+}
+
 template <int G, int VEC>
 static void launch_group(int32_t rows, int32_t nnz, const int32_t *pos, const int32_t *crd, const float *vals, const float *B,
                          int32_t k, int64_t ldb, float *C, int64_t ldc, int32_t tile, int32_t over, bool small,
@@ -271,6 +546,30 @@ hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const
     else if (k <= 128) PSK_GO(2, 4);
     else return hipErrorInvalidValue;
 #undef PSK_GO
+    return take_launch_status();
+}
+
+hipError_t launch_spmm_csr_wave(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
+                                const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
+                                int32_t tile, int32_t over, const Workspace &w, hipStream_t s, const int32_t *records)
+{
+    if (nnz <= 0) return hipSuccess;
+    if (k < 4) return hipErrorInvalidValue;
+    const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
+    const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? cols : 1);
+    const dim3 grid((unsigned)xcd_grid((ntiles + 3) / 4), (unsigned)((k + 255) / 256));
+#define PSK_GO_(GG, SM)                                                                                           \
+    PSK_LAUNCH((k_spmm_wave<GG, SM>), grid, dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
+               (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, records)
+#define PSK_GO(GG) do { if (small) PSK_GO_(GG, true); else PSK_GO_(GG, false); } while (0)
+    if (k <= 8) PSK_GO(32);
+    else if (k <= 16) PSK_GO(16);
+    else if (k <= 32) PSK_GO(8);
+    else if (k <= 64) PSK_GO(4);
+    else if (k <= 128) PSK_GO(2);
+    else PSK_GO(1);
+#undef PSK_GO
+#undef PSK_GO_
     return take_launch_status();
 }
 

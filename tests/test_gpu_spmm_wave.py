@@ -1,0 +1,92 @@
+"""SpMM with many tiles, where a wave works on a tile alone (1536 tiles and more): group widths, rows that end inside a group's
+run, at its borders and behind the tile, blocks without a row end, tiles staged in several blocks, runs of more empty rows
+than 16 bits number, NaN and Inf.  Oracle and bar as for the other SpMM tests: |got - ref| <= 1e-5 * sum |a b| + 1e-30."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2001_00532_amd as psk  # noqa: E402
+
+NNZ = 1536 * 256 + 77                        # many tiles of 256, the last one short
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def rows_of(pattern, rng, nnz):
+    if pattern == "short":
+        L = rng.choice([0, 1, 2, 3, 9], size=nnz)
+    elif pattern == "middle":
+        L = rng.integers(10, 60, size=nnz // 10)
+    else:
+        L = rng.choice([0, 1, 255, 256, 257, 384, 385, 700, 890], size=nnz // 200)
+    return L[:int(np.searchsorted(np.cumsum(L), nnz))]
+
+
+def product(A, cols, Bh, k, tile, phases=(7,)):
+    Bd = dev(Bh)[:, :k]
+    C = torch.full((A.rows, k + 1), float("nan"), device="cuda")
+    ws = psk.workspace(psk.PSK_OP_SPMM_CSR, A.rows, A.nnz, k=k, tile=tile)
+    for ph in phases:
+        psk.psk_spmm_csr(A.rows, cols, A.nnz, dev(A.pos), dev(A.crd), dev(A.vals), Bd, C[:, :k], tile=tile, ws=ws, phases=ph)
+    torch.cuda.synchronize()
+    got = C.cpu().numpy()
+    assert np.isnan(got[:, k:]).all(), "columns past k were written"
+    return got[:, :k]
+
+
+@pytest.mark.parametrize("pattern", ["short", "middle", "long"])
+@pytest.mark.parametrize("k", [4, 5, 8, 9, 16, 31, 32, 33, 64, 67, 128, 131, 256, 260])
+def test_group_widths(k, pattern):
+    rng = np.random.default_rng(k)
+    for tile, nnz in ((256, NNZ), (2048, 1536 * 2048 + 5)) if k in (8, 33) else ((256, NNZ),):
+        A = wl.csr_from_lengths(rows_of(pattern, rng, nnz + 1000), 900, seed=k)
+        assert A.nnz >= 1536 * tile
+        Bh = wl.dense_uniform(900 * (k + 1), 3, wl.S_B).reshape(900, k + 1)
+        ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh[:, :k])
+        got = product(A, 900, Bh, k, tile)
+        ok, worst = oracle.within_tolerance(got, ref, mag)
+        assert ok, "k %d tile %d %s: %.3g of the bar" % (k, tile, pattern, worst)
+        assert (product(A, 900, Bh, k, tile, (1, 2, 4)) == got).all(), "one phase at a time"
+
+
+def test_runs_of_empty_rows():
+    rng = np.random.default_rng(1)
+    part = rng.choice([1, 2, 40], size=10_000)
+    L = np.concatenate([part, np.zeros(150_000, dtype=part.dtype), part, np.zeros(66_000, dtype=part.dtype), part, part])
+    A = wl.csr_from_lengths(L, 900, seed=1)
+    assert A.nnz >= 1536 * 256
+    Bh = wl.dense_uniform(900 * 18, 3, wl.S_B).reshape(900, 18)
+    ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh[:, :17])
+    ok, worst = oracle.within_tolerance(product(A, 900, Bh, 17, 256), ref, mag)
+    assert ok, "%.3g of the bar" % worst
+
+
+@pytest.mark.parametrize("pattern", ["short", "long"])
+@pytest.mark.parametrize("k", [7, 32, 128])
+def test_nan_and_inf_reach_only_their_rows(k, pattern):
+    """Row 0 of B among them: places of a block that hold no entry must not bring it in."""
+    rng = np.random.default_rng(k)
+    A = wl.csr_from_lengths(rows_of(pattern, rng, NNZ + 1000), 900, seed=k)
+    crd = A.crd.copy()
+    crd[crd == 0] = 1
+    keep = rng.random(crd.size) < 1e-4       # few entries refer to the special rows
+    crd[(crd < 4) & ~keep] = 5
+    Bh = wl.dense_uniform(900 * (k + 1), 3, wl.S_B).reshape(900, k + 1)
+    Bh[0], Bh[1], Bh[2], Bh[3] = np.nan, np.inf, -np.inf, np.nan
+    A = dataclasses.replace(A, crd=crd)
+    with np.errstate(invalid="ignore"):
+        ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh[:, :k])
+    got = product(A, 900, Bh, k, 256)
+    assert (np.isnan(got) == np.isnan(ref)).all()
+    fin = np.isfinite(ref) & np.isfinite(mag)
+    assert (got[~fin & ~np.isnan(ref)] == ref[~fin & ~np.isnan(ref)]).all()
+    assert (np.abs(got[fin] - ref[fin]) <= 1e-5 * mag[fin] + 1e-30).all()
