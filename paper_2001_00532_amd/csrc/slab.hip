@@ -30,8 +30,8 @@ constexpr int BUILD_BT = kSlabBuildBlock;     // CSR positions per block of the 
 // Per value type: columns per slab (what fits into the LDS next to the staging area) and values per 16 bytes.
 typedef double v2d __attribute__((ext_vector_type(2)));
 template <typename T> struct SlabOf;
-template <> struct SlabOf<float>  { static constexpr int W = kSlabCols,    G = 4, WAVES = 16; typedef v4f V; };
-template <> struct SlabOf<double> { static constexpr int W = kSlabColsF64, G = 2, WAVES = kSlabWavesF64; typedef v2d V; };
+template <> struct SlabOf<float>  { static constexpr int W = kSlabCols,    G = 4, WAVES = 16, STAGE = SLAB_CH; typedef v4f V; };
+template <> struct SlabOf<double> { static constexpr int W = kSlabColsF64, G = 2, WAVES = 16, STAGE = SLAB_CH / 2; typedef v2d V; };
 
 // Where the value of slot j is stored.  A lane of the pair kernel owns 8 consecutive slots of a chunk; stored in
 // slot order its 16-byte loads would each touch every other 16 bytes of the chunk.  Inside each chunk the values
@@ -97,16 +97,17 @@ __device__ __forceinline__ T wave_segscan(T v, int f)
 // ------------------------------------------------------------------ step 1 of the product
 // Persistent workgroups: every workgroup owns one piece of cpw consecutive chunks (the position space DIVIDED into
 // equal pieces, Section 5), walks them slab by slab, loads the slab's part of x into LDS once and lets its
-// waves (16; 8 for fp64) take the chunks of that slab round-robin.  A lane owns 8 consecutive slots (two 16-byte loads of
+// 16 waves take the chunks of that slab round-robin.  A lane owns 8 consecutive slots (two 16-byte loads of
 // values, one of columns); the next chunk's loads are issued before the current one is processed.
 // Inside a chunk (no branches): the lane walks its 8 slots with a running sum that restarts after a pair
 // end and writes every running sum to LDS -- to the pair's place in the chunk (number of pair ends before
 // it) when the slot ends a pair, to a dummy word otherwise; a segmented DPP scan then hands each lane the
 // open sum of the lanes below it, which is added to the lane's first pair.  The chunk's pair sums, now
 // compact in LDS, leave with full-width coalesced stores to P[chunk_pair[c] ...].
-// LDS: 127.9 KB of x + 2 KB of pair sums per wave + the dummy words = the CU's 160 KB (fp64: 8 waves, 127.75 KB of
-// x = 16 352 columns, + 4 KB of pair sums per wave; 16 waves with 12 256 columns measured the same, 191.5 against
-// 190.3 us on the power-law configuration, and make more pairs).
+// LDS: 127.9 KB of x + 2 KB of pair sums per wave + the dummy words = the CU's 160 KB.  fp64: 127.75 KB of x = 16 352 columns and
+// room for the sums of half a chunk's slots, which leave in two rounds where a chunk has more pairs (with few entries per pair),
+// so that 16 waves fit: eight waves of a whole chunk each left the vector units waiting.  Power-law configuration 186.1 -> 178.4 us per
+// product; 400 000 rows x 3 M columns, power-law 47.7 -> 42.7; uniform, 10 per row x 3 M (two rounds in most chunks) 90.2 -> 86.8.
 template <typename T>
 __global__ __launch_bounds__(SlabOf<T>::WAVES * WAVE) void k_slab_pairs(const T *__restrict__ svals,
                                                      const unsigned short *__restrict__ scol,
@@ -116,15 +117,16 @@ __global__ __launch_bounds__(SlabOf<T>::WAVES * WAVE) void k_slab_pairs(const T 
                                                      int nslabs, int nchunks, int cpw)
 {
     constexpr int WAVES = SlabOf<T>::WAVES;
+    constexpr int STAGE = SlabOf<T>::STAGE;
     constexpr int W = SlabOf<T>::W, G = SlabOf<T>::G, NV = 8 / G;      // NV 16-byte loads of values per lane
     typedef typename SlabOf<T>::V V;
     __shared__ T xs[W];
-    __shared__ T stage[WAVES * SLAB_CH + 32];         // + one dummy word per LDS bank
-    static_assert(sizeof(T) * (W + WAVES * SLAB_CH + 32) <= 163840, "the window and the staging area fill the CU's LDS");
+    __shared__ T stage[WAVES * STAGE + 32];           // + one dummy word per LDS bank
+    static_assert(sizeof(T) * (W + WAVES * STAGE + 32) <= 163840, "the window and the staging area fill the CU's LDS");
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
-    T *st = stage + wave * SLAB_CH;
-    const int dummy = (WAVES - wave) * SLAB_CH + (lane & 31);      // index, relative to st, of a word nobody reads
+    T *st = stage + wave * STAGE;
+    const int dummy = (WAVES - wave) * STAGE + (lane & 31);      // index, relative to st, of a word nobody reads
     // piece of this workgroup: neighbouring pieces go to workgroups of the same die, so that the slabs of x they share
     // are fetched into that die's L2 once (measured on the power-law matrix: 76.2 against 79.4 us)
     const int piece = xcd_tile(blockIdx.x, (nchunks + cpw - 1) / cpw);
@@ -194,21 +196,29 @@ __global__ __launch_bounds__(SlabOf<T>::WAVES * WAVE) void k_slab_pairs(const T 
             }
             const int cnt = __popc(ends);
             const int first = wave_scan_add(cnt) - cnt;         // place of this lane's first pair end in the chunk
-            T run = 0;
-            int place = first;
+            T run = 0, sum[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const bool e = (ends >> j) & 1u;
                 run += p[j];
-                st[e ? place : dummy] = run;
-                run = e ? T(0) : run;
-                place += e ? 1 : 0;
+                sum[j] = run;
+                run = (ends >> j) & 1u ? T(0) : run;
             }
             // `run` is the lane's open sum; the lane below hands over the open sum of all lanes below it
             const T open = wave_segscan<T>(run, cnt ? 1 : 0);
             const T carry = __shfl_up(open, 1, WAVE);
-            if (cnt && lane) st[first] += carry;                // head + carry (a chunk's first slot starts a pair)
-            for (int k = lane; k < np; k += WAVE) P[pbase + k] = st[k];
+            for (int k0 = 0; k0 < np; k0 += STAGE) {            // (one round unless the staging area is smaller than a chunk)
+                int place = first - k0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const bool e = (ends >> j) & 1u;
+                    st[e && (STAGE == SLAB_CH || (unsigned)place < (unsigned)STAGE) ? place : dummy] = sum[j];
+                    place += e ? 1 : 0;
+                }
+                // head + carry (a chunk's first slot starts a pair)
+                if (cnt && lane && (STAGE == SLAB_CH || (unsigned)(first - k0) < (unsigned)STAGE)) st[first - k0] += carry;
+                const int n = STAGE == SLAB_CH ? np : min(np - k0, STAGE);
+                for (int k = lane; k < n; k += WAVE) P[pbase + k0 + k] = st[k];
+            }
         }
         c0 = ce;
         ++s;
