@@ -10,31 +10,46 @@
 
 namespace psk {
 
+// Largest i in [0, n] with a[i] <= target (a[0] <= target taken for granted), by L neighbouring lanes: a round probes L places at
+// equal steps and leaves one L + 1-th.  Every lane of the L gets the result.
+template <int L>
+__device__ __forceinline__ int lanes_search(const int *__restrict__ a, int n, int target)
+{
+    const unsigned lane = threadIdx.x & (WAVE - 1), sub = lane % L;
+    unsigned lo = 0, hi = (unsigned)n;
+    while (__ballot(lo < hi)) {
+        const unsigned step = (hi - lo) / (L + 1) + 1, i = lo + (sub + 1) * step;
+        const bool below = lo < hi && i <= hi && a[i <= hi ? i : hi] <= target;
+        const unsigned long long all = __ballot(below);
+        const unsigned c = (unsigned)__popcll(L == WAVE ? all : (all >> (lane - sub)) & ((1ull << (L % WAVE)) - 1ull));
+        if (lo < hi) {
+            lo += c * step;
+            hi = min(hi, lo + step - 1);
+        }
+    }
+    return (int)lo;
+}
+
 // tile_fiber[t] = largest q in [0, nfibers] with pos_l[q] <= min(t*tile, nnz); tile_slice[t] = largest s in
-// [0, nslices] with pos_k[s] <= tile_fiber[t]: two chained binary searches (Section 6.2), one lane per entry.
+// [0, nslices] with pos_k[s] <= tile_fiber[t]: two chained searches (Section 6.2), L lanes per entry.  Bound by the chain of dependent
+// loads: 4 M fibers in 500 000 slices take 41 of them one by one (a lane per entry); see the launcher for what more lanes give.
+template <int L>
 __global__ __launch_bounds__(256) void k_partition_csf3(int nslices, int nfibers, int nnz,
                                                         const int *__restrict__ pos_k,
                                                         const int *__restrict__ pos_l, int tile, int ntiles,
                                                         int *__restrict__ tile_slice,
                                                         int *__restrict__ tile_fiber)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t > ntiles) return;
+    const long long g = ((long long)blockIdx.x * 256 + threadIdx.x) / L;
+    const int t = g < ntiles ? (int)g : ntiles;             // (lanes behind the last entry repeat it: the ballots need whole waves)
     const long long first = (long long)t * tile;
     const int target = first < nnz ? (int)first : nnz;
-    int lo = 0, hi = nfibers;
-    while (lo < hi) {
-        const int mid = lo + ((hi - lo + 1) >> 1);
-        if (pos_l[mid] <= target) lo = mid; else hi = mid - 1;
+    const int q = lanes_search<L>(pos_l, nfibers, target);
+    const int s = lanes_search<L>(pos_k, nslices, q);
+    if (threadIdx.x % L == 0 && g <= ntiles) {
+        tile_fiber[t] = q;
+        tile_slice[t] = s;
     }
-    const int q = lo;
-    lo = 0; hi = nslices;
-    while (lo < hi) {
-        const int mid = lo + ((hi - lo + 1) >> 1);
-        if (pos_k[mid] <= q) lo = mid; else hi = mid - 1;
-    }
-    tile_fiber[t] = q;
-    tile_slice[t] = lo;
 }
 
 hipError_t launch_partition_csf3(int32_t nslices, int32_t nfibers, int32_t nnz, const int32_t *pos_k,
@@ -42,8 +57,15 @@ hipError_t launch_partition_csf3(int32_t nslices, int32_t nfibers, int32_t nnz, 
                                  hipStream_t s)
 {
     const int ntiles = nnz <= 0 ? 0 : (int)(((int64_t)nnz + tile - 1) / tile);
-    PSK_LAUNCH(k_partition_csf3, dim3((ntiles + 1 + 255) / 256), dim3(256), 0, s, nslices, nfibers, nnz, pos_k,
-                       pos_l, tile, ntiles, tile_slice, tile_fiber);
+#define PSK_GO(L)                                                                                                 \
+    PSK_LAUNCH(k_partition_csf3<L>, dim3((unsigned)(((int64_t)(ntiles + 1) * L + 255) / 256)), dim3(256), 0, s, nslices, nfibers, \
+               nnz, pos_k, pos_l, tile, ntiles, tile_slice, tile_fiber)
+    // 666 tiles, 120 000 fibers 8.6 us with a lane per entry, 6.7 with 64 (16: 8.2); 2 843 and 500 000 9.8, 6.9; 9 096 and 1.6 M 10.5, 7.5;  22 788
+    // and 4 M 11.0, 17 (4 lanes 8.4, 8 9.2);  72 766 and 1.6 M 10.5, 36 (4: 7.2);  182 297 and 4 M 14.0 (4: 16.2)
+    if (ntiles <= 12000) PSK_GO(64);
+    else if (ntiles <= 100000) PSK_GO(4);
+    else PSK_GO(1);
+#undef PSK_GO
     return take_launch_status();
 }
 
