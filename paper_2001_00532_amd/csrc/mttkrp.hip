@@ -6,7 +6,7 @@
 // above the cut the same way it tracks the row of a CSR matrix -- here two levels, fiber and slice.
 #include "psk_dev.h"
 #include "psk_internal.h"
-#include <type_traits>
+
 
 namespace psk {
 
@@ -343,63 +343,35 @@ __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const 
     if (straddle) finalize(r1);
 }
 
-// j > 16: a lane owns four adjacent columns and the 64/G lanes of a group take a chunk of consecutive leaves for themselves.
-// A group walks its leaves one after the other, with its own open fiber and open slice, so nothing is exchanged between
-// groups; in one step the wave's groups fetch G rows of D with one 16-byte load per lane.  The first and the last open
-// segment of every group go to records that wave 0 chains in position order at the end.  blockIdx.y walks chunks of
-// 256/G columns.  (Chunks of 32 columns for j = 64, so that the L2s hold half of D at a time, gained nothing: 1694 us at
-// D = 25.6 MB, the halves of D's rows share the cache sets.)
+// j >= 4: a lane owns four adjacent columns and each group of 64/G lanes walks a run of consecutive leaves of its own, with its own
+// open fiber and open slice.  A leaf closes where its fiber ends or its group's run does (marked in the staged leaf itself, so
+// nothing is written per leaf of a fiber): there the fiber's sum is multiplied by its C row, which is requested with the D rows.  The
+// groups of a wave meet in one segmented sum at the end, two records per wave are chained in position order.  blockIdx.y
+// walks chunks of 256/G columns.
+// Bound by the L2: a row of D that lies there costs 4.0 ps per 128 bytes on the whole chip; rows from memory come at the fabric's 7.5
+// TB/s.  What it replaces (k_mttkrp_groups: a record per group, up to 64 of them chained one after the other; single columns per
+// lane for j <= 16) and this kernel, us with all launches: 5.8 M leaves, D of 20 000 rows, j = 6 105 -> 59, 16 125 -> 62, 24 127 -> 82, 64 157 -> 129,
+// 96 248 -> 187;  1.4 M leaves, j = 12 64 -> 26, 64 60 -> 48;  0.2 M, j = 64 54 -> 28.
+// Sums of leaves: even and odd ones apart, groups and records in fp64 (errors, j = 16 1.49e-7 -> 0.82e-7 of the result, 64 1.69 -> 1.25, 200 2.68 ->
+// 1.95).
 // SMALL: byte offsets into C and D fit 32 bits.
-template <bool SMALL> struct OffT;
-template <> struct OffT<true> { typedef unsigned type; };
-template <> struct OffT<false> { typedef unsigned long long type; };
-
-// f(0), f(1), ... f(N - 1) with the index as a constant
-template <int N, typename F, int... I>
-__device__ __forceinline__ void for_each_index_(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, typename F>
-__device__ __forceinline__ void for_each_index(F f) { for_each_index_<N>(f, std::make_integer_sequence<int, N>{}); }
-
-// The value of lane J of every group of GW = 8 or 16 lanes, in all lanes of the group (swizzle of 32 lanes: keep the group's
-// bits, set the others to J).
-template <int GW, int J>
-__device__ __forceinline__ unsigned group_bcast(unsigned v)
-{
-    static_assert(GW == 8 || GW == 16, "group width");
-    return (unsigned)__builtin_amdgcn_ds_swizzle((int)v, (J << 5) | (0x1f & ~(GW - 1)));
-}
-template <int GW, int J>
-__device__ __forceinline__ float group_bcast(float v)
-{
-    return __builtin_bit_cast(float, group_bcast<GW, J>(__builtin_bit_cast(unsigned, v)));
-}
-template <int GW, int J>
-__device__ __forceinline__ unsigned long long group_bcast(unsigned long long v)
-{
-    return ((unsigned long long)group_bcast<GW, J>((unsigned)(v >> 32)) << 32) | group_bcast<GW, J>((unsigned)v);
-}
-
 template <int G, bool SMALL>
-__global__ __launch_bounds__(256) void k_mttkrp_groups(int nslices, int nnz, const int *__restrict__ crd_i,
-                                                       const int *__restrict__ pos_k,
-                                                       const int *__restrict__ crd_k,
-                                                       const int *__restrict__ pos_l,
-                                                       const int *__restrict__ crd_l,
-                                                       const float *__restrict__ vals,
-                                                       const float *__restrict__ C, long long ldc,
-                                                       const float *__restrict__ D, long long ldd, int jdim,
-                                                       float *__restrict__ A, long long lda,
-                                                       const int *__restrict__ tile_slice,
-                                                       const int *__restrict__ tile_fiber,
-                                                       int *__restrict__ carry_row,
-                                                       float *__restrict__ carry_val, int ntiles, int T)
+__global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const int *__restrict__ crd_i,
+                                                     const int *__restrict__ pos_k, const int *__restrict__ crd_k,
+                                                     const int *__restrict__ pos_l, const int *__restrict__ crd_l,
+                                                     const float *__restrict__ vals, const float *__restrict__ C, long long ldc,
+                                                     const float *__restrict__ D, long long ldd, int jdim,
+                                                     float *__restrict__ A, long long lda, const int *__restrict__ tile_slice,
+                                                     const int *__restrict__ tile_fiber, int *__restrict__ carry_row,
+                                                     float *__restrict__ carry_val, int ntiles, int T)
 {
-    constexpr int THREADS = 256, NW = THREADS / WAVE, GW = WAVE / G, NG = NW * G, LONGF = 32, U = 4;
-    extern __shared__ int smeta[];                // sflag[T], sk[T], long-fiber queue [3 * T / LONGF]
-    int *sflag = smeta, *sk = smeta + T, *slong = smeta + 2 * T;
-    __shared__ v4f srec[2 * NG][GW];
-    __shared__ int srec_row[2 * NG];              // -2 unused, -1 open segment, >= 0 slice that ended
-    __shared__ int nlong;
+    constexpr int THREADS = 256, NW = THREADS / WAVE, GW = WAVE / G, NG = NW * G, U = 4, LD = 8;
+    extern __shared__ int smem[];                 // per leaf: {D offset or l | closes, value}, k where it closes, slice that ends
+    int2 *const ent = reinterpret_cast<int2 *>(smem);
+    int *const kof = smem + 2 * (T + NG);
+    unsigned short *const send = reinterpret_cast<unsigned short *>(kof + T);
+    __shared__ double srec[2 * NW][GW][4];
+    __shared__ int srec_row[2 * NW];              // -2 unused, -1 open segment, >= 0 slice that ended
 
     const int t = xcd_tile(blockIdx.x, ntiles);
     if (t < 0) return;
@@ -412,11 +384,19 @@ __global__ __launch_bounds__(256) void k_mttkrp_groups(int nslices, int nnz, con
     const int col0 = (blockIdx.y * GW + gl) * 4;
     const bool active = col0 < jdim;
     const int col = col0 < jdim - 4 ? col0 : jdim - 4;      // the last lane shares columns with its neighbour, same values
+    // a run of leaves for each group, an odd number of places apart (the groups' reads hit different banks)
+    const int run = (cnt + NG - 1) / NG, step = run | 1;
+    const unsigned inv = 0xffffffffu / (unsigned)run + 1;            // i / run = i * inv / 2^32 for i < T
+    auto place = [&](int i) { return step == run ? i : i + (int)__umulhi((unsigned)i, inv); };
 
-    for (int i = tid; i < T; i += THREADS) { sflag[i] = -1; sk[i] = 0; }
-    if (tid < 2 * NG) srec_row[tid] = -2;
-    if (tid == 0) nlong = 0;
-
+    int l[LD];
+    float v[LD];
+    const buf_t lb = buffer_of(crd_l + t0, cnt * 4), vb = buffer_of(vals + t0, cnt * 4);
+#pragma unroll
+    for (int u = 0; u < LD; ++u) {                // (places behind the tile's end read as 0)
+        l[u] = __builtin_amdgcn_raw_buffer_load_b32(lb, tid * 4 + u * THREADS * 4, 0, BUFFER_NT);
+        v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vb, tid * 4 + u * THREADS * 4, 0, BUFFER_NT));
+    }
     const int r0 = tile_slice[t], r1 = tile_slice[t + 1];
     const int q0 = tile_fiber[t], q1 = tile_fiber[t + 1];
     const int leaf_r0 = pos_l[pos_k[r0]], leaf_r1 = pos_l[pos_k[r1]];   // first leaf of slices r0, r1
@@ -425,148 +405,154 @@ __global__ __launch_bounds__(256) void k_mttkrp_groups(int nslices, int nnz, con
     const bool straddle = leaf_r1 != t1;          // slice r1 continues into the next tile
     const int rend = straddle ? r1 + 1 : r1;
     const int qend = (pos_l[q1] != t1) ? q1 + 1 : q1;   // fibers with leaves in this tile: q0 .. qend-1
+    const bool near = rend - rbeg < 0xfffe;       // the slices' numbers fit 16 bits
+    for (int i = tid; i < T / 2; i += THREADS) reinterpret_cast<int *>(send)[i] = 0;
+    if (tid < 2 * NW) srec_row[tid] = -2;
     if (tid == 0 && blockIdx.y == 0 && !has_carry) carry_row[t] = -1;
-    auto store = [&](float *row, v4f v) { __builtin_nontemporal_store((v4f_u)v, reinterpret_cast<v4f_u *>(row + col)); };
+    auto store = [&](int r, v4f o) {
+        __builtin_nontemporal_store((v4f_u)o, reinterpret_cast<v4f_u *>(A + (long long)(crd_i ? crd_i[r] : r) * lda + col));
+    };
+#pragma unroll
+    for (int u = 0; u < LD; ++u) {
+        const int i = tid + u * THREADS;
+        if (i < cnt) ent[place(i)] = make_int2(SMALL ? (int)((unsigned)l[u] * (unsigned)ldd * 4u) : l[u], __builtin_bit_cast(int, v[u]));
+    }
     __syncthreads();
 
-    // ---- slice ends of this tile, zero rows for slices without leaves
+    // ---- a leaf closes where its fiber ends or its run does, and there needs the fiber's k
+    for (int q = q0 + tid; q < qend; q += THREADS) {
+        int lo = pos_l[q] - t0, hi = pos_l[q + 1] - t0;
+        const int kk = crd_k[q];
+        const bool ends = hi <= cnt;
+        lo = lo < 0 ? 0 : lo;
+        hi = hi > cnt ? cnt : hi;
+        if (lo >= hi) continue;
+        auto close = [&](int i) {
+            ent[place(i)].x |= SMALL ? 1 : (int)0x80000000u;
+            kof[i] = kk;
+        };
+        for (int b = (lo / run + 1) * run; b < hi; b += run) close(b - 1);
+        if (ends || hi == cnt) close(hi - 1);
+    }
+    // ---- slice ends, zero rows for slices without leaves
     for (int rb = rbeg + wave * WAVE; rb < rend; rb += THREADS) {
         const int r = rb + lane;
         const bool valid = r < rend;
         const int ps = valid ? pos_l[pos_k[r]] : 0, pe = valid ? pos_l[pos_k[r + 1]] : 1;
         if (valid && pe > ps) {
             const int e = pe - 1 - t0;
-            if (e >= 0 && e < cnt) sflag[e] = r;
+            if (e >= 0 && e < cnt) send[e] = (unsigned short)(near ? r - rbeg + 1 : 0xffff);
         }
         unsigned long long empty = __ballot(valid && pe == ps);
         while (empty) {
             const int j = __ffsll((long long)empty) - 1;
             empty &= empty - 1;
-            if (active && g == 0) store(A + (long long)(crd_i ? crd_i[rb + j] : rb + j) * lda, v4f{});
-        }
-    }
-    // ---- mode-k coordinate of every leaf of the tile
-    for (int q = q0 + tid; q < qend; q += THREADS) {
-        int lo = pos_l[q] - t0, hi = pos_l[q + 1] - t0;
-        lo = lo < 0 ? 0 : lo;
-        hi = hi > cnt ? cnt : hi;
-        const int kk = crd_k[q];
-        if (hi - lo < LONGF) {
-            for (int i = lo; i < hi; ++i) sk[i] = (i == hi - 1) ? ~kk : kk;
-        } else {
-            const int e = atomicAdd(&nlong, 1);
-            if (e < T / LONGF) { slong[3 * e] = kk; slong[3 * e + 1] = lo; slong[3 * e + 2] = hi; }
-        }
-    }
-    __syncthreads();
-    {
-        const int nl = nlong < T / LONGF ? nlong : T / LONGF;
-        for (int e = wave; e < nl; e += NW) {
-            const int kk = slong[3 * e], lo = slong[3 * e + 1], hi = slong[3 * e + 2];
-            for (int i = lo + lane; i < hi; i += WAVE) sk[i] = (i == hi - 1) ? ~kk : kk;
+            if (active && g == 0) store(rb + j, v4f{});
         }
     }
     __syncthreads();
 
-    // ---- the group's leaves.  A lane holds one leaf of its group's next GW; a step broadcasts the leaf's D offset and value
-    // inside the group.  Which leaves close a fiber is one ballot per GW leaves; the C row is requested where that happens,
-    // together with the D rows.  A group's last leaf closes its part of the open fiber.  FULL: every group has T / NG leaves.
-    const int gi = wave * G + g, per = (cnt + NG - 1) / NG;
-    const int gbeg = gi * per < cnt ? gi * per : cnt;
-    const int gend = gbeg + per < cnt ? gbeg + per : cnt;
-    v4f acc = {}, facc = {};                      // open slice, and sum of b * D(l, :) over the leaves of the open fiber
-    bool seen = false;
+    auto slice_at = [&](int i) -> int {           // the slice that ends at leaf i of the tile
+        if (near) return rbeg + send[i] - 1;
+        int lo = r0, hi = r1;                     // a long run of empty slices: max { r : pos_l[pos_k[r]] <= t0 + i }
+        while (lo < hi) {
+            const int mid = lo + ((hi - lo + 1) >> 1);
+            if (pos_l[pos_k[mid]] <= t0 + i) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
     const char *const Cb = reinterpret_cast<const char *>(C + col), *const Db = reinterpret_cast<const char *>(D + col);
-    typedef typename OffT<SMALL>::type off_t;
-    off_t l_n = 0;
-    float v_n = 0.0f;
-    auto fetch = [&](int b) {                     // the leaves b .. b + GW - 1 of the group, one per lane
-        l_n = 0;
-        v_n = 0.0f;
-        if (b + gl < per && gbeg + b + gl < gend) {
-            l_n = (off_t)ld_stream(crd_l + t0 + gbeg + b + gl) * (off_t)(ldd * 4);
-            v_n = ld_stream(vals + t0 + gbeg + b + gl);
+    auto row_of_D = [&](int x) -> v4f_u {
+        if constexpr (SMALL) return *reinterpret_cast<const v4f_u *>(Db + ((unsigned)x & ~1u));
+        else return *reinterpret_cast<const v4f_u *>(Db + (long long)(x & 0x7fffffff) * ldd * 4);
+    };
+    auto row_of_C = [&](int k) -> v4f_u {
+        if constexpr (SMALL) return *reinterpret_cast<const v4f_u *>(Cb + (unsigned)k * (unsigned)ldc * 4u);
+        else return *reinterpret_cast<const v4f_u *>(Cb + (long long)k * ldc * 4);
+    };
+    auto closes = [&](int x) -> bool { return SMALL ? (x & 1) != 0 : x < 0; };
+    const int gi = wave * G + g, j0 = gi * run, len = cnt - j0 < run ? cnt - j0 : run, first = gi * step;
+    float even[4] = {}, odd[4] = {};              // sum of b * D(l, :) over the leaves of the open fiber, even and odd ones
+    float acc[4] = {}, head[4] = {};              // open slice; the first slice that ended in this run, without what lies before
+    int hrow = -1;
+    auto walk = [&](int i, auto all) {            // U leaves; all: every group has them
+        v4f_u d[U], c[U];
+        int2 e[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool have = all() || i + u < len;
+            e[u] = ent[have ? first + i + u : 0];
+            d[u] = row_of_D(e[u].x);
+            if (have && closes(e[u].x)) c[u] = row_of_C(kof[j0 + i + u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool have = all() || i + u < len;
+            float(&to)[4] = u & 1 ? odd : even;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) to[q] = have ? fmaf(__builtin_bit_cast(float, e[u].y), d[u][q], to[q]) : to[q];
+            if (have && closes(e[u].x)) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc[q] = fmaf(c[u][q], even[q] + odd[q], acc[q]);
+                    even[q] = odd[q] = 0.0f;
+                }
+                if (send[j0 + i + u]) {
+                    const int r = slice_at(j0 + i + u);
+                    if (hrow < 0) {
+                        hrow = r;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) head[q] = acc[q];
+                    } else if (active) store(r, v4f{acc[0], acc[1], acc[2], acc[3]});
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[q] = 0.0f;
+                }
+            }
         }
     };
-    auto walk = [&](auto full) {
-        constexpr bool FULL = decltype(full)::value;
-        fetch(0);
-        for (int b = 0; b < per; b += GW) {
-            const off_t l_l = l_n;
-            const float v_l = v_n;
-            const int mine = gbeg + b + gl;
-            const bool here = FULL || (b + gl < per && mine < gend);
-            const int k_l = here ? sk[mine] : 0;
-            const unsigned long long all = __ballot(here && (k_l < 0 || mine == gend - 1));
-            const unsigned closes = (unsigned)(all >> (g * GW));        // bit j: leaf b + j of the group closes
-            fetch(b + GW);
-            const int n = FULL ? GW : (per - b < GW ? per - b : GW);
-            for_each_index<GW / U>([&](auto part) {
-                constexpr int J0 = decltype(part)::value * U;
-                if (!FULL && J0 >= n) return;
-                v4f_u c[U], d[U];
-                float a[U];
-                int ke[U];
-                for_each_index<U>([&](auto uu) {
-                    constexpr int u = decltype(uu)::value, j = J0 + u;
-                    a[u] = group_bcast<GW, j>(v_l);
-                    d[u] = *reinterpret_cast<const v4f_u *>(Db + group_bcast<GW, j>(l_l));
-                    ke[u] = 0;
-                    if ((closes >> j) & 1u) {
-                        ke[u] = sk[gbeg + b + j];
-                        c[u] = *reinterpret_cast<const v4f_u *>(Cb + (off_t)(ke[u] < 0 ? ~ke[u] : ke[u]) * (off_t)(ldc * 4));
-                    }
-                });
-                for_each_index<U>([&](auto uu) {
-                    constexpr int u = decltype(uu)::value, j = J0 + u;
-                    if (FULL || (j < n && gbeg + b + j < gend)) {
+    int i = 0;
+    for (; i + U <= run && (long long)cnt >= (long long)(NG - 1) * run + i + U; i += U) walk(i, [] { return true; });
+    for (; i < run; i += U) walk(i, [] { return false; });
+
+    // ---- what the groups before this one leave of its first slice
+    {
+        double x[4];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) facc[v] = fmaf(a[u], d[u][v], facc[v]);
-                    }
-                    if ((closes >> j) & 1u) {
+        for (int q = 0; q < 4; ++q) x[q] = (double)acc[q];
+        const unsigned long long has = __ballot(hrow >= 0);
+        group_segscan<GW, GW>(x, has, g);
+        const int lead = has ? __ffsll((long long)has) - 1 : WAVE, lead_g = lead / GW;      // the first group with an end
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) { acc[v] = fmaf(c[u][v], facc[v], acc[v]); facc[v] = 0.0f; }
-                        const int f = ke[u] < 0 ? sflag[gbeg + b + j] : -1;
-                        if (f >= 0) {             // ... and the slice
-                            if (!seen) {
-                                seen = true;
-                                srec[2 * gi][gl] = acc;
-                                if (gl == 0) srec_row[2 * gi] = f;
-                            } else if (active) {
-                                store(A + (long long)(crd_i ? crd_i[f] : f) * lda, acc);
-                            }
-                            acc = v4f{};
-                        }
-                    }
-                });
-            });
+        for (int q = 0; q < 4; ++q) {
+            const double p = __shfl_up(x[q], GW & (WAVE - 1), WAVE);
+            const double h = (double)head[q] + (g == 0 ? 0.0 : p);
+            if (has && g == lead_g) srec[2 * wave][gl][q] = h;
+            else head[q] = (float)h;
+            if (g == G - 1) srec[2 * wave + (has ? 1 : 0)][gl][q] = x[q];
         }
-    };
-    if (cnt == T && per % GW == 0) walk(std::true_type{});
-    else walk(std::false_type{});
-    if (gbeg < gend) {
-        const int slot = seen ? 2 * gi + 1 : 2 * gi;
-        srec[slot][gl] = acc;
-        if (gl == 0) srec_row[slot] = -1;
+        if (hrow >= 0 && g != lead_g && active) store(hrow, v4f{head[0], head[1], head[2], head[3]});
+        if (has && lane == lead) srec_row[2 * wave] = hrow;
+        if (lane == 0 && wave * G * run < cnt) srec_row[2 * wave + (has ? 1 : 0)] = -1;
     }
     __syncthreads();
 
     // ---- chain the records (wave 0, group 0)
     if (wave != 0 || g != 0) return;
-    v4f run = {};
+    double sum[4] = {};
     auto finalize = [&](int r) {
+        const v4f o = {(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]};
         if (has_carry && r == r0) {
-            if (active) *reinterpret_cast<v4f_u *>(carry_val + (long long)t * jdim + col) = run;
+            if (active) *reinterpret_cast<v4f_u *>(carry_val + (long long)t * jdim + col) = o;
             if (lane == 0 && blockIdx.y == 0) carry_row[t] = r;
-        } else if (active) {
-            store(A + (long long)(crd_i ? crd_i[r] : r) * lda, run);
-        }
-        run = v4f{};
+        } else if (active) store(r, o);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum[q] = 0.0;
     };
-    for (int rec = 0; rec < 2 * NG; ++rec) {
+    for (int rec = 0; rec < 2 * NW; ++rec) {
         const int code = srec_row[rec];
         if (code == -2) continue;
-        run += srec[rec][gl];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum[q] += srec[rec][gl][q];
         if (code >= 0) finalize(code);
     }
     if (straddle) finalize(r1);
@@ -590,42 +576,38 @@ hipError_t launch_mttkrp_main(int64_t dim_k, int64_t dim_l, int32_t nslices, int
     const int nx = xcd_grid(ntiles);
     const int64_t most = 0xffffffffll / 4;
     const bool small = ldd <= most / (dim_l > 0 ? dim_l : 1) && ldc <= most / (dim_k > 0 ? dim_k : 1);
-#define PSK_GROUPS(G)                                                                                           \
-    do {                                                                                                         \
-        if (small) PSK_GO((k_mttkrp_groups<G, true>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                  \
-        else PSK_GO((k_mttkrp_groups<G, false>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                       \
-    } while (0)
     const uintptr_t al = reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D) | reinterpret_cast<uintptr_t>(A);
     int vec = 1;                                  // adjacent columns that a lane of the wide kernel can load at once
     if (j > 64 && j % 2 == 0 && ldc % 2 == 0 && ldd % 2 == 0 && lda % 2 == 0 && (al & 7) == 0) vec = 2;
     if (j > 128 && j % 4 == 0 && ldc % 4 == 0 && ldd % 4 == 0 && lda % 4 == 0 && (al & 15) == 0) vec = 4;
     const bool lines = ldd % 32 == 0 && (reinterpret_cast<uintptr_t>(D) & 127) == 0;      // rows of D begin 128-byte lines
-    // Groups of four columns per lane or the wide kernel (VEC columns per lane; us groups / wide):
-    //   j <= 16: wide (one column per lane in 8 or 4 groups); 16: 379 / 353 at 23 M leaves
-    //   j <= 64: groups, 1.1 to 1.8 times as fast (0.4 to 9 M leaves: 24 39 / 70, 64 52 / 76;  D 12.8 MB, 9.4 M leaves, 64: 314 / 328) ...
-    //   big: ... but where neither D fits a die's L2 nor the leaves leave room for it in the memory-side cache, both move D's rows
-    //     at the fabric's rate and the wide kernel asks for less at once (46.9 M leaves, 100 000 rows of D: 24 1066 / 994, 28 1288 /
-    //     1148, 44 1666 / 1633, 64 1639 / 1608;  D 8.6 MB: 36 1145 / 1174), rows of up to 32 columns that fill lines excepted (32: 872 / 969)
-    //   j > 64: a group walks A once per 64 columns and neighbouring chunks share a line of every row that does not begin one:
-    //     few workgroups either way (0.9 M leaves: 66 65 / 91, 128 68 / 91;  0.4 M: 200 67 / 90;  1.4 M, 90 000 rows: 96 132 / 108): groups;
-    //     many, rows that begin lines (23 M: 96 1110 / 1135, 128 1407 / 1559, 256 2773 / 3400;  3.2 M: 128 267 / 277;  2.1 M: 128 121 /
-    //     114, 160 161 / 133, 256 210 / 240): groups;
-    //     otherwise wide (23 M: 66 1361 / 1011, 86 1652 / 1371, 112 1619 / 1488, 200 3442 / 2846) where its lanes can own two columns
-    //     (87 1649 / 1872).
-    const bool big = nnz >= (1 << 24) && 4 * dim_l * j > (int64_t(9) << 20);
-    const int64_t groups = (int64_t)ntiles * ((j + 63) / 64);        // workgroups, above 64 columns
-    if (j <= 8) PSK_GO((k_mttkrp_pos<1, 8>), dim3(nx));
-    else if (j <= 16) PSK_GO((k_mttkrp_pos<1, 4>), dim3(nx));
-    else if (j <= 32) {
-        if (big && !lines) PSK_GO((k_mttkrp_pos<1, 2>), dim3(nx));
-        else PSK_GROUPS(8);
-    } else if (j <= 64) {
-        if (big) PSK_GO((k_mttkrp_pos<1, 1>), dim3(nx));
-        else PSK_GROUPS(4);
-    } else if (vec == 1 || groups <= 1100 || (lines && groups >= 3100)) PSK_GROUPS(4);
+#define PSK_RUNS(G)                                                                                             \
+    do {                                                                                                         \
+        const size_t lds = ((size_t)2 * (tile + 4 * G) + tile) * 4 + (size_t)tile * 2;                           \
+        if (small) PSK_GO((k_mttkrp_runs<G, true>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                    \
+        else PSK_GO((k_mttkrp_runs<G, false>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                         \
+    } while (0)
+    // Columns per group of lanes (us, all launches):
+    //   few tiles: narrow chunks, so that the runs are short.  100 tiles, j = 24 16 columns 25, 32 31;  64: 16 29, 32 35, 64 46.  357 tiles, 24: 16 27, 32 31;
+    //     48: 16 35, 32 37, 64 48;  64: 16 48, 32 38, 64 49;  128: 32 71, 64 61, 128 74.  666 tiles, 24: 16 42, 32 32;  64: 32 55, 64 49;  128: 64 81, 128 70
+    //   halves: rows of D that begin 128-byte lines and a D above the L2's size: 32 columns, so that the L2s hold the rows of one
+    //     chunk at a time.  D 9.8 MB, 2.9 M leaves, 64: 129 -> 90;  12 MB, 18.6 M, 64: 64 columns 557, 32 425;  24 MB, 46.7 M, 64: 1646, 1416, 128: 49 MB 3530,
+    //     2969;  but D 4.9 MB, 5.8 M: 129, 132
+    //   more than 128 columns (A would be walked twice): the wide kernel (60 000 slices, 200 columns: 359 against 371 in 256 columns), unless
+    //     halves (160: 266 -> 196, 256: 374 -> 296), its lanes cannot own two columns, or tiles are few (100: 200 60 -> 45)
+    const bool halves = lines && 4 * dim_l * j > (int64_t(6) << 20);
+    if (j >= 4 && (j <= 128 || vec == 1 || halves || ntiles <= 256)) {
+        if (j <= 8) PSK_RUNS(32);
+        else if (j <= 16 || (ntiles <= 450 && j <= 48) || (ntiles <= 200 && j <= 128)) PSK_RUNS(16);
+        else if (ntiles <= 450 && j > 96 && j <= 128) PSK_RUNS(4);
+        else if (j <= 32 || halves || ntiles <= 450) PSK_RUNS(8);
+        else if (j <= 64) PSK_RUNS(4);
+        else if (j <= 128) PSK_RUNS(2);
+        else PSK_RUNS(1);
+    } else if (j < 4) PSK_GO((k_mttkrp_pos<1, 8>), dim3(nx));
     else if (vec == 2) PSK_GO((k_mttkrp_pos<2, 1>), dim3(nx, (j + 127) / 128));
     else PSK_GO((k_mttkrp_pos<4, 1>), dim3(nx, (j + 255) / 256));
-#undef PSK_GROUPS
+#undef PSK_RUNS
 #undef PSK_GO
     return take_launch_status();
 }

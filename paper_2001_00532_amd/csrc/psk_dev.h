@@ -198,6 +198,44 @@ __device__ __forceinline__ TileSpan get_record(const int *__restrict__ records, 
     return s;
 }
 
+// A range of memory for buffer loads: reads behind `bytes` return 0.
+typedef __amdgpu_buffer_rsrc_t buf_t;
+constexpr int BUFFER_NT = 2;                      // non-temporal
+__device__ __forceinline__ buf_t buffer_of(const void *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+
+// Orders a wave's own reads and writes of LDS.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Sums over the groups of GW lanes of a wave, in fp64: every lane receives the sum of the lanes with its place in a group; and inside
+// segments: inclusive sums over groups, a lane of `heads` = its group starts a segment.
+template <int GW>
+__device__ __forceinline__ double group_sum(double v)
+{
+#pragma unroll
+    for (int d = GW; d < WAVE; d <<= 1) v += __shfl_xor(v, d, WAVE);
+    return v;
+}
+template <int GW, int D>
+__device__ __forceinline__ void group_segscan(double (&x)[4], unsigned long long heads, int g)
+{
+    if constexpr (D < WAVE) {
+        const bool take = g >= D / GW && ((heads >> (threadIdx.x & (WAVE - 1))) & 1) == 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double p = __shfl_up(x[q], D, WAVE);
+            x[q] += take ? p : 0.0;
+        }
+        group_segscan<GW, 2 * D>(x, heads | (heads << D), g);
+    }
+}
+
 // ---- per-workgroup trace (only in the instrumented build, -DPSK_CU_TRACE): every workgroup of a traced kernel
 // records its start and end on the 100 MHz wall clock and the compute unit it ran on (HW_ID: cu, sh, se;
 // XCC_ID: die) into a caller-supplied buffer of 3 x 64 bits per workgroup, from which the host forms each
