@@ -514,22 +514,22 @@ hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const
 
 hipError_t launch_spmm_csr_wave(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
-                                int32_t tile, int32_t over, const Workspace &w, hipStream_t s, const int32_t *records)
+                                int32_t tile, int32_t over, int32_t chunk, const Workspace &w, hipStream_t s, const int32_t *records)
 {
     if (nnz <= 0) return hipSuccess;
     if (k < 4) return hipErrorInvalidValue;
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
+    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4);
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? cols : 1);
-    const dim3 grid((unsigned)xcd_grid((ntiles + 3) / 4), (unsigned)((k + 255) / 256));
 #define PSK_GO_(GG, SM)                                                                                           \
-    PSK_LAUNCH((k_spmm_wave<GG, SM>), grid, dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
+    PSK_LAUNCH((k_spmm_wave<GG, SM>), dim3(nx, (unsigned)((k + 256 / GG - 1) / (256 / GG))), dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
                (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, records)
 #define PSK_GO(GG) do { if (small) PSK_GO_(GG, true); else PSK_GO_(GG, false); } while (0)
-    if (k <= 8) PSK_GO(32);
-    else if (k <= 16) PSK_GO(16);
-    else if (k <= 32) PSK_GO(8);
-    else if (k <= 64) PSK_GO(4);
-    else if (k <= 128) PSK_GO(2);
+    if (chunk <= 8) PSK_GO(32);
+    else if (chunk <= 16) PSK_GO(16);
+    else if (chunk <= 32) PSK_GO(8);
+    else if (chunk <= 64) PSK_GO(4);
+    else if (chunk <= 128) PSK_GO(2);
     else PSK_GO(1);
 #undef PSK_GO
 #undef PSK_GO_

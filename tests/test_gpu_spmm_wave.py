@@ -90,3 +90,15 @@ def test_nan_and_inf_reach_only_their_rows(k, pattern):
     fin = np.isfinite(ref) & np.isfinite(mag)
     assert (got[~fin & ~np.isnan(ref)] == ref[~fin & ~np.isnan(ref)]).all()
     assert (np.abs(got[fin] - ref[fin]) <= 1e-5 * mag[fin] + 1e-30).all()
+
+
+@pytest.mark.parametrize("k,cols,pattern", [(64, 22_000, "short"), (96, 15_000, "middle"), (128, 12_000, "long"), (128, 30_000, "short"),
+                                            (256, 9_000, "middle"), (320, 12_000, "short")])
+def test_columns_in_chunks(k, cols, pattern):
+    """Rows of B that begin 128-byte lines and a B above the L2's size; long and short rows."""
+    rng = np.random.default_rng(k)
+    A = wl.csr_from_lengths(rows_of(pattern, rng, NNZ + 1000), cols, seed=k)
+    Bh = wl.dense_uniform(cols * k, 3, wl.S_B).reshape(cols, k)
+    ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh)
+    ok, worst = oracle.within_tolerance(product(A, cols, Bh, k, 256), ref, mag)
+    assert ok, "%.3g of the bar" % worst
