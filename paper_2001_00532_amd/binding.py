@@ -53,6 +53,8 @@ class PskError(RuntimeError):
 
 _lib = None
 _lib_path = LIB_PATH
+_marshal = None                                  # the native side of a call (csrc/marshal.cpp)
+_spmv_address = {}
 
 
 def use_instrumented_library() -> None:
@@ -66,7 +68,7 @@ def use_instrumented_library() -> None:
 
 def lib() -> ctypes.CDLL:
     """The loaded library.  Raises if it has not been built (python -m paper_2001_00532_amd.build)."""
-    global _lib
+    global _lib, _marshal, _ptr
     if _lib is None:
         if not os.path.exists(_lib_path):
             raise RuntimeError("%s is not built; run `python -m paper_2001_00532_amd.build`" % os.path.basename(_lib_path))
@@ -135,11 +137,20 @@ def lib() -> ctypes.CDLL:
         L.psk_spmv_csr_rowsplit.restype = ci
         L.psk_spmm_csr_rowsplit.argtypes = [i64, i64, i64, p, p, p, p, i32, i64, p, i64, p]
         L.psk_spmm_csr_rowsplit.restype = ci
+        if _marshal is None:
+            try:
+                from . import _marshal as native
+            except ImportError as e:
+                raise RuntimeError("_marshal.so is not built; run `python -m paper_2001_00532_amd.build`") from e
+            native.use(_ptr_checked, _stream)
+            _marshal, _ptr = native, native.ptr
+        for f64, f in ((0, L.psk_spmv_csr), (1, L.psk_spmv_csr_f64)):
+            _spmv_address[f64] = ctypes.cast(f, ctypes.c_void_p).value
         _lib = L
     return _lib
 
 
-def _ptr(t, dtype=None):
+def _ptr_checked(t, dtype=None):
     """Device address of a tensor (None -> NULL).  Checks device, dtype and contiguity of the last dim.  (An int: ctypes
     converts it by the declared argument types; making a c_void_p of it first costs as much as the checks.)"""
     if t is None:
@@ -151,6 +162,9 @@ def _ptr(t, dtype=None):
     if t.stride(-1) != 1 and t.numel():
         raise ValueError("innermost dimension must be contiguous")
     return t.data_ptr()
+
+
+_ptr = _ptr_checked                              # lib() puts the native one here
 
 
 def _stream(stream=None):
@@ -290,10 +304,15 @@ def psk_spmv_csr(rows, cols, nnz, pos, crd, vals, x, y, tile=0, col_passes=1, ph
     if ws is None:
         _temporary_ws_ok(phases, "psk_spmv_csr")
         ws = _csr_ws(rows, nnz, tile, pos.device, stream)
-    st = lib().psk_spmv_csr(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
-                            _ptr(vals, torch.float32), _ptr(x, torch.float32), _ptr(y, torch.float32), int(tile),
-                            int(col_passes), int(phases), _ptr(ws), ws.numel(), _stream(stream))
-    _check(st, "psk_spmv_csr")
+    L = _lib or lib()
+    st = _marshal.spmv(0, _spmv_address[0], rows, cols, nnz, pos, crd, vals, x, y, tile, col_passes, phases, ws,
+                       None if stream is None else stream.cuda_stream)
+    if st is None:                               # something that is not a plain tensor
+        st = L.psk_spmv_csr(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
+                                _ptr(vals, torch.float32), _ptr(x, torch.float32), _ptr(y, torch.float32), int(tile),
+                                int(col_passes), int(phases), _ptr(ws), ws.numel(), _stream(stream))
+    if st:
+        _check(st, "psk_spmv_csr")
     return y
 
 
@@ -418,10 +437,15 @@ def psk_spmv_csr_f64(rows, cols, nnz, pos, crd, vals, x, y, tile=0, col_passes=1
     if ws is None:
         _temporary_ws_ok(phases, "psk_spmv_csr_f64")
         ws = workspace(PSK_OP_SPMV_CSR_F64, rows, nnz, tile=tile, device=pos.device, stream=stream)
-    st = lib().psk_spmv_csr_f64(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
-                                _ptr(vals, torch.float64), _ptr(x, torch.float64), _ptr(y, torch.float64),
-                                int(tile), int(col_passes), int(phases), _ptr(ws), ws.numel(), _stream(stream))
-    _check(st, "psk_spmv_csr_f64")
+    L = _lib or lib()
+    st = _marshal.spmv(1, _spmv_address[1], rows, cols, nnz, pos, crd, vals, x, y, tile, col_passes, phases, ws,
+                       None if stream is None else stream.cuda_stream)
+    if st is None:                               # something that is not a plain tensor
+        st = L.psk_spmv_csr_f64(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
+                                    _ptr(vals, torch.float64), _ptr(x, torch.float64), _ptr(y, torch.float64),
+                                    int(tile), int(col_passes), int(phases), _ptr(ws), ws.numel(), _stream(stream))
+    if st:
+        _check(st, "psk_spmv_csr_f64")
     return y
 
 

@@ -1,4 +1,5 @@
-"""Builds libpsk.so (the C-ABI library) from csrc/*.hip with hipcc for gfx950.
+"""Builds libpsk.so (the C-ABI library) from csrc/*.hip with hipcc for gfx950, and _marshal.so (the Python side of a call) from
+csrc/marshal.cpp with the host compiler.
 
 Run as ``python -m paper_2001_00532_amd.build``.  Objects go to ``_build/`` (ignored by git), the
 library lands next to this file so that it travels with the source tree.
@@ -17,6 +18,8 @@ OBJDIR = os.path.join(HERE, "_build")
 # the instrumented build (-DPSK_CU_TRACE: per-workgroup start/end/CU records, see psk_cu_trace_set)
 OUT_TRACE = os.path.join(HERE, "libpsk_trace.so")
 OBJDIR_TRACE = os.path.join(HERE, "_build_trace")
+
+OUT_MARSHAL = os.path.join(HERE, "_marshal.so")
 
 SOURCES = ["api.hip", "partition.hip", "spmv_csr.hip", "spmm.hip", "spmv_bcsr.hip", "mttkrp.hip", "spmv_csr_f64.hip", "spmv_csr_divide.hip", "spmv_bcsr_g.hip", "spmm_narrow.hip", "slab.hip", "api_slab.hip", "calibrate.hip"]
 HEADERS = ["psk_dev.h", "psk_internal.h", os.path.join("..", "..", "include", "psk.h")]
@@ -53,6 +56,8 @@ def stale() -> bool:
     if not os.path.exists(OUT):
         return True
     t = os.path.getmtime(OUT)
+    if not os.path.exists(OUT_MARSHAL) or os.path.getmtime(os.path.join(CSRC, "marshal.cpp")) > os.path.getmtime(OUT_MARSHAL):
+        return True
     deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS]
     return any(os.path.getmtime(d) > t for d in deps)
 
@@ -63,6 +68,21 @@ def _link(objs, out: str) -> None:
     os.replace(out + ".tmp", out)
 
 
+def _marshal() -> None:
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = [a for p in include_paths() + [sysconfig.get_paths()["include"]] for a in ("-isystem", p)]
+    abi = "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", abi, *inc,
+                           os.path.join(CSRC, "marshal.cpp"), "-o", OUT_MARSHAL + ".tmp", "-L" + lib, "-Wl,-rpath," + lib,
+                           "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    os.replace(OUT_MARSHAL + ".tmp", OUT_MARSHAL)
+
+
 def build(force: bool = True) -> str:
     """Compile every kernel file and link libpsk.so and the instrumented libpsk_trace.so.  With force=False only
     when sources are newer."""
@@ -71,10 +91,12 @@ def build(force: bool = True) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     os.makedirs(OBJDIR_TRACE, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        host = ex.submit(_marshal)
         plain = [ex.submit(_compile, s) for s in SOURCES]
         traced = [ex.submit(_compile, s, OBJDIR_TRACE, ("-DPSK_CU_TRACE",)) for s in SOURCES]
         objs = [f.result() for f in plain]
         objs_t = [f.result() for f in traced]
+        host.result()
     _link(objs, OUT)
     _link(objs_t, OUT_TRACE)
     return OUT
