@@ -21,7 +21,7 @@ OBJDIR_TRACE = os.path.join(HERE, "_build_trace")
 
 OUT_MARSHAL = os.path.join(HERE, "_marshal.so")
 
-SOURCES = ["api.hip", "partition.hip", "spmv_csr.hip", "spmm.hip", "spmv_bcsr.hip", "mttkrp.hip", "spmv_csr_f64.hip", "spmv_csr_divide.hip", "spmv_bcsr_g.hip", "spmm_narrow.hip", "slab.hip", "api_slab.hip", "calibrate.hip"]
+SOURCES = ["api.hip", "partition.hip", "spmv_csr.hip", "spmm.hip", "spmv_bcsr.hip", "mttkrp.hip", "spmv_csr_f64.hip", "spmv_csr_divide.hip", "spmv_bcsr_g.hip", "spmm_narrow.hip", "spmm_blocks.hip", "slab.hip", "api_slab.hip", "calibrate.hip"]
 HEADERS = ["psk_dev.h", "psk_internal.h", os.path.join("..", "..", "include", "psk.h")]
 
 FLAGS = [

@@ -565,13 +565,13 @@ int psk_spmm_bcsr(int64_t brows, int64_t bcols, int64_t nblocks, int32_t bs, con
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int32_t ntiles = (int32_t)psk_num_tiles(nblocks, tile);
     hipError_t e = hipSuccess;
-    const int search = searches(phases, ntiles);
+    const int search = spmm_blocks_by_wave(bs, bcols, nblocks, k, tile) ? 0 : searches(phases, ntiles);
     if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(brows, nblocks, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         if (ntiles == 0) {
             e = launch_fill_zero_2d(C, brows * bs, k, ldc, s);
         } else {
-            e = launch_spmm_bcsr_main(bs, (int32_t)brows, (int32_t)nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s, search);
+            e = launch_spmm_bcsr_main(bs, (int32_t)brows, (int32_t)bcols, (int32_t)nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, ws, s, search);
         }
     }
     if ((phases & PSK_PHASE_FIXUP) && e == hipSuccess)

@@ -222,15 +222,15 @@ __device__ __forceinline__ double group_sum(double v)
     for (int d = GW; d < WAVE; d <<= 1) v += __shfl_xor(v, d, WAVE);
     return v;
 }
-template <int GW, int D>
-__device__ __forceinline__ void group_segscan(double (&x)[4], unsigned long long heads, int g)
+template <int GW, int D, typename T>
+__device__ __forceinline__ void group_segscan(T (&x)[4], unsigned long long heads, int g)
 {
     if constexpr (D < WAVE) {
         const bool take = g >= D / GW && ((heads >> (threadIdx.x & (WAVE - 1))) & 1) == 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const double p = __shfl_up(x[q], D, WAVE);
-            x[q] += take ? p : 0.0;
+            const T p = __shfl_up(x[q], D, WAVE);
+            x[q] += take ? p : T(0);
         }
         group_segscan<GW, 2 * D>(x, heads | (heads << D), g);
     }

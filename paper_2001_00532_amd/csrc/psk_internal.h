@@ -178,7 +178,20 @@ hipError_t launch_spmv_bcsr_g_main(int32_t bs, int32_t brows, int32_t nblocks, c
 hipError_t launch_spmv_bcsr4_main(int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *x, float *y, int32_t tile,
                                   const Workspace &w, hipStream_t s, int search);
-hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
+// Blocks: a wave per tile (spmm_blocks.hip, reads the table) or a workgroup, whose 64 lanes own one column each or more.  us workgroup / wave:
+//   k = 8, 4 x 4, 1.8 M blocks 244 / 64;  8 x 8, 0.9 M 386 / 92;  2 x 2, 3.6 M 263 / 79;  k = 32 246 / 165, 400 / 196, 268 / 151;  48 262 / 227, 405 / 298, 271 / 224;
+//   64: B 220 MB 300 / 308, 414 / 340, 290 / 307;  20 MB, 0.16 M blocks 34.8 / 31.5, 2 x 2, 0.8 M 67 / 59;  66 and more: 345 / 340, 517 / 511, 352 / 354, 200 921 / 1090
+//   few tiles, where the workgroups' kernel searches its rows and saves a launch: 4 x 4, k = 8, 62 tiles 12.6 / 10.9;  8 x 8, 32 20.1 / 17.0; but 48 20.0 / 24.0
+//     (4 x 4 12.9 / 13.8) and 2 x 2 9.6 / 11.0, up to 500 tiles 28.1 / 31.6 (13.9 / 14.1, 10.2 / 10.8), with 875 40.5 / 32.7 (19.3 / 16.2, 12.5 / 10.6)
+inline bool spmm_blocks_by_wave(int32_t bs, int64_t bcols, int64_t nblocks, int32_t k, int32_t tile)
+{
+    const int64_t ntiles = (nblocks + tile - 1) / tile;
+    return k >= 4 && (k <= 48 || (k <= 64 && (bs == 8 || bcols * bs * k <= (int64_t(24) << 18)))) && ntiles >= (bs >= 4 && k <= 32 ? 1 : 600);
+}
+hipError_t launch_spmm_bcsr_wave(int32_t bs, int32_t brows, int32_t bcols, int32_t nblocks, const int32_t *pos, const int32_t *crd,
+                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc, int32_t tile,
+                                 int32_t over, const Workspace &w, hipStream_t s);
+hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t bcols, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
                                   int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search);
 

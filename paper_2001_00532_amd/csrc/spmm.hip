@@ -365,11 +365,13 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
 }
 
-hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t nblocks, const int32_t *pos, const int32_t *crd,
+hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t bcols, int32_t nblocks, const int32_t *pos, const int32_t *crd,
                                  const float *vals, const float *B, int32_t k, int64_t ldb, float *C,
                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search)
 {
     const int32_t over = spmm_overhang_blocks(brows, nblocks, tile);
+    if (spmm_blocks_by_wave(bs, bcols, nblocks, k, tile))
+        return launch_spmm_bcsr_wave(bs, brows, bcols, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s);
     if (bs == 2) return launch_spmm_pos<2>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
     if (bs == 4) return launch_spmm_pos<4>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
     if (bs == 8) return launch_spmm_pos<8>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);

@@ -1,0 +1,87 @@
+"""Block SpMM of up to 64 columns, a wave per tile: group widths, block rows that end inside a group's run, at its borders and
+behind the tile, empty block rows (more than 16 bits number among them), few and many tiles, NaN and Inf.  Oracle and bar as for
+the other SpMM tests: |got - ref| <= 1e-5 * sum |a b| + 1e-30."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2001_00532_amd as psk  # noqa: E402
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def product(A, bs, Bh, k, tile=0, phases=(7,)):
+    C = torch.full((A.rows * bs, k + 1), float("nan"), device="cuda")
+    ws = psk.workspace(psk.PSK_OP_SPMM_BCSR, A.rows, A.nnz, k=k, bs=bs, tile=tile)
+    pos, crd, vals, B = dev(A.pos), dev(A.crd), dev(A.vals), dev(Bh)[:, :k]
+    for ph in phases:
+        psk.psk_spmm_bcsr(A.rows, A.cols, A.nnz, bs, pos, crd, vals, B, C[:, :k], tile=tile, ws=ws, phases=ph)
+    torch.cuda.synchronize()
+    got = C.cpu().numpy()
+    assert np.isnan(got[:, k:]).all(), "columns past k were written"
+    return got[:, :k]
+
+
+PATTERNS = {"short": [0, 1, 2, 3, 9], "middle": [5, 8, 12], "long": [0, 1, 63, 64, 65, 96, 97, 200, 290]}
+
+
+@pytest.mark.parametrize("bs", [2, 4, 8])
+@pytest.mark.parametrize("k", [4, 5, 8, 9, 16, 17, 32, 33, 48, 64])
+def test_widths(bs, k):
+    for pattern, lengths in PATTERNS.items():
+        rng = np.random.default_rng(k + bs)
+        L = rng.choice(lengths, size=41_000 // int(np.mean(lengths)) + 400)
+        A = wl.csr_from_lengths(L, 300, seed=k, bs=bs)
+        assert A.nnz >= 600 * 64
+        Bh = wl.dense_uniform(300 * bs * (k + 1), 3, wl.S_B).reshape(300 * bs, k + 1)
+        ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, np.ascontiguousarray(Bh[:, :k]), bs)
+        got = product(A, bs, Bh, k)
+        ok, worst = oracle.within_tolerance(got, ref, mag)
+        assert ok, "bs %d k %d %s: %.3g of the bar" % (bs, k, pattern, worst)
+        assert (product(A, bs, Bh, k, 0, (1, 2, 4)) == got).all(), "one phase at a time"
+
+
+@pytest.mark.parametrize("bs,k,rows,tile", [(4, 8, 1, 0), (8, 32, 3, 0), (4, 20, 40, 512), (8, 4, 200, 256)])
+def test_few_tiles(bs, k, rows, tile):
+    A = wl.csr_from_lengths(np.full(rows, 37), 300, seed=k, bs=bs)
+    Bh = wl.dense_uniform(300 * bs * (k + 1), 3, wl.S_B).reshape(300 * bs, k + 1)
+    ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, np.ascontiguousarray(Bh[:, :k]), bs)
+    ok, worst = oracle.within_tolerance(product(A, bs, Bh, k, tile), ref, mag)
+    assert ok, "%.3g of the bar" % worst
+
+
+def test_runs_of_empty_block_rows():
+    L = np.concatenate([[3, 0, 5], np.zeros(70_000, dtype=int), [2, 7], np.zeros(500, dtype=int), [9] * 30])
+    A = wl.csr_from_lengths(L, 300, seed=2, bs=4)
+    Bh = wl.dense_uniform(300 * 4 * 13, 3, wl.S_B).reshape(1200, 13)
+    ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, np.ascontiguousarray(Bh[:, :12]), 4)
+    ok, worst = oracle.within_tolerance(product(A, 4, Bh, 12), ref, mag)
+    assert ok, "%.3g of the bar" % worst
+
+
+@pytest.mark.parametrize("bs", [2, 4, 8])
+def test_nan_and_inf_reach_only_their_block_rows(bs):
+    rng = np.random.default_rng(bs)
+    A = wl.csr_from_lengths(rng.choice([0, 1, 2, 9, 70], size=2600), 300, seed=bs, bs=bs)
+    assert A.nnz >= 600 * 64 or bs >= 4
+    crd = A.crd.copy()
+    crd[(crd < 3) & (rng.random(crd.size) > 1e-3)] = 5
+    A = dataclasses.replace(A, crd=crd)
+    Bh = wl.dense_uniform(300 * bs * 25, 3, wl.S_B).reshape(300 * bs, 25)
+    Bh[0], Bh[bs], Bh[2 * bs + 1] = np.nan, np.inf, -np.inf
+    with np.errstate(invalid="ignore"):
+        ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, np.ascontiguousarray(Bh[:, :24]), bs)
+    got = product(A, bs, Bh, 24)
+    assert (np.isnan(got) == np.isnan(ref)).all()
+    fin = np.isfinite(ref) & np.isfinite(mag)
+    assert (got[~fin & ~np.isnan(ref)] == ref[~fin & ~np.isnan(ref)]).all()
+    assert (np.abs(got[fin] - ref[fin]) <= 1e-5 * mag[fin] + 1e-30).all()
