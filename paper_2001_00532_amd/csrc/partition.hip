@@ -101,7 +101,7 @@ hipError_t launch_partition(int64_t rows, int64_t nnz, const int32_t *pos, int32
 // around that place.  Only the order changes: tiles, carries and sums stay as they are.
 // All tiles in one order by column (what this replaces) leaves the tiles in flight anywhere in their sweeps, so B * span had to
 // fit the L2; and it took two kernels of 6 + 24 us for 195 000 tiles, this one 13.  10^5 rows of 1000, k = 32 (B 12.8 MB, same tile
-// kernel) 864 -> 790 us for the product;  40 000 of 1000, k = 100 (38 MB) 2500 -> 1560.
+// kernel) 864 -> 790 us for the product, 700 with tiles walked in order;  40 000 of 1000, k = 100 (38 MB) 2500 -> 1092.
 // Counting sort by 1024 steps of columns; the order inside a step is of no concern.
 constexpr int SWEEP_BINS = 1024;
 __global__ __launch_bounds__(1024) void k_tile_sweeps(int rows, int nnz, int ntiles, int tile, int cols, int over, int len,
@@ -138,14 +138,16 @@ __global__ __launch_bounds__(1024) void k_tile_sweeps(int rows, int nnz, int nti
 
 // The records go to the workspace's tile_cols (8 ints per tile).
 hipError_t launch_tile_sweeps(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd, int32_t tile,
-                              int32_t over, const Workspace &w, hipStream_t s)
+                              int32_t over, bool tight, const Workspace &w, hipStream_t s)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
-    // A die holds about 768 tiles (waves); 768 / span of them cover the columns once.  Runs of 700 / 1000 / 1400 over span, us: 4000 per
-    // row, k = 128 815 / 819 / 813;  1000, k = 64 888 / 834 / 778;  1000, k = 100 1554 / 1564 / 1730;  k = 32 818 / 790 / 814.  Runs of more than
-    // 4096 tiles keep too few workgroups busy here: 20 000 per row, 40 M entries, k = 32 (limit 1024 / 4096 / none) 291 / 278 / 436;
-    // 10 000, k = 64 764 / 489 / 522.
-    const double len = 1000.0 * nnz / ((double)rows * tile);
+    // A die holds 512 tiles (waves); 512 / span of them cover the columns once.  Longer runs make the order of a run's tiles finer, shorter ones
+    // keep the tiles in flight closer to each other, which counts where what they sweep over together is more than the L2 holds
+    // (`tight`).  Runs of 350 / 500 / 600 / 700 / 1000 over span, us: tight: 1000 per row, k = 100, B 38 MB 1201 / 1085 / 1326 / 1482 / 1632;  others: k = 32
+    // 730 / 703 / 693 / 699 / 716;  k = 64 594 / 567 / 558 / 560 / 612;  lengths log-normal, k = 64 776 / 697 / 676 / 666 / 653;  4000 rows, k = 256 238 / 180 /
+    // 171 / 170 / 171.  Runs of more than 4096 tiles keep too few workgroups busy here: 20 000 per row, 40 M entries, k = 32 (limit 1024 / 4096 /
+    // none) 291 / 278 / 436;  10 000, k = 64 764 / 489 / 522.
+    const double len = (tight ? 500.0 : 700.0) * nnz / ((double)rows * tile);
     const int run = len < 256 ? 256 : (len > 4096 ? 4096 : (int)len);
     PSK_LAUNCH(k_tile_sweeps, dim3((unsigned)((ntiles + run - 1) / run)), dim3(1024), 0, s, rows, nnz, ntiles, tile, cols, over, run,
                pos, crd, w.tile_row, w.tile_cols);

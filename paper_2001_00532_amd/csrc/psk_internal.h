@@ -144,7 +144,7 @@ hipError_t launch_carry_fixup_f64(int32_t ntiles, int32_t tile, const int32_t *p
 // CSR SpMM
 // records of the tiles in w.tile_cols, in the order in which they sweep over the columns (reads the table)
 hipError_t launch_tile_sweeps(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd, int32_t tile,
-                              int32_t over, const Workspace &w, hipStream_t s);
+                              int32_t over, bool tight, const Workspace &w, hipStream_t s);
 // A row that reaches at most this far past the end of a tile is finished by that tile (tile_span in psk_dev.h).  It saves most of
 // the carries when rows are shorter than tiles; CSR rows of half a tile and more would only make the tiles unequal (0.5 to 1.5 T
 // positions) and leave few carries less: us with tile / 2 | with 0, tile 512: rows of 30, k = 128 41 | 43;  60 404 | 407;  200 457 | 465 (k = 32

@@ -319,16 +319,31 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     // Tiles in the order of their sweeps over the columns (launch_tile_sweeps) when rows are long.  It pays where B (MB: b_mb) is larger
     // than the L2 and its rows are used by several of the 768 tiles that a die works on at once: the sweeps of a die read B
     // rows / 768 times, so 2 * cols < 768 * mean row.  us before / ordered, columns sorted in the rows:
-    //   1000 per row, k = 32, B 12.8 MB 873 / 790 (10^5 rows);  k = 64, 12.8 MB 794 / 642;  k = 64, 24 MB 1236 / 834;  k = 100, 38 MB 2495 / 1564;
+    //   1000 per row, k = 32, B 12.8 MB 873 / 700 (10^5 rows);  k = 64, 12.8 MB 777 / 560;  k = 64, 24 MB 1476 / 691;  k = 100, 38 MB 2411 / 1092;
     //   k = 128, 14.6 MB 1086 / 667, 49 MB (4000 per row) 1340 / 819;  k = 256, 16 MB 414 / 178 (4000 rows), 64 MB 536 / 403;  700 per row (span 0.73),
     //   k = 256, 59 MB 3783 / 3297.  On the other side: span 0.93 413 / 420, B of 6 MB 1000 per row k = 16 41 / 47, k = 32 45 / 49.
     // Columns that are not sorted inside the rows gain nothing from the order; it costs the kernel that makes it (13 us of 870).
-    const int32_t *records = nullptr;
     const int32_t over = spmm_overhang(rows, nnz, tile);
     const int64_t ntiles = ((int64_t)nnz + tile - 1) / tile;
     const double span = (double)rows * tile / nnz, b_mb = (double)cols * k * 4 / (1 << 20);
-    if (ntiles >= 4096 && b_mb >= 8 && span <= 0.8 && 2.0 * cols * rows <= 768.0 * nnz) {
-        const hipError_t e = launch_tile_sweeps(rows, cols, nnz, pos, crd, tile, over, w, s);
+    const bool ordered = ntiles >= 4096 && b_mb >= 8 && span <= 0.8 && 2.0 * cols * rows <= 768.0 * nnz;
+    // Columns in chunks, where rows of B begin 128-byte lines and the part of B that the tiles in flight gather from (`reach`: all of it,
+    // ordered about span of it) does not fit the L2: one chunk after the other, as wide as fits.  A is read once per chunk.  us
+    // whole / 64 / 32 columns at a time, 16 M entries, 16 per row: k = 64, B 5 MB 231 / - / 218, 12 MB 417 / - / 291, 24 MB 516 / - / 449, 80 MB 589 / - / 602;
+    //   k = 128, 5 MB 414 / 367 / 427, 12 MB 798 / 525 / 429, 40 MB 1082 / 1001 / 842;  k = 256, 12 MB 1600 / 717 / 837, 40 MB 2196 / 1525 / 1038, 80 MB 2320 /
+    //   1994 / 1706.  4 per row: k = 64, 24 MB 615 / - / 594, 40 MB 637 / - / 667.  Ordered, 1000 per row: k = 128, 49 MB 1824 / 1632 / 1262, 15 MB 644 / 675 / 763;  k = 64,
+    //   24 MB 824 / - / 641, 12 MB 657 / - / 697;  4000 per row, k = 128, 49 MB 790 / 942 / 1048.
+    const bool lines = ldb % 32 == 0 && (reinterpret_cast<uintptr_t>(B) & 127) == 0;
+    const double reach = ordered ? span * b_mb : b_mb, fits = ordered ? 8.2 : 4.2;
+    int32_t chunk = k <= 256 ? k : 256;
+    if (lines && reach > fits && k >= 64 && k % 32 == 0) {
+        int32_t c = 128;
+        while (c > 32 && (c >= k || k % c != 0 || reach * c / k > fits)) c /= 2;
+        if (ordered || reach * c / k <= (k == 64 ? 12.5 : 13.5)) chunk = c;
+    }
+    const int32_t *records = nullptr;
+    if (ordered) {
+        const hipError_t e = launch_tile_sweeps(rows, cols, nnz, pos, crd, tile, over, reach * (chunk < k ? chunk : k) / k > fits, w, s);
         if (e != hipSuccess) return e;
         records = w.tile_cols;
     }
@@ -340,20 +355,6 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     //   B 6 MB: 4 per row k = 32 128 / 67;  16, k = 24 68 / 61;  100, k = 24 56 / 62;  1000, k = 32 45 / 49;  100, k = 96 137 / 101;  16, k = 200 209 / 212
     //   B 16 MB and more: 4 per row k = 16 86 / 79, k = 32 131 / 90, 500 MB 145 / 114;  4, k = 64 176 / 184;  100, k = 32 66 / 72;  10^6 rows of 16, 488 MB, k = 128
     //   1224 / 1250;  more than 256 columns (A is walked again): 4 per row 469 / 484, 16 315 / 289
-    // Columns in chunks, where rows of B begin 128-byte lines and the part of B that the tiles in flight gather from (`reach`: all of it,
-    // ordered about span of it) does not fit the L2: one chunk after the other, as wide as fits.  A is read once per chunk.  us
-    // whole / 64 / 32 columns at a time, 16 M entries, 16 per row: k = 64, B 5 MB 231 / - / 218, 12 MB 417 / - / 291, 24 MB 516 / - / 449, 80 MB 589 / - / 602;
-    //   k = 128, 5 MB 414 / 367 / 427, 12 MB 798 / 525 / 429, 40 MB 1082 / 1001 / 842;  k = 256, 12 MB 1600 / 717 / 837, 40 MB 2196 / 1525 / 1038, 80 MB 2320 /
-    //   1994 / 1706.  4 per row: k = 64, 24 MB 615 / - / 594, 40 MB 637 / - / 667.  Ordered, 1000 per row: k = 128, 49 MB 1824 / 1632 / 1262, 15 MB 644 / 675 / 763;  k = 64,
-    //   24 MB 824 / - / 641, 12 MB 657 / - / 697;  4000 per row, k = 128, 49 MB 790 / 942 / 1048.
-    const bool lines = ldb % 32 == 0 && (reinterpret_cast<uintptr_t>(B) & 127) == 0;
-    const double reach = records ? span * b_mb : b_mb, fits = records ? 8.2 : 4.2;
-    int32_t chunk = k <= 256 ? k : 256;
-    if (lines && reach > fits && k >= 64 && k % 32 == 0) {
-        int32_t c = 128;
-        while (c > 32 && (c >= k || k % c != 0 || reach * c / k > fits)) c /= 2;
-        if (records || reach * c / k <= (k == 64 ? 12.5 : 13.5)) chunk = c;
-    }
     const bool shorts = nnz < 32ll * rows;
     //   k = 8, 100 per row: 1953 tiles 15.1 / 17.2, 3906 21.8 / 22.2, 7812 34.9 / 33.0
     const bool wave = k >= 4 && ntiles >= (k <= 8 && !shorts ? 6000 : 1536) &&

@@ -283,7 +283,10 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     const bool first_y = blockIdx.y == 0;
 
     if (lane == 0 && first_y && !s.has_carry) carry_row[t] = -1;
-    const bool solid = s.straddle && rbeg == r1;  // no row ends in this tile
+    // No row ends in this tile, or few do and tiles sweep over the columns together: the groups take neighbouring positions, row by row.
+    // (Runs of their own put the groups of a tile at G places of its sweep, all over what the L2 is to hold: 10^5 rows of 1000, k = 32
+    // 40.9 M L2 misses and 772 us, so 30.2 M and 700;  40 000 rows, k = 100, B 38 MB 1457 / 1092.  At most 2, 4 or 10 ends: the same.)
+    const bool inorder = (s.straddle && rbeg == r1) || (records && rend - rbeg <= 4);
     const bool near = rend - rbeg < 0xffff;       // the rows' numbers fit 16 bits
 
     const char *const Bb = reinterpret_cast<const char *>(B);
@@ -321,9 +324,10 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     for (int b0 = 0; b0 < cnt || b0 == 0; b0 += bn) {
         const int n = cnt - b0 < bn ? cnt - b0 : bn;
         // a run of positions for each group, an odd number of places apart (the groups' reads hit different banks)
-        const int run = (n + G - 1) / G, step = solid ? run : run | 1;
+        const int run = (n + G - 1) / G, step = inorder ? run : run | 1;
         const unsigned inv = run > 0 ? 0xffffffffu / (unsigned)run + 1 : 0;               // i / run = i * inv / 2^32 for i < kWaveBlock
         auto place = [&](int i) { return step == run ? i : i + (int)__umulhi((unsigned)i, inv); };
+        int pe;                                   // a lane per row: where it ends
         {
             // (places behind the block's end read as 0: the range check of the buffer loads)
             const buf_t cb = buffer_of(crd + t0 + b0, n > 0 ? n * 4 : 0), vb = buffer_of(vals + t0 + b0, n > 0 ? n * 4 : 0);
@@ -334,7 +338,8 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
                 c[u] = __builtin_amdgcn_raw_buffer_load_b32(cb, lane * 4 + u * WAVE * 4, 0, BUFFER_NT);
                 v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vb, lane * 4 + u * WAVE * 4, 0, BUFFER_NT));
             }
-            int ps = r < rend ? pos[r] : 0, pe = r < rend ? pos[r + 1] : 1;
+            int ps = r < rend ? pos[r] : 0;
+            pe = r < rend ? pos[r + 1] : 1;
 #pragma unroll
             for (int u = 0; u < LD; ++u) {
                 const int i = u * WAVE + lane;
@@ -360,38 +365,54 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
             wave_fence();
         }
         if (n <= 0) break;
-        if (solid) {
-            // no row ends here: the groups take neighbouring positions
-            for (int i = 0; i < n; i += U * G) {
-                V b[U];
-                float a[U], even[4] = {}, odd[4] = {};
+        if (inorder) {
+            auto sweep = [&](int from, int to) {  // positions from .. to - 1 of the block
+                for (int i = from; i < to; i += U * G) {
+                    V b[U];
+                    float a[U], even[4] = {}, odd[4] = {};
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int j = i + u * G + g;
-                    const int2 e = ent[j < n ? j : n - 1];
-                    a[u] = __builtin_bit_cast(float, e.y);
-                    b[u] = row_of_B(e.x);
+                    for (int u = 0; u < U; ++u) {
+                        const int j = i + u * G + g;
+                        const int2 e = ent[j < to ? j : to - 1];
+                        a[u] = __builtin_bit_cast(float, e.y);
+                        b[u] = row_of_B(e.x);
+                    }
+                    if (i + U * G <= to) {
+#pragma unroll
+                        for (int u = 0; u < U; u += 2)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                even[q] = fmaf(a[u], b[u][q], even[q]);
+                                odd[q] = fmaf(a[u + 1], b[u + 1][q], odd[q]);
+                            }
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+                            if (i + u * G + g < to) {
+                                float(&sum)[4] = u & 1 ? odd : even;
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) sum[q] = fmaf(a[u], b[u][q], sum[q]);
+                            }
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) open[q] += (double)(even[q] + odd[q]);
                 }
-                if (i + U * G <= n) {
+            };
+            int at = 0;
+            for (int r = rbeg; r < rend; ++r) {
+                const int end = __builtin_amdgcn_readlane(pe, r - rbeg) - t0 - b0;
+                if (end > n) break;
+                // (empty rows, and rows that ended in an earlier block: end <= at; a row whose last position is the first of the tile has end 1)
+                if (end <= at) continue;
+                sweep(at, end);
+                double o[4];
+                total(open, o);
+                if (active && g == 0) emit(r, o);
 #pragma unroll
-                    for (int u = 0; u < U; u += 2)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            even[q] = fmaf(a[u], b[u][q], even[q]);
-                            odd[q] = fmaf(a[u + 1], b[u + 1][q], odd[q]);
-                        }
-                } else {
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        if (i + u * G + g < n) {
-                            float(&to)[4] = u & 1 ? odd : even;
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) to[q] = fmaf(a[u], b[u][q], to[q]);
-                        }
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) open[q] += (double)(even[q] + odd[q]);
+                for (int q = 0; q < 4; ++q) open[q] = 0.0;
+                at = end;
             }
+            if (at < n) sweep(at, n);
         } else {
             const int j0 = g * run, len = n - j0 < run ? n - j0 : run;
             const int first = g * step;           // place of the run (lanes without a position read the block's first entry)
