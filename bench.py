@@ -346,7 +346,7 @@ def bench_mttkrp(args, torch, psk, wl):
         "ns_per_nnz": round(wall / args.steps * 1e9 / nnz, 6),
         "phases_us_median": {"main": round(statistics.median(main_ms) * 1e3, 2),
                              "all": round(statistics.median(all_ms) * 1e3, 2)},
-        "roofline": {"bound": "hbm", "kernel": "k_mttkrp_pos", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": "k_mttkrp_runs", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_source": traffic_src, "algorithmic_bytes": comp, "no_reuse_bytes": noreuse,
                      "no_reuse_GBs": round(noreuse / (main_avg * 1e-3) / 1e9, 2),

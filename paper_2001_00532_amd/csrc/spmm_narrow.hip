@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     if (lane == 0 && first_y && !s.has_carry) carry_row[t] = -1;
     // No row ends in this tile, or few do and tiles sweep over the columns together: the groups take neighbouring positions, row by row.
     // (Runs of their own put the groups of a tile at G places of its sweep, all over what the L2 is to hold: 10^5 rows of 1000, k = 32
-    // 40.9 M L2 misses and 772 us, so 30.2 M and 700;  40 000 rows, k = 100, B 38 MB 1457 / 1092.  At most 2, 4 or 10 ends: the same.)
+    // 40.9 M L2 misses and 772 us, so 26.3 M and 690;  40 000 rows, k = 100, B 38 MB 1457 and 1092.  At most 2, 4 or 10 ends: the same.)
     const bool inorder = (s.straddle && rbeg == r1) || (records && rend - rbeg <= 4);
     const bool near = rend - rbeg < 0xffff;       // the rows' numbers fit 16 bits
 
