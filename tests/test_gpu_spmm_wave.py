@@ -70,26 +70,50 @@ def test_runs_of_empty_rows():
     assert ok, "%.3g of the bar" % worst
 
 
-@pytest.mark.parametrize("pattern", ["short", "long"])
-@pytest.mark.parametrize("k", [7, 32, 128])
-def test_nan_and_inf_reach_only_their_rows(k, pattern):
+def with_specials(A, rng):
+    """Every 7th row with entries refers to NaN, to Inf, to -Inf, to both, or to three finite products whose sum passes the fp32 range
+    (rows 0 to 3 of B), at early, middle and last places of the row; nobody else does.  The number of entries of each kind."""
+    crd, vals = np.maximum(A.crd, 4), A.vals.copy()
+    lengths = np.diff(A.pos)
+    count = np.zeros(4, dtype=int)
+    for i, r in enumerate(np.flatnonzero(lengths >= 3)[::7]):
+        n = int(lengths[r])
+        at = [int(rng.integers(min(n, 8))), int(rng.integers(n)), n - 1][(i // 5) % 3]
+        kinds = ((0,), (1,), (2,), (1, 2), (3, 3, 3))[i % 5]
+        for m, c in enumerate(kinds):
+            p = A.pos[r] + (at + m) % n
+            crd[p], vals[p] = c, 1.0
+            count[c] += 1
+    return dataclasses.replace(A, crd=crd, vals=vals), count
+
+
+def same_specials(got, ref, mag):
+    """As the sum in 64 bits, rounded: NaN, infinities (an overflow among them) and the rest within the bar."""
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = ref.astype(np.float32)
+        assert np.isnan(want).any() and np.isposinf(want).any() and np.isneginf(want).any() and (np.isinf(want) & np.isfinite(ref)).any()
+        assert (np.isnan(got) == np.isnan(want)).all(), "%d places are NaN and should not be" % (np.isnan(got) & ~np.isnan(want)).sum()
+        inf = np.isinf(want)
+        assert (np.isinf(got) == inf).all() and (got[inf] == want[inf]).all()
+        fin = np.isfinite(want)
+        assert (np.abs(got[fin] - ref[fin]) <= 1e-5 * mag[fin] + 1e-30).all()
+
+
+@pytest.mark.parametrize("length", [5, 16, 100, 700])
+@pytest.mark.parametrize("k,tile", [(7, 256), (32, 256), (128, 256), (200, 256), (32, 2048)])
+def test_nan_inf_and_overflow_reach_only_their_rows(k, tile, length):
     """Row 0 of B among them: places of a block that hold no entry must not bring it in."""
-    rng = np.random.default_rng(k)
-    A = wl.csr_from_lengths(rows_of(pattern, rng, NNZ + 1000), 900, seed=k)
-    crd = A.crd.copy()
-    crd[crd == 0] = 1
-    keep = rng.random(crd.size) < 1e-4       # few entries refer to the special rows
-    crd[(crd < 4) & ~keep] = 5
+    rng = np.random.default_rng(k + length)
+    tiles = 6000 if k <= 8 else 1536
+    A = wl.csr_from_lengths(np.full((tiles * tile + 77) // length + 2, length), 900, seed=k)
+    assert A.nnz >= tiles * tile
+    A, count = with_specials(A, rng)
+    assert (count >= 10).all()
     Bh = wl.dense_uniform(900 * (k + 1), 3, wl.S_B).reshape(900, k + 1)
-    Bh[0], Bh[1], Bh[2], Bh[3] = np.nan, np.inf, -np.inf, np.nan
-    A = dataclasses.replace(A, crd=crd)
+    Bh[0], Bh[1], Bh[2], Bh[3] = np.nan, np.inf, -np.inf, 2e38
     with np.errstate(invalid="ignore"):
         ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh[:, :k])
-    got = product(A, 900, Bh, k, 256)
-    assert (np.isnan(got) == np.isnan(ref)).all()
-    fin = np.isfinite(ref) & np.isfinite(mag)
-    assert (got[~fin & ~np.isnan(ref)] == ref[~fin & ~np.isnan(ref)]).all()
-    assert (np.abs(got[fin] - ref[fin]) <= 1e-5 * mag[fin] + 1e-30).all()
+    same_specials(product(A, 900, Bh, k, tile), ref, mag)
 
 
 @pytest.mark.parametrize("k,cols,pattern", [(64, 22_000, "short"), (96, 15_000, "middle"), (128, 12_000, "long"), (128, 30_000, "short"),
