@@ -236,6 +236,64 @@ __device__ __forceinline__ void group_segscan(T (&x)[4], unsigned long long head
     }
 }
 
+// For N positions p[u] of a tile whose table entries are r0 and r1: max { r in [r0, r1] : pos[r] <= p[u] }, the N searches side by side.
+template <int N>
+__device__ __forceinline__ void rows_by_search(const int *__restrict__ pos, int r0, int r1, const int (&p)[N], int (&row)[N])
+{
+#pragma unroll
+    for (int u = 0; u < N; ++u) row[u] = r0;
+    for (unsigned step = r1 > r0 ? 1u << (31 - __builtin_clz(r1 - r0)) : 0; step; step >>= 1) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int at = (int)min((unsigned)row[u] + step, (unsigned)r1);
+            row[u] = pos[at] <= p[u] ? at : row[u];
+        }
+    }
+}
+
+// Clears the empty rows (BS rows of C each, k >= 4 columns) of tiles whose rows span more than GAP: wave number `index` looks up the tile
+// that owns row index * GAP (tile t owns the rows from its table entry, tile 0 from row 0, to the next entry).
+template <int BS, int GAP>
+__device__ __forceinline__ void clear_gap_rows(int index, int rows, const int *__restrict__ pos, const int *__restrict__ tile_row, int T,
+                                               float *__restrict__ C, int k, long long ldc)
+{
+    const long long q = (long long)index * GAP;
+    if (q >= rows) return;
+    const int last = pos[q + 1] - 1;              // position before the end of row q: the last tile that owns row q holds it
+    const int t = last < 0 ? 0 : last / T;
+    const int lo = t == 0 ? 0 : tile_row[t], hi = tile_row[t + 1];
+    if (hi - lo <= GAP) return;
+    const int beg = q - GAP < lo ? lo : (int)q;   // from the tile's first row on where no earlier wave's row lies in it
+    const int end = hi - q < GAP ? hi : (int)q + GAP;
+    const int lane = threadIdx.x & (WAVE - 1), quads = (k + 3) / 4;
+    int shift = 0;                                // 2^shift lanes per row, `at_once` rows per store
+    while (shift < 6 && (1 << shift) < quads) ++shift;
+    const int at_once = WAVE >> shift, g = lane >> shift;
+    for (long long rb = beg; rb < end; rb += WAVE) {
+        const bool mine = rb + lane < end && pos[rb + lane] == pos[rb + lane + 1];
+        const unsigned long long empty = __ballot(mine);
+        for (int c = lane & ((1 << shift) - 1); c < quads; c += 1 << shift) {
+            float *to = C + (rb + g) * BS * ldc + (4 * c < k - 4 ? 4 * c : k - 4);
+            for (int i = g; i < WAVE; i += at_once, to += at_once * BS * ldc) {
+                if (~empty && !((empty >> i) & 1)) continue;
+#pragma unroll
+                for (int ii = 0; ii < BS; ++ii) *reinterpret_cast<v4f_u *>(to + ii * ldc) = v4f_u{};
+            }
+        }
+    }
+}
+
+// Of the rows rb .. rb + 63, those of `empty` are handed to `clear`, a row to each of the wave's G groups at a time.
+template <int G, typename F>
+__device__ __forceinline__ void each_empty_row(unsigned long long empty, int rb, int g, F clear)
+{
+    while (empty) {
+        const int j = __ffsll((long long)empty) - 1;
+        if (G == 1 || (j + g < WAVE && ((empty >> ((j + g) & (WAVE - 1))) & 1))) clear(rb + j + g);
+        empty &= ~(((1ull << G) - 1) << j);
+    }
+}
+
 // ---- per-workgroup trace (only in the instrumented build, -DPSK_CU_TRACE): every workgroup of a traced kernel
 // records its start and end on the 100 MHz wall clock and the compute unit it ran on (HW_ID: cu, sh, se;
 // XCC_ID: die) into a caller-supplied buffer of 3 x 64 bits per workgroup, from which the host forms each

@@ -25,7 +25,12 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     int *const ent = smem + wave * (T + over);                          // block column, bit 31: a block row ends
     unsigned short *const srow = reinterpret_cast<unsigned short *>(smem + 4 * (T + over)) + wave * (T + over);   // which
-    const int quad = xcd_tile(blockIdx.x, (ntiles + 3) / 4), t = quad * 4 + wave;
+    const int quads = (ntiles + 3) / 4, filler = (int)blockIdx.x - xcd_grid(quads);
+    if (filler >= 0) {
+        clear_gap_rows<BS, kSpmmGapRows>(filler * 4 + wave, rows, pos, tile_row, T, C, k, ldc);
+        return;
+    }
+    const int quad = xcd_tile(blockIdx.x, quads), t = quad * 4 + wave;
     if (quad < 0 || t >= ntiles) return;          // (no barriers: waves don't wait for each other)
     const int col0 = gl * 4;
     const bool active = col0 < k;
@@ -37,15 +42,13 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
     const int rbeg = __builtin_amdgcn_readfirstlane(s.rbeg), rend = __builtin_amdgcn_readfirstlane(s.rend);
     if (lane == 0 && !s.has_carry) carry_row[t] = -1;
     const bool near = rend - rbeg < 0xffff;       // the rows' numbers fit 16 bits
+    const bool gap = r1 - (t == 0 ? 0 : r0) > kSpmmGapRows;       // the empty rows are cleared by the last workgroups of the grid
 
     auto row_at = [&](int i) -> int {             // the block row that ends at position i of the tile
         if (near) return rbeg + srow[i];
-        int lo = r0, hi = r1;                     // a long run of empty rows: max { r : pos[r] <= t0 + i }
-        while (lo < hi) {
-            const int mid = lo + ((hi - lo + 1) >> 1);
-            if (pos[mid] <= t0 + i) lo = mid; else hi = mid - 1;
-        }
-        return lo;
+        int row[1];
+        rows_by_search<1>(pos, r0, r1, {t0 + i}, row);
+        return row[0];
     };
     auto store = [&](int r, const float (&o)[BS][4]) {
 #pragma unroll
@@ -64,22 +67,27 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
 
     for (int i = lane; i < cnt; i += WAVE) ent[i] = ld_stream(crd + t0 + i);
     wave_fence();
-    for (int rb = rbeg; rb < rend; rb += WAVE) {
+    auto mark = [&](int e, int row) {             // position e of the tile ends the block row
+        ent[e] |= (int)0x80000000u;
+        srow[e] = (unsigned short)(near ? row - rbeg : 0);
+    };
+    for (int rb = rbeg; !gap && rb < rend; rb += WAVE) {
         const int r = rb + lane;
         const bool valid = r < rend;
         const int ps = valid ? pos[r] : 0, pe = valid ? pos[r + 1] : 1;
         const int e = pe - 1 - t0;
-        if (valid && pe > ps && e >= 0 && e < cnt) {
-            ent[e] |= (int)0x80000000u;
-            srow[e] = (unsigned short)(near ? r - rbeg : 0);
-        }
-        unsigned long long empty = __ballot(valid && pe == ps);
-        while (empty) {
-            const int j = __ffsll((long long)empty) - 1;
-            empty &= empty - 1;
+        if (valid && pe > ps && e >= 0 && e < cnt) mark(e, r);
+        each_empty_row<G>(__ballot(valid && pe == ps), rb, g, [&](int row) {
             const float z[BS][4] = {};
-            if (active && g == 0) store(rb + j, z);
-        }
+            if (active) store(row, z);
+        });
+    }
+    for (int i = lane; gap && i < cnt; i += 2 * WAVE) {
+        const int p[2] = {t0 + i, t0 + min(i + WAVE, cnt - 1)};
+        int row[2];
+        rows_by_search(pos, r0, r1, p, row);
+        if (pos[row[0] + 1] == p[0] + 1) mark(i, row[0]);
+        if (i + WAVE < cnt && pos[row[1] + 1] == p[1] + 1) mark(i + WAVE, row[1]);
     }
     wave_fence();
     if (cnt <= 0) return;
@@ -178,9 +186,9 @@ static void launch_blocks(int32_t rows, int32_t cols, int32_t nnz, const int32_t
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? (int64_t)cols * BS : 1);
-    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4), lds = 4u * (unsigned)(tile + over) * 6u;
+    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4), fillers = (unsigned)spmm_fillers(rows), lds = 4u * (unsigned)(tile + over) * 6u;
 #define PSK_GO_(GG, SM)                                                                                           \
-    PSK_LAUNCH((k_spmm_wave_blocks<BS, GG, SM>), dim3(nx), dim3(256), lds, s, rows, nnz, pos, crd, \
+    PSK_LAUNCH((k_spmm_wave_blocks<BS, GG, SM>), dim3(nx + fillers), dim3(256), lds, s, rows, nnz, pos, crd, \
                vals, B, k, (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over)
 #define PSK_GO(GG) do { if (small) PSK_GO_(GG, true); else PSK_GO_(GG, false); } while (0)
     if (k <= 8) PSK_GO(32);

@@ -268,7 +268,12 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     int2 *const ent = reinterpret_cast<int2 *>(smem) + wave * PLACES;       // {offset or column | row end, value}
     unsigned short *const srow = reinterpret_cast<unsigned short *>(smem + 4 * 2 * PLACES) + wave * kWaveBlock;   // row that ends
-    const int quad = xcd_tile(blockIdx.x, (ntiles + 3) / 4), slot = quad * 4 + wave;
+    const int quads = (ntiles + 3) / 4, filler = (int)blockIdx.x - xcd_grid(quads);
+    if (filler >= 0) {
+        if (blockIdx.y == 0) clear_gap_rows<1, kSpmmGapRows>(filler * 4 + wave, rows, pos, tile_row, T, C, k, ldc);
+        return;
+    }
+    const int quad = xcd_tile(blockIdx.x, quads), slot = quad * 4 + wave;
     if (quad < 0 || slot >= ntiles) return;                                     // (no barriers: waves don't wait for each other)
     const int col0 = blockIdx.y * (GW * 4) + gl * 4;
     const bool active = col0 < k;
@@ -281,6 +286,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     const int r0 = __builtin_amdgcn_readfirstlane(s.r0), r1 = __builtin_amdgcn_readfirstlane(s.r1);
     const int rbeg = __builtin_amdgcn_readfirstlane(s.rbeg), rend = __builtin_amdgcn_readfirstlane(s.rend);
     const bool first_y = blockIdx.y == 0;
+    const bool gap = r1 - (t == 0 ? 0 : r0) > kSpmmGapRows;       // the empty rows are cleared by the last workgroups of the grid
 
     if (lane == 0 && first_y && !s.has_carry) carry_row[t] = -1;
     // No row ends in this tile, or few do and tiles sweep over the columns together: the groups take neighbouring positions, row by row.
@@ -298,12 +304,9 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     auto ends_row = [&](int x) -> bool { return SMALL ? (x & 1) != 0 : x < 0; };
     auto row_at = [&](int b0, int i) -> int {     // the row that ends at place i of the block
         if (near) return rbeg + srow[i];
-        int lo = r0, hi = r1;                     // a long run of empty rows: max { r : pos[r] <= t0 + b0 + i }
-        while (lo < hi) {
-            const int mid = lo + ((hi - lo + 1) >> 1);
-            if (pos[mid] <= t0 + b0 + i) lo = mid; else hi = mid - 1;
-        }
-        return lo;
+        int row[1];
+        rows_by_search<1>(pos, r0, r1, {t0 + b0 + i}, row);
+        return row[0];
     };
     auto store = [&](int r, const auto (&o)[4]) {
         __builtin_nontemporal_store(V{(float)o[0], (float)o[1], (float)o[2], (float)o[3]}, reinterpret_cast<V *>(C + (long long)r * ldc + col));
@@ -320,6 +323,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     };
 
     double open[4] = {};                          // this group's share of the row that is open
+    int rfrom = rbeg;                             // rows before this one have ended in earlier blocks
     const int nb = (cnt + kWaveBlock - 1) / kWaveBlock, bn = nb ? (cnt + nb - 1) / nb : 0;
     for (int b0 = 0; b0 < cnt || b0 == 0; b0 += bn) {
         const int n = cnt - b0 < bn ? cnt - b0 : bn;
@@ -331,35 +335,48 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
         {
             // (places behind the block's end read as 0: the range check of the buffer loads)
             const buf_t cb = buffer_of(crd + t0 + b0, n > 0 ? n * 4 : 0), vb = buffer_of(vals + t0 + b0, n > 0 ? n * 4 : 0);
-            int c[LD], r = rbeg + lane;
+            int c[LD], r = rfrom + lane;
             float v[LD];
 #pragma unroll
             for (int u = 0; u < LD; ++u) {
                 c[u] = __builtin_amdgcn_raw_buffer_load_b32(cb, lane * 4 + u * WAVE * 4, 0, BUFFER_NT);
                 v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vb, lane * 4 + u * WAVE * 4, 0, BUFFER_NT));
             }
-            int ps = r < rend ? pos[r] : 0;
-            pe = r < rend ? pos[r + 1] : 1;
+            int ps = !gap && r < rend ? pos[r] : 0;
+            pe = !gap && r < rend ? pos[r + 1] : 1;
 #pragma unroll
             for (int u = 0; u < LD; ++u) {
                 const int i = u * WAVE + lane;
                 if (i < n) ent[place(i)] = make_int2(SMALL ? (int)((unsigned)c[u] * (unsigned)ldb * 4u) : c[u], __builtin_bit_cast(int, v[u]));
             }
             wave_fence();
-            for (int rb = rbeg; rb < rend; rb += WAVE) {
+            auto mark = [&](int e, int row) {     // place e of the block ends the row
+                ent[place(e)].x |= SMALL ? 1 : (int)0x80000000u;
+                srow[e] = (unsigned short)(near ? row - rbeg : 0);
+            };
+            for (int rb = rfrom; !gap && rb < rend; rb += WAVE) {
                 const int e = pe - 1 - t0 - b0;
-                const bool here = r < rend && pe > ps && e >= 0 && e < n;
-                if (here) {
-                    ent[place(e)].x |= SMALL ? 1 : (int)0x80000000u;
-                    srow[e] = (unsigned short)(near ? r - rbeg : 0);
-                }
-                unsigned long long empty = b0 == 0 ? __ballot(r < rend && pe == ps) : 0;
+                if (r < rend && pe > ps && e >= 0 && e < n) mark(e, r);
+                const unsigned long long empty = __ballot(r < rend && pe == ps), later = __ballot(r < rend && pe > ps && e >= n);
                 r += WAVE;
                 if (rb + WAVE < rend) { ps = r < rend ? pos[r] : 0; pe = r < rend ? pos[r + 1] : 1; }
-                while (empty) {
-                    const int j = __ffsll((long long)empty) - 1;
-                    empty &= empty - 1;
-                    if (active && g == 0) __builtin_nontemporal_store(V{}, reinterpret_cast<V *>(C + (long long)(rb + j) * ldc + col));
+                each_empty_row<G>(empty, rb, g, [&](int row) {
+                    if (active) __builtin_nontemporal_store(V{}, reinterpret_cast<V *>(C + (long long)row * ldc + col));
+                });
+                rfrom = rb;
+                if (later) break;                 // the other rows end, or lie empty, in later blocks
+            }
+            if (gap) {
+                constexpr int N = 3;
+#pragma unroll 1
+                for (int i = lane; i < n; i += N * WAVE) {
+                    int p[N], row[N];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) p[u] = t0 + b0 + min(i + u * WAVE, n - 1);
+                    rows_by_search(pos, r0, r1, p, row);
+#pragma unroll
+                    for (int u = 0; u < N; ++u)
+                        if (i + u * WAVE < n && pos[row[u] + 1] == p[u] + 1) mark(i + u * WAVE, row[u]);
                 }
             }
             wave_fence();
@@ -543,10 +560,10 @@ hipError_t launch_spmm_csr_wave(int32_t rows, int32_t cols, int32_t nnz, const i
     if (nnz <= 0) return hipSuccess;
     if (k < 4) return hipErrorInvalidValue;
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
-    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4);
+    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4), fillers = (unsigned)spmm_fillers(rows);
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? cols : 1);
 #define PSK_GO_(GG, SM)                                                                                           \
-    PSK_LAUNCH((k_spmm_wave<GG, SM>), dim3(nx, (unsigned)((k + 256 / GG - 1) / (256 / GG))), dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
+    PSK_LAUNCH((k_spmm_wave<GG, SM>), dim3(nx + fillers, (unsigned)((k + 256 / GG - 1) / (256 / GG))), dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
                (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, records)
 #define PSK_GO(GG) do { if (small) PSK_GO_(GG, true); else PSK_GO_(GG, false); } while (0)
     if (chunk <= 8) PSK_GO(32);

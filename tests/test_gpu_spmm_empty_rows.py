@@ -1,0 +1,99 @@
+"""Long runs of empty rows where a wave works on a tile alone: they are cleared by workgroups of their own, so that their time is
+that of writing C, and the rows around them are found by search.  Runs around the length from which that is done, at the
+beginning, in the middle, at the end and one after the other; tiles staged in several blocks; blocks.  Oracle and bar as for the other
+SpMM tests: |got - ref| <= 1e-5 * sum |a b| + 1e-30."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2001_00532_amd as psk  # noqa: E402
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def gaps(kind, entries, rng, rows_per_entry):
+    """Row lengths with about `entries` entries."""
+    part = lambda n: rng.choice([1, 2, 40, 300], size=max(1, n // 86))
+    zero = lambda n: np.zeros(n, dtype=np.int64)
+    if kind == "edges":
+        runs = [zero(1025)]
+        for n in (1, 1022, 1023, 1024, 1025, 2047, 2048, 2049, 3 * 1024, 65_534, 65_535, 65_536, 16 * 1024 * 4 + 3):
+            runs += [part(entries // 14), zero(n)]
+        return np.concatenate(runs + [part(entries // 14), zero(5000)])
+    if kind == "long rows":                       # a run inside a tile that a row reaches into and another one leaves
+        runs = []
+        for n in (1000, 1024, 1500, 40_000):
+            runs += [part(entries // 8), np.array([900, 3]), zero(n), np.array([5, 5000]), zero(n), np.array([1])]
+        return np.concatenate(runs + [part(entries // 2)])
+    return (rng.random(entries * rows_per_entry) < 1 / rows_per_entry).astype(np.int64)      # "sparse": every tile spans such a number of rows
+
+
+CASES = [(k, tile, kind) for k, tile in ((4, 256), (17, 256), (32, 512), (32, 2048), (128, 256), (200, 256)) for kind in ("edges", "long rows")]
+
+
+@pytest.mark.parametrize("k,tile,kind", CASES + [(4, 256, "sparse"), (17, 256, "sparse"), (12, 2048, "sparse")])
+def test_rows_around_long_runs(k, tile, kind):
+    rng = np.random.default_rng(k)
+    A = wl.csr_from_lengths(gaps(kind, int(1.15 * 1536 * tile), rng, max(2, 2048 // tile)), 5200, seed=k)
+    assert A.nnz >= 1536 * tile
+    Bh = wl.dense_uniform(5200 * k, 3, wl.S_B).reshape(5200, k)
+    ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh)
+    C = torch.full((A.rows, k + 1), float("nan"), device="cuda")
+    psk.psk_spmm_csr(A.rows, 5200, A.nnz, dev(A.pos), dev(A.crd), dev(A.vals), dev(Bh), C[:, :k], tile=tile)
+    got = C.cpu().numpy()
+    assert np.isnan(got[:, k:]).all(), "columns past k were written"
+    ok, worst = oracle.within_tolerance(got[:, :k], ref, mag)
+    assert ok, "%.3g of the bar" % worst
+    assert (got[:-1, :k][np.diff(A.pos)[:-1] == 0] == 0).all()
+
+
+@pytest.mark.parametrize("kind", ["edges", "long rows", "sparse"])
+@pytest.mark.parametrize("bs,k,tile", [(2, 8, 0), (4, 5, 0), (4, 32, 0), (8, 16, 0), (4, 12, 512)])
+def test_block_rows_around_long_runs(bs, k, tile, kind):
+    rng = np.random.default_rng(k)
+    A = wl.csr_from_lengths(gaps(kind, 45_000, rng, 20), 5200, seed=k, bs=bs)
+    Bh = wl.dense_uniform(5200 * bs * k, 3, wl.S_B).reshape(5200 * bs, k)
+    ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, Bh, bs)
+    C = torch.full((A.rows * bs, k + 1), float("nan"), device="cuda")
+    psk.psk_spmm_bcsr(A.rows, 5200, A.nnz, bs, dev(A.pos), dev(A.crd), dev(A.vals), dev(Bh), C[:, :k], tile=tile)
+    got = C.cpu().numpy()
+    assert np.isnan(got[:, k:]).all(), "columns past k were written"
+    ok, worst = oracle.within_tolerance(got[:, :k], ref, mag)
+    assert ok, "%.3g of the bar" % worst
+
+
+@pytest.mark.parametrize("bs,k", [(1, 32), (1, 128), (4, 16)])
+def test_a_run_takes_the_time_of_clearing_it(bs, k):
+    """The product of 848 000 entries takes less than 0.2 ms and C is cleared in 0.1 to 0.2 ms; one wave alone walked the run in 40 to 200 ms."""
+    L = np.concatenate([np.full(53_000, 8), np.zeros((1 << 21) // bs, dtype=np.int64), np.full(53_000, 8)])
+    A = wl.csr_from_lengths(L, 2000, seed=k, bs=bs)
+    pos, crd, vals = dev(A.pos), dev(A.crd), dev(A.vals)
+    B = dev(wl.dense_uniform(2000 * bs * k, 3, wl.S_B).reshape(2000 * bs, k))
+    C = torch.empty((A.rows * bs, k), device="cuda")
+    ws = psk.workspace(psk.PSK_OP_SPMM_CSR if bs == 1 else psk.PSK_OP_SPMM_BCSR, A.rows, A.nnz, k=k, bs=bs)
+
+    def once(f):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b)
+
+    def product():
+        if bs == 1:
+            psk.psk_spmm_csr(A.rows, 2000, A.nnz, pos, crd, vals, B, C, ws=ws)
+        else:
+            psk.psk_spmm_bcsr(A.rows, 2000, A.nnz, bs, pos, crd, vals, B, C, ws=ws)
+
+    took = min(once(product) for _ in range(5))
+    clear = min(once(lambda: C.zero_()) for _ in range(5))
+    print("product %.3f ms, clearing C %.3f ms" % (took, clear), flush=True)
+    assert took <= 4 * clear + 0.5
