@@ -18,7 +18,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
                                                           const int *__restrict__ tile_row, int *__restrict__ carry_row,
                                                           float *__restrict__ carry_val, int ntiles, int T, int over)
 {
-    constexpr int GW = WAVE / G, U = BS == 2 ? 4 : (BS == 4 ? 2 : 1);
+    constexpr int GW = WAVE / G, U = BS == 2 ? 4 : (BS == 4 ? 2 : 1), GAP = spmm_gap_rows(G, BS);
     typedef v4f_u V;
     extern __shared__ int smem[];
     const int lane = threadIdx.x & (WAVE - 1), g = lane / GW, gl = lane % GW;
@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
     unsigned short *const srow = reinterpret_cast<unsigned short *>(smem + 4 * (T + over)) + wave * (T + over);   // which
     const int quads = (ntiles + 3) / 4, filler = (int)blockIdx.x - xcd_grid(quads);
     if (filler >= 0) {
-        clear_gap_rows<BS, kSpmmGapRows>(filler * 4 + wave, rows, pos, tile_row, T, C, k, ldc);
+        clear_gap_rows<BS, GAP>(filler * 4 + wave, rows, pos, tile_row, T, C, k, ldc);
         return;
     }
     const int quad = xcd_tile(blockIdx.x, quads), t = quad * 4 + wave;
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
     const int rbeg = __builtin_amdgcn_readfirstlane(s.rbeg), rend = __builtin_amdgcn_readfirstlane(s.rend);
     if (lane == 0 && !s.has_carry) carry_row[t] = -1;
     const bool near = rend - rbeg < 0xffff;       // the rows' numbers fit 16 bits
-    const bool gap = r1 - (t == 0 ? 0 : r0) > kSpmmGapRows;       // the empty rows are cleared by the last workgroups of the grid
+    const bool gap = r1 - (t == 0 ? 0 : r0) > GAP;       // the empty rows are cleared by the last workgroups of the grid
 
     auto row_at = [&](int i) -> int {             // the block row that ends at position i of the tile
         if (near) return rbeg + srow[i];
@@ -186,7 +186,7 @@ static void launch_blocks(int32_t rows, int32_t cols, int32_t nnz, const int32_t
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? (int64_t)cols * BS : 1);
-    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4), fillers = (unsigned)spmm_fillers(rows), lds = 4u * (unsigned)(tile + over) * 6u;
+    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4), fillers = (unsigned)spmm_fillers(rows, spmm_gap_rows(1, BS)), lds = 4u * (unsigned)(tile + over) * 6u;
 #define PSK_GO_(GG, SM)                                                                                           \
     PSK_LAUNCH((k_spmm_wave_blocks<BS, GG, SM>), dim3(nx + fillers), dim3(256), lds, s, rows, nnz, pos, crd, \
                vals, B, k, (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over)

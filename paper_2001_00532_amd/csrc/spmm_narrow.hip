@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
                                                    float *__restrict__ carry_val, int ntiles, int T, int over,
                                                    const int *__restrict__ records)
 {
-    constexpr int GW = WAVE / G, U = 8, LD = kWaveBlock / WAVE;
+    constexpr int GW = WAVE / G, U = 8, LD = kWaveBlock / WAVE, GAP = spmm_gap_rows(G, 1);
     constexpr int PLACES = kWaveBlock + G;        // (runs an odd number of places apart)
     typedef v4f_u V;
     extern __shared__ int smem[];
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     unsigned short *const srow = reinterpret_cast<unsigned short *>(smem + 4 * 2 * PLACES) + wave * kWaveBlock;   // row that ends
     const int quads = (ntiles + 3) / 4, filler = (int)blockIdx.x - xcd_grid(quads);
     if (filler >= 0) {
-        if (blockIdx.y == 0) clear_gap_rows<1, kSpmmGapRows>(filler * 4 + wave, rows, pos, tile_row, T, C, k, ldc);
+        if (blockIdx.y == 0) clear_gap_rows<1, GAP>(filler * 4 + wave, rows, pos, tile_row, T, C, k, ldc);
         return;
     }
     const int quad = xcd_tile(blockIdx.x, quads), slot = quad * 4 + wave;
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     const int r0 = __builtin_amdgcn_readfirstlane(s.r0), r1 = __builtin_amdgcn_readfirstlane(s.r1);
     const int rbeg = __builtin_amdgcn_readfirstlane(s.rbeg), rend = __builtin_amdgcn_readfirstlane(s.rend);
     const bool first_y = blockIdx.y == 0;
-    const bool gap = r1 - (t == 0 ? 0 : r0) > kSpmmGapRows;       // the empty rows are cleared by the last workgroups of the grid
+    const bool gap = r1 - (t == 0 ? 0 : r0) > GAP;       // the empty rows are cleared by the last workgroups of the grid
 
     if (lane == 0 && first_y && !s.has_carry) carry_row[t] = -1;
     // No row ends in this tile, or few do and tiles sweep over the columns together: the groups take neighbouring positions, row by row.
@@ -560,10 +560,10 @@ hipError_t launch_spmm_csr_wave(int32_t rows, int32_t cols, int32_t nnz, const i
     if (nnz <= 0) return hipSuccess;
     if (k < 4) return hipErrorInvalidValue;
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
-    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4), fillers = (unsigned)spmm_fillers(rows);
+    const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4);
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? cols : 1);
 #define PSK_GO_(GG, SM)                                                                                           \
-    PSK_LAUNCH((k_spmm_wave<GG, SM>), dim3(nx + fillers, (unsigned)((k + 256 / GG - 1) / (256 / GG))), dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
+    PSK_LAUNCH((k_spmm_wave<GG, SM>), dim3(nx + (unsigned)spmm_fillers(rows, spmm_gap_rows(GG, 1)), (unsigned)((k + 256 / GG - 1) / (256 / GG))), dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
                (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, records)
 #define PSK_GO(GG) do { if (small) PSK_GO_(GG, true); else PSK_GO_(GG, false); } while (0)
     if (chunk <= 8) PSK_GO(32);

@@ -23,13 +23,13 @@ def gaps(kind, entries, rng, rows_per_entry):
     part = lambda n: rng.choice([1, 2, 40, 300], size=max(1, n // 86))
     zero = lambda n: np.zeros(n, dtype=np.int64)
     if kind == "edges":
-        runs = [zero(1025)]
-        for n in (1, 1022, 1023, 1024, 1025, 2047, 2048, 2049, 3 * 1024, 65_534, 65_535, 65_536, 16 * 1024 * 4 + 3):
-            runs += [part(entries // 14), zero(n)]
-        return np.concatenate(runs + [part(entries // 14), zero(5000)])
+        runs = [zero(2049)]
+        for n in (1, 1022, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 3 * 1024, 65_534, 65_535, 65_536, 16 * 1024 * 4 + 3):
+            runs += [part(entries // 17), zero(n)]
+        return np.concatenate(runs + [part(entries // 17), zero(5000)])
     if kind == "long rows":                       # a run inside a tile that a row reaches into and another one leaves
         runs = []
-        for n in (1000, 1024, 1500, 40_000):
+        for n in (1000, 2046, 2048, 3500, 40_000):
             runs += [part(entries // 8), np.array([900, 3]), zero(n), np.array([5, 5000]), zero(n), np.array([1])]
         return np.concatenate(runs + [part(entries // 2)])
     return (rng.random(entries * rows_per_entry) < 1 / rows_per_entry).astype(np.int64)      # "sparse": every tile spans such a number of rows
@@ -41,7 +41,7 @@ CASES = [(k, tile, kind) for k, tile in ((4, 256), (17, 256), (32, 512), (32, 20
 @pytest.mark.parametrize("k,tile,kind", CASES + [(4, 256, "sparse"), (17, 256, "sparse"), (12, 2048, "sparse")])
 def test_rows_around_long_runs(k, tile, kind):
     rng = np.random.default_rng(k)
-    A = wl.csr_from_lengths(gaps(kind, int(1.15 * 1536 * tile), rng, max(2, 2048 // tile)), 5200, seed=k)
+    A = wl.csr_from_lengths(gaps(kind, int(1.15 * 1536 * tile), rng, max(2, 3072 // tile)), 5200, seed=k)
     assert A.nnz >= 1536 * tile
     Bh = wl.dense_uniform(5200 * k, 3, wl.S_B).reshape(5200, k)
     ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh)
@@ -58,7 +58,7 @@ def test_rows_around_long_runs(k, tile, kind):
 @pytest.mark.parametrize("bs,k,tile", [(2, 8, 0), (4, 5, 0), (4, 32, 0), (8, 16, 0), (4, 12, 512)])
 def test_block_rows_around_long_runs(bs, k, tile, kind):
     rng = np.random.default_rng(k)
-    A = wl.csr_from_lengths(gaps(kind, 45_000, rng, 20), 5200, seed=k, bs=bs)
+    A = wl.csr_from_lengths(gaps(kind, 45_000, rng, 40), 5200, seed=k, bs=bs)
     Bh = wl.dense_uniform(5200 * bs * k, 3, wl.S_B).reshape(5200 * bs, k)
     ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, Bh, bs)
     C = torch.full((A.rows * bs, k + 1), float("nan"), device="cuda")
