@@ -177,10 +177,10 @@ constexpr int32_t kGroupColumns = 128;
 hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                   const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
                                   int32_t tile, int32_t over, const Workspace &w, hipStream_t s, int search, const int32_t *records);
-// k >= 4, many tiles: a wave per tile (reads the table) and per `chunk` columns, up to 256
+// k >= 4, many tiles: a wave per tile (reads the table) and per `chunk` columns, up to 256; plain: rows of C are stored through the L2
 hipError_t launch_spmm_csr_wave(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
-                                int32_t tile, int32_t over, int32_t chunk, const Workspace &w, hipStream_t s, const int32_t *records);
+                                int32_t tile, int32_t over, int32_t chunk, bool plain, const Workspace &w, hipStream_t s, const int32_t *records);
 hipError_t launch_spmm_rowsplit(int32_t rows, const int32_t *pos, const int32_t *crd, const float *vals,
                                 const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
                                 hipStream_t s);

@@ -334,13 +334,25 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     //   1994 / 1706.  4 per row: k = 64, 24 MB 615 / - / 594, 40 MB 637 / - / 667.  Ordered, 1000 per row: k = 128, 49 MB 1824 / 1632 / 1262, 15 MB 644 / 675 / 763;  k = 64,
     //   24 MB 824 / - / 641, 12 MB 657 / - / 697;  4000 per row, k = 128, 49 MB 790 / 942 / 1048.
     const bool lines = ldb % 32 == 0 && (reinterpret_cast<uintptr_t>(B) & 127) == 0;
-    const double reach = ordered ? span * b_mb : b_mb, fits = ordered ? 8.2 : 4.2;
-    int32_t chunk = k <= 256 ? k : 256;
+    // Rows of C that fill 64-byte pieces can be stored past the L2 as they come.  Others share a piece with their neighbours, which the kernels
+    // with a wave per tile store at other times: with few entries per row that is most of what these kernels do, and then the L2 has to put the
+    // pieces together (`plain` stores, while C fits the memory-side cache) or a workgroup stores neighbouring rows at once.
+    const bool pieces = k % 16 == 0 && ldc % 16 == 0 && (reinterpret_cast<uintptr_t>(C) & 63) == 0;
+    const double reach = ordered ? span * b_mb : b_mb, fits = ordered ? 8.2 : 4.2, per = (double)nnz / rows;
+    const int vec = pick_vec(B, k, ldb, C, ldc);
+    const int32_t whole = k <= 256 ? k : 256;
+    int32_t chunk = whole;
     if (lines && reach > fits && k >= 64 && k % 32 == 0) {
         int32_t c = 128;
         while (c > 32 && (c >= k || k % c != 0 || reach * c / k > fits)) c /= 2;
         if (ordered || reach * c / k <= (k == 64 ? 12.5 : 13.5)) chunk = c;
     }
+    // A chunk as large as the part of B that fits gains little where B is a little larger than that, and nothing where a row of C is all there is to do:
+    // us workgroups / chunks / wave, whole rows: k = 160, 6 per row, B 4.4 MB 200 / 245 / 183;  k = 224, 10 per row, 4.4 MB 213 / 255 / 190;  160, 1 per row, 5 MB
+    // 267 / 294 / -, 1.3 per row, 16 MB 300 / 236 / 303;  rows of C of k + 4: 224, 8 per row, 5 MB 121 / 201 / 114, 1 per row 2.5 times;  128, 100 per row, 8 MB 309 / 206 / 298.
+    const bool could = chunk < whole && !ordered;
+    if (could && !(pieces ? reach > (k <= 128 || (k % 128 == 0 && per >= 2) ? fits : 6.0) && (per >= 1.15 || b_mb > 6.1) : reach > 7 && per >= 8)) chunk = whole;
+    const bool chunked = chunk < whole;
     const int32_t *records = nullptr;
     if (ordered) {
         const hipError_t e = launch_tile_sweeps(rows, cols, nnz, pos, crd, tile, over, reach * (chunk < k ? chunk : k) / k > fits, w, s);
@@ -350,18 +362,41 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     // A wave per tile (k_spmm_wave) or a workgroup.  The first is limited by the L2, so it gains where B fits it; rows of B from
     // memory come at the fabric's rate in all kernels, and the workgroups' are a little better at that.  us, 4 M entries unless
     // stated, workgroup / wave:
-    //   tiles: 1016, B 2 MB 26 / 32 (4 per row, k = 64), 12.5 / 13.8 (100, k = 32);  1953: 40 / 34, 17.4 / 17.3, k = 128 44 / 30;  3906: 70 / 45, 27.2 / 23.3, 74 / 50
+    //   tiles: 1016, B 2 MB 26 / 32 (4 per row, k = 64), 12.5 / 13.8 (100, k = 32);  1953: 40 / 34, 17.4 / 17.3, k = 128 44 / 30;  3906: 70 / 45, 27.2 / 23.3, 74 / 50;
+    //     long rows: k = 8, 100 per row: 1953 15.1 / 17.2, 3906 21.8 / 22.2, 7812 34.9 / 33.0;  k = 12, 1563 16 / 19, 2344 17 / 20;  k = 52, 1563 0.97, 2344 0.96
+    //     (time of the second, of 1); 72 columns and more from 4.2 MB, 1563 tiles: 53 / 64;  more than 128 in quads: 1563 up to 50 / 60, 3125 up to 53 / 59, 3907 0.8 to 1.0
     //   B 2 MB: 4 per row k = 32 131 / 56;  16, k = 16 52 / 35;  1000, k = 64 60 / 49;  4, k = 6 61 / 57
     //   B 6 MB: 4 per row k = 32 128 / 67;  16, k = 24 68 / 61;  100, k = 24 56 / 62;  1000, k = 32 45 / 49;  100, k = 96 137 / 101;  16, k = 200 209 / 212
+    //   B 8 MB: k = 72, 3 per row 53 / 67, 8 per row 154 / 133
     //   B 16 MB and more: 4 per row k = 16 86 / 79, k = 32 131 / 90, 500 MB 145 / 114;  4, k = 64 176 / 184;  100, k = 32 66 / 72;  10^6 rows of 16, 488 MB, k = 128
     //   1224 / 1250;  more than 256 columns (A is walked again): 4 per row 469 / 484, 16 315 / 289
-    const bool shorts = nnz < 32ll * rows;
-    //   k = 8, 100 per row: 1953 tiles 15.1 / 17.2, 3906 21.8 / 22.2, 7812 34.9 / 33.0
-    const bool wave = k >= 4 && ntiles >= (k <= 8 && !shorts ? 6000 : 1536) &&
-                      (records || chunk < (k < 256 ? k : 256) || b_mb <= 4.5 || (shorts && k <= 64 && b_mb <= 6) || (k > 64 && k <= 128 && b_mb <= 8) ||
-                       (k > 8 && k <= 32 && nnz < 8ll * rows)) &&
-                      (k <= 256 || nnz >= 8ll * rows);
-    if (wave) return launch_spmm_csr_wave(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, chunk, w, s, records);
+    //   more than 128 in quads, up to two entries per row: 1 to 10 % lost (k = 256, 1 per row 248 / 272, 2.3 per row 911 / 710)
+    const bool shorts = nnz < 32ll * rows, quads = k > 128 && vec == 4 && !chunked && !records;
+    const int64_t tiles_for_wave = records || chunked                       ? (k <= 8 && !shorts ? 6000 : 1536)
+                                   : k <= 8 && !shorts                      ? 6000
+                                   : (quads && k < 240) || (k <= 16 && !shorts) ? 3600
+                                   : quads                                  ? 2000
+                                   : k <= 64 ? (!shorts && k % 32 ? 2000 : 1536)
+                                             : (k <= 128 && shorts && b_mb > 4.2 ? 2000 : 1536);
+    bool wave = k >= 4 && ntiles >= tiles_for_wave && (k <= 256 || per >= 8) &&
+                (records || chunked || b_mb <= 4.5 || (shorts && k <= 64 && b_mb <= 6) || (k > 64 && k <= 128 && b_mb <= (per >= 7 ? 8 : 6.1)) ||
+                 (k > 8 && k <= 32 && per < 8) || (k > 128 && could && b_mb <= (vec == 1 ? 10 : 6))) &&
+                !(quads && per < (ntiles >= 7000 ? 2.15 : 2.5));
+    // Few entries per row of C and no whole pieces: `lo`, the entries per row from which a wave per tile with plain stores is the faster one (it is
+    // again below 0.75, where most rows are empty).  us workgroup / wave past the L2 / wave plain, 2 M entries: 1 per row, k = 8, B 1 MB 39 / 87 / 32, 4 MB 41 / 89 / 43;
+    //   k = 12, 4 MB 54 / 116 / 53, 16 MB 65 / 119 / 73;  k = 24, 4 MB 83 / 126 / 71, 16 MB 90 / 129 / 93;  k = 100, 1 MB 280 / 300 / 187;  2 per row, k = 8, 4 MB 36 / 49 / 32;
+    //   k = 24, 4 MB 75 / 72 / 47;  3 per row, k = 8, 6 MB, 4 M 67 / 86 / 80;  k = 72, 8 MB 53 / 67 / 67;  4 per row, k = 40 35 / 24 / 27;  C of 416 MB, k = 13, 1 per row 195 / 496 / 258
+    const bool few = wave && !pieces && !chunked && !records && k <= 128 && per < 3.5;
+    const bool fits_mall = (double)rows * ldc * 4 <= 256.0 * (1 << 20);
+    bool plain = false;
+    if (few && per < 0.75) plain = k <= 64;
+    else if (few) {
+        const double lo = !fits_mall ? 2.6 : k <= 8 ? (b_mb <= 2.1 ? 1.85 : b_mb <= 4.5 ? 2.6 : 3.5) : k <= 16 ? (b_mb <= 4.5 ? 0 : 2.5) :
+                          k <= 32 ? (b_mb <= 8 ? 0 : 1.85) : k <= 64 || b_mb <= 2.1 || (per < 1.85 && (b_mb <= 5.1 || vec == 1)) ? 0 : 3.5;
+        wave = per >= lo;
+        plain = fits_mall;
+    }
+    if (wave) return launch_spmm_csr_wave(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, chunk, plain, w, s, records);
     if (groups) return launch_spmm_csr_narrow(rows, cols, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search, records);
     return launch_spmm_pos<1>(rows, nnz, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
 }

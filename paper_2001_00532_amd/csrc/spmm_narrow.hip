@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos_group(int rows, int nnz, const
 // workgroups wait on barriers) and now: 40 000 rows of 1000 x 25 000, k = 32 360 -> 252;  6000 columns, k = 128 1130 -> 690;  10^6 rows of 16,
 // 25 000 columns, k = 16 186 -> 111, k = 32 228 -> 128;  of 5, k = 32 141 -> 75.  Eight steps of loads in flight against four: k = 8 231 -> 205, k = 128
 // 705 -> 660; more waves per CU (fewer registers) gain nothing.
-template <int G, bool SMALL>
+template <int G, bool SMALL, bool PLAIN>
 __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int *__restrict__ pos, const int *__restrict__ crd,
                                                    const float *__restrict__ vals, const float *__restrict__ B, int k,
                                                    long long ldb, float *__restrict__ C, long long ldc,
@@ -309,7 +309,10 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
         return row[0];
     };
     auto store = [&](int r, const auto (&o)[4]) {
-        __builtin_nontemporal_store(V{(float)o[0], (float)o[1], (float)o[2], (float)o[3]}, reinterpret_cast<V *>(C + (long long)r * ldc + col));
+        const V v = {(float)o[0], (float)o[1], (float)o[2], (float)o[3]};
+        V *const to = reinterpret_cast<V *>(C + (long long)r * ldc + col);
+        if constexpr (PLAIN) *to = v;
+        else __builtin_nontemporal_store(v, to);
     };
     auto emit = [&](int r, const double (&o)[4]) {                  // a row that may have begun in an earlier tile
         if (s.has_carry && r == r0) {
@@ -361,7 +364,8 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
                 r += WAVE;
                 if (rb + WAVE < rend) { ps = r < rend ? pos[r] : 0; pe = r < rend ? pos[r + 1] : 1; }
                 each_empty_row<G>(empty, rb, g, [&](int row) {
-                    if (active) __builtin_nontemporal_store(V{}, reinterpret_cast<V *>(C + (long long)row * ldc + col));
+                    const float zero[4] = {};
+                    if (active) store(row, zero);
                 });
                 rfrom = rb;
                 if (later) break;                 // the other rows end, or lie empty, in later blocks
@@ -555,17 +559,18 @@ hipError_t launch_spmm_csr_narrow(int32_t rows, int32_t cols, int32_t nnz, const
 
 hipError_t launch_spmm_csr_wave(int32_t rows, int32_t cols, int32_t nnz, const int32_t *pos, const int32_t *crd,
                                 const float *vals, const float *B, int32_t k, int64_t ldb, float *C, int64_t ldc,
-                                int32_t tile, int32_t over, int32_t chunk, const Workspace &w, hipStream_t s, const int32_t *records)
+                                int32_t tile, int32_t over, int32_t chunk, bool plain, const Workspace &w, hipStream_t s, const int32_t *records)
 {
     if (nnz <= 0) return hipSuccess;
     if (k < 4) return hipErrorInvalidValue;
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4);
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? cols : 1);
-#define PSK_GO_(GG, SM)                                                                                           \
-    PSK_LAUNCH((k_spmm_wave<GG, SM>), dim3(nx + (unsigned)spmm_fillers(rows, spmm_gap_rows(GG, 1)), (unsigned)((k + 256 / GG - 1) / (256 / GG))), dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
+    plain = plain && small;
+#define PSK_GO_(GG, SM, PL)                                                                                       \
+    PSK_LAUNCH((k_spmm_wave<GG, SM, PL>), dim3(nx + (unsigned)spmm_fillers(rows, spmm_gap_rows(GG, 1)), (unsigned)((k + 256 / GG - 1) / (256 / GG))), dim3(256), 4u * ((kWaveBlock + GG) * 8u + kWaveBlock * 2u), s, rows, nnz, pos, crd, vals, B, k, (long long)ldb, C, \
                (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over, records)
-#define PSK_GO(GG) do { if (small) PSK_GO_(GG, true); else PSK_GO_(GG, false); } while (0)
+#define PSK_GO(GG) do { if (plain) PSK_GO_(GG, true, true); else if (small) PSK_GO_(GG, true, false); else PSK_GO_(GG, false, false); } while (0)
     if (chunk <= 8) PSK_GO(32);
     else if (chunk <= 16) PSK_GO(16);
     else if (chunk <= 32) PSK_GO(8);
