@@ -354,8 +354,8 @@ __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const 
 // 96 248 -> 187;  1.4 M leaves, j = 12 64 -> 26, 64 60 -> 48;  0.2 M, j = 64 54 -> 28.
 // Sums of leaves: even and odd ones apart, groups and records in fp64 (errors, j = 16 1.49e-7 -> 0.82e-7 of the result, 64 1.69 -> 1.25, 200 2.68 ->
 // 1.95).
-// SMALL: byte offsets into C and D fit 32 bits.
-template <int G, bool SMALL>
+// SMALL: byte offsets into C and D fit 32 bits.  PLAIN: rows of A are stored through the L2.
+template <int G, bool SMALL, bool PLAIN>
 __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const int *__restrict__ crd_i,
                                                      const int *__restrict__ pos_k, const int *__restrict__ crd_k,
                                                      const int *__restrict__ pos_l, const int *__restrict__ crd_l,
@@ -410,7 +410,9 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
     if (tid < 2 * NW) srec_row[tid] = -2;
     if (tid == 0 && blockIdx.y == 0 && !has_carry) carry_row[t] = -1;
     auto store = [&](int r, v4f o) {
-        __builtin_nontemporal_store((v4f_u)o, reinterpret_cast<v4f_u *>(A + (long long)(crd_i ? crd_i[r] : r) * lda + col));
+        v4f_u *const to = reinterpret_cast<v4f_u *>(A + (long long)(crd_i ? crd_i[r] : r) * lda + col);
+        if constexpr (PLAIN) *to = o;
+        else __builtin_nontemporal_store((v4f_u)o, to);
     };
 #pragma unroll
     for (int u = 0; u < LD; ++u) {
@@ -584,22 +586,38 @@ hipError_t launch_mttkrp_main(int64_t dim_k, int64_t dim_l, int32_t nslices, int
 #define PSK_RUNS(G)                                                                                             \
     do {                                                                                                         \
         const size_t lds = ((size_t)2 * (tile + 4 * G) + tile) * 4 + (size_t)tile * 2;                           \
-        if (small) PSK_GO((k_mttkrp_runs<G, true>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                    \
-        else PSK_GO((k_mttkrp_runs<G, false>), dim3(nx, (j + 256 / G - 1) / (256 / G)));                         \
+        const dim3 grid(nx, (j + 256 / G - 1) / (256 / G));                                                      \
+        if (small && plain) PSK_GO((k_mttkrp_runs<G, true, true>), grid);                                        \
+        else if (small) PSK_GO((k_mttkrp_runs<G, true, false>), grid);                                           \
+        else PSK_GO((k_mttkrp_runs<G, false, false>), grid);                                                     \
     } while (0)
+    // Few leaves per slice and rows of A that don't fill 64-byte pieces: their parts reach memory one by one, a slice here and one
+    // there.  Through the L2 where A fits the memory-side cache (j = 18, a leaf each, A 63 MB 121 -> 49 us, before this kernel 97;  52, 74 MB 99 -> 45, 67;  160, A 194 MB
+    // 182 -> 66, 141; no gain below 32 MB); above that whole rows at once (160, 965 MB: 32 columns 947, whole 384;  96, 2367 MB: whole 1211, 64 columns 1674;  but
+    // up to 64 columns still through the L2, 0.91 of the time), or the wide kernel where its lanes own two columns and more (160, 300 MB 0.96).
+    const bool few = (j % 16 != 0 || lda % 16 != 0 || (reinterpret_cast<uintptr_t>(A) & 63) != 0) && (int64_t)nnz < 5ll * nslices;
+    const double a_mb = (double)nslices * (double)lda * 4 / (1 << 20);
+    const bool large = few && a_mb > 256, plain = few && a_mb > 32 && (j <= 64 ? (int64_t)nnz < 3ll * nslices : !large);
     // Columns per group of lanes (us, all launches):
     //   few tiles: narrow chunks, so that the runs are short.  100 tiles, j = 24 16 columns 25, 32 31;  64: 16 29, 32 35, 64 46.  357 tiles, 24: 16 27, 32 31;
-    //     48: 16 35, 32 37, 64 48;  64: 16 48, 32 38, 64 49;  128: 32 71, 64 61, 128 74.  666 tiles, 24: 16 42, 32 32;  64: 32 55, 64 49;  128: 64 81, 128 70
+    //     48: 16 35, 32 37, 64 48;  64: 16 48, 32 38, 64 49;  128: 32 71, 64 61, 128 74.  666 tiles, 24: 16 42, 32 32;  64: 32 55, 64 49;  128: 64 81, 128 70.
+    //     448 tiles, 40: 16 61, 32 47, 64 42.  194 tiles, 100: 16 60, 32 46, 64 43
     //   halves: rows of D that begin 128-byte lines and a D above the L2's size: 32 columns, so that the L2s hold the rows of one
     //     chunk at a time.  D 9.8 MB, 2.9 M leaves, 64: 129 -> 90;  12 MB, 18.6 M, 64: 64 columns 557, 32 425;  24 MB, 46.7 M, 64: 1646, 1416, 128: 49 MB 3530,
-    //     2969;  but D 4.9 MB, 5.8 M: 129, 132
+    //     2969;  but D 4.9 MB, 5.8 M: 129, 132;
+    //     more than 128 columns from 5 MB on (256, 6 MB: 3.2 M 420 -> 335, 7.2 M 1782 -> 1186, both in 64 columns)
     //   more than 128 columns (A would be walked twice): the wide kernel (60 000 slices, 200 columns: 359 against 371 in 256 columns), unless
-    //     halves (160: 266 -> 196, 256: 374 -> 296), its lanes cannot own two columns, or tiles are few (100: 200 60 -> 45)
-    const bool halves = lines && 4 * dim_l * j > (int64_t(6) << 20);
-    if (j >= 4 && (j <= 128 || vec == 1 || halves || ntiles <= 256)) {
+    //     halves (160: 266 -> 196, 256: 374 -> 296), its lanes cannot own two columns, or tiles are few (100: 200 60 -> 45;  up to 370
+    //     tiles and more than 5 leaves per slice (whose parts of A are then not what takes the time): 160, 295 tiles 77 -> 43 in 64 columns, 130, 265 to 360 80 -> 57;  fewer: 343 tiles, 3 per slice 105, 135)
+    const bool halves = lines && !large && 4 * dim_l * j > (int64_t(j <= 128 ? 6 : 5) << 20);
+    const bool some = j > 128 && vec > 1 && ntiles <= 370 && (int64_t)nnz >= 6ll * nslices;
+    if (j >= 4 && (j <= 128 || vec == 1 || halves || ntiles <= 256 || some)) {
         if (j <= 8) PSK_RUNS(32);
-        else if (j <= 16 || (ntiles <= 450 && j <= 48) || (ntiles <= 200 && j <= 128)) PSK_RUNS(16);
-        else if (ntiles <= 450 && j > 96 && j <= 128) PSK_RUNS(4);
+        else if (j <= 16 || (ntiles <= 450 && j <= 32) || (ntiles <= 300 && j <= 48) || (ntiles <= (j <= 64 ? 200 : 150) && j <= 128)) PSK_RUNS(16);
+        else if (large && j > 64 && (j <= 128 || ntiles <= 256)) PSK_RUNS(2);
+        else if (large && j > 128) PSK_RUNS(1);
+        else if (some && !halves && ntiles > 256) PSK_RUNS(4);
+        else if (ntiles > 200 && ntiles <= 450 && j > 96 && j <= 128) PSK_RUNS(4);
         else if (j <= 32 || halves || ntiles <= 450) PSK_RUNS(8);
         else if (j <= 64) PSK_RUNS(4);
         else if (j <= 128) PSK_RUNS(2);

@@ -47,3 +47,52 @@ def test_table(tile):
     s, f = psk.psk_partition_csf3(dev(T.pos_k), dev(T.pos_l), T.nnz, tile)
     ref_s, ref_f = oracle.partition_csf3(T.pos_k, T.pos_l, tile)
     assert (s.cpu().numpy() == ref_s).all() and (f.cpu().numpy() == ref_f).all()
+
+
+def few_leaves(j, pad, per, slices, seed):
+    """Slices of about `per` leaves, rows of A of j + pad elements."""
+    rng = np.random.default_rng(seed)
+    T = wl.csf3_from_lengths(np.ones(slices, dtype=np.int64), rng.choice([0, 1, 2, 3][:per + 1], size=slices) if per < 3 else np.full(slices, per),
+                             (slices, 300, 900), seed=seed)
+    return T, wl.dense_uniform(300 * j, 4, wl.S_B).reshape(300, j), wl.dense_uniform(900 * j, 5, wl.S_B).reshape(900, j)
+
+
+@pytest.mark.parametrize("j,pad,per,slices", [(5, 0, 1, 450_000), (12, 1, 2, 300_000), (18, 0, 3, 120_000), (33, 0, 1, 140_000), (64, 4, 1, 140_000), (66, 0, 2, 140_000),
+                                              (100, 4, 4, 100_000), (130, 0, 1, 100_000), (160, 1, 3, 60_000), (200, 0, 1, 50_000), (72, 0, 1, 950_000), (257, 0, 1, 270_000)])
+def test_few_leaves_per_slice(j, pad, per, slices):
+    """Rows of A that share 64-byte pieces with their neighbours: stored through the L2 (A from 32 to 256 MB), whole above."""
+    T, C, D = few_leaves(j, pad, per, slices, j)
+    ref, mag = oracle.mttkrp_csf3(T.pos_k, T.crd_k, T.pos_l, T.crd_l, T.vals, C, D)
+    out = torch.full((slices, j + pad), float("nan"), device="cuda")
+    psk.psk_mttkrp_csf3((slices, 300, 900), None, dev(T.pos_k), dev(T.crd_k), dev(T.pos_l), dev(T.crd_l), dev(T.vals), dev(C), dev(D), out[:, :j])
+    got = out.cpu().numpy()
+    assert np.isnan(got[:, j:]).all(), "columns past j were written"
+    ok, worst = oracle.within_tolerance(got[:, :j], ref, mag)
+    assert ok, "%.3g of the bar" % worst
+
+
+def test_narrow_rows_take_no_longer_than_wide_ones():
+    """800 000 slices of one leaf: rows of 18 columns share 64-byte pieces of A and rows of 32 fill them.  Stored past the L2 one by one the
+    former took 111 us, the latter 62."""
+    took = {}
+    for j in (18, 32):
+        T, C, D = few_leaves(j, 0, 4, 10, j)
+        n = 800_000
+        k = np.arange(n, dtype=np.int32) % 300
+        l = (np.arange(n, dtype=np.int64) * 7919 % 900).astype(np.int32)
+        pos = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+        out = torch.empty((n, j), device="cuda")
+        args = ((n, 300, 900), None, pos, dev(k), pos, dev(l), torch.ones(n, device="cuda"), dev(C), dev(D), out)
+        ws = psk.workspace(psk.PSK_OP_MTTKRP_CSF3, n, n, k=j)
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                psk.psk_mttkrp_csf3(*args, ws=ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        took[j] = min(times)
+    print(took, flush=True)
+    assert took[18] <= 1.2 * took[32]
