@@ -8,8 +8,11 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
+
+from .build import built_for
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpsk.so")
@@ -53,8 +56,26 @@ class PskError(RuntimeError):
 
 _lib = None
 _lib_path = LIB_PATH
-_marshal = None                                  # the native side of a call (csrc/marshal.cpp)
+_marshal = None                                  # the native side of a call (csrc/marshal.cpp), None: the Python functions do its work
 _spmv_address = {}
+
+
+def _spmv(*args):                                # lib() puts the native one here; None: not done
+    return None
+
+
+def _native_side():
+    """_marshal.so if it is there and was built for this torch and Python (it reads tensors through their C++ objects).  Without
+    it everything works as with it, a call takes 1.5 us longer."""
+    try:
+        from . import _marshal as native
+        if native.built_for == built_for():
+            return native
+        why = "it was built for %s, this is %s" % (native.built_for, built_for())
+    except (ImportError, AttributeError) as e:
+        why = str(e)
+    warnings.warn("the native side of a call is not used (%s); `python -m paper_2001_00532_amd.build` builds it" % why)
+    return None
 
 
 def use_instrumented_library() -> None:
@@ -68,7 +89,7 @@ def use_instrumented_library() -> None:
 
 def lib() -> ctypes.CDLL:
     """The loaded library.  Raises if it has not been built (python -m paper_2001_00532_amd.build)."""
-    global _lib, _marshal, _ptr
+    global _lib, _marshal, _ptr, _spmv
     if _lib is None:
         if not os.path.exists(_lib_path):
             raise RuntimeError("%s is not built; run `python -m paper_2001_00532_amd.build`" % os.path.basename(_lib_path))
@@ -138,12 +159,10 @@ def lib() -> ctypes.CDLL:
         L.psk_spmm_csr_rowsplit.argtypes = [i64, i64, i64, p, p, p, p, i32, i64, p, i64, p]
         L.psk_spmm_csr_rowsplit.restype = ci
         if _marshal is None:
-            try:
-                from . import _marshal as native
-            except ImportError as e:
-                raise RuntimeError("_marshal.so is not built; run `python -m paper_2001_00532_amd.build`") from e
-            native.use(_ptr_checked, _stream)
-            _marshal, _ptr = native, native.ptr
+            native = _native_side()
+            if native is not None:
+                native.use(_ptr_checked, _stream)
+                _marshal, _ptr, _spmv = native, native.ptr, native.spmv
         for f64, f in ((0, L.psk_spmv_csr), (1, L.psk_spmv_csr_f64)):
             _spmv_address[f64] = ctypes.cast(f, ctypes.c_void_p).value
         _lib = L
@@ -305,9 +324,9 @@ def psk_spmv_csr(rows, cols, nnz, pos, crd, vals, x, y, tile=0, col_passes=1, ph
         _temporary_ws_ok(phases, "psk_spmv_csr")
         ws = _csr_ws(rows, nnz, tile, pos.device, stream)
     L = _lib or lib()
-    st = _marshal.spmv(0, _spmv_address[0], rows, cols, nnz, pos, crd, vals, x, y, tile, col_passes, phases, ws,
-                       None if stream is None else stream.cuda_stream)
-    if st is None:                               # something that is not a plain tensor
+    st = _spmv(0, _spmv_address[0], rows, cols, nnz, pos, crd, vals, x, y, tile, col_passes, phases, ws,
+               None if stream is None else stream.cuda_stream)
+    if st is None:                               # something that is not a plain tensor, or no native side
         st = L.psk_spmv_csr(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
                                 _ptr(vals, torch.float32), _ptr(x, torch.float32), _ptr(y, torch.float32), int(tile),
                                 int(col_passes), int(phases), _ptr(ws), ws.numel(), _stream(stream))
@@ -438,9 +457,9 @@ def psk_spmv_csr_f64(rows, cols, nnz, pos, crd, vals, x, y, tile=0, col_passes=1
         _temporary_ws_ok(phases, "psk_spmv_csr_f64")
         ws = workspace(PSK_OP_SPMV_CSR_F64, rows, nnz, tile=tile, device=pos.device, stream=stream)
     L = _lib or lib()
-    st = _marshal.spmv(1, _spmv_address[1], rows, cols, nnz, pos, crd, vals, x, y, tile, col_passes, phases, ws,
-                       None if stream is None else stream.cuda_stream)
-    if st is None:                               # something that is not a plain tensor
+    st = _spmv(1, _spmv_address[1], rows, cols, nnz, pos, crd, vals, x, y, tile, col_passes, phases, ws,
+               None if stream is None else stream.cuda_stream)
+    if st is None:                               # something that is not a plain tensor, or no native side
         st = L.psk_spmv_csr_f64(int(rows), int(cols), int(nnz), _ptr(pos, torch.int32), _ptr(crd, torch.int32),
                                     _ptr(vals, torch.float64), _ptr(x, torch.float64), _ptr(y, torch.float64),
                                     int(tile), int(col_passes), int(phases), _ptr(ws), ws.numel(), _stream(stream))

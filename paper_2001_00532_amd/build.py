@@ -20,6 +20,7 @@ OUT_TRACE = os.path.join(HERE, "libpsk_trace.so")
 OBJDIR_TRACE = os.path.join(HERE, "_build_trace")
 
 OUT_MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL_FOR = os.path.join(OBJDIR, "marshal_built_for")
 
 SOURCES = ["api.hip", "partition.hip", "spmv_csr.hip", "spmm.hip", "spmv_bcsr.hip", "mttkrp.hip", "spmv_csr_f64.hip", "spmv_csr_divide.hip", "spmv_bcsr_g.hip", "spmm_narrow.hip", "spmm_blocks.hip", "slab.hip", "api_slab.hip", "calibrate.hip"]
 HEADERS = ["psk_dev.h", "psk_internal.h", os.path.join("..", "..", "include", "psk.h")]
@@ -52,11 +53,28 @@ def _compile(src: str, objdir: str = OBJDIR, extra=()) -> str:
     return obj
 
 
+def built_for() -> str:
+    """What _marshal.so depends on beside its source."""
+    import torch
+
+    return "torch %s, Python %d.%d" % (torch.__version__, *sys.version_info[:2])
+
+
+def _marshal_stale() -> bool:
+    if not os.path.exists(OUT_MARSHAL) or os.path.getmtime(os.path.join(CSRC, "marshal.cpp")) > os.path.getmtime(OUT_MARSHAL):
+        return True
+    try:
+        with open(MARSHAL_FOR) as f:
+            return f.read() != built_for()
+    except OSError:
+        return True
+
+
 def stale() -> bool:
     if not os.path.exists(OUT):
         return True
     t = os.path.getmtime(OUT)
-    if not os.path.exists(OUT_MARSHAL) or os.path.getmtime(os.path.join(CSRC, "marshal.cpp")) > os.path.getmtime(OUT_MARSHAL):
+    if _marshal_stale():
         return True
     deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS]
     return any(os.path.getmtime(d) > t for d in deps)
@@ -69,6 +87,7 @@ def _link(objs, out: str) -> None:
 
 
 def _marshal() -> None:
+    """_marshal.so, for this torch and Python.  Where it can't be built the package works without it."""
     import sysconfig
 
     import torch
@@ -76,11 +95,19 @@ def _marshal() -> None:
 
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     inc = [a for p in include_paths() + [sysconfig.get_paths()["include"]] for a in ("-isystem", p)]
-    abi = "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)
-    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", abi, *inc,
-                           os.path.join(CSRC, "marshal.cpp"), "-o", OUT_MARSHAL + ".tmp", "-L" + lib, "-Wl,-rpath," + lib,
-                           "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    defs = ["-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DPSK_BUILT_FOR="%s"' % built_for()]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *defs, *inc, os.path.join(CSRC, "marshal.cpp"),
+           "-o", OUT_MARSHAL + ".tmp", "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    try:
+        subprocess.check_call(cmd)
+    except (OSError, subprocess.CalledProcessError) as e:
+        sys.stderr.write("_marshal.so could not be built, the package works without it: %s\n" % e)
+        if os.path.exists(OUT_MARSHAL):
+            os.remove(OUT_MARSHAL)
+        return
     os.replace(OUT_MARSHAL + ".tmp", OUT_MARSHAL)
+    with open(MARSHAL_FOR, "w") as f:
+        f.write(built_for())
 
 
 def build(force: bool = True) -> str:

@@ -107,4 +107,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", PSK_BUILT_FOR) < 0) Py_CLEAR(m);      // the torch and Python whose headers these are
+    return m;
+}

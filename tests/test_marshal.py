@@ -1,4 +1,8 @@
 """The native side of a call: plain tensors by their C++ object, everything else as the Python function decides."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -26,6 +30,55 @@ def test_what_is_not_plain_is_refused_as_before():
         psk.psk_spmv_csr(1, 1, 1, i, i, f, f, f, ws=f)
     with pytest.raises((TypeError, ValueError)):
         psk.psk_spmv_csr("a", 1, 1, i, i, f, f, f, ws=f)
+
+
+WITHOUT = """
+import sys, types, warnings
+import torch
+{prepare}
+import paper_2001_00532_amd as psk, paper_2001_00532_amd.binding as binding
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    psk.lib()
+assert len(seen) == 1 and {words!r} in str(seen[0].message), [str(w.message) for w in seen]
+assert binding._marshal is None and binding._ptr is binding._ptr_checked
+assert psk.psk_default_tile(psk.PSK_OP_SPMV_CSR) > 0
+if torch.cuda.is_available():
+    for dtype, f, op in ((torch.float32, psk.psk_spmv_csr, psk.PSK_OP_SPMV_CSR), (torch.float64, psk.psk_spmv_csr_f64, psk.PSK_OP_SPMV_CSR_F64)):
+        i = lambda *a: torch.tensor(a, dtype=torch.int32, device="cuda")
+        v = lambda *a: torch.tensor(a, dtype=dtype, device="cuda")
+        y = f(3, 3, 3, i(0, 2, 2, 3), i(0, 2, 1), v(1, 2, 3), v(1, 10, 100), torch.empty(3, dtype=dtype, device="cuda"), ws=psk.workspace(op, 3, 3))
+        assert y.cpu().tolist() == [201, 0, 30]
+f, i = torch.zeros(4), torch.zeros(4, dtype=torch.int32)
+try:
+    psk.psk_spmv_csr(1, 1, 1, i, i, f, f, f, ws=f)
+except ValueError as e:
+    assert "device tensor" in str(e)
+else:
+    raise AssertionError("a host tensor was taken")
+print("as before")
+"""
+
+
+def without(prepare, words):
+    r = subprocess.run([sys.executable, "-c", WITHOUT.format(prepare=prepare, words=words)], capture_output=True, text=True,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == 0 and "as before" in r.stdout, r.stderr
+
+
+MISSING = ("sys.modules['paper_2001_00532_amd._marshal'] = None", "_marshal")
+FOREIGN = ("m = types.ModuleType('paper_2001_00532_amd._marshal'); m.built_for = 'torch 1.0, Python 2.7'; sys.modules[m.__name__] = m", "torch 1.0")
+
+
+@pytest.mark.parametrize("prepare,words", [MISSING, FOREIGN])
+def test_everything_works_without_the_native_side(prepare, words):
+    """Not built, or built for another torch: the Python functions do its work, as for tensors that are not plain."""
+    without(prepare, words)
+
+
+@pytest.mark.gpu
+def test_products_without_the_native_side():
+    without(*MISSING)
 
 
 @pytest.mark.gpu
