@@ -1,13 +1,12 @@
 """Block SpMM of up to 64 columns, a wave per tile: group widths, block rows that end inside a group's run, at its borders and
 behind the tile, empty block rows (more than 16 bits number among them), few and many tiles, NaN and Inf.  Oracle and bar as for
 the other SpMM tests: |got - ref| <= 1e-5 * sum |a b| + 1e-30."""
-import dataclasses
-
 import numpy as np
 import pytest
 
 import oracle
 import workloads as wl
+from test_gpu_spmm_wave import same_specials, with_specials
 
 pytestmark = pytest.mark.gpu
 
@@ -68,20 +67,40 @@ def test_runs_of_empty_block_rows():
     assert ok, "%.3g of the bar" % worst
 
 
-@pytest.mark.parametrize("bs", [2, 4, 8])
-def test_nan_and_inf_reach_only_their_block_rows(bs):
-    rng = np.random.default_rng(bs)
-    A = wl.csr_from_lengths(rng.choice([0, 1, 2, 9, 70], size=2600), 300, seed=bs, bs=bs)
-    assert A.nnz >= 600 * 64 or bs >= 4
-    crd = A.crd.copy()
-    crd[(crd < 3) & (rng.random(crd.size) > 1e-3)] = 5
-    A = dataclasses.replace(A, crd=crd)
-    Bh = wl.dense_uniform(300 * bs * 25, 3, wl.S_B).reshape(300 * bs, 25)
-    Bh[0], Bh[bs], Bh[2 * bs + 1] = np.nan, np.inf, -np.inf
+@pytest.mark.parametrize("length", [3, 9, 70])
+@pytest.mark.parametrize("bs,k", [(2, 24), (2, 7), (4, 8), (4, 32), (4, 48), (8, 16), (8, 64)])
+def test_nan_inf_and_overflow_reach_only_their_block_rows(bs, k, length):
+    """Block column 0 among them: places that hold no block must not bring it in.  (8 x 8: the same kinds in the first column of the block.)"""
+    rng = np.random.default_rng(bs + length)
+    A = wl.csr_from_lengths(np.full(600 * 64 // length + 40, length), 300, seed=bs, bs=bs)
+    assert A.nnz >= 600 * 64
+    A, count = with_specials(A, rng, bs)
+    assert (count >= 10).all()
+    Bh = wl.dense_uniform(300 * bs * k, 3, wl.S_B).reshape(300 * bs, k)
+    Bh[0], Bh[bs], Bh[2 * bs], Bh[3 * bs] = np.nan, np.inf, -np.inf, 2e38
     with np.errstate(invalid="ignore"):
-        ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, np.ascontiguousarray(Bh[:, :24]), bs)
-    got = product(A, bs, Bh, 24)
-    assert (np.isnan(got) == np.isnan(ref)).all()
-    fin = np.isfinite(ref) & np.isfinite(mag)
-    assert (got[~fin & ~np.isnan(ref)] == ref[~fin & ~np.isnan(ref)]).all()
-    assert (np.abs(got[fin] - ref[fin]) <= 1e-5 * mag[fin] + 1e-30).all()
+        ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, Bh, bs)
+    same_specials(product(A, bs, Bh, k), ref, mag)
+
+
+@pytest.mark.parametrize("bs,k", [(2, 8), (2, 40), (4, 5), (4, 32), (4, 64), (8, 12), (8, 48)])
+def test_offsets_beyond_32_bits(bs, k):
+    """B as rows far apart: from 2^30 floats of rows * ldb on the byte offsets into B don't fit 32 bits.  One row stride on either side, the last
+    rows of B referred to."""
+    cols = 280
+    A = wl.csr_from_lengths(np.full(5500, 8), cols, seed=k, bs=bs)
+    assert A.crd.max() == cols - 1 and A.nnz >= 600 * 64
+    n = cols * bs
+    Bh = wl.dense_uniform(n * k, 5, wl.S_B).reshape(n, k)
+    ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, Bh, bs)
+    most = (2 ** 32 - 1) // 4 // n
+    buf = torch.empty(n * (most + 1), device="cuda")
+    for ld in (most, most + 1):
+        B = buf[:n * ld].view(n, ld)[:, ld - k:]
+        B.copy_(dev(Bh))
+        C = torch.full((A.rows * bs, k), float("nan"), device="cuda")
+        print("bcsr spmm wave offsets bs", bs, "k", k, "ld", ld, flush=True)
+        psk.psk_spmm_bcsr(A.rows, cols, A.nnz, bs, dev(A.pos), dev(A.crd), dev(A.vals), B, C)
+        torch.cuda.synchronize()
+        ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, mag)
+        assert ok, "bs %d k %d ld %d: %.3g of the bar" % (bs, k, ld, worst)

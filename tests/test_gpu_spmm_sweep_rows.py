@@ -2,13 +2,12 @@
 tiles and of the blocks that longer tiles are staged in, empty rows between, tiles with as many row ends as are still walked row by row
 and with more, operands in one piece and in chunks of columns, phases one by one, NaN and Inf.  Oracle and bar as for the
 other SpMM tests: |got - ref| <= 1e-5 * sum |a b| + 1e-30."""
-import dataclasses
-
 import numpy as np
 import pytest
 
 import oracle
 import workloads as wl
+from test_gpu_spmm_wave import same_specials, with_specials
 
 pytestmark = pytest.mark.gpu
 
@@ -63,16 +62,18 @@ def test_row_ends(tile, k):
     assert (product(A, Bh, k, tile, (1, 2, 4)) == got).all(), "one phase at a time"
 
 
-def test_nan_and_inf_reach_only_their_rows():
-    A, Bh = operand(256, 32, 5)
-    crd = np.maximum(A.crd, 3)
-    crd[7::40009], crd[11::50021], crd[13::60013] = 0, 1, 2
-    A = dataclasses.replace(A, crd=crd)
-    Bh[0], Bh[1], Bh[2] = np.nan, np.inf, -np.inf
+@pytest.mark.parametrize("tile,k", [(256, 32), (256, 64), (512, 24), (1024, 96)])
+def test_nan_inf_and_overflow_reach_only_their_rows(tile, k):
+    """In short rows of tiles with more row ends than are walked row by row, and in rows of several tiles."""
+    A, Bh = operand(tile, k, 5)
+    lengths = np.diff(A.pos)
+    first = A.pos[:-1] // tile
+    ends = np.bincount(A.pos[1:][lengths > 0] // tile, minlength=A.nnz // tile + 2)          # about: rows that end in each tile
+    short, long = (lengths >= 3) & (lengths < 8) & (ends[first] > 5), lengths > 2 * tile
+    rows = np.sort(np.concatenate([np.flatnonzero(short)[::2], np.flatnonzero(long)[::3]]))
+    A, count = with_specials(A, np.random.default_rng(k), rows=rows)
+    assert short.sum() >= 100 and long.sum() >= 100 and (count >= 10).all()
+    Bh[0], Bh[1], Bh[2], Bh[3] = np.nan, np.inf, -np.inf, 2e38
     with np.errstate(invalid="ignore"):
         ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh)
-    got = product(A, Bh, 32, 256)
-    assert np.isnan(ref).any() and (np.isnan(got) == np.isnan(ref)).all()
-    fin = np.isfinite(ref) & np.isfinite(mag)
-    assert (got[~fin & ~np.isnan(ref)] == ref[~fin & ~np.isnan(ref)]).all()
-    assert (np.abs(got[fin] - ref[fin]) <= 1e-5 * mag[fin] + 1e-30).all()
+    same_specials(product(A, Bh, k, tile), ref, mag)

@@ -70,21 +70,22 @@ def test_runs_of_empty_rows():
     assert ok, "%.3g of the bar" % worst
 
 
-def with_specials(A, rng):
-    """Every 7th row with entries refers to NaN, to Inf, to -Inf, to both, or to three finite products whose sum passes the fp32 range
-    (rows 0 to 3 of B), at early, middle and last places of the row; nobody else does.  The number of entries of each kind."""
-    crd, vals = np.maximum(A.crd, 4), A.vals.copy()
+def with_specials(A, rng, bs=1, rows=None):
+    """Every 7th row of three entries and more (or every one of `rows`) refers to NaN, to Inf, to -Inf, to both, or to three finite products
+    whose sum passes the fp32 range (rows 0 to 3 of B; of blocks their first rows), at early, middle and last places of the row;
+    nobody else does.  The number of entries of each kind."""
+    crd, vals = np.maximum(A.crd, 4), A.vals.reshape(A.nnz, bs, bs).copy()
     lengths = np.diff(A.pos)
     count = np.zeros(4, dtype=int)
-    for i, r in enumerate(np.flatnonzero(lengths >= 3)[::7]):
+    for i, r in enumerate(np.flatnonzero(lengths >= 3)[::7] if rows is None else rows):
         n = int(lengths[r])
         at = [int(rng.integers(min(n, 8))), int(rng.integers(n)), n - 1][(i // 5) % 3]
         kinds = ((0,), (1,), (2,), (1, 2), (3, 3, 3))[i % 5]
         for m, c in enumerate(kinds):
             p = A.pos[r] + (at + m) % n
-            crd[p], vals[p] = c, 1.0
+            crd[p], vals[p, :, 0] = c, 1.0
             count[c] += 1
-    return dataclasses.replace(A, crd=crd, vals=vals), count
+    return dataclasses.replace(A, crd=crd, vals=vals.reshape(A.vals.shape)), count
 
 
 def same_specials(got, ref, mag):
@@ -169,3 +170,25 @@ def test_narrow_rows_take_no_longer_than_wide_ones():
         took[k] = min(times)
     print(took, flush=True)
     assert max(took[8], took[12]) <= 1.35 * took[16]
+
+
+@pytest.mark.parametrize("k,per", [(6, 16), (16, 3), (32, 16), (40, 300), (64, 16), (100, 16), (200, 300)])
+def test_offsets_beyond_32_bits(k, per):
+    """B as rows far apart: from 2^30 floats of cols * ldb on the byte offsets into B don't fit 32 bits, and the end of a row is marked in
+    the column instead of in the offset.  One row stride on either side, the last rows of B referred to."""
+    cols = 1100
+    A = wl.csr_from_lengths(np.full((2000 * 256) // per + 5, per), cols, seed=k)
+    assert A.crd.max() == cols - 1 and A.nnz >= 1536 * 256
+    Bh = wl.dense_uniform(cols * k, 5, wl.S_B).reshape(cols, k)
+    ref, mag = oracle.spmm_csr(A.pos, A.crd, A.vals, Bh)
+    most = (2 ** 32 - 1) // 4 // cols
+    buf = torch.empty(cols * (most + 1), device="cuda")
+    for ld in (most, most + 1):
+        B = buf[:cols * ld].view(cols, ld)[:, ld - k:]            # the last columns: offsets up to the end of the buffer
+        B.copy_(dev(Bh))
+        C = torch.full((A.rows, k), float("nan"), device="cuda")
+        print("spmm wave offsets k", k, "ld", ld, flush=True)
+        psk.psk_spmm_csr(A.rows, cols, A.nnz, dev(A.pos), dev(A.crd), dev(A.vals), B, C, tile=256)
+        torch.cuda.synchronize()
+        ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, mag)
+        assert ok, "k %d ld %d: %.3g of the bar" % (k, ld, worst)
