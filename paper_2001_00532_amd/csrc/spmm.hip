@@ -317,12 +317,11 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     const bool groups = k <= 32 || (k <= 64 && nnz >= 8ll * rows) ||
                         (k > 64 && k <= kGroupColumns && pick_vec(B, k, ldb, C, ldc) == 1);
     // Tiles in the order of their sweeps over the columns (launch_tile_sweeps) when rows are long.  It pays where B (MB: b_mb) is larger
-    // than the L2 and its rows are used by several of the 768 tiles that a die works on at once: the sweeps of a die read B
-    // rows / 768 times, so 2 * cols < 768 * mean row.  us before / ordered, columns sorted in the rows:
-    //   1000 per row, k = 32, B 12.8 MB 873 / 700 (10^5 rows);  k = 64, 12.8 MB 777 / 560;  k = 64, 24 MB 1476 / 691;  k = 100, 38 MB 2411 / 1092;
-    //   k = 128, 14.6 MB 1086 / 667, 49 MB (4000 per row) 1340 / 819;  k = 256, 16 MB 414 / 178 (4000 rows), 64 MB 536 / 403;  700 per row (span 0.73),
-    //   k = 256, 59 MB 3783 / 3297.  On the other side: span 0.93 413 / 420, B of 6 MB 1000 per row k = 16 41 / 47, k = 32 45 / 49.
-    // Columns that are not sorted inside the rows gain nothing from the order; it costs the kernel that makes it (13 us of 870).
+    // than the L2 and its rows are used by several of the tiles in flight: a row of B is used by one of cols * rows / nnz rows of A.  us in CSR order / ordered,
+    // columns sorted in the rows, 40 M entries, 1000 per row, one of 230: k = 32 641 / 412, k = 128 2647 / 1579;  345: 670 / 502, 2694 / 1940;  460: 687 / 554, 2703 / 2212;  690: 722 /
+    // 617, 2726 / 2521;  1035: 750 / 661, 2734 / 2717 (alike with 700 and 4000 per row, 100 M entries, k = 16 and 64).  Columns that are not sorted gain nothing: one of 300 677 / 690,
+    // 2728 / 2763;  500 732 / 741, k = 64 1415 / 1535, k = 128 1895 / 2006.  So the line is drawn at 384, where those lose no more than 2 % and the others gain a quarter and more.
+    // Shares of the columns per tile (span): 0.73 (700 per row, k = 256, 59 MB) 3783 / 3297, 0.93 413 / 420;  B of 6 MB, 1000 per row, k = 16 41 / 47, k = 32 45 / 49.
     const int32_t over = spmm_overhang(rows, nnz, tile);
     const int64_t ntiles = ((int64_t)nnz + tile - 1) / tile;
     const double span = (double)rows * tile / nnz, b_mb = (double)cols * k * 4 / (1 << 20);
@@ -333,6 +332,9 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     //   k = 128, 5 MB 414 / 367 / 427, 12 MB 798 / 525 / 429, 40 MB 1082 / 1001 / 842;  k = 256, 12 MB 1600 / 717 / 837, 40 MB 2196 / 1525 / 1038, 80 MB 2320 /
     //   1994 / 1706.  4 per row: k = 64, 24 MB 615 / - / 594, 40 MB 637 / - / 667.  Ordered, 1000 per row: k = 128, 49 MB 1824 / 1632 / 1262, 15 MB 644 / 675 / 763;  k = 64,
     //   24 MB 824 / - / 641, 12 MB 657 / - / 697;  4000 per row, k = 128, 49 MB 790 / 942 / 1048.
+    //   Up to which size (whole / 32, 8 M entries): 16 per row, k = 64, 38 MB 282 / 269, 50 MB 293 / 285, 75 MB 299 / 306;  96, 60 MB 414 / 414, 80 MB 421 / 439;  128, 81 MB 577 / 549,
+    //   162 MB 593 / 609;  256, 162 MB 1202 / 1090, 216 MB 1207 / 1147, 324 MB 1204 / 1203 (64 per row alike);  4 per row, 64, 24 MB 313 / 303, 28 MB 317 / 315, 38 MB 325 / 337;  128, 59 MB 658 / 637, 81 MB
+    //   670 / 674;  96, 44 MB 498 / 490, 60 MB 507 / 513;  256, 119 MB 1396 / 1262, 324 MB 1391 / 1442: 32 columns of 24 MB, 13.5 with few entries per row.
     const bool lines = ldb % 32 == 0 && (reinterpret_cast<uintptr_t>(B) & 127) == 0;
     // Rows of C that fill 64-byte pieces can be stored past the L2 as they come.  Others share a piece with their neighbours, which the kernels
     // with a wave per tile store at other times: with few entries per row that is most of what these kernels do, and then the L2 has to put the
@@ -345,7 +347,7 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     if (lines && reach > fits && k >= 64 && k % 32 == 0) {
         int32_t c = 128;
         while (c > 32 && (c >= k || k % c != 0 || reach * c / k > fits)) c /= 2;
-        if (ordered || reach * c / k <= (k == 64 ? 12.5 : 13.5)) chunk = c;
+        if (ordered || reach * c / k <= (per >= 8 ? 24.0 : 13.5)) chunk = c;
     }
     // A chunk as large as the part of B that fits gains little where B is a little larger than that, and nothing where a row of C is all there is to do:
     // us workgroups / chunks / wave, whole rows: k = 160, 6 per row, B 4.4 MB 200 / 245 / 183;  k = 224, 10 per row, 4.4 MB 213 / 255 / 190;  160, 1 per row, 5 MB
