@@ -251,45 +251,56 @@ __device__ __forceinline__ void rows_by_search(const int *__restrict__ pos, int 
     }
 }
 
-// Clears the empty rows (BS rows of C each, k >= 4 columns) of tiles whose rows span more than GAP: wave number `index` looks up the tile
-// that owns row index * GAP (tile t owns the rows from its table entry, tile 0 from row 0, to the next entry).
-template <int BS, int GAP>
-__device__ __forceinline__ void clear_gap_rows(int index, int rows, const int *__restrict__ pos, const int *__restrict__ tile_row, int T,
-                                               float *__restrict__ C, int k, long long ldc)
+// Clears the empty rows (BS rows of C each, k >= 4 columns) of tiles whose rows span more than GAP.  first(r): position at which row r begins;
+// tile t owns the rows from its table entry, tile 0 from row 0, to the next entry.  Wave number `index` stands for the rows from index *
+// GAP / 4 on (an eighth of a tile's span and less by one wave: a compute unit writes 30 to 40 GB/s, so a span is shared by several; waves that
+// follow each other are in different workgroups).  rowmap: the row of C, or nullptr.
+template <int BS, int GAP, typename F>
+__device__ __forceinline__ void clear_gap_rows(int index, int rows, F first, const int *__restrict__ tile_row, int T,
+                                               float *__restrict__ C, int k, long long ldc, const int *__restrict__ rowmap)
 {
-    const long long q = (long long)index * GAP;
+    constexpr int PART = GAP / 4;
+    const long long q = (long long)index * PART;
     if (q >= rows) return;
-    const int last = pos[q + 1] - 1;              // position before the end of row q: the last tile that owns row q holds it
+    const int last = first(q + 1) - 1;            // position before the end of row q: the last tile that owns row q holds it
     const int t = last < 0 ? 0 : last / T;
     const int lo = t == 0 ? 0 : tile_row[t], hi = tile_row[t + 1];
     if (hi - lo <= GAP) return;
-    const int beg = q - GAP < lo ? lo : (int)q;   // from the tile's first row on where no earlier wave's row lies in it
-    const int end = hi - q < GAP ? hi : (int)q + GAP;
+    const int beg = q - PART < lo ? lo : (int)q;  // from the tile's first row on where no earlier wave's row lies in it
+    const int end = hi - q < PART ? hi : (int)q + PART;
     const int lane = threadIdx.x & (WAVE - 1), quads = (k + 3) / 4;
     int shift = 0;                                // 2^shift lanes per row, `at_once` rows per store
     while (shift < 6 && (1 << shift) < quads) ++shift;
     const int at_once = WAVE >> shift, g = lane >> shift;
     for (long long rb = beg; rb < end; rb += WAVE) {
-        const bool mine = rb + lane < end && pos[rb + lane] == pos[rb + lane + 1];
+        const bool mine = rb + lane < end && first(rb + lane) == first(rb + lane + 1);
         const unsigned long long empty = __ballot(mine);
         for (int c = lane & ((1 << shift) - 1); c < quads; c += 1 << shift) {
-            float *to = C + (rb + g) * BS * ldc + (4 * c < k - 4 ? 4 * c : k - 4);
+            const int col = 4 * c < k - 4 ? 4 * c : k - 4;
+            float *to = C + (rb + g) * BS * ldc + col;
             for (int i = g; i < WAVE; i += at_once, to += at_once * BS * ldc) {
                 if (~empty && !((empty >> i) & 1)) continue;
+                float *const at = rowmap ? C + (long long)rowmap[rb + i] * BS * ldc + col : to;
 #pragma unroll
-                for (int ii = 0; ii < BS; ++ii) *reinterpret_cast<v4f_u *>(to + ii * ldc) = v4f_u{};
+                for (int ii = 0; ii < BS; ++ii) *reinterpret_cast<v4f_u *>(at + ii * ldc) = v4f_u{};
             }
         }
     }
 }
 
-// Of the rows rb .. rb + 63, those of `empty` are handed to `clear`, a row to each of the wave's G groups at a time.
+// Of 64 rows, those of `empty` are cleared, a row by each of the wave's G groups at a time: clear(j) clears row j + g, j the same in all
+// lanes (so that a row's address is a scalar and what the lane adds to it, once: with a multiplication per lane each step took 100 ns).
 template <int G, typename F>
-__device__ __forceinline__ void each_empty_row(unsigned long long empty, int rb, int g, F clear)
+__device__ __forceinline__ void each_empty_row(unsigned long long empty, int g, F clear)
 {
+    if (~empty == 0) {
+#pragma unroll 4
+        for (int j = 0; j < WAVE; j += G) clear(j);
+        return;
+    }
     while (empty) {
         const int j = __ffsll((long long)empty) - 1;
-        if (G == 1 || (j + g < WAVE && ((empty >> ((j + g) & (WAVE - 1))) & 1))) clear(rb + j + g);
+        if (G == 1 || (j + g < WAVE && ((empty >> ((j + g) & (WAVE - 1))) & 1))) clear(j);
         empty &= ~(((1ull << G) - 1) << j);
     }
 }

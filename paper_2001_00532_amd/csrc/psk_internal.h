@@ -147,19 +147,18 @@ hipError_t launch_tile_sweeps(int32_t rows, int32_t cols, int32_t nnz, const int
                               int32_t over, bool tight, const Workspace &w, hipStream_t s);
 // The kernels with a wave per tile (k >= 4) neither walk nor clear a long run of empty rows alone: where a tile's rows, by the table, span more than
 // `gap`, the wave finds the rows of its positions by search, and workgroups of their own at the end of the same launch clear the empty
-// rows.  A wave of theirs stands for `gap` rows, looks up the tile that owns the first of them and clears what is empty from there to
+// rows.  A wave of theirs stands for `gap` / 4 rows, looks up the tile that owns the first of them and clears what is empty from there to
 // the next wave's row if the tile is of this kind (so the row of such a wave lies in every such tile).  us by one wave / so / by the four waves of
-// a workgroup per tile (k_spmm_pos_group, k_spmm_pos): one run in 1.9 M entries, k = 64, of 2000 rows 257 / 41 / 73, 30 000 3403 / 43 / 495,
-// 10^6 115 900 / 76 / 14 600;  10^6 entries in 2 * 10^7 rows, k = 32 1465 / 580 / 638;  4 x 4 blocks, k = 32, 30 000 2777 / 47 / 610.  At the head of the launch these
-// workgroups unbalance the tiles: 1.3 M entries in 2 M rows, k = 256 425 -> 472.  Runs of up to `gap` are cleared by the tile's wave, a
-// row to each of its G groups of lanes (k = 256 has one: a run of 500 96 us by a workgroup, 117 so).  The search costs the more the more positions a tile
-// has: scattered entries, 512 in 1280 rows, k = 48 640 us with a gap of 1024, 478 with 2048; with one or two groups the walk costs more (a run of
-// 2000, k = 256 133 and 204), and so it does for tiles of 64 blocks (in 1280 rows, k = 8 68 and 243).
-constexpr int32_t spmm_gap_rows(int groups, int bs) { return bs > 1 || groups <= 2 ? 1024 : 2048; }
-inline int32_t spmm_fillers(int32_t rows, int32_t gap)        // these workgroups
+// a workgroup per tile (k_spmm_pos_group, k_spmm_pos): one run in 1.9 M entries, k = 64, of 30 000 rows 3403 / 30 / 495, 10^6 115 900 / 76 / 14 600.
+// At the head of the launch these workgroups unbalance the tiles: 1.3 M entries in 2 M rows, k = 256 425 -> 472.
+// Shorter runs are cleared by the tile's wave, a row to each of its G groups of lanes; a compute unit writes 30 to 40 GB/s, so that costs the
+// more the wider the rows are.  us by a workgroup / walked / left to others, 1.5 M entries, 400 per row, a run of 500 | 1000 | 2000: k = 30 31 / 26 / - | 38 / 31 /
+// - | 54 / 38 / 28;  64 35 / 31 / - | 43 / 38 / - | 59 / 48 / 31;  100 67 / 52 / 42 | 74 / 62 / 43 | 87 / - / 44;  256 76 / 94 / 68 | 84 / 113 / 70;  4 x 4 blocks, k = 45 34 / 28 / - | 44 / 38 /
+// 18 | 64 / - / 19.  Scattered entries, one row in 2.5 (tiles of 1280 rows), where the search is paid by every tile: k = 8 98 / 33 / 40, 48 153 / 129 / 115, 128 274 / 292 / 258.
+constexpr int32_t spmm_gap_rows(int groups, int bs) { return bs > 1 ? 512 : (groups <= 2 ? 256 : 1024); }
+inline int32_t spmm_fillers(int32_t rows, int32_t gap)        // these workgroups: a multiple of the dies, so that the next chunk of columns meets the same ones
 {
-    const int64_t per = (int64_t)gap * 4;
-    return rows > gap ? (int32_t)((rows + per - 1) / per) : 0;
+    return rows > gap ? (int32_t)(((int64_t)rows + 8 * gap - 1) / (8 * gap)) * 8 : 0;
 }
 // A row that reaches at most this far past the end of a tile is finished by that tile (tile_span in psk_dev.h).  It saves most of
 // the carries when rows are shorter than tiles; CSR rows of half a tile and more would only make the tiles unequal (0.5 to 1.5 T

@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
     unsigned short *const srow = reinterpret_cast<unsigned short *>(smem + 4 * (T + over)) + wave * (T + over);   // which
     const int quads = (ntiles + 3) / 4, filler = (int)blockIdx.x - xcd_grid(quads);
     if (filler >= 0) {
-        clear_gap_rows<BS, GAP>(filler * 4 + wave, rows, pos, tile_row, T, C, k, ldc);
+        clear_gap_rows<BS, GAP>(wave * ((int)gridDim.x - xcd_grid(quads)) + filler, rows, [&](long long r) { return pos[r]; }, tile_row, T, C, k, ldc, nullptr);
         return;
     }
     const int quad = xcd_tile(blockIdx.x, quads), t = quad * 4 + wave;
@@ -50,11 +50,10 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
         rows_by_search<1>(pos, r0, r1, {t0 + i}, row);
         return row[0];
     };
+    auto put = [&](float *to, V v) { __builtin_nontemporal_store(v, reinterpret_cast<V *>(to)); };
     auto store = [&](int r, const float (&o)[BS][4]) {
 #pragma unroll
-        for (int ii = 0; ii < BS; ++ii)
-            __builtin_nontemporal_store(V{o[ii][0], o[ii][1], o[ii][2], o[ii][3]},
-                                        reinterpret_cast<V *>(C + ((long long)r * BS + ii) * ldc + col));
+        for (int ii = 0; ii < BS; ++ii) put(C + ((long long)r * BS + ii) * ldc + col, V{o[ii][0], o[ii][1], o[ii][2], o[ii][3]});
     };
     auto emit = [&](int r, const float (&o)[BS][4]) {              // a block row that may have begun in an earlier tile
         if (s.has_carry && r == r0) {
@@ -71,16 +70,34 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
         ent[e] |= (int)0x80000000u;
         srow[e] = (unsigned short)(near ? row - rbeg : 0);
     };
-    for (int rb = rbeg; !gap && rb < rend; rb += WAVE) {
-        const int r = rb + lane;
-        const bool valid = r < rend;
-        const int ps = valid ? pos[r] : 0, pe = valid ? pos[r + 1] : 1;
-        const int e = pe - 1 - t0;
-        if (valid && pe > ps && e >= 0 && e < cnt) mark(e, r);
-        each_empty_row<G>(__ballot(valid && pe == ps), rb, g, [&](int row) {
-            const float z[BS][4] = {};
-            if (active) store(row, z);
+    const long long group_off = (long long)g * BS * ldc + col;
+    auto row_step = [&](int rb, int from, int to) {                 // block rows rb .. rb + 63, one per lane with its positions
+        const bool valid = rb + lane < rend;
+        const int e = to - 1 - t0;
+        if (valid && to > from && e >= 0 && e < cnt) mark(e, rb + lane);
+        each_empty_row<G>(__ballot(valid && to == from), g, [&](int j) {
+            float *const at = C + (long long)(rb + j) * BS * ldc + group_off;
+#pragma unroll
+            for (int ii = 0; ii < BS; ++ii)
+                if (active) put(at + ii * ldc, V{});
         });
+    };
+    if (gap || rend - rbeg <= WAVE) {
+        const int q = min(rbeg + lane, rend);     // (pos has an entry behind the last row)
+        if (!gap && rend > rbeg) row_step(rbeg, pos[q], pos[min(q + 1, rend)]);
+    } else {                                      // (with one step requested at a time each waits for its own)
+#pragma unroll 1
+        for (int rb = rbeg; rb < rend; rb += 4 * WAVE) {
+            int from[4], to[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int q = min(rb + u * WAVE + lane, rend - 1);
+                from[u] = pos[q];
+                to[u] = pos[q + 1];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) row_step(rb + u * WAVE, from[u], to[u]);
+        }
     }
     for (int i = lane; gap && i < cnt; i += 2 * WAVE) {
         const int p[2] = {t0 + i, t0 + min(i + WAVE, cnt - 1)};
@@ -187,7 +204,7 @@ static void launch_blocks(int32_t rows, int32_t cols, int32_t nnz, const int32_t
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? (int64_t)cols * BS : 1);
     const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4), fillers = (unsigned)spmm_fillers(rows, spmm_gap_rows(1, BS)), lds = 4u * (unsigned)(tile + over) * 6u;
-#define PSK_GO_(GG, SM)                                                                                           \
+#define PSK_GO_(GG, SM)                                                                                       \
     PSK_LAUNCH((k_spmm_wave_blocks<BS, GG, SM>), dim3(nx + fillers), dim3(256), lds, s, rows, nnz, pos, crd, \
                vals, B, k, (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over)
 #define PSK_GO(GG) do { if (small) PSK_GO_(GG, true); else PSK_GO_(GG, false); } while (0)

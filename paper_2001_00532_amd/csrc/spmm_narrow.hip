@@ -1,9 +1,11 @@
-// CSR SpMM for dense operands of up to 128 columns.  The wide SpMM kernel maps the 64 lanes of a wave to 64*VEC columns of
-// B and takes one position per step; with few columns most of its instructions are spent on book-keeping per position.
-// Here a lane owns VEC = 4 adjacent columns and the wave is split into G groups of 64/G lanes that take G consecutive
-// positions in one step, so that one 16-byte load per lane fetches G rows of B.  Every lane keeps the partial sums of its
-// group for the open row; at a row end the sums of the groups are added across the wave.  Cut, row-end flags, records and
-// carries: as in the wide kernel.
+// CSR SpMM with several positions per step.  The wide SpMM kernel maps the 64 lanes of a wave to 64*VEC columns of B and takes one
+// position per step; with few columns most of its instructions are spent on book-keeping per position.  Here a lane owns VEC = 4
+// adjacent columns and the wave is split into G groups of 64/G lanes, so that one 16-byte load per lane fetches G rows of B.
+//   k_spmm_pos_group: a workgroup per tile, up to 128 columns; the groups take G consecutive positions in one step, every lane keeps the
+//     partial sums of its group for the open row, at a row end the sums of the groups are added across the wave.  Row-end flags, records
+//     and carries: as in the wide kernel.
+//   k_spmm_wave: a wave per tile, any k >= 4 (256/G columns at a time); the groups walk runs of positions of their own.
+// The cut is the wide kernel's in both; which of the three takes a product is decided in launch_spmm_csr_main.
 #include "psk_dev.h"
 #include "psk_internal.h"
 
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
     unsigned short *const srow = reinterpret_cast<unsigned short *>(smem + 4 * 2 * PLACES) + wave * kWaveBlock;   // row that ends
     const int quads = (ntiles + 3) / 4, filler = (int)blockIdx.x - xcd_grid(quads);
     if (filler >= 0) {
-        if (blockIdx.y == 0) clear_gap_rows<1, GAP>(filler * 4 + wave, rows, pos, tile_row, T, C, k, ldc);
+        if (blockIdx.y == 0) clear_gap_rows<1, GAP>(wave * ((int)gridDim.x - xcd_grid(quads)) + filler, rows, [&](long long r) { return pos[r]; }, tile_row, T, C, k, ldc, nullptr);
         return;
     }
     const int quad = xcd_tile(blockIdx.x, quads), slot = quad * 4 + wave;
@@ -309,11 +311,12 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
         rows_by_search<1>(pos, r0, r1, {t0 + b0 + i}, row);
         return row[0];
     };
+    auto put = [&](float *to, V v) {
+        if constexpr (PLAIN) *reinterpret_cast<V *>(to) = v;
+        else __builtin_nontemporal_store(v, reinterpret_cast<V *>(to));
+    };
     auto store = [&](int r, const auto (&o)[4]) {
-        const V v = {(float)o[0], (float)o[1], (float)o[2], (float)o[3]};
-        V *const to = reinterpret_cast<V *>(C + (long long)r * ldc + col);
-        if constexpr (PLAIN) *to = v;
-        else __builtin_nontemporal_store(v, to);
+        put(C + (long long)r * ldc + col, V{(float)o[0], (float)o[1], (float)o[2], (float)o[3]});
     };
     auto emit = [&](int r, const double (&o)[4]) {                  // a row that may have begun in an earlier tile
         if (s.has_carry && r == r0) {
@@ -358,16 +361,34 @@ __global__ __launch_bounds__(256) void k_spmm_wave(int rows, int nnz, const int 
                 srow[e] = (unsigned short)(near ? row - rbeg : 0);
             };
             // (every block of a long tile walks all of the tile's rows: to begin with those of the block costs each tile more, 4 per row, k = 16 44.6 -> 47.0 us)
-            for (int rb = rbeg; rb < rwalk; rb += WAVE) {
-                const int e = pe - 1 - t0 - b0;
-                if (r < rwalk && pe > ps && e >= 0 && e < n) mark(e, r);
-                const unsigned long long empty = b0 == 0 ? __ballot(r < rwalk && pe == ps) : 0;
-                r += WAVE;
-                if (rb + WAVE < rwalk) { ps = r < rwalk ? pos[r] : 0; pe = r < rwalk ? pos[r + 1] : 1; }
-                each_empty_row<G>(empty, rb, g, [&](int row) {
-                    const float zero[4] = {};
-                    if (active) store(row, zero);
+            const long long group_off = (long long)g * ldc + col;
+            auto row_step = [&](int rb, int from, int to) {         // rows rb .. rb + 63, one per lane with its positions
+                const int e = to - 1 - t0 - b0;
+                if (rb + lane < rwalk && to > from && e >= 0 && e < n) mark(e, rb + lane);
+                each_empty_row<G>(b0 == 0 ? __ballot(rb + lane < rwalk && to == from) : 0, g, [&](int j) {
+                    if (active) put(C + (long long)(rb + j) * ldc + group_off, V{});
                 });
+            };
+            if (rwalk - rbeg <= 4 * WAVE) {
+                for (int rb = rbeg; rb < rwalk; rb += WAVE) {
+                    const int from = ps, to = pe;
+                    r += WAVE;
+                    if (rb + WAVE < rwalk) { ps = r < rwalk ? pos[r] : 0; pe = r < rwalk ? pos[r + 1] : 1; }
+                    row_step(rb, from, to);
+                }
+            } else {                              // (rows of most of them empty: with one step requested ahead each waits for the next)
+#pragma unroll 1
+                for (int rb = rbeg; rb < rwalk; rb += 4 * WAVE) {
+                    int from[4], to[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int q = min(rb + u * WAVE + lane, rwalk - 1);
+                        from[u] = pos[q];
+                        to[u] = pos[q + 1];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) row_step(rb + u * WAVE, from[u], to[u]);
+                }
             }
             if (gap) {
                 constexpr int N = 3;
