@@ -80,6 +80,16 @@ __global__ __launch_bounds__(256) void k_spmm_pos(int rows, int nnz, const int *
             if (e >= 0 && e < cnt) sflag[e] = r;
         }
         unsigned long long empty = __ballot(valid && pe == ps);
+        if constexpr (BS != 4) {                  // (a row's address a scalar: 0.3 M entries, a run of 100 000 rows, k = 114 1500 -> 831 us, when tiles had
+            const int base = __builtin_amdgcn_readfirstlane(rb);   // an order in this kernel 1278;  4 x 4 blocks lose by it: k = 64 325.0 -> 326.9)
+            each_empty_row<1>(empty, 0, [&](int j) {
+                const float z[VEC] = {};
+#pragma unroll
+                for (int ii = 0; ii < BS; ++ii)
+                    if (active) st_vec<VEC>(C + ((long long)(base + j) * BS + ii) * ldc + col, z);
+            });
+            empty = 0;
+        }
         while (empty) {
             const int j = __ffsll((long long)empty) - 1;
             empty &= empty - 1;
