@@ -565,7 +565,7 @@ int psk_spmm_bcsr(int64_t brows, int64_t bcols, int64_t nblocks, int32_t bs, con
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int32_t ntiles = (int32_t)psk_num_tiles(nblocks, tile);
     hipError_t e = hipSuccess;
-    const int search = spmm_blocks_by_wave(bs, bcols, nblocks, k, tile) ? 0 : searches(phases, ntiles);
+    const int search = spmm_blocks_by_wave(bs, brows, bcols, nblocks, k, C, ldc, tile) ? 0 : searches(phases, ntiles);
     if ((phases & PSK_PHASE_PARTITION) && !search && e == hipSuccess) e = launch_partition(brows, nblocks, pos, tile, 0, ws.tile_row, s);
     if ((phases & PSK_PHASE_MAIN) && e == hipSuccess) {
         if (ntiles == 0) {

@@ -349,7 +349,7 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     // Rows of C that fill 64-byte pieces can be stored past the L2 as they come.  Others share a piece with their neighbours, which the kernels
     // with a wave per tile store at other times: with few entries per row that is most of what these kernels do, and then the L2 has to put the
     // pieces together (`plain` stores, while C fits the memory-side cache) or a workgroup stores neighbouring rows at once.
-    const bool pieces = k % 16 == 0 && ldc % 16 == 0 && (reinterpret_cast<uintptr_t>(C) & 63) == 0;
+    const bool pieces = spmm_pieces(C, k, ldc);
     const double reach = ordered ? span * b_mb : b_mb, fits = ordered ? 8.2 : 4.2, per = (double)nnz / rows;
     const int vec = pick_vec(B, k, ldb, C, ldc);
     const int32_t whole = k <= 256 ? k : 256;
@@ -418,7 +418,7 @@ hipError_t launch_spmm_bcsr_main(int32_t bs, int32_t brows, int32_t bcols, int32
                                  int64_t ldc, int32_t tile, const Workspace &w, hipStream_t s, int search)
 {
     const int32_t over = spmm_overhang_blocks(brows, nblocks, tile);
-    if (spmm_blocks_by_wave(bs, bcols, nblocks, k, tile))
+    if (spmm_blocks_by_wave(bs, brows, bcols, nblocks, k, C, ldc, tile))
         return launch_spmm_bcsr_wave(bs, brows, bcols, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s);
     if (bs == 2) return launch_spmm_pos<2>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);
     if (bs == 4) return launch_spmm_pos<4>(brows, nblocks, pos, crd, vals, B, k, ldb, C, ldc, tile, over, w, s, search);

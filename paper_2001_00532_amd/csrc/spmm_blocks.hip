@@ -10,8 +10,8 @@ namespace psk {
 // The workgroups' kernel gives a column to each of 64 lanes, most of which idle for narrow operands, and waits at barriers with tiles of
 // 64 blocks.  Bound by the L2 (a row of B that lies there 4.0 ps per 128 bytes) and the stream of the blocks: 225 000 rows of 8 blocks
 // of 4 x 4, k = 8 244 -> 64 us, k = 32 246 -> 165;  8 x 8, 40 000 of 20, k = 16 349 -> 100;  2 x 2, 40 000 of 20, k = 8 65 -> 23.
-// SMALL: byte offsets into B fit 32 bits.
-template <int BS, int G, bool SMALL>
+// SMALL: byte offsets into B fit 32 bits.  PLAIN: rows of C are stored through the L2.
+template <int BS, int G, bool SMALL, bool PLAIN>
 __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, const int *__restrict__ pos, const int *__restrict__ crd,
                                                           const float *__restrict__ vals, const float *__restrict__ B, int k,
                                                           long long ldb, float *__restrict__ C, long long ldc,
@@ -50,7 +50,10 @@ __global__ __launch_bounds__(256) void k_spmm_wave_blocks(int rows, int nnz, con
         rows_by_search<1>(pos, r0, r1, {t0 + i}, row);
         return row[0];
     };
-    auto put = [&](float *to, V v) { __builtin_nontemporal_store(v, reinterpret_cast<V *>(to)); };
+    auto put = [&](float *to, V v) {
+        if constexpr (PLAIN) *reinterpret_cast<V *>(to) = v;
+        else __builtin_nontemporal_store(v, reinterpret_cast<V *>(to));
+    };
     auto store = [&](int r, const float (&o)[BS][4]) {
 #pragma unroll
         for (int ii = 0; ii < BS; ++ii) put(C + ((long long)r * BS + ii) * ldc + col, V{o[ii][0], o[ii][1], o[ii][2], o[ii][3]});
@@ -203,11 +206,12 @@ static void launch_blocks(int32_t rows, int32_t cols, int32_t nnz, const int32_t
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
     const bool small = ldb <= 0xffffffffll / 4 / (cols > 0 ? (int64_t)cols * BS : 1);
+    const bool plain = small && spmm_blocks_plain(rows, nnz, BS, C, k, ldc);
     const unsigned nx = (unsigned)xcd_grid((ntiles + 3) / 4), fillers = (unsigned)spmm_fillers(rows, spmm_gap_rows(1, BS)), lds = 4u * (unsigned)(tile + over) * 6u;
-#define PSK_GO_(GG, SM)                                                                                       \
-    PSK_LAUNCH((k_spmm_wave_blocks<BS, GG, SM>), dim3(nx + fillers), dim3(256), lds, s, rows, nnz, pos, crd, \
+#define PSK_GO_(GG, SM, PL)                                                                                       \
+    PSK_LAUNCH((k_spmm_wave_blocks<BS, GG, SM, PL>), dim3(nx + fillers), dim3(256), lds, s, rows, nnz, pos, crd, \
                vals, B, k, (long long)ldb, C, (long long)ldc, w.tile_row, w.carry_row, w.carry_val, ntiles, tile, over)
-#define PSK_GO(GG) do { if (small) PSK_GO_(GG, true); else PSK_GO_(GG, false); } while (0)
+#define PSK_GO(GG) do { if (plain) PSK_GO_(GG, true, true); else if (small) PSK_GO_(GG, true, false); else PSK_GO_(GG, false, false); } while (0)
     if (k <= 8) PSK_GO(32);
     else if (k <= 16) PSK_GO(16);
     else if (k <= 32) PSK_GO(8);

@@ -104,3 +104,45 @@ def test_offsets_beyond_32_bits(bs, k):
         torch.cuda.synchronize()
         ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, mag)
         assert ok, "bs %d k %d ld %d: %.3g of the bar" % (bs, k, ld, worst)
+
+
+@pytest.mark.parametrize("bs,k,pad,per,brows", [(2, 12, 0, 1, 60_000), (2, 17, 3, 1, 60_000), (4, 25, 0, 1, 50_000), (4, 61, 1, 2, 30_000), (8, 57, 0, 1, 40_000), (8, 5, 2, 3, 20_000),
+                                                (2, 45, 0, 1, 570_000), (4, 9, 0, 0, 1_450_000), (4, 61, 0, 2, 210_000), (8, 45, 0, 1, 145_000), (4, 48, 0, 1, 270_000)])
+def test_few_blocks_per_row(bs, k, pad, per, brows):
+    """Rows of C that share 64-byte pieces with their neighbours, C below and above the size up to which they go through the L2, and the
+    products that go to the workgroups' kernel.  per = 0: one block row in four has a block."""
+    rng = np.random.default_rng(k)
+    A = wl.csr_from_lengths(np.full(brows, per) if per else (rng.random(brows) < 0.25).astype(np.int64), 300, seed=k, bs=bs)
+    Bh = wl.dense_uniform(300 * bs * k, 3, wl.S_B).reshape(300 * bs, k)
+    C = torch.full((A.rows * bs, k + pad), float("nan"), device="cuda")
+    psk.psk_spmm_bcsr(A.rows, 300, A.nnz, bs, dev(A.pos), dev(A.crd), dev(A.vals), dev(Bh), C[:, :k])
+    got = C.cpu().numpy()
+    assert np.isnan(got[:, k:]).all(), "columns past k were written"
+    ref, mag = oracle.spmm_bcsr(A.pos, A.crd, A.vals, Bh, bs)
+    ok, worst = oracle.within_tolerance(got[:, :k], ref, mag)
+    assert ok, "%.3g of the bar" % worst
+
+
+@pytest.mark.parametrize("bs,k,full", [(4, 28, 32), (2, 45, 48)])
+def test_narrow_rows_take_no_longer_than_wide_ones(bs, k, full):
+    """300 000 rows of one block: stored past the L2 one by one, rows that share 64-byte pieces of C took 1.7 times as long as wider ones that
+    fill them (4 x 4 66.6 us against 38.3, now 40.9)."""
+    A = wl.csr_from_lengths(np.ones(300_000 if bs == 4 else 400_000, dtype=np.int64), 4000, seed=1, bs=bs)
+    pos, crd, vals = dev(A.pos), dev(A.crd), dev(A.vals)
+    ws = psk.workspace(psk.PSK_OP_SPMM_BCSR, A.rows, A.nnz, k=full, bs=bs)
+    took = {}
+    for n in (k, full):
+        B = dev(wl.dense_uniform(4000 * bs * n, 3, wl.S_B).reshape(4000 * bs, n))
+        C = torch.empty((A.rows * bs, n), device="cuda")
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                psk.psk_spmm_bcsr(A.rows, 4000, A.nnz, bs, pos, crd, vals, B, C, ws=ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        took[n] = min(times)
+    print(took, flush=True)
+    assert took[k] <= 1.35 * took[full]
