@@ -7,7 +7,6 @@
 #include "psk_dev.h"
 #include "psk_internal.h"
 
-
 namespace psk {
 
 // Largest i in [0, n] with a[i] <= target (a[0] <= target taken for granted), by L neighbouring lanes: a round probes L places at
@@ -350,6 +349,11 @@ __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const 
     if (straddle) finalize(r1);
 }
 
+// A tile whose slices span more than this many (by the table) leaves the empty ones to workgroups at the end of the launch, as the SpMM
+// kernels do (it still walks them, which costs 0.6 us per 256).  us before / by the tile's workgroup, a slice at a time in k_mttkrp_pos / so: 1 M leaves, a run of
+// 1000, j = 64 47 / 60 / 38, 128 70 / 71 / 51;  30 000 325 / 496 / 83, 592 / 508 / 109;  200 000 1897 / 2980 / 426, 3816 / 3037 / 450.
+constexpr int kGapSlices = 1024;
+
 // j >= 4: a lane owns four adjacent columns and each group of 64/G lanes walks a run of consecutive leaves of its own, with its own
 // open fiber and open slice.  A leaf closes where its fiber ends or its group's run does (marked in the staged leaf itself, so
 // nothing is written per leaf of a fiber): there the fiber's sum is multiplied by its C row, which is requested with the D rows.  The
@@ -380,10 +384,17 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
     __shared__ double srec[2 * NW][GW][4];
     __shared__ int srec_row[2 * NW];              // -2 unused, -1 open segment, >= 0 slice that ended
 
-    const int t = xcd_tile(blockIdx.x, ntiles);
-    if (t < 0) return;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int filler = (int)blockIdx.x - xcd_grid(ntiles);
+    if (filler >= 0) {
+        if (blockIdx.y == 0)
+            clear_gap_rows<1, kGapSlices>(wave * ((int)gridDim.x - xcd_grid(ntiles)) + filler, nslices, [&](long long r) { return pos_l[pos_k[r]]; },
+                                          tile_slice, T, A, jdim, lda, crd_i);
+        return;
+    }
+    const int t = xcd_tile(blockIdx.x, ntiles);
+    if (t < 0) return;
     const int t0 = t * T;
     const int cnt = (nnz - t0 < T) ? nnz - t0 : T;
     const int t1 = t0 + cnt;
@@ -416,11 +427,11 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
     for (int i = tid; i < T / 2; i += THREADS) reinterpret_cast<int *>(send)[i] = 0;
     if (tid < 2 * NW) srec_row[tid] = -2;
     if (tid == 0 && blockIdx.y == 0 && !has_carry) carry_row[t] = -1;
-    auto store = [&](int r, v4f o) {
-        v4f_u *const to = reinterpret_cast<v4f_u *>(A + (long long)(crd_i ? crd_i[r] : r) * lda + col);
-        if constexpr (PLAIN) *to = o;
-        else __builtin_nontemporal_store((v4f_u)o, to);
+    auto put = [&](float *to, v4f o) {
+        if constexpr (PLAIN) *reinterpret_cast<v4f_u *>(to) = o;
+        else __builtin_nontemporal_store((v4f_u)o, reinterpret_cast<v4f_u *>(to));
     };
+    auto store = [&](int r, v4f o) { put(A + (long long)(crd_i ? crd_i[r] : r) * lda + col, o); };
 #pragma unroll
     for (int u = 0; u < LD; ++u) {
         const int i = tid + u * THREADS;
@@ -444,6 +455,8 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
         if (ends || hi == cnt) close(hi - 1);
     }
     // ---- slice ends, zero rows for slices without leaves
+    const long long group_off = (long long)g * lda + col;
+    const bool gap = r1 - (t == 0 ? 0 : r0) > kGapSlices;            // the empty ones are cleared by the last workgroups of the grid
     for (int rb = rbeg + wave * WAVE; rb < rend; rb += THREADS) {
         const int r = rb + lane;
         const bool valid = r < rend;
@@ -452,12 +465,9 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
             const int e = pe - 1 - t0;
             if (e >= 0 && e < cnt) send[e] = (unsigned short)(near ? r - rbeg + 1 : 0xffff);
         }
-        unsigned long long empty = __ballot(valid && pe == ps);
-        while (empty) {
-            const int j = __ffsll((long long)empty) - 1;
-            empty &= empty - 1;
-            if (active && g == 0) store(rb + j, v4f{});
-        }
+        each_empty_row<G>(__ballot(valid && !gap && pe == ps), g, [&](int j) {
+            if (active) put(crd_i ? A + (long long)crd_i[rb + j + g] * lda + col : A + (long long)(rb + j) * lda + group_off, v4f{});
+        });
     }
     __syncthreads();
 
@@ -593,7 +603,7 @@ hipError_t launch_mttkrp_main(int64_t dim_k, int64_t dim_l, int32_t nslices, int
 #define PSK_RUNS(G)                                                                                             \
     do {                                                                                                         \
         const size_t lds = ((size_t)2 * (tile + 4 * G) + tile) * 4 + (size_t)tile * 2;                           \
-        const dim3 grid(nx, (j + 256 / G - 1) / (256 / G));                                                      \
+        const dim3 grid(nx + spmm_fillers(nslices, kGapSlices), (j + 256 / G - 1) / (256 / G));                                                      \
         if (small && plain) PSK_GO((k_mttkrp_runs<G, true, true>), grid);                                        \
         else if (small) PSK_GO((k_mttkrp_runs<G, true, false>), grid);                                           \
         else PSK_GO((k_mttkrp_runs<G, false, false>), grid);                                                     \

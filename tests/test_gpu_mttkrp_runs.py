@@ -36,6 +36,53 @@ def test_runs_of_empty_slices():
     check(fps, np.full(int(fps.sum()), 9), (fps.size, 250, 700), 8, 2048)
 
 
+@pytest.mark.parametrize("mapped", [False, True])
+@pytest.mark.parametrize("j,tile", [(5, 256), (16, 2048), (64, 256), (100, 2048), (128, 256), (257, 256)])
+def test_runs_that_others_clear(j, tile, mapped):
+    """Runs of empty slices around the length from which workgroups of their own clear them, at the beginning, one after the other and at
+    the end, slices with empty fibers among them; with and without a compressed first level."""
+    rng = np.random.default_rng(j)
+    zero = lambda n: np.zeros(n, dtype=np.int64)
+    runs = [zero(1025)]
+    for n in (1, 255, 256, 300, 1022, 1023, 1024, 1025, 2047, 2049, 5000):
+        runs += [rng.integers(1, 4, size=70), zero(n)]
+    fps = np.concatenate(runs + [rng.integers(0, 4, size=700), zero(1300)])
+    T = wl.csf3_from_lengths(fps, rng.choice([0, 0, 1, 9, 70], size=int(fps.sum())), (fps.size, 250, 700), seed=j)
+    C, D = wl.dense_uniform(250 * j, 4, wl.S_B).reshape(250, j), wl.dense_uniform(700 * j, 5, wl.S_B).reshape(700, j)
+    ref, mag = oracle.mttkrp_csf3(T.pos_k, T.crd_k, T.pos_l, T.crd_l, T.vals, C, D)
+    at = np.cumsum(rng.integers(1, 3, size=fps.size)) - 1 if mapped else np.arange(fps.size)
+    out = torch.full((int(at[-1]) + 1, j + 3), float("nan"), device="cuda")
+    psk.psk_mttkrp_csf3((out.shape[0], 250, 700), dev(at.astype(np.int32)) if mapped else None, dev(T.pos_k), dev(T.crd_k), dev(T.pos_l), dev(T.crd_l),
+                        dev(T.vals), dev(C), dev(D), out[:, :j], tile=tile)
+    got = out.cpu().numpy()
+    assert np.isnan(got[:, j:]).all(), "columns past j were written"
+    ok, worst = oracle.within_tolerance(got[at, :j], ref, mag)
+    assert ok, "%.3g of the bar" % worst
+    others = np.setdiff1d(np.arange(out.shape[0]), at)
+    assert (got[others, :j] == 0).all()
+
+
+def test_a_run_takes_the_time_of_clearing_it():
+    """1 M leaves take less than 0.1 ms and A is cleared in 0.03 ms; one workgroup alone cleared the run in 3.8 ms (now 0.45)."""
+    j = 128
+    fps = np.concatenate([np.full(10_000, 10), np.zeros(200_000, dtype=np.int64), np.full(10_000, 10)])
+    T = wl.csf3_from_lengths(fps, np.full(int(fps.sum()), 5), (fps.size, 2000, 3000), seed=1)
+    args = [dev(a) for a in (T.pos_k, T.crd_k, T.pos_l, T.crd_l, T.vals)]
+    C, D = dev(wl.dense_uniform(2000 * j, 4, wl.S_B).reshape(2000, j)), dev(wl.dense_uniform(3000 * j, 5, wl.S_B).reshape(3000, j))
+    out = torch.empty((fps.size, j), device="cuda")
+    ws = psk.workspace(psk.PSK_OP_MTTKRP_CSF3, fps.size, T.nnz, k=j)
+    times = []
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        psk.psk_mttkrp_csf3((fps.size, 2000, 3000), None, *args, C, D, out, ws=ws)
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    print(times, flush=True)
+    assert min(times) <= 1.2
+
+
 @pytest.mark.parametrize("tile", [1, 7, 2048])
 def test_table(tile):
     """One, four and 64 lanes per entry (up to 12 000 and up to 100 000 tiles)."""
