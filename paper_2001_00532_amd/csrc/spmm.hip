@@ -375,8 +375,8 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     // memory come at the fabric's rate in all kernels, and the workgroups' are a little better at that.  us, 4 M entries unless
     // stated, workgroup / wave:
     //   tiles: 1016, B 2 MB 26 / 32 (4 per row, k = 64), 12.5 / 13.8 (100, k = 32);  1953: 40 / 34, 17.4 / 17.3, k = 128 44 / 30;  3906: 70 / 45, 27.2 / 23.3, 74 / 50;
-    //     long rows: k = 8, 100 per row: 1953 15.1 / 17.2, 3906 21.8 / 22.2, 7812 34.9 / 33.0;  k = 12, 1563 16 / 19, 2344 17 / 20;  k = 52, 1563 0.97, 2344 0.96
-    //     (time of the second, of 1); 72 columns and more from 4.2 MB, 1563 tiles: 53 / 64;  more than 128 in quads: 1563 up to 50 / 60, 3125 up to 53 / 59, 3907 0.8 to 1.0
+    //     long rows: k = 8, 100 per row: 1953 15.1 / 17.2, 3906 21.8 / 22.2, 7812 34.9 / 33.0;  k = 12, 1563 16 / 19, 2344 17 / 20;  92 and 400 per row, k = 39
+    //     1540 20.4 / 19.2, 1975 22.5 / 20.0, k = 60 21.1 / 19.9, 23.7 / 21.7;  72 columns and more from 4.2 MB, 1563 tiles: 53 / 64;  more than 128 in quads: 1563 up to 50 / 60, 3125 up to 53 / 59, 3907 0.8 to 1.0
     //   B 2 MB: 4 per row k = 32 131 / 56;  16, k = 16 52 / 35;  1000, k = 64 60 / 49;  4, k = 6 61 / 57
     //   B 6 MB: 4 per row k = 32 128 / 67;  16, k = 24 68 / 61;  100, k = 24 56 / 62;  1000, k = 32 45 / 49;  100, k = 96 137 / 101;  16, k = 200 209 / 212
     //   B 8 MB: k = 72, 3 per row 53 / 67, 8 per row 154 / 133
@@ -388,7 +388,7 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
                                    : k <= 8 && !shorts                      ? 6000
                                    : (quads && k < 240) || (k <= 16 && !shorts) ? 3600
                                    : quads                                  ? 2000
-                                   : k <= 64 ? (!shorts && k % 32 ? 2000 : 1536)
+                                   : k <= 64 ? 1536
                                              : (k <= 128 && shorts && b_mb > 4.2 ? 2000 : 1536);
     bool wave = k >= 4 && ntiles >= tiles_for_wave && (k <= 256 || per >= 8) &&
                 (records || chunked || b_mb <= 4.5 || (shorts && k <= 64 && b_mb <= 6) || (k > 64 && k <= 128 && b_mb <= (per >= 7 ? 8 : 6.1)) ||
