@@ -195,24 +195,26 @@ hipError_t launch_spmv_bcsr4_main(int32_t brows, int32_t nblocks, const int32_t 
                                   const Workspace &w, hipStream_t s, int search);
 // Rows of C that fill 64-byte pieces.
 inline bool spmm_pieces(const float *C, int32_t k, int64_t ldc) { return k % 16 == 0 && ldc % 16 == 0 && (reinterpret_cast<uintptr_t>(C) & 63) == 0; }
-// Rows of C that don't fill 64-byte pieces are stored through the L2 (spmm.hip has the reason) while C fits the memory-side cache, or where most
+// Rows of C that don't fill 64-byte pieces are stored through the L2 (spmm.hip has the reason) where rows have few blocks and C fits the memory-side cache, or most
 // rows are empty.  Otherwise a wave per tile is slower than a workgroup where a row of C is all there is to do.  us workgroup / past the L2 / through it:
 //   a block per row: 2 x 2, C 125 MB, k = 28 52 / 51 / 32;  206 MB, 45 60 / 72 / 43;  4 x 4, 130 MB, 28 62 / 67 / 41;  206 MB, 45 82 / 99 / 61;  240 MB, 50 80 / 100 / 89;  384 MB, 28
-//   166 / 182 / -, 274 MB, 20 155 / 134 / -;  8 x 8, 206 MB, 45 91 / 93 / 110;  411 MB, 45 161 / 148 / -;  558 MB, 61 169 / 190 / -.  Two: 4 x 4, 343 MB, 50 146 / 136 / -, 418 MB, 61 152 / 163 / -.
+//   166 / 182 / -, 274 MB, 20 155 / 134 / -;  8 x 8, 206 MB, 45 91 / 93 / 110;  411 MB, 45 161 / 148 / -;  558 MB, 61 169 / 190 / -.  Two: 2 x 2, 28 42 / 27 / 24, 4 x 4, 45 56 / 54 / 44, 343 MB,
+//   50 146 / 136 / -, 418 MB, 61 152 / 163 / -.  Three: 2 x 2, 28 41 / 22 / 23, 4 x 4, 45 54 / 43 / 44;  four: 2 x 2, 28 38 / 17 / 19.
 //   a block in four rows: 4 x 4, 288 MB, 45 126 / 128 / 80;  in 16: 2 x 2, 580 MB 257 / 187 / 163
 inline bool spmm_blocks_plain(int64_t brows, int64_t nblocks, int32_t bs, const float *C, int32_t k, int64_t ldc)
 {
-    return !spmm_pieces(C, k, ldc) && (brows * bs * ldc <= (int64_t(192) << 18) || 4 * nblocks < 3 * brows);
+    return !spmm_pieces(C, k, ldc) && 2 * nblocks < 5 * brows && (brows * bs * ldc <= (int64_t(192) << 18) || 4 * nblocks < 3 * brows);
 }
 // Blocks: a wave per tile (spmm_blocks.hip, reads the table) or a workgroup, whose 64 lanes own one column each or more.  us workgroup / wave:
 //   k = 8, 4 x 4, 1.8 M blocks 244 / 64;  8 x 8, 0.9 M 386 / 92;  2 x 2, 3.6 M 263 / 79;  k = 32 246 / 165, 400 / 196, 268 / 151;  48 262 / 227, 405 / 298, 271 / 224;
 //   64: B 220 MB 300 / 308, 414 / 340, 290 / 307;  20 MB, 0.16 M blocks 34.8 / 31.5, 2 x 2, 0.8 M 67 / 59;  66 and more: 345 / 340, 517 / 511, 352 / 354, 200 921 / 1090
 //   few tiles, where the workgroups' kernel searches its rows and saves a launch: 4 x 4, k = 8, 62 tiles 12.6 / 10.9;  8 x 8, 32 20.1 / 17.0; but 48 20.0 / 24.0
-//     (4 x 4 12.9 / 13.8) and 2 x 2 9.6 / 11.0, up to 500 tiles 28.1 / 31.6 (13.9 / 14.1, 10.2 / 10.8), with 875 40.5 / 32.7 (19.3 / 16.2, 12.5 / 10.6)
+//     (4 x 4 12.9 / 13.8) and 2 x 2 9.6 / 11.0, up to 500 tiles 28.1 / 31.6 (13.9 / 14.1, 10.2 / 10.8), with 875 40.5 / 32.7 (19.3 / 16.2, 12.5 / 10.6);  a handful of blocks in less than a tile:
+//     8 blocks of 4 x 4 6.4 / 7.2, 32 6.8 / 7.2, 48 8.4 / 7.1;  8 x 8, 16 7.4 / 7.9, 32 10.3 / 8.0
 inline bool spmm_blocks_by_wave(int32_t bs, int64_t brows, int64_t bcols, int64_t nblocks, int32_t k, const float *C, int64_t ldc, int32_t tile)
 {
     const int64_t ntiles = (nblocks + tile - 1) / tile;
-    if (k < 4 || k > 64 || (k > 48 && bs < 8 && bcols * bs * k > (int64_t(24) << 18)) || ntiles < (bs >= 4 && k <= 32 ? 1 : 600)) return false;
+    if (k < 4 || k > 64 || nblocks * bs <= 128 || (k > 48 && bs < 8 && bcols * bs * k > (int64_t(24) << 18)) || ntiles < (bs >= 4 && k <= 32 ? 1 : 600)) return false;
     if (spmm_pieces(C, k, ldc) || spmm_blocks_plain(brows, nblocks, bs, C, k, ldc)) return true;
     if (2 * nblocks < 3 * brows) return k <= (bs == 8 ? 32 : 24);
     return bs != 4 || k <= 40 || 2 * nblocks >= 5 * brows || (k <= 56 && bcols * bs * k <= (int64_t(24) << 18));

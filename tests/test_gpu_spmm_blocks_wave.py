@@ -107,7 +107,8 @@ def test_offsets_beyond_32_bits(bs, k):
 
 
 @pytest.mark.parametrize("bs,k,pad,per,brows", [(2, 12, 0, 1, 60_000), (2, 17, 3, 1, 60_000), (4, 25, 0, 1, 50_000), (4, 61, 1, 2, 30_000), (8, 57, 0, 1, 40_000), (8, 5, 2, 3, 20_000),
-                                                (2, 45, 0, 1, 570_000), (4, 9, 0, 0, 1_450_000), (4, 61, 0, 2, 210_000), (8, 45, 0, 1, 145_000), (4, 48, 0, 1, 270_000)])
+                                                (2, 45, 0, 1, 570_000), (4, 9, 0, 0, 1_450_000), (4, 61, 0, 2, 210_000), (8, 45, 0, 1, 145_000), (4, 48, 0, 1, 270_000),
+                                                (4, 20, 0, 2, 16), (4, 20, 0, 2, 17), (8, 9, 1, 2, 8), (8, 9, 1, 2, 9), (2, 30, 0, 3, 30_000)])
 def test_few_blocks_per_row(bs, k, pad, per, brows):
     """Rows of C that share 64-byte pieces with their neighbours, C below and above the size up to which they go through the L2, and the
     products that go to the workgroups' kernel.  per = 0: one block row in four has a block."""
