@@ -350,7 +350,8 @@ __global__ __launch_bounds__(256) void k_mttkrp_pos(int nslices, int nnz, const 
 }
 
 // A tile whose slices span more than this many (by the table) leaves the empty ones to workgroups at the end of the launch, as the SpMM
-// kernels do (it still walks them, which costs 0.6 us per 256).  us before / by the tile's workgroup, a slice at a time in k_mttkrp_pos / so: 1 M leaves, a run of
+// kernels do (it still walks them, which costs 0.6 us per 256).  Not with several chunks of columns, which share the clearing and lose by workgroups between
+// them (7569 slices, j = 59 31.5 -> 34.2 us).  us before / by the tile's workgroup, a slice at a time in k_mttkrp_pos / so: 1 M leaves, a run of
 // 1000, j = 64 47 / 60 / 38, 128 70 / 71 / 51;  30 000 325 / 496 / 83, 592 / 508 / 109;  200 000 1897 / 2980 / 426, 3816 / 3037 / 450.
 constexpr int kGapSlices = 1024;
 
@@ -388,9 +389,8 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int filler = (int)blockIdx.x - xcd_grid(ntiles);
     if (filler >= 0) {
-        if (blockIdx.y == 0)
-            clear_gap_rows<1, kGapSlices>(wave * ((int)gridDim.x - xcd_grid(ntiles)) + filler, nslices, [&](long long r) { return pos_l[pos_k[r]]; },
-                                          tile_slice, T, A, jdim, lda, crd_i);
+        clear_gap_rows<1, kGapSlices>(wave * ((int)gridDim.x - xcd_grid(ntiles)) + filler, nslices, [&](long long r) { return pos_l[pos_k[r]]; },
+                                      tile_slice, T, A, jdim, lda, crd_i);
         return;
     }
     const int t = xcd_tile(blockIdx.x, ntiles);
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
     }
     // ---- slice ends, zero rows for slices without leaves
     const long long group_off = (long long)g * lda + col;
-    const bool gap = r1 - (t == 0 ? 0 : r0) > kGapSlices;            // the empty ones are cleared by the last workgroups of the grid
+    const bool gap = gridDim.y == 1 && r1 - (t == 0 ? 0 : r0) > kGapSlices;            // the empty ones are cleared by the last workgroups of the grid
     for (int rb = rbeg + wave * WAVE; rb < rend; rb += THREADS) {
         const int r = rb + lane;
         const bool valid = r < rend;
@@ -603,7 +603,8 @@ hipError_t launch_mttkrp_main(int64_t dim_k, int64_t dim_l, int32_t nslices, int
 #define PSK_RUNS(G)                                                                                             \
     do {                                                                                                         \
         const size_t lds = ((size_t)2 * (tile + 4 * G) + tile) * 4 + (size_t)tile * 2;                           \
-        const dim3 grid(nx + spmm_fillers(nslices, kGapSlices), (j + 256 / G - 1) / (256 / G));                                                      \
+        const int chunks = (j + 256 / G - 1) / (256 / G);                                                        \
+        const dim3 grid(nx + (chunks == 1 ? spmm_fillers(nslices, kGapSlices) : 0), chunks);                                                      \
         if (small && plain) PSK_GO((k_mttkrp_runs<G, true, true>), grid);                                        \
         else if (small) PSK_GO((k_mttkrp_runs<G, true, false>), grid);                                           \
         else PSK_GO((k_mttkrp_runs<G, false, false>), grid);                                                     \
