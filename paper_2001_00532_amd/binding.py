@@ -66,7 +66,7 @@ def _spmv(*args):                                # lib() puts the native one her
 
 def _native_side():
     """_marshal.so if it is there and was built for this torch and Python (it reads tensors through their C++ objects).  Without
-    it everything works as with it, a call takes 1.5 us longer."""
+    it everything works as with it, a small CSR product takes 6.4 us in place of 3.9."""
     try:
         from . import _marshal as native
         if native.built_for == built_for():

@@ -443,7 +443,6 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
     for (int q = q0 + tid; q < qend; q += THREADS) {
         int lo = pos_l[q] - t0, hi = pos_l[q + 1] - t0;
         const int kk = crd_k[q];
-        const bool ends = hi <= cnt;
         lo = lo < 0 ? 0 : lo;
         hi = hi > cnt ? cnt : hi;
         if (lo >= hi) continue;
@@ -452,7 +451,7 @@ __global__ __launch_bounds__(256) void k_mttkrp_runs(int nslices, int nnz, const
             kof[i] = kk;
         };
         for (int b = (lo / run + 1) * run; b < hi; b += run) close(b - 1);
-        if (ends || hi == cnt) close(hi - 1);
+        close(hi - 1);                            // (a fiber that goes on behind the tile: its run ends here)
     }
     // ---- slice ends, zero rows for slices without leaves
     const long long group_off = (long long)g * lda + col;

@@ -141,7 +141,7 @@ hipError_t launch_tile_sweeps(int32_t rows, int32_t cols, int32_t nnz, const int
                               int32_t over, bool tight, const Workspace &w, hipStream_t s)
 {
     const int ntiles = (int)(((int64_t)nnz + tile - 1) / tile);
-    // A die holds 512 tiles (waves); 512 / span of them cover the columns once.  Longer runs make the order of a run's tiles finer, shorter ones
+    // A die holds 512 tiles (32 compute units, 16 waves of up to 128 registers each); 512 / span of them cover the columns once.  Longer runs make the order of a run's tiles finer, shorter ones
     // keep the tiles in flight closer to each other, which counts where what they sweep over together is more than the L2 holds
     // (`tight`).  Runs of 350 / 500 / 600 / 700 / 1000 over span, us: tight: 1000 per row, k = 100, B 38 MB 1201 / 1085 / 1326 / 1482 / 1632;  others: k = 32
     // 730 / 703 / 693 / 699 / 716;  k = 64 594 / 567 / 558 / 560 / 612;  lengths log-normal, k = 64 776 / 697 / 676 / 666 / 653;  4000 rows, k = 256 238 / 180 /

@@ -335,7 +335,7 @@ hipError_t launch_spmm_csr_main(int32_t rows, int32_t cols, int32_t nnz, const i
     const int32_t over = spmm_overhang(rows, nnz, tile);
     const int64_t ntiles = ((int64_t)nnz + tile - 1) / tile;
     const double span = (double)rows * tile / nnz, b_mb = (double)cols * k * 4 / (1 << 20);
-    const bool ordered = ntiles >= 4096 && b_mb >= 8 && span <= 0.8 && 2.0 * cols * rows <= 768.0 * nnz;
+    const bool ordered = ntiles >= 4096 && b_mb >= 8 && span <= 0.8 && (double)cols * rows <= 384.0 * nnz;
     // Columns in chunks, where rows of B begin 128-byte lines and the part of B that the tiles in flight gather from (`reach`: all of it,
     // ordered about span of it) does not fit the L2: one chunk after the other, as wide as fits.  A is read once per chunk.  us
     // whole / 64 / 32 columns at a time, 16 M entries, 16 per row: k = 64, B 5 MB 231 / - / 218, 12 MB 417 / - / 291, 24 MB 516 / - / 449, 80 MB 589 / - / 602;

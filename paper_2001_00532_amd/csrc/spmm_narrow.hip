@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256) void k_spmm_pos_group(int rows, int nnz, const
 //   lanes), and one segmented sum per block hands each group what the groups before it leave of its first row.
 // Bound by the requests to the L2: a row of B in the L2 costs 4.0 ps per 128 bytes on the whole chip however it is asked for, and
 // the stream of entries, 8 bytes each from memory, adds 0.8 to 1.7; measured 6.4 ps at k = 32.  Before, us (k_spmm_pos_group / k_spmm_pos, whose
-// workgroups wait on barriers) and now: 40 000 rows of 1000 x 25 000, k = 32 360 -> 252;  6000 columns, k = 128 1130 -> 690;  10^6 rows of 16,
+// workgroups wait on barriers) and now: 40 000 rows of 1000 x 25 000, k = 32 360 -> 252;  6000 columns, k = 128 1130 -> 650;  10^6 rows of 16,
 // 25 000 columns, k = 16 186 -> 111, k = 32 228 -> 128;  of 5, k = 32 141 -> 75.  Eight steps of loads in flight against four: k = 8 231 -> 205, k = 128
 // 705 -> 660; more waves per CU (fewer registers) gain nothing.
 template <int G, bool SMALL, bool PLAIN>
